@@ -405,7 +405,8 @@ int cp_seed_partition(const cp_graph *g, int32_t k, const int64_t *speeds, void 
  * time; here, from a start partition, every single move of a vertex of the current
  * critical path (cp_critical_path's path) to another device is a candidate; candidate
  * number i * (k-1) + r moves path vertex number i to the r-th device other than its own.
- * All candidates are evaluated with cp_eval in batches of `chunk`; those that break a
+ * Every candidate's CP is what cp_eval would return for it (it is computed from both levels
+ * of the current partition: only paths through the moved vertex change); candidates that break a
  * placement constraint (section 2, as in cp_validate) are left out; the candidate with
  * the smallest CP (lowest number on ties) is taken if it is smaller than the current CP,
  * and the step repeats; otherwise, or after max_moves moves, the search stops.
@@ -413,10 +414,8 @@ int cp_seed_partition(const cp_graph *g, int32_t k, const int64_t *speeds, void 
  *
  *   assignment   device uint8 [n]: in the start partition, out the result
  *   pairs, pins  device, as for cp_validate (NULL with a count of 0)
- *   chunk        candidates per cp_eval call (>= 1); what cp_eval gains from a larger batch
- *                (partitions that share a workgroup's packet stream from 512 on) the search
- *                gains too: a million-vertex graph is searched twice as fast with 1,024
- *                candidates per call as with 256
+ *   chunk        >= 1; has no effect on the result or the time (all candidates of a step are
+ *                compared at once)
  *   workspace    device, 256-byte aligned, >= cp_search_workspace_bytes(g, k, chunk)
  *   cp_trace     host int64 [max_moves + 1]: CP of the start, then after each move
  *   moves        host int32 [max_moves][2] = {vertex, new device}, or NULL
