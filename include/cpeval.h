@@ -89,6 +89,9 @@ extern "C" {
 #define CP_PLAN_SHARED_WINDOW_4  4   /* ... 4 partitions */
 #define CP_PLAN_STREAMED_WINDOW  6   /* as 2, but the compute wavefronts fetch the graph themselves, two ticks ahead, into
                                         registers; LDS holds only what depends on the partition */
+#define CP_PLAN_LANE_WINDOW      7   /* as 2, but one workgroup = 4 or 8 partitions in the lanes of its wavefronts, both
+                                        sweeps in one launch; CP_PLAN_AUTO takes it by itself where it is the faster form
+                                        of the window plans (cp_eval_choose_plan then still names the plan it stands in for) */
 #define CP_PLAN_COLUMN_SLICE     5   /* the wave-column layout, but one persistent workgroup owns 64 partitions and
                                         walks all levels in one launch per sweep (never chosen by CP_PLAN_AUTO) */
 

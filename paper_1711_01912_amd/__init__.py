@@ -12,6 +12,7 @@ from .binding import (  # noqa: F401
     OUT_VERTEX_MAJOR,
     PLAN_AUTO,
     PLAN_COLUMN_SLICE,
+    PLAN_LANE_WINDOW,
     PLAN_RESIDENT_WINDOW,
     PLAN_SHARED_WINDOW_2,
     PLAN_STREAMED_WINDOW,

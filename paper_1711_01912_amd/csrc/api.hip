@@ -244,15 +244,53 @@ int choose_window_plan(const Packed &p, int32_t k, size_t tick_bytes, size_t lds
     return best;
 }
 
+// The lane-window kernel: both sweeps in one launch, a workgroup per sweep and G partitions.  Measured: a
+// tick is a chain of 0.3 us, and a compute unit relaxes an item in 0.05 us (0.1 with 64-bit words), whichever
+// of its workgroups the item belongs to (19,800 to 121,000 vertices, 195 to 2,000 ticks, 80 to 1,024
+// workgroups; within 20 %).
+double lane_sweep_us(const LaneDir &d, const LaneCfg &c, int32_t batch, int sweeps) {
+    const double wgs = std::ceil((double)batch / c.groups) * sweeps;
+    const double per_cu = std::max(1.0, std::floor(std::min((double)kLdsBudget / (double)(c.lds_bytes + 512),
+                                                            32.0 / (c.nc + c.nlw + c.nsw))));
+    const double rounds = std::ceil(wgs / (256.0 * per_cu));
+    const double items = (double)d.units * c.groups / 8 / std::max(d.ticks, 1);      // per tick
+    return rounds * d.ticks * (0.3 + (c.word == 8 ? 0.1 : 0.05) * items * std::min(per_cu, std::ceil(wgs / 256.0)));
+}
+
+// The cheapest shape for this batch: true and its time if the lane-window kernel applies.
+bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, int32_t batch, int tick_bytes, bool with_out,
+                  bool by_partition, int sweeps, size_t lds_limit, LaneCfg &out, double *us_out) {
+    if (!p.have_lanes || k > kMagicMaxK) return false;
+    // the multiply-shift forms go with 32-bit ring words, the rounded form with 64-bit ones
+    const int word = p.lane_word == 4 && tabs.magic_ok ? 4 : 8;
+    if (word == 8 && !tabs.round_ok) return false;
+    // the outputs of a group are addressed with 32-bit offsets
+    const uint64_t span = (uint64_t)p.n * (by_partition ? 32 : (uint64_t)batch) * (uint64_t)tick_bytes;
+    if (with_out && span >= (1ull << 32)) return false;
+    bool found = false;
+    for (int groups : {4, 8}) {
+        LaneCfg c;
+        if (!lane_config(p.lane_b, p.lane_t, k, groups, word, with_out, lds_limit, c)) continue;
+        const double us = std::max(lane_sweep_us(p.lane_b, c, batch, sweeps), lane_sweep_us(p.lane_t, c, batch, sweeps));
+        if (!found || us < *us_out) {
+            found = true;
+            *us_out = us;
+            out = c;
+        }
+    }
+    return found;
+}
+
 size_t tables_bytes(int32_t k) { return align_up(table_words(k) * 8); }
 
 // One call's tables as they lie in device memory: the 8-byte entries (multiply-shift constants,
 // or plain divisors), then, where they exist, the 4-byte entries.
-std::vector<uint64_t> table_image(const CostTables &tabs, int32_t k) {
+std::vector<uint64_t> table_image(const CostTables &tabs, int32_t k, bool round) {
     std::vector<uint64_t> img(table_words(k), 0);
     const size_t entries = table_entries(k);
-    std::memcpy(img.data(), tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data(),
-                entries * 8);
+    const void *from = round ? (const void *)tabs.round.data()
+                             : (tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data());
+    std::memcpy(img.data(), from, entries * 8);
     if (tabs.tab4_ok) std::memcpy(img.data() + entries, tabs.tab4.data(), entries * 4);
     return img;
 }
@@ -265,7 +303,7 @@ int check_eval_sizes(const cp_graph *g, int32_t batch, int32_t k, int assign_lay
     if (batch < 1 || k < 1 || k > 255) return CP_ERR_SIZE;
     if (assign_layout != CP_ASSIGN_PARTITION_MAJOR && assign_layout != CP_ASSIGN_VERTEX_MAJOR)
         return CP_ERR_ARG;
-    if (plan < CP_PLAN_AUTO || plan > CP_PLAN_STREAMED_WINDOW) return CP_ERR_ARG;
+    if (plan < CP_PLAN_AUTO || plan > CP_PLAN_LANE_WINDOW) return CP_ERR_ARG;
     return CP_OK;
 }
 
@@ -420,9 +458,14 @@ int cp_eval_workspace_bytes(const cp_graph *g, int32_t batch, int32_t k, int ass
     if (out_layout == CP_OUT_PARTITION_MAJOR && may_column)
         column += 2 * column_scratch_bytes(g->packed, batch, tick_dtype);
     // the resident-window plan gathers the device ids into sweep order, once per direction
-    if (plan != CP_PLAN_WAVE_COLUMN && plan != CP_PLAN_COLUMN_SLICE && g->packed.have_window)
+    if (plan != CP_PLAN_WAVE_COLUMN && plan != CP_PLAN_COLUMN_SLICE && plan != CP_PLAN_LANE_WINDOW &&
+        g->packed.have_window)
         window = pperm_bytes(g->packed, g->packed.win_b, batch) + pperm_bytes(g->packed, g->packed.win_t, batch);
-    *out_bytes = bytes + std::max(column, window);
+    // the lane-window plan regroups the device ids
+    size_t lanes = 0;
+    if ((plan == CP_PLAN_AUTO || plan == CP_PLAN_LANE_WINDOW) && g->packed.have_lanes && k <= kMagicMaxK)
+        for (int groups : {4, 8}) lanes = std::max(lanes, lane_ids_bytes(g->packed.n, batch, groups, 2));
+    *out_bytes = bytes + std::max({column, window, lanes});
     return CP_OK;
 }
 
@@ -505,6 +548,51 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
             if (window_us - mask_us <= column_plan_us(p, batch, (size_t)tick_dtype)) use = wplan;
         }
     }
+    // several partitions in the lanes of a workgroup, both sweeps in one launch
+    LaneCfg lane_cfg;
+    const int lane_sweeps = ((blevel_out || cp_out) ? 1 : 0) + (tlevel_out ? 1 : 0);
+    bool lanes = false;
+    if ((plan == CP_PLAN_AUTO || plan == CP_PLAN_LANE_WINDOW) && lane_sweeps > 0) {
+        double lane_us = 0.0;
+        lanes = choose_lanes(p, tabs, k, batch, tick_dtype, blevel_out || tlevel_out,
+                             out_layout == CP_OUT_PARTITION_MAJOR, lane_sweeps,
+                             device_window_lds_limit(), lane_cfg, &lane_us);
+        if (lanes && plan == CP_PLAN_AUTO) {
+            // against the plan chosen so far: its sweeps (side by side where they would share the launch),
+            // the device ids it gathers per sweep at about 1 us per MB, and the mask pass that its t sweep
+            // may save it
+            const double mb = (double)p.n * batch * 1e-6;
+            const bool both = lane_sweeps == 2;
+            double other_us = column_plan_us(p, batch, (size_t)tick_dtype) * (both ? 1.0 : 0.5);
+            if (use == CP_PLAN_RESIDENT_WINDOW) {
+                const double b_us = window_sweep_us(p.win_b, cfg_b, batch), t_us = window_sweep_us(p.win_t, cfg_t, batch);
+                WindowCfg x, y;
+                other_us = both ? b_us + t_us : (tlevel_out ? t_us : b_us);
+                if (both && out_layout == CP_OUT_PARTITION_MAJOR && tick_dtype == CP_TICK_I32 &&
+                    window_pair_config(p.win_b, p.win_t, k, device_window_lds_limit(), x, y)) {
+                    if (window_wg_per_cu(cfg_b) == 1.0 && window_wg_per_cu(cfg_t) == 1.0) other_us *= 0.66;
+                    else if (2.0 * std::ceil((double)batch / 256.0) <= std::min(window_wg_per_cu(x), window_wg_per_cu(y)))
+                        other_us = 1.2 * std::max(b_us, t_us);
+                }
+            } else if (use == CP_PLAN_SHARED_WINDOW_2 || use == CP_PLAN_SHARED_WINDOW_4) {
+                const int shared_by = use == CP_PLAN_SHARED_WINDOW_4 ? 4 : 2;
+                other_us = ((blevel_out || cp_out) ? shared_sweep_us(p.win_b, shared_by, batch) : 0.0) +
+                           (tlevel_out ? shared_sweep_us(p.win_t, shared_by, batch) : 0.0);
+                if (mask_out && out_layout == CP_OUT_PARTITION_MAJOR)
+                    lane_us += 5.0 + (double)p.n * batch * (2.0 * tick_dtype + 0.125) / kMaskPassBytesPerUs;
+            }
+            if (use != CP_PLAN_WAVE_COLUMN) {
+                const bool rows = assign_layout == CP_ASSIGN_PARTITION_MAJOR &&
+                                  ((uint64_t)p.n * (uint64_t)batch) % 16 == 0 && ((uintptr_t)assignments % 16) == 0;
+                other_us += mb * ((rows && p.win_b.direct_ok ? 0.0 : 1.0) + (rows && p.win_t.direct_ok ? 0.0 : 1.0)) *
+                            (both ? 1.0 : 0.5);
+            }
+            lanes = 5.0 + 0.7 * mb + lane_us < other_us &&
+                    tables_bytes(k) + lane_ids_bytes(p.n, batch, lane_cfg.groups, lane_sweeps) <= workspace_bytes;
+        }
+    }
+    if (plan == CP_PLAN_LANE_WINDOW && !lanes) return CP_ERR_ARG;
+    if (lanes) use = CP_PLAN_LANE_WINDOW;
     if (use == CP_PLAN_RESIDENT_WINDOW && !can_window) return CP_ERR_ARG;
     // several partitions per workgroup behind one graph stream
     const bool shared = use == CP_PLAN_SHARED_WINDOW_2 || use == CP_PLAN_SHARED_WINDOW_4;
@@ -516,11 +604,11 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const bool streamed = use == CP_PLAN_STREAMED_WINDOW;
     if (streamed && (!tabs.magic_ok || !stream_fits(p, k, (size_t)tick_dtype, device_window_lds_limit(), &st_b, &st_t)))
         return CP_ERR_ARG;
-    const bool windowish = use == CP_PLAN_RESIDENT_WINDOW || shared || streamed;
+    const bool windowish = use == CP_PLAN_RESIDENT_WINDOW || shared || streamed || lanes;
     const bool columnish = !windowish;       // wave-column, or its persistent column-slice form
     if (use == CP_PLAN_COLUMN_SLICE && (!tabs.magic_ok || k > kMagicMaxK)) return CP_ERR_ARG;
     // the wave-column plan reads CP off the stored b-levels; the window sweeps keep a running maximum
-    if (cp_out && !blevel_out && (!windowish || p.win_b.far_cap > 0)) return CP_ERR_ARG;
+    if (cp_out && !blevel_out && (!windowish || (!lanes && p.win_b.far_cap > 0))) return CP_ERR_ARG;
 
     // Device ids reach the resident-window sweep either straight from the caller's rows
     // (16-byte loads: the rows must be contiguous, and whole-buffer size and base must be
@@ -528,8 +616,8 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const bool rows_ok = assign_layout == CP_ASSIGN_PARTITION_MAJOR &&
                          ((uint64_t)p.n * (uint64_t)batch) % 16 == 0 && ((uintptr_t)assignments % 16) == 0;
     const bool direct_b = rows_ok && p.win_b.direct_ok, direct_t = rows_ok && p.win_t.direct_ok;
-    const bool gather_b = windowish && (blevel_out || cp_out) && !direct_b;
-    const bool gather_t = windowish && tlevel_out && !direct_t;
+    const bool gather_b = windowish && !lanes && (blevel_out || cp_out) && !direct_b;
+    const bool gather_t = windowish && !lanes && tlevel_out && !direct_t;
 
     // workspace: only what this call uses (cp_eval_workspace_bytes is an upper bound over
     // every way the call may go)
@@ -538,6 +626,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const size_t pperm_b_bytes = gather_b ? pperm_bytes(p, p.win_b, batch) : 0;
     const size_t pperm_t_bytes = gather_t ? pperm_bytes(p, p.win_t, batch) : 0;
     need += pperm_b_bytes + pperm_t_bytes;
+    if (lanes) need += lane_ids_bytes(p.n, batch, lane_cfg.groups, lane_sweeps);
     const bool by_partition = out_layout == CP_OUT_PARTITION_MAJOR;
     const bool via_scratch = by_partition && columnish;
     const size_t scratch_at = need;
@@ -571,7 +660,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     CP_MARK(CP_STAGE_PREP);
     rc = launch_clear(cp_out, batch, status_out, stream);
     if (rc) return rc;
-    const std::vector<uint64_t> tab_img = table_image(tabs, k);
+    const std::vector<uint64_t> tab_img = table_image(tabs, k, lanes && lane_cfg.word == 8);
     rc = upload_tables(tab_img.data(), tab_img.size(), d_tab, st, tables_by_kernel);
     if (rc) return rc;
     const uint8_t *pT = assignments;
@@ -666,7 +755,22 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
 
     // ---- stage: b-level sweep
     CP_MARK(CP_STAGE_BLEVEL);
-    if (blevel_out || cp_out) {
+    if (lanes) {
+        s.edge_tab = d_tab;
+        s.edge_tab4 = d_tab4;
+        s.val = blevel_out;
+        s.cp_out = cp_out;
+        SweepLaunch t = s;
+        t.tsweep = true;
+        t.edge_tab = d_tab + kk * 8;
+        t.edge_tab4 = d_tab4 ? d_tab4 + kk : nullptr;
+        t.val = tlevel_out;
+        t.cp_out = nullptr;
+        rc = launch_window_lanes(s, t, p.lane_b, p.lane_t, lane_cfg, blevel_out || cp_out, tlevel_out != nullptr,
+                                 d_tab + tables_bytes(k), stream);
+        if (rc) return rc;
+        if (launches) launches[0] = 1;
+    } else if (blevel_out || cp_out) {
         s.tsweep = false;
         s.dir = &p.col_b;
         s.win = &p.win_b;
@@ -718,7 +822,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
 
     // ---- stage: t-level sweep
     CP_MARK(CP_STAGE_TLEVEL);
-    if (tlevel_out && !paired) {
+    if (tlevel_out && !paired && !lanes) {
         s.tsweep = true;
         s.dir = &p.col_t;
         s.win = &p.win_t;

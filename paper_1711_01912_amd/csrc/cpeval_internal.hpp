@@ -26,6 +26,14 @@ constexpr int kWindowFarTicks = 12;      // a neighbour this many ticks back (or
 constexpr int kWindowFarLead = 4;        // ticks a far wavefront runs ahead (twice: read list, then gather)
 constexpr int kWindowMaxFarWaves = 4;    // 64 far reads per tick each
 constexpr int kWindowMaxGroups = 8;     // partitions one workgroup may hold
+constexpr int kLaneUnit = 8;             // lane-window plan: sub-rows of a unit
+constexpr int kLaneIdBits = 6;           // a ring word is value << 6 | device id
+constexpr int kLaneTickVerts = 256;      // vertices of a tick
+constexpr int kLaneTickBytes = 12 * 1024; // packet of a tick
+// Ring of a workgroup of 8 partitions, beside stage slots and tables.  Graphs whose ring only fits 4 at a
+// time are slower than under the other window plans (211,000 vertices in 1,000 levels, 512 partitions:
+// 1.8 against 1.5 ms for both sweeps): they are not packed for this one.
+constexpr size_t kLaneRingBytes = 80 * 1024;
 constexpr int kMaskWords = 72;           // 32-bit mask words one tick's id range may touch (fused mask)
 
 inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a; }
@@ -91,6 +99,24 @@ struct WindowDir {
     bool ent4 = false;       // 4-byte entries
 };
 
+// One sweep direction of the lane-window plan (window_lanes.hip): several partitions per
+// workgroup, side by side in the lanes.  A vertex's edges are cut into sub-rows of `width` entries
+// (2 or 4, one for the whole graph); a unit is 8 sub-rows, and a tick has an even number of units (the
+// last one may be all padding).  What a tick needs is one packet:
+//   units     8 x {ring slot of the vertex, c}, then width x 8 x {ring slot of the neighbour, t}: entry j of
+//             sub-row r at j * 8 + r.  Padding entries read slot `slots`, which holds 0, with t = 0;
+//             padding sub-rows write to slot `slots + 1`, which nothing reads
+//   vertices  {id, c} in ring order
+// rounded up to 16 bytes.
+struct LaneDir {
+    size_t stream_off = 0;   // the packets, tick after tick
+    size_t tick_off = 0;     // uint32 [ticks] units | vertices << 16
+    size_t pos_off = 0;      // int32 [n] position of a vertex: the positions of a tick follow those of the last
+    int32_t ticks = 0, slots = 0, max_chunks = 0, max_units = 0, max_verts = 0, width = 0;
+    int64_t units = 0;       // of all ticks
+};
+inline uint32_t lane_unit_bytes(int width) { return 64u * (1u + (uint32_t)width); }
+
 struct Packed {
     int32_t n = 0, L = 0;
     int64_t m = 0;
@@ -101,6 +127,9 @@ struct Packed {
     size_t sources_off = 0;     // int32 [num_sources]
     bool have_window = false;
     WindowDir win_b, win_t;
+    bool have_lanes = false;
+    int32_t lane_word = 4;      // bytes of a ring word of the lane-window plan
+    LaneDir lane_b, lane_t;
     int32_t max_width = 0;
     std::vector<uint8_t> blob;  // host image of the device blob
 };
@@ -130,6 +159,11 @@ struct CostTables {
     // bank, which takes the bank conflicts out of the kernels' table reads.
     bool tab4_ok = false;
     std::vector<uint32_t> tab4;         // same layout; 0 = free transfer
+    // The rounded form, exact for every 32-bit N = a + dm1 (no condition on the product):
+    //   q = (N * mul) >> 32, one more if N - q * (dm1 + 1) > dm1      with mul = floor(2^32/d), dm1 = d - 1
+    // A free transfer is {0, 2^32 - 1}, which yields 0.
+    bool round_ok = false;
+    std::vector<Magic> round;           // same layout as magic
 };
 
 // Returns CP_OK, CP_ERR_SPEED or CP_ERR_BANDWIDTH.

@@ -26,6 +26,14 @@ __device__ __forceinline__ uint32_t magic_div(uint32_t a, uint32_t entry) {
     return (uint32_t)(((uint64_t)nn * (entry | 0xffu) + nn) >> 32);
 }
 
+// The same through the rounded form (CostTables::round): exact whatever the product, at the price of
+// the remainder.
+__device__ __forceinline__ uint32_t round_div(uint32_t a, Magic mg) {
+    const uint32_t nn = a + mg.dm1;
+    const uint32_t q = __umulhi(nn, mg.mul);
+    return q + (nn - q * (mg.dm1 + 1u) > mg.dm1 ? 1u : 0u);
+}
+
 // ceil(a/d) by division; d = 0 marks a free transfer.
 __device__ __forceinline__ uint64_t plain_div(uint64_t a, uint64_t d) {
     return d ? (a + d - 1) / d : 0;

@@ -391,6 +391,127 @@ bool pack_window_dir(BlobWriter &w, int32_t n, int32_t L, const int64_t *c, int6
     return true;
 }
 
+// Lane-window packing for one direction (layout: see LaneDir).  Returns false if the ring of a
+// workgroup of 8 partitions would be too long.
+bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes, int width, const Csr &csr,
+                   const int32_t *level_ptr, const int32_t *level_vtx, bool forward, const ColumnDir &col, LaneDir &dir) {
+    // Positions: by level, inside a level by vertex number, so that outputs are written along rows.
+    std::vector<int32_t> order((size_t)n), pos((size_t)n), slot((size_t)n);
+    for (size_t s = 0; s < col.lvl_begin.size(); ++s) {
+        const size_t l = forward ? s : col.lvl_begin.size() - 1 - s;
+        const auto to = order.begin() + col.lvl_begin[s];
+        std::copy(level_vtx + level_ptr[l], level_vtx + level_ptr[l + 1], to);
+        if (!std::is_sorted(to, to + col.lvl_count[s])) std::sort(to, to + col.lvl_count[s]);
+    }
+    // The vertices between an edge's two levels are a lower bound of the ring: most graphs that do not
+    // fit are turned away here.
+    const size_t row_bytes = (8 + 1) * word_bytes;
+    std::vector<int32_t> level_end((size_t)n);
+    for (size_t s = 0; s < col.lvl_begin.size(); ++s) {
+        const int32_t a = col.lvl_begin[s], b = a + col.lvl_count[s];
+        for (int32_t i = a; i < b; ++i) {
+            const int32_t v = order[i];
+            level_end[v] = b;
+            for (int32_t e = csr.ptr[v]; e < csr.ptr[v + 1]; ++e)
+                if ((uint64_t)(b - level_end[csr.idx[e]]) * row_bytes > kLaneRingBytes) return false;
+        }
+    }
+    for (int32_t i = 0; i < n; ++i) pos[order[i]] = i;
+    auto degree = [&](int32_t i) { return csr.ptr[order[i] + 1] - csr.ptr[order[i]]; };
+
+    const uint32_t unit_bytes = lane_unit_bytes(width);
+    auto pieces = [&](int32_t i) { return std::max(1, (degree(i) + width - 1) / width); };
+
+    // Ticks: runs of at most kLaneTickVerts vertices of a level, and about kLaneTickBytes of packet.
+    std::vector<int32_t> tick_a, tick_b;
+    for (size_t s = 0; s < col.lvl_begin.size(); ++s) {
+        const int32_t a = col.lvl_begin[s], b = a + col.lvl_count[s];
+        int32_t start = a;
+        int64_t bytes = 0;
+        for (int32_t i = a; i < b; ++i) {
+            const int64_t add = 8 + (int64_t)pieces(i) * unit_bytes / kLaneUnit;
+            if (i > start && (i - start == kLaneTickVerts || bytes + add > kLaneTickBytes)) {
+                tick_a.push_back(start);
+                tick_b.push_back(i);
+                start = i;
+                bytes = 0;
+            }
+            bytes += add;
+        }
+        if (b > start) {
+            tick_a.push_back(start);
+            tick_b.push_back(b);
+        }
+    }
+    const int32_t T = (int32_t)tick_a.size();
+    // Ring: while tick s runs, the values its edges read and those of tick s - 1 (on their way to the
+    // output) are live, and the device ids of the two ticks after s are written already.
+    int64_t need = 1;
+    for (int32_t s = 0; s < T; ++s) {
+        int32_t oldest = tick_a[std::max(s - 1, 0)];
+        for (int32_t i = tick_a[s]; i < tick_b[s]; ++i)
+            for (int32_t e = csr.ptr[order[i]]; e < csr.ptr[order[i] + 1]; ++e) oldest = std::min(oldest, pos[csr.idx[e]]);
+        need = std::max<int64_t>(need, (int64_t)tick_b[std::min(s + 2, T - 1)] - oldest);
+        if ((uint64_t)need * row_bytes > kLaneRingBytes) return false;
+    }
+    dir.ticks = T;
+    dir.slots = (int32_t)need;
+    dir.width = width;
+    for (int32_t i = 0, at = 0; i < n; ++i) {
+        slot[order[i]] = at;
+        if (++at == dir.slots) at = 0;
+    }
+
+    std::vector<uint32_t> tab((size_t)std::max(T, 1), 0), stream;
+    stream.reserve((size_t)(csr.ptr[n] + n) * 4);
+    for (int32_t s = 0; s < T; ++s) {
+        const int32_t a = tick_a[s], b = tick_b[s];
+        int64_t rows = 0;
+        for (int32_t i = a; i < b; ++i) rows += pieces(i);
+        const int64_t units = (rows + 2 * kLaneUnit - 1) / (2 * kLaneUnit) * 2;
+        if (units >= (1 << 16)) return false;
+        const uint32_t bytes = (uint32_t)units * unit_bytes + 8u * (uint32_t)(b - a), chunks = (bytes + 15) / 16;
+        const size_t base = stream.size();                  // in words
+        if (base / 4 + chunks >= (1ull << 31)) return false;
+        stream.resize(base + 4 * (size_t)chunks, 0);
+        tab[s] = (uint32_t)units | (uint32_t)(b - a) << 16;
+        uint32_t *const first_unit = stream.data() + base;
+        int64_t row = 0;
+        auto put_row = [&](uint32_t to, uint32_t cv, int32_t e, int32_t len) {
+            uint32_t *x = first_unit + (size_t)(row / kLaneUnit) * (unit_bytes / 4) + 2 * (row % kLaneUnit);
+            x[0] = to;
+            x[1] = cv;
+            for (int j = 0; j < width; ++j) {
+                x += 2 * kLaneUnit;
+                x[0] = j < len ? (uint32_t)slot[csr.idx[e + j]] : (uint32_t)dir.slots;
+                x[1] = j < len ? (uint32_t)csr.wt[e + j] : 0;
+            }
+            ++row;
+        };
+        for (int32_t i = a; i < b; ++i) {
+            const int32_t v = order[i], d = degree(i);
+            for (int32_t j = 0; j == 0 || j < d; j += width) put_row((uint32_t)slot[v], (uint32_t)c[v], csr.ptr[v] + j, d - j);
+        }
+        while (row < units * kLaneUnit) put_row((uint32_t)dir.slots + 1, 0, 0, 0);
+        uint32_t *verts = stream.data() + base + (size_t)units * unit_bytes / 4;
+        for (int32_t i = a; i < b; ++i) {
+            verts[2 * (i - a)] = (uint32_t)order[i];
+            verts[2 * (i - a) + 1] = (uint32_t)c[order[i]];
+        }
+        dir.units += units;
+        dir.max_chunks = std::max(dir.max_chunks, (int32_t)chunks);
+        dir.max_units = std::max(dir.max_units, (int32_t)units);
+        dir.max_verts = std::max(dir.max_verts, b - a);
+    }
+    dir.stream_off = w.reserve(4 * std::max<size_t>(stream.size(), 4));
+    std::memcpy(w.at<uint32_t>(dir.stream_off), stream.data(), 4 * stream.size());
+    dir.tick_off = w.reserve(4 * tab.size());
+    std::memcpy(w.at<uint32_t>(dir.tick_off), tab.data(), 4 * tab.size());
+    dir.pos_off = w.reserve(4 * (size_t)n);
+    std::memcpy(w.at<int32_t>(dir.pos_off), pos.data(), 4 * (size_t)n);
+    return true;
+}
+
 }  // namespace
 
 int pack_graph(int32_t n, int64_t m, int32_t L,
@@ -522,6 +643,22 @@ int pack_graph(int32_t n, int64_t m, int32_t L,
                       pack_window_dir(w, n, L, c, max_t, info.min_tick_bytes == 4, pred, order_t, P.col_t, P.win_t);
             if (ok) P.have_window = true;
             else P.blob.resize(mark);
+        }
+        P.have_lanes = false;
+        P.lane_word = u0 < (1ull << (32 - kLaneIdBits)) ? 4 : 8;
+        if (P.narrow && u0 < (1ull << (64 - kLaneIdBits))) {
+            const size_t mark = P.blob.size();
+            // entries per sub-row: an item costs about 28 instructions and 8 per entry
+            int64_t rows2 = 0, rows4 = 0;
+            for (const int32_t *ptr : {succ_ptr, pred_ptr})
+                for (int32_t v = 0; v < n; ++v) {
+                    rows2 += std::max(1, (ptr[v + 1] - ptr[v] + 1) / 2);
+                    rows4 += std::max(1, (ptr[v + 1] - ptr[v] + 3) / 4);
+                }
+            const int width = rows2 * (28 + 8 * 2) < rows4 * (28 + 8 * 4) ? 2 : 4;
+            P.have_lanes = pack_lane_dir(w, n, c, (size_t)P.lane_word, width, succ, level_ptr, level_vtx, false, P.col_b, P.lane_b) &&
+                           pack_lane_dir(w, n, c, (size_t)P.lane_word, width, pred, level_ptr, level_vtx, true, P.col_t, P.lane_t);
+            if (!P.have_lanes) P.blob.resize(mark);
         }
         P.blob.resize(align_up(P.blob.size()));
     } catch (const std::bad_alloc &) {

@@ -1,0 +1,99 @@
+"""The lane-window plan against the oracle at the edges of its packets, its groups of lanes and its ring."""
+import numpy as np
+import pytest
+
+from workloads import make_workload, random_layered_dag
+
+import test_gpu_parity as T
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1711_01912_amd as cpe
+    cpe.load_library()
+    return cpe
+
+
+def _case(seed, widths, deg, span, k, P, c_hi=50, t_hi=300, rates=20, extra=0, renumber=False):
+    rng = np.random.default_rng(seed)
+    n, level, src, dst = random_layered_dag(rng, widths, 1, deg, span)
+    if extra:                                     # rows of several sub-rows: one vertex feeds and one reads a whole level
+        first, last = np.arange(widths[0]), np.arange(n - widths[-1], n)
+        src = np.concatenate([src, np.zeros(len(last), dtype=np.int64), first[1:]])
+        dst = np.concatenate([dst, last, np.full(len(first) - 1, n - 1)])
+    if renumber:
+        name = rng.permutation(n)
+        old, level = level, np.empty_like(level)
+        level[name] = old
+        src, dst = name[src], name[dst]
+    return T._custom("lanes", n, src, dst, rng.integers(0, t_hi, len(src)), rng.integers(0, c_hi, n),
+                     rng.integers(1, 9, k), rng.integers(1, rates, (k, k)), rng.integers(0, k, (P, n), dtype=np.uint8),
+                     level)
+
+
+def _check(gpu, oracle, w, **kw):
+    from gpu_util import assert_equal_to_oracle, run_gpu
+    ref = oracle.evaluate_workload(w, threads=8)
+    g = gpu.CpGraph.from_workload(w, device="cuda:0")
+    for layout, out_layout in ((0, 1), (1, 0), (0, 0)):
+        res = run_gpu(w, gpu.PLAN_LANE_WINDOW, layout=layout, graph=g, out_layout=out_layout, **kw)
+        assert_equal_to_oracle(res, ref, f"layout {layout}, outputs {out_layout}")
+    for want in (("cp",), ("tl",), ("b",)):       # one sweep alone
+        res = run_gpu(w, gpu.PLAN_LANE_WINDOW, graph=g, out_layout=1, want=want, **kw)
+        for key in want:
+            assert np.array_equal(res[key], ref[key]), key
+    g.close()
+
+
+@pytest.mark.parametrize("P", [1, 7, 8, 9, 33, 300, 3000])
+def test_batches_around_a_group(gpu, oracle, P):
+    _check(gpu, oracle, _case(P, [9] * 12, 3, 3, 5, P))
+
+
+@pytest.mark.parametrize("widths,deg,span,extra", [
+    ([1], 1, 1, 0), ([1] * 9, 2, 3, 0), ([3, 70, 1, 64, 65, 2], 9, 2, 0),
+    ([300, 1, 520, 255, 256, 257], 3, 1, 0),      # levels cut into ticks, ticks of one vertex between
+    ([40] * 6, 8, 5, 1), ([17] * 30, 17, 4, 1),   # sub-rows of every length, vertices of many sub-rows
+])
+def test_levels_and_rows(gpu, oracle, widths, deg, span, extra):
+    for renumber in (False, True):
+        _check(gpu, oracle, _case(len(widths) + deg, widths, deg, span, 4, 37, extra=extra, renumber=renumber))
+
+
+@pytest.mark.parametrize("k", [1, 2, 33, 64])
+def test_device_counts(gpu, oracle, k):
+    _check(gpu, oracle, _case(k, [11] * 9, 4, 3, k, 41))
+
+
+@pytest.mark.parametrize("c_hi,t_hi,rates", [(2 ** 20, 2 ** 28, 64), (2 ** 31, 2 ** 31, 3), (9, 2 ** 31, 2 ** 20)])
+def test_weights_that_need_the_remainder(gpu, oracle, c_hi, t_hi, rates):
+    w = _case(5, [13] * 40, 4, 4, 6, 50, c_hi=c_hi, t_hi=t_hi, rates=rates)
+    _check(gpu, oracle, w)
+
+
+def test_64_bit_ticks_of_a_small_graph_and_the_perceptron(gpu, oracle):
+    _check(gpu, oracle, _case(8, [9] * 12, 3, 3, 5, 20), tick_bytes=8)
+    _check(gpu, oracle, make_workload("mlp", P=70))
+
+
+def test_bad_device_id_and_refusals(gpu):
+    import torch
+    w = _case(3, [9] * 12, 3, 3, 5, 20)
+    g = gpu.CpGraph.from_workload(w, device="cuda:0")
+    a = torch.from_numpy(w.assignments.copy()).to("cuda:0")
+    a[19, w.n - 1] = 5
+    with pytest.raises(ValueError):
+        gpu.cp_eval(g, a, w.speeds, w.bandwidth, plan=gpu.PLAN_LANE_WINDOW)
+    wide = _case(4, [3000] * 4, 2, 1, 3, 2)       # the ring of the smallest group does not fit
+    g2 = gpu.CpGraph.from_workload(wide, device="cuda:0")
+    with pytest.raises(gpu.CpError) as e:
+        gpu.cp_eval(g2, torch.from_numpy(wide.assignments).to("cuda:0"), wide.speeds, wide.bandwidth,
+                    plan=gpu.PLAN_LANE_WINDOW)
+    assert e.value.code == -12
+    g.close()
+    g2.close()
