@@ -65,29 +65,36 @@ int stage_and_copy(const void *src, size_t bytes, void *dst, hipStream_t st) {
 constexpr int kTableChunkWords = 448;                       // 3.5 KB of kernel arguments
 struct TableChunk { uint64_t v[kTableChunkWords]; };
 
-__global__ void table_write_kernel(TableChunk chunk, uint64_t *dst, int32_t count) {
+// The first chunk's launch also clears what a call starts from: the status word and, where there is one, CP.
+__global__ void table_write_kernel(TableChunk chunk, uint64_t *dst, int32_t count, int64_t *cp_out, int32_t batch,
+                                   int32_t *status) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < count) dst[i] = chunk.v[i];
+    if (cp_out)
+        for (int j = i; j < batch; j += gridDim.x * blockDim.x) cp_out[j] = 0;
+    if (status && i == 0) *status = CP_STATUS_OK;
 }
 
-int write_tables_by_kernel(const void *src, size_t entries, void *dst, hipStream_t st) {
+// What a call needs before its kernels: cleared CP and status, and its cost tables in device memory.  Up to
+// 64 devices (66 KB) the tables travel as kernel arguments: nothing is allocated, nothing waits, and calls
+// on different streams or threads do not meet, and at 11 devices or fewer one launch does it all.  Larger
+// tables go through the pinned staging ring above.
+int prepare_call(const void *src, size_t entries, void *dst, int64_t *cp_out, int32_t batch, int32_t *status,
+                 hipStream_t st, bool by_kernel_only = false) {
+    if (!by_kernel_only && entries > table_words(kMagicMaxK)) {
+        const int rc = launch_clear(cp_out, batch, status, st);
+        return rc ? rc : stage_and_copy(src, entries * 8, dst, st);
+    }
     const uint64_t *from = (const uint64_t *)src;
     uint64_t *to = (uint64_t *)dst;
     for (size_t at = 0; at < entries; at += kTableChunkWords) {
         TableChunk chunk;
         const int32_t count = (int32_t)std::min<size_t>(kTableChunkWords, entries - at);
         std::memcpy(chunk.v, from + at, (size_t)count * 8);
-        hipLaunchKernelGGL(table_write_kernel, dim3((count + 255) / 256), dim3(256), 0, st, chunk, to + at, count);
+        hipLaunchKernelGGL(table_write_kernel, dim3((count + 255) / 256), dim3(256), 0, st, chunk, to + at, count,
+                           at ? nullptr : cp_out, batch, at ? nullptr : status);
     }
     return hipGetLastError() == hipSuccess ? CP_OK : CP_ERR_HIP;
-}
-
-// Cost tables of one call into device memory.  Up to 64 devices (66 KB) they travel as kernel
-// arguments: nothing is allocated, nothing waits, and calls on different streams or threads
-// do not meet.  Larger tables go through the pinned staging ring above.
-int upload_tables(const void *src, size_t entries, void *dst, hipStream_t st, bool by_kernel_only = false) {
-    if (by_kernel_only || entries <= table_words(kMagicMaxK)) return write_tables_by_kernel(src, entries, dst, st);
-    return stage_and_copy(src, entries * 8, dst, st);
 }
 
 // Scratch memory of cp_eval_static: one array per GPU, part of the loaded code object, never
@@ -245,16 +252,27 @@ int choose_window_plan(const Packed &p, int32_t k, size_t tick_bytes, size_t lds
 }
 
 // The lane-window kernel: both sweeps in one launch, a workgroup per sweep and G partitions.  Measured: a
-// tick is a chain of 0.3 us, and a compute unit relaxes an item in 0.05 us (0.1 with 64-bit words), whichever
-// of its workgroups the item belongs to (19,800 to 121,000 vertices, 195 to 2,000 ticks, 80 to 1,024
-// workgroups; within 20 %).
+// tick is a chain of 0.3 us, to which every workgroup of a compute unit adds 0.07 us and its items: 0.05 us
+// each with 4 entries a sub-row, 0.037 with 2, twice that with 64-bit words (2,000 to 121,000 vertices, 195 to
+// 702 ticks, 80 to 1,024 workgroups, one to four of them on a unit; within 25 %).
 double lane_sweep_us(const LaneDir &d, const LaneCfg &c, int32_t batch, int sweeps) {
     const double wgs = std::ceil((double)batch / c.groups) * sweeps;
     const double per_cu = std::max(1.0, std::floor(std::min((double)kLdsBudget / (double)(c.lds_bytes + 512),
-                                                            32.0 / (c.nc + c.nlw + c.nsw))));
-    const double rounds = std::ceil(wgs / (256.0 * per_cu));
+                                                            (c.nfw > 0 && c.word == 8 ? 24.0 : 32.0) /
+                                                                (c.nc + c.nlw + c.nsw + c.nfw))));
     const double items = (double)d.units * c.groups / 8 / std::max(d.ticks, 1);      // per tick
-    return rounds * d.ticks * (0.3 + (c.word == 8 ? 0.1 : 0.05) * items * std::min(per_cu, std::ceil(wgs / 256.0)));
+    const double each = 0.07 + items * (c.width == 2 ? 0.037 : 0.05) * (c.word == 8 ? 2.0 : 1.0);
+    const double full = std::floor(wgs / (256.0 * per_cu)), rest = std::ceil((wgs - full * 256.0 * per_cu) / 256.0);
+    return d.ticks * (full * (0.3 + per_cu * each) + (rest > 0.0 ? 0.3 + rest * each : 0.0));
+}
+
+// The resident-window kernel where its workgroups share compute units: a unit relaxes a slice in 0.1 us
+// whichever workgroup it belongs to, and rows per vertex cost 1.4 times as much (121,000 vertices in 701
+// levels of three slices, 777 partitions: 1.2 and 1.4 ms; 19,800 in 660 levels of one, 4,096: 1.65 ms).
+double crowded_window_sweep_us(const WindowDir &d, const WindowCfg &c, int32_t batch, bool by_partition) {
+    const double per_cu = window_wg_per_cu(c), wgs = std::ceil((double)batch / std::max(1, c.groups));
+    const double rounds = std::ceil(wgs / (256.0 * per_cu)), there = std::min(per_cu, std::ceil(wgs / 256.0));
+    return rounds * d.ticks * std::max(0.65 + 0.03 * d.smax, 0.1 * d.smax * there) * (by_partition ? 1.0 : 1.4);
 }
 
 // The cheapest shape for this batch: true and its time if the lane-window kernel applies.
@@ -270,7 +288,8 @@ bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, int32_t ba
     bool found = false;
     for (int groups : {4, 8}) {
         LaneCfg c;
-        if (!lane_config(p.lane_b, p.lane_t, k, groups, word, with_out, lds_limit, c)) continue;
+        if (!lane_config(p.lane_b, p.lane_t, p.n, k, groups, word, with_out,
+                         ((int64_t)batch + groups - 1) / groups * sweeps, lds_limit, c)) continue;
         const double us = std::max(lane_sweep_us(p.lane_b, c, batch, sweeps), lane_sweep_us(p.lane_t, c, batch, sweeps));
         if (!found || us < *us_out) {
             found = true;
@@ -464,7 +483,8 @@ int cp_eval_workspace_bytes(const cp_graph *g, int32_t batch, int32_t k, int ass
     // the lane-window plan regroups the device ids
     size_t lanes = 0;
     if ((plan == CP_PLAN_AUTO || plan == CP_PLAN_LANE_WINDOW) && g->packed.have_lanes && k <= kMagicMaxK)
-        for (int groups : {4, 8}) lanes = std::max(lanes, lane_ids_bytes(g->packed.n, batch, groups, 2));
+        for (int groups : {4, 8}) 
+            lanes = std::max(lanes, lane_work_bytes(&g->packed.lane_b, &g->packed.lane_t, g->packed.n, batch, groups, 8));
     *out_bytes = bytes + std::max({column, window, lanes});
     return CP_OK;
 }
@@ -552,11 +572,15 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     LaneCfg lane_cfg;
     const int lane_sweeps = ((blevel_out || cp_out) ? 1 : 0) + (tlevel_out ? 1 : 0);
     bool lanes = false;
+    size_t lane_work = 0;
     if ((plan == CP_PLAN_AUTO || plan == CP_PLAN_LANE_WINDOW) && lane_sweeps > 0) {
         double lane_us = 0.0;
         lanes = choose_lanes(p, tabs, k, batch, tick_dtype, blevel_out || tlevel_out,
                              out_layout == CP_OUT_PARTITION_MAJOR, lane_sweeps,
                              device_window_lds_limit(), lane_cfg, &lane_us);
+        if (lanes)
+            lane_work = lane_work_bytes((blevel_out || cp_out) ? &p.lane_b : nullptr, tlevel_out ? &p.lane_t : nullptr, p.n,
+                                        batch, lane_cfg.groups, lane_cfg.word);
         if (lanes && plan == CP_PLAN_AUTO) {
             // against the plan chosen so far: its sweeps (side by side where they would share the launch),
             // the device ids it gathers per sweep at about 1 us per MB, and the mask pass that its t sweep
@@ -565,7 +589,9 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
             const bool both = lane_sweeps == 2;
             double other_us = column_plan_us(p, batch, (size_t)tick_dtype) * (both ? 1.0 : 0.5);
             if (use == CP_PLAN_RESIDENT_WINDOW) {
-                const double b_us = window_sweep_us(p.win_b, cfg_b, batch), t_us = window_sweep_us(p.win_t, cfg_t, batch);
+                const bool by_rows = out_layout == CP_OUT_PARTITION_MAJOR;
+                const double b_us = crowded_window_sweep_us(p.win_b, cfg_b, batch, by_rows);
+                const double t_us = crowded_window_sweep_us(p.win_t, cfg_t, batch, by_rows);
                 WindowCfg x, y;
                 other_us = both ? b_us + t_us : (tlevel_out ? t_us : b_us);
                 if (both && out_layout == CP_OUT_PARTITION_MAJOR && tick_dtype == CP_TICK_I32 &&
@@ -588,7 +614,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                             (both ? 1.0 : 0.5);
             }
             lanes = 5.0 + 0.7 * mb + lane_us < other_us &&
-                    tables_bytes(k) + lane_ids_bytes(p.n, batch, lane_cfg.groups, lane_sweeps) <= workspace_bytes;
+                    tables_bytes(k) + lane_work <= workspace_bytes;
         }
     }
     if (plan == CP_PLAN_LANE_WINDOW && !lanes) return CP_ERR_ARG;
@@ -626,7 +652,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const size_t pperm_b_bytes = gather_b ? pperm_bytes(p, p.win_b, batch) : 0;
     const size_t pperm_t_bytes = gather_t ? pperm_bytes(p, p.win_t, batch) : 0;
     need += pperm_b_bytes + pperm_t_bytes;
-    if (lanes) need += lane_ids_bytes(p.n, batch, lane_cfg.groups, lane_sweeps);
+    if (lanes) need += lane_work;
     const bool by_partition = out_layout == CP_OUT_PARTITION_MAJOR;
     const bool via_scratch = by_partition && columnish;
     const size_t scratch_at = need;
@@ -658,10 +684,8 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
 
     // ---- stage: prep
     CP_MARK(CP_STAGE_PREP);
-    rc = launch_clear(cp_out, batch, status_out, stream);
-    if (rc) return rc;
     const std::vector<uint64_t> tab_img = table_image(tabs, k, lanes && lane_cfg.word == 8);
-    rc = upload_tables(tab_img.data(), tab_img.size(), d_tab, st, tables_by_kernel);
+    rc = prepare_call(tab_img.data(), tab_img.size(), d_tab, cp_out, batch, status_out, st, tables_by_kernel);
     if (rc) return rc;
     const uint8_t *pT = assignments;
     if (need_pT) {
@@ -924,11 +948,9 @@ int cp_critical_path(const cp_graph *g, int32_t batch, int32_t k,
     }
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
-    rc = launch_clear(nullptr, 1, status_out, stream);
-    if (rc) return rc;
     uint8_t *d_tab = (uint8_t *)workspace;
     const void *tab_src = tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data();
-    rc = upload_tables(tab_src, table_entries(k), d_tab, st);
+    rc = prepare_call(tab_src, table_entries(k), d_tab, nullptr, 1, status_out, st);
     if (rc) return rc;
     SweepLaunch s;
     s.blob = (const uint8_t *)g->device_blob;
@@ -1085,11 +1107,9 @@ int cp_simulate(const cp_graph *g, int32_t batch, int32_t k,
     const uint64_t window = std::min<uint64_t>(w_min + x_min - 1, 1u << 30);
 
     hipStream_t st = (hipStream_t)stream;
-    rc = launch_clear(nullptr, 1, status_out, stream);
-    if (rc) return rc;
     uint8_t *ws = (uint8_t *)workspace;
     const void *tab_src = tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data();
-    rc = upload_tables(tab_src, table_entries(k), ws, st);
+    rc = prepare_call(tab_src, table_entries(k), ws, nullptr, 1, status_out, st);
     if (rc) return rc;
     SimulateLaunch s;
     s.blob = (const uint8_t *)g->device_blob;

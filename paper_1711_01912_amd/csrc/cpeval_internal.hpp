@@ -30,6 +30,8 @@ constexpr int kLaneUnit = 8;             // lane-window plan: sub-rows of a unit
 constexpr int kLaneIdBits = 6;           // a ring word is value << 6 | device id
 constexpr int kLaneTickVerts = 256;      // vertices of a tick
 constexpr int kLaneTickBytes = 12 * 1024; // packet of a tick
+constexpr int kLaneFarTicks = 16;        // a neighbour this many ticks back (or more) may be a far read
+constexpr int kLaneMaxFar = 96;          // far reads of a tick
 // Ring of a workgroup of 8 partitions, beside stage slots and tables.  Graphs whose ring only fits 4 at a
 // time are slower than under the other window plans (211,000 vertices in 1,000 levels, 512 partitions:
 // 1.8 against 1.5 ms for both sweeps): they are not packed for this one.
@@ -107,10 +109,17 @@ struct WindowDir {
 //             sub-row r at j * 8 + r.  Padding entries read slot `slots`, which holds 0, with t = 0;
 //             padding sub-rows write to slot `slots + 1`, which nothing reads
 //   vertices  {id, c} in ring order
-// rounded up to 16 bytes.
+//   far out   ring slots of the vertices that far reads of later ticks ask for
+// rounded up to 16 bytes.  Where the ring cannot hold every neighbour, one computed far_ticks or more ticks
+// earlier is a far read: its entry names a row behind the ring, slots + 2 + (tick & 1) * far_cap + number,
+// which a far wavefront fills before the tick starts from a copy of the word kept in the workspace.
 struct LaneDir {
     size_t stream_off = 0;   // the packets, tick after tick
-    size_t tick_off = 0;     // uint32 [ticks] units | vertices << 16
+    size_t tick_off = 0;     // uint32 [ticks] units | vertices << 14 | far out << 23
+    size_t far_off = 0;      // int32 [ticks][far_cap] numbers of the vertices the tick's far reads ask for, counted in the
+                             // order they are computed; padding: 0
+    int32_t far_cap = 0;     // far reads per tick, a multiple of 16; 0 = none anywhere
+    int32_t far_count = 0;   // vertices some far read asks for
     size_t pos_off = 0;      // int32 [n] position of a vertex: the positions of a tick follow those of the last
     int32_t ticks = 0, slots = 0, max_chunks = 0, max_units = 0, max_verts = 0, width = 0;
     int64_t units = 0;       // of all ticks

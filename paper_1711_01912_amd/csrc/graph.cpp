@@ -403,19 +403,7 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
         std::copy(level_vtx + level_ptr[l], level_vtx + level_ptr[l + 1], to);
         if (!std::is_sorted(to, to + col.lvl_count[s])) std::sort(to, to + col.lvl_count[s]);
     }
-    // The vertices between an edge's two levels are a lower bound of the ring: most graphs that do not
-    // fit are turned away here.
     const size_t row_bytes = (8 + 1) * word_bytes;
-    std::vector<int32_t> level_end((size_t)n);
-    for (size_t s = 0; s < col.lvl_begin.size(); ++s) {
-        const int32_t a = col.lvl_begin[s], b = a + col.lvl_count[s];
-        for (int32_t i = a; i < b; ++i) {
-            const int32_t v = order[i];
-            level_end[v] = b;
-            for (int32_t e = csr.ptr[v]; e < csr.ptr[v + 1]; ++e)
-                if ((uint64_t)(b - level_end[csr.idx[e]]) * row_bytes > kLaneRingBytes) return false;
-        }
-    }
     for (int32_t i = 0; i < n; ++i) pos[order[i]] = i;
     auto degree = [&](int32_t i) { return csr.ptr[order[i] + 1] - csr.ptr[order[i]]; };
 
@@ -444,15 +432,41 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
         }
     }
     const int32_t T = (int32_t)tick_a.size();
+    std::vector<int32_t> tick_of((size_t)n);
+    for (int32_t s = 0; s < T; ++s)
+        for (int32_t i = tick_a[s]; i < tick_b[s]; ++i) tick_of[order[i]] = s;
     // Ring: while tick s runs, the values its edges read and those of tick s - 1 (on their way to the
-    // output) are live, and the device ids of the two ticks after s are written already.
-    int64_t need = 1;
-    for (int32_t s = 0; s < T; ++s) {
-        int32_t oldest = tick_a[std::max(s - 1, 0)];
-        for (int32_t i = tick_a[s]; i < tick_b[s]; ++i)
-            for (int32_t e = csr.ptr[order[i]]; e < csr.ptr[order[i] + 1]; ++e) oldest = std::min(oldest, pos[csr.idx[e]]);
-        need = std::max<int64_t>(need, (int64_t)tick_b[std::min(s + 2, T - 1)] - oldest);
-        if ((uint64_t)need * row_bytes > kLaneRingBytes) return false;
+    // output) are live, and the device ids of the two ticks after s are written already.  far_ticks = 0:
+    // every neighbour in the ring.  Returns false if that is too long, or a tick has too many far reads.
+    int64_t need = 0;
+    std::vector<int32_t> far_seen((size_t)n, -1);      // last tick with a far read of the vertex
+    auto ring_fits = [&](int32_t far_ticks) {
+        need = 1;
+        dir.far_cap = 0;
+        std::fill(far_seen.begin(), far_seen.end(), -1);
+        for (int32_t s = 0; s < T; ++s) {
+            int32_t oldest = tick_a[std::max(s - 1, 0)], far = 0;
+            for (int32_t i = tick_a[s]; i < tick_b[s]; ++i)
+                for (int32_t e = csr.ptr[order[i]]; e < csr.ptr[order[i] + 1]; ++e) {
+                    const int32_t u = csr.idx[e];
+                    if (far_ticks == 0 || s - tick_of[u] < far_ticks) oldest = std::min(oldest, pos[u]);
+                    else if (far_seen[u] != s) { far_seen[u] = s; ++far; }
+                }
+            need = std::max<int64_t>(need, (int64_t)tick_b[std::min(s + 2, T - 1)] - oldest);
+            dir.far_cap = std::max(dir.far_cap, (far + 15) / 16 * 16);
+            if ((uint64_t)(need + 2 * dir.far_cap) * row_bytes > kLaneRingBytes || dir.far_cap > kLaneMaxFar) return false;
+        }
+        return true;
+    };
+    int32_t far_ticks = 0;
+    if (!ring_fits(0)) {
+        far_ticks = kLaneFarTicks;
+        while (far_ticks < T && !ring_fits(far_ticks)) {
+            // a longer ring helps against too many far reads only
+            if (dir.far_cap <= kLaneMaxFar) return false;
+            far_ticks *= 2;
+        }
+        if (far_ticks >= T) return false;
     }
     dir.ticks = T;
     dir.slots = (int32_t)need;
@@ -462,6 +476,19 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
         if (++at == dir.slots) at = 0;
     }
 
+    // vertices that far reads ask for, numbered in the order they are computed
+    std::vector<int32_t> far_no, far_list;
+    if (far_ticks) {
+        far_no.assign((size_t)n, -1);
+        for (int32_t i = 0; i < n; ++i)
+            for (int32_t e = csr.ptr[order[i]]; e < csr.ptr[order[i] + 1]; ++e)
+                if (tick_of[order[i]] - tick_of[csr.idx[e]] >= far_ticks) far_no[csr.idx[e]] = 0;
+        for (int32_t i = 0; i < n; ++i)
+            if (far_no[order[i]] == 0) far_no[order[i]] = dir.far_count++;
+        far_list.assign((size_t)T * dir.far_cap, 0);
+        std::fill(far_seen.begin(), far_seen.end(), -1);
+    }
+    std::vector<int32_t> far_row(far_ticks ? (size_t)n : 0);     // row of the vertex among the current tick's far reads
     std::vector<uint32_t> tab((size_t)std::max(T, 1), 0), stream;
     stream.reserve((size_t)(csr.ptr[n] + n) * 4);
     for (int32_t s = 0; s < T; ++s) {
@@ -469,13 +496,24 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
         int64_t rows = 0;
         for (int32_t i = a; i < b; ++i) rows += pieces(i);
         const int64_t units = (rows + 2 * kLaneUnit - 1) / (2 * kLaneUnit) * 2;
-        if (units >= (1 << 16)) return false;
-        const uint32_t bytes = (uint32_t)units * unit_bytes + 8u * (uint32_t)(b - a), chunks = (bytes + 15) / 16;
+        if (units >= (1 << 14)) return false;
+        uint32_t far_out = 0, far_in = 0;
+        for (int32_t i = a; far_ticks && i < b; ++i) far_out += far_no[order[i]] >= 0;
+        const uint32_t bytes = (uint32_t)units * unit_bytes + 8u * (uint32_t)(b - a) + 4 * far_out, chunks = (bytes + 15) / 16;
         const size_t base = stream.size();                  // in words
         if (base / 4 + chunks >= (1ull << 31)) return false;
         stream.resize(base + 4 * (size_t)chunks, 0);
-        tab[s] = (uint32_t)units | (uint32_t)(b - a) << 16;
+        tab[s] = (uint32_t)units | (uint32_t)(b - a) << 14 | far_out << 23;
         uint32_t *const first_unit = stream.data() + base;
+        auto source = [&](int32_t u) {
+            if (!far_ticks || s - tick_of[u] < far_ticks) return (uint32_t)slot[u];
+            if (far_seen[u] != s) {
+                far_seen[u] = s;
+                far_row[u] = (int32_t)far_in;
+                far_list[(size_t)s * dir.far_cap + far_in++] = far_no[u];
+            }
+            return (uint32_t)(dir.slots + 2 + (s & 1) * dir.far_cap + far_row[u]);
+        };
         int64_t row = 0;
         auto put_row = [&](uint32_t to, uint32_t cv, int32_t e, int32_t len) {
             uint32_t *x = first_unit + (size_t)(row / kLaneUnit) * (unit_bytes / 4) + 2 * (row % kLaneUnit);
@@ -483,7 +521,7 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
             x[1] = cv;
             for (int j = 0; j < width; ++j) {
                 x += 2 * kLaneUnit;
-                x[0] = j < len ? (uint32_t)slot[csr.idx[e + j]] : (uint32_t)dir.slots;
+                x[0] = j < len ? source(csr.idx[e + j]) : (uint32_t)dir.slots;
                 x[1] = j < len ? (uint32_t)csr.wt[e + j] : 0;
             }
             ++row;
@@ -498,6 +536,9 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
             verts[2 * (i - a)] = (uint32_t)order[i];
             verts[2 * (i - a) + 1] = (uint32_t)c[order[i]];
         }
+        uint32_t *out = verts + 2 * (b - a);
+        for (int32_t i = a; far_ticks && i < b; ++i)
+            if (far_no[order[i]] >= 0) *out++ = (uint32_t)slot[order[i]];
         dir.units += units;
         dir.max_chunks = std::max(dir.max_chunks, (int32_t)chunks);
         dir.max_units = std::max(dir.max_units, (int32_t)units);
@@ -507,6 +548,10 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
     std::memcpy(w.at<uint32_t>(dir.stream_off), stream.data(), 4 * stream.size());
     dir.tick_off = w.reserve(4 * tab.size());
     std::memcpy(w.at<uint32_t>(dir.tick_off), tab.data(), 4 * tab.size());
+    if (far_ticks) {
+        dir.far_off = w.reserve(4 * far_list.size());
+        std::memcpy(w.at<int32_t>(dir.far_off), far_list.data(), 4 * far_list.size());
+    }
     dir.pos_off = w.reserve(4 * (size_t)n);
     std::memcpy(w.at<int32_t>(dir.pos_off), pos.data(), 4 * (size_t)n);
     return true;

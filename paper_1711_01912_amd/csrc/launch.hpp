@@ -92,14 +92,15 @@ struct LaneCfg {
     int groups = 0;    // partitions per workgroup: 4 or 8
     int nl = 0;        // 16-byte loads per loader lane per tick
     int width = 0, word = 0;           // entries of a sub-row, bytes of a ring word (8: tables in the rounded form)
-    int nc = 0, nlw = 0, nsw = 0;      // compute, loader and store wavefronts
+    int nc = 0, nlw = 0, nsw = 0, nfw = 0;     // compute, loader, store and far wavefronts
     size_t stage_off = 0, stage_bytes = 0, tab_off = 0, ticks_off = 0, lds_bytes = 0;
 };
 // False if the graph cannot run that way under `lds_limit` bytes of LDS.
-bool lane_config(const LaneDir &db, const LaneDir &dt, int32_t k, int groups, int word_bytes, bool with_out,
-                 size_t lds_limit, LaneCfg &out);
-// Workspace: the device ids regrouped for that many partitions per workgroup, for one sweep or two.
-size_t lane_ids_bytes(int32_t n, int32_t P, int groups, int sweeps);
+bool lane_config(const LaneDir &db, const LaneDir &dt, int32_t n, int32_t k, int groups, int word_bytes, bool with_out,
+                 int64_t workgroups, size_t lds_limit, LaneCfg &out);
+// Workspace of the sweeps a call asks for (null: not that one): the device ids regrouped for that many
+// partitions per workgroup, and the far reads' copies.
+size_t lane_work_bytes(const LaneDir *db, const LaneDir *dt, int32_t n, int32_t P, int groups, int word_bytes);
 int launch_window_lanes(const SweepLaunch &sb, const SweepLaunch &st, const LaneDir &db, const LaneDir &dt,
                         const LaneCfg &cfg, bool want_b, bool want_t, uint8_t *ids, void *stream);
 

@@ -18,7 +18,7 @@
 // maximum taken over whole words, whose upper bits are the maximum of the sums.  Words are 32 bits while
 // every value is below 2^26, else 64.
 //
-// LDS: [ring, (R+2) rows of G + 1 words][4 stage slots][cost tables][tick words].  The extra word of a
+// LDS: [ring, (R+2) rows of G + 1 words, then 2 x far_cap rows][4 stage slots][cost tables][tick words].  The extra word of a
 // row spreads the rows over the banks, both for lanes that read G words of a row and for lanes that
 // read one partition's words of many rows.  Row R holds 0 (padding entries read it), row R+1 takes what
 // padding sub-rows write.
@@ -29,6 +29,13 @@
 //   compute   relax tick t; the next item's records and entries are read ahead, across the barrier
 //   stores    write tick t-1 from the ring to the outputs: along a partition's row, or along a
 //             vertex's row, as the caller asked.  The t sweep's ring holds tl + w, they take w off again.
+//   far       where the ring cannot hold every neighbour: the store wavefronts also keep a copy of the words
+//             that far reads will ask for in the workspace ([groups][numbers][G], 32 or 16 bytes together);
+//             far wavefronts load the numbers of tick t + 1 + 2X, the words of tick t + 1 + X, and write
+//             those of tick t + 1 behind the ring.  A word is copied in the iteration after its tick, every
+//             store wavefront waits each iteration until its copies of kFarWait iterations ago have
+//             reached the L2, and the fetch, past the L1, is issued X + 1 iterations before the tick that
+//             reads it: a distance of kFarWait + X + 3 ticks or more is safe, kLaneFarTicks is that.
 // A vertex with several sub-rows needs no care: words are published with LDS maxima into rows that hold
 // the device ids already.
 #include <hip/hip_runtime.h>
@@ -42,6 +49,10 @@
 namespace cpeval {
 namespace {
 
+constexpr int kFarLead = 4;      // X: ticks between the requests of a far wavefront
+constexpr int kFarWait = 8;      // iterations a copy may be on its way
+constexpr int kFarPieces = 4;    // far reads a far wavefront serves per tick: this many times 64 / G
+static_assert(kFarWait + kFarLead + 3 < kLaneFarTicks, "far reads need their distance");
 constexpr int kSlots = 4;        // stage slots: being stored, computed, read ahead, filled
 
 __device__ __forceinline__ void lds_barrier() {
@@ -62,11 +73,14 @@ struct LaneArgs {
     int32_t out64;             // outputs are 64-bit
     int64_t *cp_out;           // [P] or NULL
     const void *edge_tab, *vert_tab;
+    const int32_t *far_list;   // [T][far_cap]
+    void *far;                 // words [groups][far_count][G]
+    int32_t far_cap, far_count;
     int32_t n, P, k, T, R;
 };
 
 struct LaneShape {
-    int32_t nc, nlw, nsw;      // compute, loader and store wavefronts
+    int32_t nc, nlw, nsw, nfw; // compute, loader, store and far wavefronts
     uint32_t stage_off, stage_bytes, tab_off, ticks_off;
 };
 
@@ -91,9 +105,11 @@ __device__ __forceinline__ Word add_shifted(Word value, uint32_t x) {
     return value + ((Word)x << kLaneIdBits);
 }
 
+__device__ __forceinline__ uint32_t tick_units(uint32_t word) { return word & 0x3fffu; }
+__device__ __forceinline__ uint32_t tick_verts(uint32_t word) { return word >> 14 & 0x1ffu; }
 __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 
-template <typename Word, bool TSWEEP, int G, int W, int FORM, int NL>
+template <typename Word, bool TSWEEP, int G, int W, int FORM, int NL, bool FAR>
 __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &sh, uint8_t *lds,
                                            unsigned long long *red, int32_t grp) {
     constexpr int kDepth = 8 / NL;           // ticks a loader runs ahead of the stage, NL 16-byte loads a lane each
@@ -115,7 +131,7 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
         Tab *to = (Tab *)(lds + sh.tab_off);
         for (int i = tid; i < k * k; i += nt) to[i] = ((const Tab *)a.edge_tab)[i];
         for (int i = tid; i < k; i += nt) to[k * k + i] = ((const Tab *)a.vert_tab)[i];
-        for (int i = tid; i < 2 * VS; i += nt) ring[(size_t)R * VS + i] = 0;
+        for (int i = tid; i < (2 + 2 * a.far_cap) * VS; i += nt) ring[(size_t)R * VS + i] = 0;
         uint32_t *dst = (uint32_t *)(lds + sh.ticks_off);
         for (int i = tid; i < T + 2; i += nt) dst[i] = i < T ? a.tick_tab[i] : 0;     // two empty ticks behind the last
         if (tid < G) red[tid] = 0;
@@ -123,10 +139,56 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
     lds_barrier();                           // tables and tick words are there
     // iterations of every role's loop: the ticks, one more for the last tick's stores, rounded up
     // so that the loaders' registers can be named
-    const int N = (T + 1 + kDepth - 1) / kDepth * kDepth;
+    static_assert(4 % kDepth == 0 && kFarLead == 4, "one rounding for all");
+    const int N = (T + 1 + 3) / 4 * 4;
     const int32_t q0 = grp * G;
 
-    if (wave >= sh.nc + sh.nlw) {
+    if (FAR && wave >= sh.nc + sh.nlw + sh.nsw) {
+        // ------------------------------------------------ far wavefronts
+        constexpr int X = kFarLead;
+        const int fw = wave - sh.nc - sh.nlw - sh.nsw;
+        const int g = lane % G, cap = a.far_cap;
+        if (cap == 0) {                      // (the other sweep has far reads)
+            for (int t = -1; t < N; ++t) lds_barrier();
+        } else {
+        const Word *words_of = (const Word *)a.far + (size_t)grp * (size_t)a.far_count * G + g;
+        uint32_t lst[X][kFarPieces];
+        Word got[X][kFarPieces];
+        int row[kFarPieces];                 // (past the cap: its last row once more)
+#pragma unroll
+        for (int i = 0; i < kFarPieces; ++i) row[i] = min((fw * kFarPieces + i) * RPW + lane / G, cap - 1);
+        auto list_load = [&](int s, int r) {
+#pragma unroll
+            for (int i = 0; i < kFarPieces; ++i)
+                lst[r][i] = (uint32_t)a.far_list[(size_t)min(s, T - 1) * (size_t)cap + (size_t)row[i]];
+        };
+#pragma unroll
+        for (int j = 1; j <= X; ++j) {
+            // (a first word each, in the order of the loop: the waits for what the loop asked for earlier would
+            // otherwise have to cover a first iteration with fewer requests behind)
+#pragma unroll
+            for (int i = 0; i < kFarPieces; ++i)
+                got[j % X][i] = __hip_atomic_load(words_of, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            list_load(j + X, j % X);
+        }
+        lds_barrier();
+        for (int t0 = 0; t0 < N; t0 += X) {
+#pragma unroll
+            for (int r = 0; r < X; ++r) {
+                const int t = t0 + r, sl = (r + 1) % X;
+                lds_barrier();
+                Word *to = ring + (size_t)(R + 2 + ((t + 1) & 1) * cap) * VS + g;
+#pragma unroll
+                for (int i = 0; i < kFarPieces; ++i) to[row[i] * VS] = got[sl][i];
+#pragma unroll
+                for (int i = 0; i < kFarPieces; ++i)
+                    got[sl][i] = __hip_atomic_load(words_of + (size_t)lst[sl][i] * G, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+                list_load(t + 1 + 2 * X, sl);
+            }
+        }
+        }
+    } else if (wave >= sh.nc + sh.nlw) {
         // ------------------------------------------------ store wavefronts
         // Two pieces at a time, so that their LDS reads overlap; a piece is up to 64 outputs.
         const int sw = wave - sh.nc - sh.nlw, nsw = sh.nsw;
@@ -135,6 +197,8 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
         char *base = (char *)a.out + (size_t)q0 * (size_t)a.out_sq * (a.out64 ? 8 : 4);
         const bool by_row = a.out_sv == 1;
         uint32_t slot0 = 0;                  // of the tick being stored
+        int copied = 0;                      // numbers given to far copies so far
+        uint64_t recent = 0;                 // stores of each of the last kFarWait iterations, a byte each
         auto ring_slot = [&](int vi) {
             const uint32_t s = slot0 + (uint32_t)vi;
             return s >= (uint32_t)R ? s - (uint32_t)R : s;
@@ -165,9 +229,23 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
             if (t < 1 || t > T) continue;
             const uint32_t tick = uniform(word);
             word = words[t];                 // of the next iteration's tick
-            const int w = (int)(tick >> 16);
-            const uint2 *verts = (const uint2 *)(stage + (size_t)((t - 1) % kSlots) * sh.stage_bytes + (tick & 0xffffu) * UNIT);
-            if (by_row) {
+            const int w = (int)tick_verts(tick);
+            const uint2 *verts = (const uint2 *)(stage + (size_t)((t - 1) % kSlots) * sh.stage_bytes + tick_units(tick) * UNIT);
+            if (FAR && a.far_cap > 0) {
+                // the copies first: what is left of this iteration's stores may stay on its way
+                const int copies = (int)(tick >> 23);
+                const uint32_t *slots = (const uint32_t *)(verts + w);
+                Word *to = (Word *)a.far + ((size_t)grp * (size_t)a.far_count + (size_t)copied) * G + lane % G;
+                for (int f0 = sw * RPW; f0 < copies; f0 += nsw * RPW) {
+                    const int f = f0 + lane / G;
+                    const uint32_t slot = slots[min(f, copies - 1)];
+                    const Word x = ring[__umul24(slot, (uint32_t)VS) + lane % G];
+                    if (f < copies) __hip_atomic_store(to + (size_t)f * G, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                copied += copies;
+            }
+            if (!a.out) {
+            } else if (by_row) {
                 // along the partitions' rows: 2^wl vertices x 2^(6-wl) partitions a piece
                 const int wl = w >= 64 ? 6 : 32 - __clz(w - 1);
                 const int vl = lane & ((1 << wl) - 1), gl = lane >> wl, gs = 64 >> wl;
@@ -193,6 +271,28 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
             }
             slot0 += (uint32_t)w;
             if (slot0 >= (uint32_t)R) slot0 -= (uint32_t)R;
+            if (FAR && a.far_cap > 0) {
+                // copies of kFarWait iterations ago have arrived once no more stores are on their way than
+                // the later iterations issued (counted as the loops above issue them, or fewer)
+                uint32_t sure = (uint32_t)max(0, ((int)(tick >> 23) - sw * RPW + nsw * RPW - 1) / (nsw * RPW));
+                if (a.out && by_row) {
+                    const int gs = w >= 64 ? 1 : 64 >> (32 - __clz(w - 1));
+                    sure += (uint32_t)((w + 63) / 64 * max(0, (live - sw * gs + nsw * gs - 1) / (nsw * gs)));
+                } else if (a.out) {
+                    sure += (uint32_t)max(0, (w - sw * RPW + nsw * RPW - 1) / (nsw * RPW));
+                }
+                recent = recent << 8 | min(sure, 31u);
+                uint32_t later = 0;
+#pragma unroll
+                for (int i = 0; i < kFarWait; ++i) later += (uint32_t)(recent >> (8 * i)) & 0xffu;
+#define CP_WAIT(N)                                                                  \
+    if (later >= N) {                                                               \
+        asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory");                       \
+    } else
+                CP_WAIT(48) CP_WAIT(32) CP_WAIT(24) CP_WAIT(20) CP_WAIT(16) CP_WAIT(12) CP_WAIT(8) CP_WAIT(6) CP_WAIT(4)
+                CP_WAIT(2) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+#undef CP_WAIT
+            }
         }
     } else if (wave >= sh.nc) {
         // ------------------------------------------------ loader wavefronts
@@ -209,8 +309,8 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
         // the tick words come from LDS because a scalar load's wait is a wait for LDS too).
         auto issue = [&](int s, int r) {
             const uint32_t word = uniform(words[min(s, T - 1)]);
-            verts[r] = word >> 16;
-            const uint32_t chunks = ((word & 0xffffu) * UNIT + 8 * verts[r] + 15) / 16;
+            verts[r] = tick_verts(word);
+            const uint32_t chunks = (tick_units(word) * UNIT + 8 * verts[r] + 4 * (word >> 23) + 15) / 16;
 #pragma unroll
             for (int i = 0; i < NL; ++i) {
                 const uint32_t c = (uint32_t)((i * sh.nlw + lw) * 64 + lane);
@@ -277,7 +377,7 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
         };
         Word best = 0;
         lds_barrier();
-        int items = (int)(uniform(words[0]) & 0xffffu) / IU;
+        int items = (int)tick_units(uniform(words[0])) / IU;
         ask(item_at(0, wave));               // (past the tick's last item: stage bytes nobody uses)
         for (int t = 0; t < N; ++t) {
             lds_barrier();
@@ -310,7 +410,7 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
                 atomicMax(mine, fin);
                 best = max(best, fin);
             }
-            items = (int)(uniform(word_next) & 0xffffu) / IU;
+            items = (int)tick_units(uniform(word_next)) / IU;
         }
         if (a.cp_out) atomicMax(&red[g], (unsigned long long)(best >> kLaneIdBits));
     }
@@ -323,8 +423,8 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
 
 // Both sweeps (sweeps = 3) or one of them; workgroups of one partition group sit side by side, and an
 // XCD gets consecutive groups, so that lines of a vertex's row meet in one L2.
-template <typename Word, int G, int W, int FORM, int NL>
-__global__ __launch_bounds__(kWindowMaxWaves * 64) void window_lanes_kernel(LaneArgs b, LaneArgs t, LaneShape sh,
+template <typename Word, int G, int W, int FORM, int NL, bool FAR>
+__global__ __launch_bounds__(kWindowMaxWaves * 64, FAR && sizeof(Word) == 4 ? 8 : 4) void window_lanes_kernel(LaneArgs b, LaneArgs t, LaneShape sh,
                                                                             int32_t sweeps, int32_t total,
                                                                             int32_t per_xcd) {
     extern __shared__ uint4 lds16[];
@@ -333,8 +433,8 @@ __global__ __launch_bounds__(kWindowMaxWaves * 64) void window_lanes_kernel(Lane
     if (id >= total) return;                   // whole workgroup: no barrier has been reached yet
     const bool second = sweeps == 3 ? (id & 1) != 0 : sweeps == 2;
     const int32_t grp = sweeps == 3 ? id >> 1 : id;
-    if (second) lane_sweep<Word, true, G, W, FORM, NL>(t, sh, (uint8_t *)lds16, red, grp);
-    else lane_sweep<Word, false, G, W, FORM, NL>(b, sh, (uint8_t *)lds16, red, grp);
+    if (second) lane_sweep<Word, true, G, W, FORM, NL, FAR>(t, sh, (uint8_t *)lds16, red, grp);
+    else lane_sweep<Word, false, G, W, FORM, NL, FAR>(b, sh, (uint8_t *)lds16, red, grp);
 }
 
 // Device ids as the loaders want them: [groups][n][G] by position of either sweep, groups past the batch
@@ -368,7 +468,7 @@ __global__ __launch_bounds__(256) void group_ids_kernel(const uint8_t *__restric
     if (bad) *status = CP_STATUS_BAD_DEVICE_ID;
 }
 
-LaneArgs lane_args(const SweepLaunch &s, const LaneDir &d, const uint8_t *ids, int form) {
+LaneArgs lane_args(const SweepLaunch &s, const LaneDir &d, const uint8_t *ids, int form, uint8_t *far) {
     LaneArgs a{};
     a.stream = (const uint4 *)(s.blob + d.stream_off);
     a.tick_tab = (const uint32_t *)(s.blob + d.tick_off);
@@ -382,36 +482,44 @@ LaneArgs lane_args(const SweepLaunch &s, const LaneDir &d, const uint8_t *ids, i
     a.cp_out = s.cp_out;
     a.edge_tab = form == kMagic4 ? (const void *)s.edge_tab4 : s.edge_tab;
     a.vert_tab = form == kMagic4 ? (const void *)s.vert_tab4 : s.vert_tab;
+    a.far_list = (const int32_t *)(s.blob + d.far_off);
+    a.far = far;
+    a.far_cap = d.far_cap;
+    a.far_count = d.far_count;
     a.n = s.n; a.P = s.P; a.k = s.k; a.T = d.ticks; a.R = d.slots;
     return a;
 }
 
-template <typename Word, int G, int W, int FORM, int NL>
+template <typename Word, int G, int W, int FORM, int NL, bool FAR>
 int launch_lanes_k(const LaneArgs &b, const LaneArgs &t, const LaneCfg &cfg, int sweeps, int32_t P, hipStream_t st) {
-    auto kern = window_lanes_kernel<Word, G, W, FORM, NL>;
+    auto kern = window_lanes_kernel<Word, G, W, FORM, NL, FAR>;
     if (cfg.lds_bytes > 64 * 1024 &&
         hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)cfg.lds_bytes) !=
             hipSuccess)
         return CP_ERR_HIP;
     LaneShape sh{};
-    sh.nc = cfg.nc; sh.nlw = cfg.nlw; sh.nsw = cfg.nsw;
+    sh.nc = cfg.nc; sh.nlw = cfg.nlw; sh.nsw = cfg.nsw; sh.nfw = cfg.nfw;
     sh.stage_off = (uint32_t)cfg.stage_off;
     sh.stage_bytes = (uint32_t)cfg.stage_bytes;
     sh.tab_off = (uint32_t)cfg.tab_off;
     sh.ticks_off = (uint32_t)cfg.ticks_off;
     const int32_t total = (P + G - 1) / G * (sweeps == 3 ? 2 : 1), per_xcd = (total + 7) / 8;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3((cfg.nc + cfg.nlw + cfg.nsw) * 64), cfg.lds_bytes, st,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3((cfg.nc + cfg.nlw + cfg.nsw + cfg.nfw) * 64), cfg.lds_bytes, st,
                        b, t, sh, (int32_t)sweeps, total, per_xcd);
     return hipGetLastError() == hipSuccess ? CP_OK : CP_ERR_HIP;
 }
 
+template <typename Word, int G, int W, int FORM>
+int launch_lanes_n(const LaneArgs &b, const LaneArgs &t, const LaneCfg &cfg, int sweeps, int32_t P, hipStream_t st) {
+    if (cfg.nfw > 0) return launch_lanes_k<Word, G, W, FORM, 2, true>(b, t, cfg, sweeps, P, st);
+    return cfg.nl == 4 ? launch_lanes_k<Word, G, W, FORM, 4, false>(b, t, cfg, sweeps, P, st)
+                       : launch_lanes_k<Word, G, W, FORM, 2, false>(b, t, cfg, sweeps, P, st);
+}
+
 template <typename Word, int G, int FORM>
 int launch_lanes_g(const LaneArgs &b, const LaneArgs &t, const LaneCfg &cfg, int sweeps, int32_t P, hipStream_t st) {
-    if (cfg.width == 2)
-        return cfg.nl == 4 ? launch_lanes_k<Word, G, 2, FORM, 4>(b, t, cfg, sweeps, P, st)
-                           : launch_lanes_k<Word, G, 2, FORM, 2>(b, t, cfg, sweeps, P, st);
-    return cfg.nl == 4 ? launch_lanes_k<Word, G, 4, FORM, 4>(b, t, cfg, sweeps, P, st)
-                       : launch_lanes_k<Word, G, 4, FORM, 2>(b, t, cfg, sweeps, P, st);
+    return cfg.width == 2 ? launch_lanes_n<Word, G, 2, FORM>(b, t, cfg, sweeps, P, st)
+                          : launch_lanes_n<Word, G, 4, FORM>(b, t, cfg, sweeps, P, st);
 }
 
 template <typename Word, int FORM>
@@ -422,37 +530,59 @@ int launch_lanes_w(const LaneArgs &b, const LaneArgs &t, const LaneCfg &cfg, int
 
 }  // namespace
 
-bool lane_config(const LaneDir &db, const LaneDir &dt, int32_t k, int groups, int word_bytes, bool with_out,
-                 size_t lds_limit, LaneCfg &out) {
+bool lane_config(const LaneDir &db, const LaneDir &dt, int32_t n, int32_t k, int groups, int word_bytes, bool with_out,
+                 int64_t workgroups, size_t lds_limit, LaneCfg &out) {
     const size_t static_lds = 512;
-    const size_t G = (size_t)groups, rows = (size_t)std::max(db.slots, dt.slots) + 2;
+    const size_t G = (size_t)groups, rows = (size_t)std::max(db.slots + 2 * db.far_cap, dt.slots + 2 * dt.far_cap) + 2;
     const int chunks = std::max(db.max_chunks, dt.max_chunks), verts = std::max(db.max_verts, dt.max_verts);
     if (db.width != dt.width) return false;
     LaneCfg c;
     c.groups = groups;
     c.width = db.width;
     c.word = word_bytes;
+    const int far_cap = std::max(db.far_cap, dt.far_cap);
+    c.nfw = far_cap > 0 ? (far_cap * groups / 64 + kFarPieces - 1) / kFarPieces : 0;
     // wide ticks: fewer loaders with more loads each, which need not run as far ahead
-    c.nl = chunks > 256 ? 4 : 2;
+    c.nl = chunks > 256 && c.nfw == 0 ? 4 : 2;
     c.nlw = std::max((verts + 63) / 64, (chunks + 64 * c.nl - 1) / (64 * c.nl));
     if (c.nlw > 8) return false;
-    const double verts_avg = (double)db.max_verts, units = std::max(db.max_units, dt.max_units);
-    c.nsw = with_out ? std::max(1, std::min(4, (int)std::ceil(verts_avg * groups / 64 / 6))) : 0;
-    c.nc = std::max(1, std::min({kWindowMaxWaves - c.nlw - c.nsw, (int)std::ceil(units * groups / 8)}));
     c.stage_off = align_up(rows * (G + 1) * (size_t)word_bytes, 16);
     c.stage_bytes = (size_t)c.nlw * c.nl * 1024;
     c.tab_off = c.stage_off + kSlots * c.stage_bytes;
     // a wavefront without items still reads the place of its first one: stage bytes, or what lies behind them
     c.ticks_off = c.tab_off + sizeof(Magic) * ((size_t)k * k + k);
-    const size_t reach = c.tab_off + (size_t)(c.nc + 1) * (8 / groups) * lane_unit_bytes(c.width);
+    const size_t reach = c.tab_off + (size_t)(kWindowMaxWaves + 1) * (8 / groups) * lane_unit_bytes(c.width);
     c.lds_bytes = std::max(c.ticks_off + 4 * ((size_t)std::max(db.ticks, dt.ticks) + 2), reach);
     if (c.lds_bytes + static_lds > lds_limit || rows * (G + 1) >= (1u << 24)) return false;
+    // Workgroups that will share a compute unit share its 32 wavefronts (24 with far reads and 64-bit
+    // words).  Compute wavefronts for half of an average tick's items, store wavefronts for two pieces of
+    // its outputs each: more of either only adds idle instructions to a unit that is short of issue slots
+    // (19,800 vertices, 4,096 partitions: 5 + 1 of them 2.11 ms, 3 + 2 1.59 ms; 29,000 vertices with 64-bit
+    // words: 11 + 2 of them 325 us, 4 + 3 285 us).
+    const int waves = far_cap > 0 && word_bytes == 8 ? 24 : 32;
+    const int share = (int)std::max<int64_t>(1, std::min<int64_t>((workgroups + 255) / 256,
+                                                                  (int64_t)(kLdsBudget / (c.lds_bytes + static_lds))));
+    const int most = std::min(kWindowMaxWaves, std::max(waves / share, c.nlw + c.nfw + 2));
+    const double ticks = (double)std::min(db.ticks, dt.ticks);
+    const int outs = (int)std::ceil((double)n / ticks * groups / 64 / 2);
+    const int items = (int)std::ceil((double)std::max(db.units, dt.units) / ticks * groups / 8 * 0.55);
+    c.nsw = with_out || far_cap > 0 ? std::max(1, std::min({4, outs, most - c.nlw - c.nfw - 1})) : 0;
+    c.nc = std::max(1, std::min(most - c.nlw - c.nsw - c.nfw, items));
     out = c;
     return true;
 }
 
-size_t lane_ids_bytes(int32_t n, int32_t P, int groups, int sweeps) {
-    return (size_t)sweeps * align_up((size_t)((P + groups - 1) / groups) * groups * (size_t)n);
+size_t lane_ids_bytes(int32_t n, int32_t P, int groups) {
+    return align_up((size_t)((P + groups - 1) / groups) * groups * (size_t)n);
+}
+
+size_t lane_work_bytes(const LaneDir *db, const LaneDir *dt, int32_t n, int32_t P, int groups, int word_bytes) {
+    size_t bytes = 0;
+    for (const LaneDir *d : {db, dt})
+        if (d)
+            bytes += lane_ids_bytes(n, P, groups) +
+                     align_up((size_t)((P + groups - 1) / groups) * groups * (size_t)d->far_count * (size_t)word_bytes);
+    return bytes;
 }
 
 int launch_window_lanes(const SweepLaunch &sb, const SweepLaunch &st, const LaneDir &db, const LaneDir &dt,
@@ -462,7 +592,10 @@ int launch_window_lanes(const SweepLaunch &sb, const SweepLaunch &st, const Lane
     const int sweeps = (want_b ? 1 : 0) | (want_t ? 2 : 0);
     if (grid.y > 65535 || sweeps == 0) return CP_ERR_ARG;
     uint8_t *ids_b = want_b ? ids : nullptr;
-    uint8_t *ids_t = want_t ? ids + (want_b ? lane_ids_bytes(sb.n, sb.P, cfg.groups, 1) : 0) : nullptr;
+    uint8_t *ids_t = want_t ? ids + (want_b ? lane_ids_bytes(sb.n, sb.P, cfg.groups) : 0) : nullptr;
+    uint8_t *far_b = ids + (size_t)(want_b + want_t) * lane_ids_bytes(sb.n, sb.P, cfg.groups);
+    uint8_t *far_t = far_b + (want_b ? lane_work_bytes(&db, nullptr, sb.n, sb.P, cfg.groups, cfg.word) -
+                                           lane_ids_bytes(sb.n, sb.P, cfg.groups) : 0);
     const int32_t *pos_b = (const int32_t *)(sb.blob + db.pos_off), *pos_t = (const int32_t *)(sb.blob + dt.pos_off);
 #define CP_GROUP(G)                                                                                           \
     hipLaunchKernelGGL(group_ids_kernel<G>, grid, block, 0, hs, sb.assign, sb.a_stride_p, sb.a_stride_v, sb.n, \
@@ -473,7 +606,7 @@ int launch_window_lanes(const SweepLaunch &sb, const SweepLaunch &st, const Lane
 #undef CP_GROUP
     if (hipGetLastError() != hipSuccess) return CP_ERR_HIP;
     const int form = cfg.word == 8 ? kRound8 : (sb.edge_tab4 ? kMagic4 : kMagic8);
-    const LaneArgs b = lane_args(sb, db, ids_b, form), t = lane_args(st, dt, ids_t, form);
+    const LaneArgs b = lane_args(sb, db, ids_b, form, far_b), t = lane_args(st, dt, ids_t, form, far_t);
     if (form == kRound8) return launch_lanes_w<unsigned long long, kRound8>(b, t, cfg, sweeps, sb.P, hs);
     if (form == kMagic4) return launch_lanes_w<uint32_t, kMagic4>(b, t, cfg, sweeps, sb.P, hs);
     return launch_lanes_w<uint32_t, kMagic8>(b, t, cfg, sweeps, sb.P, hs);

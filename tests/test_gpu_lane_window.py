@@ -81,6 +81,28 @@ def test_64_bit_ticks_of_a_small_graph_and_the_perceptron(gpu, oracle):
     _check(gpu, oracle, make_workload("mlp", P=70))
 
 
+@pytest.mark.parametrize("widths,P,far", [([30] * 120, 37, "all"), ([50, 3] * 60, 9, "all"), ([30] * 120, 8, "few")])
+def test_neighbours_too_far_back_for_the_ring(gpu, oracle, widths, P, far):
+    """Every vertex of the first half also feeds its mirror image in the second half; the ring holds neither sweep."""
+    rng = np.random.default_rng(len(widths) + P)
+    n, level, src, dst = random_layered_dag(rng, widths, 1, 3, 2)
+    x = np.arange(n // 2)
+    if far == "few":                              # a long edge here and there, ticks without any between
+        x = x[::97]
+    x = x[level[n - 1 - x] > level[x]]
+    src, dst = np.concatenate([src, x]), np.concatenate([dst, n - 1 - x])
+    w = T._custom("far", n, src, dst, rng.integers(0, 300, len(src)), rng.integers(0, 50, n), rng.integers(1, 9, 5),
+                  rng.integers(1, 20, (5, 5)), rng.integers(0, 5, (P, n), dtype=np.uint8), level)
+    _check(gpu, oracle, w)
+
+
+def test_far_reads_of_the_modules_and_with_64_bit_words(gpu, oracle):
+    _check(gpu, oracle, make_workload("inception", P=11))
+    w = make_workload("inception", P=9, modules=12)
+    w.succ_t[:] = w.succ_t * 1000
+    _check(gpu, oracle, w)
+
+
 def test_bad_device_id_and_refusals(gpu):
     import torch
     w = _case(3, [9] * 12, 3, 3, 5, 20)
