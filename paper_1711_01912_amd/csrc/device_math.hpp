@@ -53,4 +53,15 @@ __device__ __forceinline__ long long dpp_i64(long long x) {
     return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
+// The smallest x of the wavefront, the same in every lane: rows of 16 by register permutations, the four rows'
+// minima through scalar registers.
+__device__ __forceinline__ uint32_t min_over_wave(uint32_t x) {
+    x = min(x, dpp_u32<0xB1>(x));
+    x = min(x, dpp_u32<0x4E>(x));
+    x = min(x, dpp_u32<0x141>(x));
+    x = min(x, dpp_u32<0x140>(x));
+    return min(min((uint32_t)__builtin_amdgcn_readlane((int)x, 0), (uint32_t)__builtin_amdgcn_readlane((int)x, 16)),
+               min((uint32_t)__builtin_amdgcn_readlane((int)x, 32), (uint32_t)__builtin_amdgcn_readlane((int)x, 48)));
+}
+
 }  // namespace cpeval

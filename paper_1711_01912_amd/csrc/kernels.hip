@@ -389,6 +389,8 @@ __global__ __launch_bounds__(256) void transpose_ticks_kernel(const T *__restric
 
 // ---------------------------------------------------------------- one critical path
 
+constexpr int kPathThreads = 256;
+
 struct PathArgs {
     const int32_t *ptr;      // successor CSR over original ids
     const int32_t *idx;
@@ -415,10 +417,13 @@ struct PathArgs {
 // successor u with b(v) = w(v) + x(v->u) + b(u), lanes across the successors.
 // With LDS_TAB the k*k + k table entries are staged in LDS first (one dependent
 // global load less per step of the walk).
+// The workgroup's wavefronts look for the start together, eight sources in flight per lane; the first one walks.
+// (One wavefront with one source in flight per lane spent more on 10,000 sources than on the walk.)
 template <typename Tick, typename WT, bool MAGIC, bool LDS_TAB>
-__global__ __launch_bounds__(64) void critical_path_kernel(PathArgs a) {
+__global__ __launch_bounds__(kPathThreads) void critical_path_kernel(PathArgs a) {
     extern __shared__ __align__(16) uint64_t path_lds[];
-    const int lane = threadIdx.x;
+    __shared__ uint32_t starts[kPathThreads / 64];
+    const int lane = threadIdx.x & 63, tid = threadIdx.x, nt = blockDim.x;
     const int32_t q = blockIdx.x;
     const int32_t k = a.k;
     const Tick *b = (const Tick *)a.b + (int64_t)q * a.b_sq;
@@ -429,24 +434,34 @@ __global__ __launch_bounds__(64) void critical_path_kernel(PathArgs a) {
     const void *etab = a.edge_tab, *vtab = a.vert_tab;
     if (LDS_TAB) {
         const uint64_t *ge = (const uint64_t *)a.edge_tab, *gv = (const uint64_t *)a.vert_tab;
-        for (int i = lane; i < k * k; i += 64) path_lds[i] = ge[i];
-        for (int i = lane; i < k; i += 64) path_lds[k * k + i] = gv[i];
-        __syncthreads();
+        for (int i = tid; i < k * k; i += nt) path_lds[i] = ge[i];
+        for (int i = tid; i < k; i += nt) path_lds[k * k + i] = gv[i];
         etab = path_lds;
         vtab = path_lds + k * k;
     }
     const Magic *etab_m = (const Magic *)etab, *vtab_m = (const Magic *)vtab;
     const int64_t *etab_g = (const int64_t *)etab, *vtab_g = (const int64_t *)vtab;
     int32_t *path = a.path + (int64_t)q * a.max_len;
-    for (int i = lane; i < a.max_len; i += 64) path[i] = -1;
+    for (int i = tid; i < a.max_len; i += nt) path[i] = -1;
 
     const long long cpq = a.cp[q];
-    int32_t v = 0x7fffffff;
-    for (int32_t i = lane; i < a.nsrc; i += 64) {
-        const int32_t s = a.sources[i];
-        if ((long long)b[(int64_t)s * bsv] == cpq) v = min(v, s);
+    uint32_t low = 0x7fffffff;
+    for (int32_t i = tid; i < a.nsrc; i += 8 * nt) {
+        int32_t src[8];
+        long long bs[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) src[j] = a.sources[min(i + j * nt, a.nsrc - 1)];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) bs[j] = (long long)b[(int64_t)src[j] * bsv];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) low = bs[j] == cpq ? min(low, (uint32_t)src[j]) : low;
     }
-    for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off));
+    low = min_over_wave(low);
+    if (lane == 0) starts[tid >> 6] = low;
+    __syncthreads();                         // (the tables are in LDS, and the row is cleared, too)
+    if (tid >= 64) return;
+    for (int i = 1; i < nt >> 6; ++i) low = min(low, starts[i]);
+    int32_t v = (int32_t)low;
 
     // What the walk needs of the current vertex: its device, c, b and row bounds.  For the
     // start they are loaded here; afterwards every lane fetches them for the successor it
@@ -491,17 +506,18 @@ __global__ __launch_bounds__(64) void critical_path_kernel(PathArgs a) {
                 next = u; n_p = pu_raw; n_c = cu; n_b = bu; n_e0 = u0; n_e1 = u1;
             }
         }
-        int32_t best = next;
-        for (int off = 32; off > 0; off >>= 1) best = min(best, __shfl_xor(best, off));
-        if (best != 0x7fffffff) {
-            const int from = __ffsll((long long)__ballot(next == best)) - 1;
-            pv = __shfl(n_p, from);
-            cv = (WT)__shfl(n_c, from);
-            bv = (Tick)__shfl(n_b, from);
-            e0 = __shfl(n_e0, from);
-            e1 = __shfl(n_e1, from);
+        // (register permutations and scalar reads: six shuffles and five broadcasts through LDS were a third
+        // of a step)
+        const uint32_t best = min_over_wave((uint32_t)next);
+        if (best != 0x7fffffffu) {
+            const int from = __ffsll((long long)__ballot((uint32_t)next == best)) - 1;
+            pv = wave_bcast<uint32_t>(n_p, from);
+            cv = wave_bcast<WT>(n_c, from);
+            bv = wave_bcast<Tick>(n_b, from);
+            e0 = wave_bcast<int32_t>(n_e0, from);
+            e1 = wave_bcast<int32_t>(n_e1, from);
         }
-        v = best;
+        v = (int32_t)best;
     }
     if (bad_id) *a.status = CP_STATUS_BAD_DEVICE_ID;
     if (lane == 0) a.len[q] = len;
@@ -1481,14 +1497,12 @@ int launch_critical_path(const SweepLaunch &s, const int32_t *sources, int32_t n
     hipStream_t st = (hipStream_t)stream;
     const bool lds_tab = s.k <= kMagicMaxK;
     const size_t lds = lds_tab ? ((size_t)s.k * s.k + s.k) * 8 : 0;
-#define CP_PATH(TICK, WT, MAGIC)                                                                           \
-    do {                                                                                                   \
-        if (lds_tab)                                                                                       \
-            hipLaunchKernelGGL((critical_path_kernel<TICK, WT, MAGIC, true>), dim3((unsigned)s.P), dim3(64), \
-                               lds, st, a);                                                                \
-        else                                                                                               \
-            hipLaunchKernelGGL((critical_path_kernel<TICK, WT, MAGIC, false>), dim3((unsigned)s.P),        \
-                               dim3(64), 0, st, a);                                                        \
+    // one wavefront where that many sources leave the others nothing to do
+    const dim3 grid((unsigned)s.P), block((unsigned)(nsrc > 512 ? kPathThreads : 64));
+#define CP_PATH(TICK, WT, MAGIC)                                                                            \
+    do {                                                                                                    \
+        if (lds_tab) hipLaunchKernelGGL((critical_path_kernel<TICK, WT, MAGIC, true>), grid, block, lds, st, a); \
+        else hipLaunchKernelGGL((critical_path_kernel<TICK, WT, MAGIC, false>), grid, block, 0, st, a);      \
     } while (0)
     if (s.tick_bytes == 4) {
         if (s.magic) CP_PATH(int32_t, uint32_t, true);
