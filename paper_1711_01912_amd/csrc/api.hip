@@ -1121,6 +1121,7 @@ int cp_simulate(const cp_graph *g, int32_t batch, int32_t k,
     s.pct = plan.pct;
     s.n = p.n; s.P = batch; s.k = k;
     s.window = (uint32_t)window;
+    s.max_in_degree = p.info.max_in_degree;
     // One partition per wavefront until the batch alone fills the GPU several times over (8,192
     // wavefronts are 8 per SIMD); past that, partitions with few devices share a wavefront.
     s.groups = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kWave / k, batch / 8192));
