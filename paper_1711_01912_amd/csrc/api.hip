@@ -288,6 +288,7 @@ bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, int32_t ba
     bool found = false;
     for (int groups : {4, 8}) {
         LaneCfg c;
+        if (((int64_t)batch + groups - 1) / groups > 65535) continue;        // the grid's second dimension
         if (!lane_config(p.lane_b, p.lane_t, p.n, k, groups, word, with_out,
                          ((int64_t)batch + groups - 1) / groups * sweeps, lds_limit, c)) continue;
         const double us = std::max(lane_sweep_us(p.lane_b, c, batch, sweeps), lane_sweep_us(p.lane_t, c, batch, sweeps));
@@ -568,6 +569,10 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
             if (window_us - mask_us <= column_plan_us(p, batch, (size_t)tick_dtype)) use = wplan;
         }
     }
+    // CP without its b array needs a window sweep's running maximum: what AUTO refuses does not hang on the cost
+    // rule and the workspace size that decide on the lane-window plan below
+    if (plan == CP_PLAN_AUTO && cp_out && !blevel_out && (use == CP_PLAN_WAVE_COLUMN || p.win_b.far_cap > 0))
+        return CP_ERR_ARG;
     // several partitions in the lanes of a workgroup, both sweeps in one launch
     LaneCfg lane_cfg;
     const int lane_sweeps = ((blevel_out || cp_out) ? 1 : 0) + (tlevel_out ? 1 : 0);

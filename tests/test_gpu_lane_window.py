@@ -119,3 +119,36 @@ def test_bad_device_id_and_refusals(gpu):
     assert e.value.code == -12
     g.close()
     g2.close()
+
+
+def test_batches_past_the_grid(gpu, oracle):
+    """More groups of eight than a grid's second dimension takes: refused by name, still evaluated under AUTO."""
+    w = _case(6, [2] * 4, 2, 2, 3, 8 * 65535 + 1)
+    g = gpu.CpGraph.from_workload(w, device="cuda:0")
+    import torch
+    a = torch.from_numpy(w.assignments).to("cuda:0")
+    with pytest.raises(gpu.CpError) as e:
+        gpu.cp_eval(g, a, w.speeds, w.bandwidth, plan=gpu.PLAN_LANE_WINDOW)
+    assert e.value.code == -12
+    from gpu_util import assert_equal_to_oracle, run_gpu
+    assert_equal_to_oracle(run_gpu(w, gpu.PLAN_AUTO, graph=g, out_layout=1), oracle.evaluate_workload(w, threads=8), "auto")
+    g.close()
+
+
+@pytest.mark.parametrize("P", [3, 300])
+@pytest.mark.parametrize("which", ["far", "column"])
+def test_cp_without_b_stays_refused_under_auto(gpu, oracle, which, P, monkeypatch):
+    """Where the plan beside the lanes needs b for CP, AUTO refuses CP alone whatever it would take; the binding adds b."""
+    from gpu_util import run_gpu
+    w = make_workload("inception", P=P) if which == "far" else _case(7, [9] * 12, 3, 3, 5, P, t_hi=2 ** 31)
+    g = gpu.CpGraph.from_workload(w, device="cuda:0")
+    ref = oracle.evaluate_workload(w, threads=8)["cp"]
+    assert np.array_equal(run_gpu(w, gpu.PLAN_AUTO, want=("cp",), graph=g)["cp"], ref)
+    from paper_1711_01912_amd import binding
+    info = dict(g.info, window_far_b=0)
+    monkeypatch.setattr(binding.CpGraph, "info", property(lambda self: info))
+    monkeypatch.setattr(binding, "choose_plan", lambda *a: gpu.PLAN_RESIDENT_WINDOW)
+    with pytest.raises(gpu.CpError) as e:
+        run_gpu(w, gpu.PLAN_AUTO, want=("cp",), graph=g)
+    assert e.value.code == -12
+    g.close()
