@@ -71,7 +71,7 @@ __global__ void table_write_kernel(TableChunk chunk, uint64_t *dst, int32_t coun
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < count) dst[i] = chunk.v[i];
     if (cp_out)
-        for (int j = i; j < batch; j += gridDim.x * blockDim.x) cp_out[j] = 0;
+        for (int64_t j = i; j < batch; j += (int64_t)gridDim.x * blockDim.x) cp_out[j] = 0;
     if (status && i == 0) *status = CP_STATUS_OK;
 }
 
@@ -91,8 +91,9 @@ int prepare_call(const void *src, size_t entries, void *dst, int64_t *cp_out, in
         TableChunk chunk;
         const int32_t count = (int32_t)std::min<size_t>(kTableChunkWords, entries - at);
         std::memcpy(chunk.v, from + at, (size_t)count * 8);
-        hipLaunchKernelGGL(table_write_kernel, dim3((count + 255) / 256), dim3(256), 0, st, chunk, to + at, count,
-                           at ? nullptr : cp_out, batch, at ? nullptr : status);
+        const bool clears = at == 0;
+        hipLaunchKernelGGL(table_write_kernel, dim3(prepare_blocks(count, clears && cp_out ? batch : 0)), dim3(256), 0, st,
+                           chunk, to + at, count, clears ? cp_out : nullptr, batch, clears ? status : nullptr);
     }
     return hipGetLastError() == hipSuccess ? CP_OK : CP_ERR_HIP;
 }

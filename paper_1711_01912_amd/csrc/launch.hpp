@@ -87,6 +87,14 @@ struct StreamCfg {
 bool stream_config(const WindowDir &d, int32_t k, size_t lds_limit, bool with_mask, StreamCfg &out);
 int launch_window_stream(const SweepLaunch &s, const StreamCfg &cfg, void *stream);
 
+// Workgroups of 256 threads of the launch that writes `words` table entries and clears `cells` CP values:
+// a thread per cell, up to kPrepareBlocks workgroups.
+constexpr int kPrepareBlocks = 2048;
+inline unsigned prepare_blocks(int32_t words, int32_t cells) {
+    return (unsigned)std::max<int64_t>({1, ((int64_t)words + 255) / 256,
+                                        std::min<int64_t>(kPrepareBlocks, ((int64_t)cells + 255) / 256)});
+}
+
 // Launch shape of the lane-window kernel, the same for both sweeps.
 struct LaneCfg {
     int groups = 0;    // partitions per workgroup: 4 or 8
