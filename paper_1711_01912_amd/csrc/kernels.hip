@@ -133,26 +133,17 @@ struct ColumnArgs {
     const void *vert_tab;   // Magic[k] or int64[k]
     int32_t *status;
     int32_t P, ncol, k, count;
-    int32_t parts, part_rows, part_blocks;   // see column_task
+    ColumnDeal deal;
 };
 
-// Which row and which 64 partitions a wavefront takes.  Blocks go round the 8 XCDs; a level's values for 64
-// partitions are a slice that an L2 can hold (10,000 vertices: 3.2 MB with the device ids), the level's
-// values for all partitions are not.  So an XCD works through its slices one after the other, all rows of one
-// before the next: the slices are dealt to the XCDs, cut into `parts` runs of rows where their number is
-// not a multiple of 8.  20 levels of 10,000 vertices, 1,024 partitions: 4.60 -> 4.36 ms per call, the
-// unconditional maximum in the inner loop included (neighbouring blocks took neighbouring slices before).
-// What bounds the kernel is vector issue: some sixteen instructions per neighbour in the t sweep, three of
-// them 64-bit products of four cycles each.
+// Which row and which 64 partitions a wavefront takes (column_place, launch.hpp).  What bounds the kernel is vector
+// issue: some sixteen instructions per neighbour in the t sweep, three of them 64-bit products of four cycles each;
+// leaving the maximum in its inner loop without a condition took 2 - 6 % off every batch.
 template <int ROWS>
 __device__ __forceinline__ bool column_task(const ColumnArgs &a, int wave, int32_t &vi, int32_t &col) {
-    const int32_t i = (int32_t)(blockIdx.x / 8);
-    const int32_t unit = i / a.part_blocks * 8 + (int32_t)(blockIdx.x % 8);
-    const int32_t row = i % a.part_blocks * ROWS + (ROWS > 1 ? wave : 0);
-    col = unit / a.parts;
-    vi = unit % a.parts * a.part_rows + row;
-    const bool live = row < a.part_rows && vi < a.count;
-    if (!live) vi = 0;
+    column_place((int32_t)blockIdx.x, ROWS > 1 ? wave : 0, a.deal, a.ncol, ROWS, vi, col);
+    const bool live = vi < a.count && col < a.ncol;
+    if (!live) vi = col = 0;
     return live;
 }
 
@@ -1135,13 +1126,11 @@ int launch_column_sweep_t(const SweepLaunch &s, hipStream_t st, int32_t *launche
     a.status = s.status;
     a.P = s.P; a.ncol = ncol; a.k = s.k;
     const int4 *rows = (const int4 *)(s.blob + dir.rows_off);
-    // units = slices x parts, a multiple of 8 (see column_task); returns the blocks of a launch
-    a.parts = ncol % 8 == 0 ? 1 : (ncol % 4 == 0 ? 2 : (ncol % 2 == 0 ? 4 : 8));
-    auto deal = [&](int32_t count, int rows_per_block) {
-        a.count = count;
-        a.part_rows = (count + a.parts - 1) / a.parts;
-        a.part_blocks = (a.part_rows + rows_per_block - 1) / rows_per_block;
-        return (int64_t)ncol * a.parts * a.part_blocks;
+    auto deal = [&](int32_t rows, int rows_per_block) {
+        a.count = rows;
+        a.deal = column_deal(rows, ncol, rows_per_block,
+                             column_by_slices(rows, ncol, (int)sizeof(Tick), (double)s.m / std::max(s.n, 1)));
+        return column_blocks(a.deal, rows, ncol, rows_per_block);
     };
     int32_t count = 0;
     for (int l = 0; l < L; ++l) {
