@@ -277,12 +277,12 @@ double crowded_window_sweep_us(const WindowDir &d, const WindowCfg &c, int32_t b
 }
 
 // The cheapest shape for this batch: true and its time if the lane-window kernel applies.
-bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, int32_t batch, int tick_bytes, bool with_out,
-                  bool by_partition, int sweeps, size_t lds_limit, LaneCfg &out, double *us_out) {
+bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, const int64_t *speeds, const int64_t *bandwidth,
+                  int32_t batch, int tick_bytes, bool with_out, bool by_partition, int sweeps, size_t lds_limit, LaneCfg &out, double *us_out) {
     if (!p.have_lanes || k > kMagicMaxK) return false;
     // the multiply-shift forms go with 32-bit ring words, the rounded form with 64-bit ones
     const int word = p.lane_word == 4 && tabs.magic_ok ? 4 : 8;
-    if (word == 8 && !tabs.round_ok) return false;
+    if (word == 8 && !round_fits(k, speeds, bandwidth, p.info.max_c, p.info.max_t)) return false;
     // the outputs of a group are addressed with 32-bit offsets
     const uint64_t span = (uint64_t)p.n * (by_partition ? 32 : (uint64_t)batch) * (uint64_t)tick_bytes;
     if (with_out && span >= (1ull << 32)) return false;
@@ -306,11 +306,11 @@ size_t tables_bytes(int32_t k) { return align_up(table_words(k) * 8); }
 
 // One call's tables as they lie in device memory: the 8-byte entries (multiply-shift constants,
 // or plain divisors), then, where they exist, the 4-byte entries.
-std::vector<uint64_t> table_image(const CostTables &tabs, int32_t k, bool round) {
+std::vector<uint64_t> table_image(const CostTables &tabs, int32_t k, const std::vector<Magic> &round) {
     std::vector<uint64_t> img(table_words(k), 0);
     const size_t entries = table_entries(k);
-    const void *from = round ? (const void *)tabs.round.data()
-                             : (tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data());
+    const void *from = !round.empty() ? (const void *)round.data()
+                                      : (tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data());
     std::memcpy(img.data(), from, entries * 8);
     if (tabs.tab4_ok) std::memcpy(img.data() + entries, tabs.tab4.data(), entries * 4);
     return img;
@@ -581,7 +581,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     size_t lane_work = 0;
     if ((plan == CP_PLAN_AUTO || plan == CP_PLAN_LANE_WINDOW) && lane_sweeps > 0) {
         double lane_us = 0.0;
-        lanes = choose_lanes(p, tabs, k, batch, tick_dtype, blevel_out || tlevel_out,
+        lanes = choose_lanes(p, tabs, k, speeds, bandwidth, batch, tick_dtype, blevel_out || tlevel_out,
                              out_layout == CP_OUT_PARTITION_MAJOR, lane_sweeps,
                              device_window_lds_limit(), lane_cfg, &lane_us);
         if (lanes)
@@ -690,7 +690,14 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
 
     // ---- stage: prep
     CP_MARK(CP_STAGE_PREP);
-    const std::vector<uint64_t> tab_img = table_image(tabs, k, lanes && lane_cfg.word == 8);
+    std::vector<uint64_t> tab_img;
+    try {
+        std::vector<Magic> round;
+        if (lanes && lane_cfg.word == 8) build_round_table(k, speeds, bandwidth, round);
+        tab_img = table_image(tabs, k, round);
+    } catch (const std::bad_alloc &) {
+        return CP_ERR_ALLOC;
+    }
     rc = prepare_call(tab_img.data(), tab_img.size(), d_tab, cp_out, batch, status_out, st, tables_by_kernel);
     if (rc) return rc;
     const uint8_t *pT = assignments;

@@ -39,16 +39,6 @@ bool magic4_for(int64_t d, int64_t amax, uint32_t &out) {
     return true;
 }
 
-// The rounded form: floor(N * floor(2^32/d) / 2^32) is the quotient or one less, since
-// N * (2^32/d - floor(2^32/d)) < 2^32; the remainder tells.  2^32/1 does not fit: 2^32 - 1 is one less
-// than it, and the same argument holds (N * 1 < 2^32).
-bool round_for(int64_t d, int64_t amax, Magic &out) {
-    if (d < 1 || d >= (int64_t)1 << 32 || (uint64_t)amax + (uint64_t)d - 1 >= (1ull << 32)) return false;
-    out.mul = (uint32_t)std::min<uint64_t>((1ull << 32) / (uint64_t)d, 0xffffffffull);
-    out.dm1 = (uint32_t)(d - 1);
-    return true;
-}
-
 }  // namespace
 
 int build_cost_tables(int32_t k, const int64_t *speeds, const int64_t *bandwidth,
@@ -65,8 +55,6 @@ int build_cost_tables(int32_t k, const int64_t *speeds, const int64_t *bandwidth
     out.magic.assign(table_entries(k), Magic{0, 0});
     out.tab4.assign(table_entries(k), 0u);
     bool ok = narrow && k <= kMagicMaxK;
-    bool okr = ok;
-    out.round.assign(table_entries(k), Magic{0, 0xffffffffu});
     // a free transfer's entry 0 multiplies by 255: 0 ticks only while the volume is below 2^24
     bool ok4 = ok && max_t < ((int64_t)1 << 24) && max_c < ((int64_t)1 << 24);
 
@@ -81,21 +69,42 @@ int build_cost_tables(int32_t k, const int64_t *speeds, const int64_t *bandwidth
             out.divisor[kk + (size_t)own * k + nbr] = dt;
             if (ok) ok = magic_for(db, max_t, out.magic[(size_t)own * k + nbr]);
             if (ok) ok = magic_for(dt, max_t, out.magic[kk + (size_t)own * k + nbr]);
-            if (okr) okr = round_for(db, max_t, out.round[(size_t)own * k + nbr]);
-            if (okr) okr = round_for(dt, max_t, out.round[kk + (size_t)own * k + nbr]);
             if (ok4) ok4 = magic4_for(db, max_t, out.tab4[(size_t)own * k + nbr]);
             if (ok4) ok4 = magic4_for(dt, max_t, out.tab4[kk + (size_t)own * k + nbr]);
         }
     for (int i = 0; i < k; ++i) {
         out.divisor[2 * kk + i] = speeds[i];
         if (ok) ok = magic_for(speeds[i], max_c, out.magic[2 * kk + i]);
-        if (okr) okr = round_for(speeds[i], max_c, out.round[2 * kk + i]);
         if (ok4) ok4 = magic4_for(speeds[i], max_c, out.tab4[2 * kk + i]);
     }
     out.magic_ok = ok;
-    out.round_ok = okr;
     out.tab4_ok = ok && ok4;
     return CP_OK;
+}
+
+bool round_fits(int32_t k, const int64_t *speeds, const int64_t *bandwidth, int64_t max_c, int64_t max_t) {
+    auto fits = [](int64_t d, int64_t amax) { return d < (int64_t)1 << 32 && (uint64_t)amax + (uint64_t)d - 1 < (1ull << 32); };
+    for (int i = 0; i < k; ++i) {
+        if (!fits(speeds[i], max_c)) return false;
+        for (int j = 0; j < k; ++j)
+            if (i != j && !fits(bandwidth[(size_t)i * k + j], max_t)) return false;
+    }
+    return true;
+}
+
+// floor(N * floor(2^32/d) / 2^32) is the quotient or one less, since N * (2^32/d - floor(2^32/d)) < 2^32; the
+// remainder tells.  2^32/1 does not fit: 2^32 - 1 is one less than it, and the same argument holds (N * 1 < 2^32).
+void build_round_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<Magic> &out) {
+    auto entry = [](int64_t d) {
+        return Magic{(uint32_t)std::min<uint64_t>((1ull << 32) / (uint64_t)d, 0xffffffffull), (uint32_t)(d - 1)};
+    };
+    const size_t kk = (size_t)k * k;
+    out.assign(table_entries(k), Magic{0, 0xffffffffu});
+    for (size_t i = 0; i < (size_t)k; ++i) {
+        for (size_t j = 0; j < (size_t)k; ++j)
+            if (i != j) out[i * k + j] = out[kk + j * k + i] = entry(bandwidth[i * k + j]);
+        out[2 * kk + i] = entry(speeds[i]);
+    }
 }
 
 }  // namespace cpeval

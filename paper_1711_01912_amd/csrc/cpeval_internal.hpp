@@ -168,16 +168,18 @@ struct CostTables {
     // bank, which takes the bank conflicts out of the kernels' table reads.
     bool tab4_ok = false;
     std::vector<uint32_t> tab4;         // same layout; 0 = free transfer
-    // The rounded form, exact for every 32-bit N = a + dm1 (no condition on the product):
-    //   q = (N * mul) >> 32, one more if N - q * (dm1 + 1) > dm1      with mul = floor(2^32/d), dm1 = d - 1
-    // A free transfer is {0, 2^32 - 1}, which yields 0.
-    bool round_ok = false;
-    std::vector<Magic> round;           // same layout as magic
 };
 
 // Returns CP_OK, CP_ERR_SPEED or CP_ERR_BANDWIDTH.
 int build_cost_tables(int32_t k, const int64_t *speeds, const int64_t *bandwidth,
                       bool narrow, int64_t max_c, int64_t max_t, CostTables &out);
+
+// The rounded form, exact for every 32-bit N = a + dm1 (no condition on the product):
+//   q = (N * mul) >> 32, one more if N - q * (dm1 + 1) > dm1      with mul = floor(2^32/d), dm1 = d - 1
+// A free transfer is {0, 2^32 - 1}, which yields 0.  Same layout as `magic`.  Only the lane-window plan with 64-bit
+// ring words reads it: the other calls do not pay for it (92 against 69 us of host time at 50 devices).
+bool round_fits(int32_t k, const int64_t *speeds, const int64_t *bandwidth, int64_t max_c, int64_t max_t);
+void build_round_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<Magic> &out);
 
 inline size_t table_entries(int32_t k) { return (size_t)2 * k * k + k; }
 // 64-bit words of one call's tables in device memory: the 8-byte entries, then the 4-byte ones

@@ -32,3 +32,7 @@ def test_large_batches_are_cleared_by_as_many_threads(harness):
 
 def test_wave_column_blocks_cover_the_rows_and_share_long_ones_out(harness):
     _holds(harness, "column")
+
+
+def test_rounded_cost_tables_are_exact_and_built_only_on_request(harness):
+    _holds(harness, "rounded")
