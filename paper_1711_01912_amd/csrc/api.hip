@@ -252,28 +252,35 @@ int choose_window_plan(const Packed &p, int32_t k, size_t tick_bytes, size_t lds
     return best;
 }
 
-// The lane-window kernel: both sweeps in one launch, a workgroup per sweep and G partitions.  Measured: a
-// tick is a chain of 0.3 us, to which every workgroup of a compute unit adds 0.07 us and its items: 0.05 us
-// each with 4 entries a sub-row, 0.037 with 2, twice that with 64-bit words (2,000 to 121,000 vertices, 195 to
-// 702 ticks, 80 to 1,024 workgroups, one to four of them on a unit; within 25 %).
-double lane_sweep_us(const LaneDir &d, const LaneCfg &c, int32_t batch, int sweeps) {
+// The lane-window kernel: both sweeps in one launch, a workgroup per sweep and G partitions.  A tick is a chain of
+// 0.2 us, 0.1 more with rows per partition; with far reads 0.2 us more and 0.003 per far read of the widest tick, and
+// 0.14 of its own with rows per partition (the store wavefronts wait for their copies behind those stores).  To the
+// chain every workgroup of a compute unit adds 0.04 us and its items, 0.042 us each, twice that with 64-bit words.
+// Fitted, with the model below, to 408 calls: 60 to 250,000 vertices, 8 to 1,900 ticks, 8 to 4,096 partitions, 2 to 50
+// devices, one sweep or both, either layout.  Over 414 others the plan is slower than the one it stands in for by
+// more than 3 % in 9 of the 339 calls it is chosen for (10 partitions of 84,000 vertices: 1.22 times), and all 414
+// take 1.82 times as long without it.  With one chain of 0.3 us for every shape it was 41 calls, up to 1.52 times:
+// batches of fewer than 1,000 partitions with far reads.
+double lane_sweep_us(const LaneDir &d, const LaneCfg &c, int32_t batch, int sweeps, bool by_partition) {
     const double wgs = std::ceil((double)batch / c.groups) * sweeps;
     const double per_cu = std::max(1.0, std::floor(std::min((double)kLdsBudget / (double)(c.lds_bytes + 512),
                                                             (c.nfw > 0 && c.word == 8 ? 24.0 : 32.0) /
                                                                 (c.nc + c.nlw + c.nsw + c.nfw))));
     const double items = (double)d.units * c.groups / 8 / std::max(d.ticks, 1);      // per tick
-    const double each = 0.07 + items * (c.width == 2 ? 0.037 : 0.05) * (c.word == 8 ? 2.0 : 1.0);
+    const double chain = 0.2 + (by_partition ? 0.1 : 0.0) +
+                         (c.nfw > 0 ? 0.2 + 0.003 * d.far_cap + (by_partition ? 0.14 : 0.0) : 0.0);
+    const double each = 0.04 + items * 0.042 * (c.word == 8 ? 2.0 : 1.0);
     const double full = std::floor(wgs / (256.0 * per_cu)), rest = std::ceil((wgs - full * 256.0 * per_cu) / 256.0);
-    return d.ticks * (full * (0.3 + per_cu * each) + (rest > 0.0 ? 0.3 + rest * each : 0.0));
+    return d.ticks * (full * (chain + per_cu * each) + (rest > 0.0 ? chain + rest * each : 0.0));
 }
 
-// The resident-window kernel where its workgroups share compute units: a unit relaxes a slice in 0.1 us
-// whichever workgroup it belongs to, and rows per vertex cost 1.4 times as much (121,000 vertices in 701
-// levels of three slices, 777 partitions: 1.2 and 1.4 ms; 19,800 in 660 levels of one, 4,096: 1.65 ms).
+// The resident-window kernel as the lane-window plan meets it: a chain of 0.63 us a tick, or, where its workgroups
+// crowd a compute unit, 0.09 us a slice whichever workgroup it belongs to, 1.3 times that with rows per vertex.
+// (window_sweep_us above, which ranks the window plans among each other, leaves the crowding out.)
 double crowded_window_sweep_us(const WindowDir &d, const WindowCfg &c, int32_t batch, bool by_partition) {
     const double per_cu = window_wg_per_cu(c), wgs = std::ceil((double)batch / std::max(1, c.groups));
     const double rounds = std::ceil(wgs / (256.0 * per_cu)), there = std::min(per_cu, std::ceil(wgs / 256.0));
-    return rounds * d.ticks * std::max(0.65 + 0.03 * d.smax, 0.1 * d.smax * there) * (by_partition ? 1.0 : 1.4);
+    return rounds * d.ticks * std::max(0.63, 0.09 * d.smax * there * (by_partition ? 1.0 : 1.3));
 }
 
 // The cheapest shape for this batch: true and its time if the lane-window kernel applies.
@@ -292,7 +299,8 @@ bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, const int6
         if (((int64_t)batch + groups - 1) / groups > 65535) continue;        // the grid's second dimension
         if (!lane_config(p.lane_b, p.lane_t, p.n, k, groups, word, with_out,
                          ((int64_t)batch + groups - 1) / groups * sweeps, lds_limit, c)) continue;
-        const double us = std::max(lane_sweep_us(p.lane_b, c, batch, sweeps), lane_sweep_us(p.lane_t, c, batch, sweeps));
+        const double us = std::max(lane_sweep_us(p.lane_b, c, batch, sweeps, by_partition),
+                                   lane_sweep_us(p.lane_t, c, batch, sweeps, by_partition));
         if (!found || us < *us_out) {
             found = true;
             *us_out = us;
@@ -548,9 +556,10 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     if (rc) return rc;
 
     // plan
+    const size_t lds_limit = device_window_lds_limit();
     WindowCfg cfg_b, cfg_t;
     const bool can_window = tabs.magic_ok && window_fits(p, k, (size_t)tick_dtype,
-                                                         device_window_lds_limit(), &cfg_b, &cfg_t, tabs.tab4_ok);
+                                                         lds_limit, &cfg_b, &cfg_t, tabs.tab4_ok);
     int use = plan;
     SharedCfg sh_b, sh_t;
     if (plan == CP_PLAN_AUTO) {
@@ -562,7 +571,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                                                     p.win_t.far_cap == 0);
             const double mask_us = sh_mask_pass ? 5.0 + (double)p.n * batch * (2.0 * tick_dtype + 0.125) / kMaskPassBytesPerUs : 0.0;
             double window_us = 0.0;
-            const int wplan = choose_window_plan(p, k, (size_t)tick_dtype, device_window_lds_limit(), cfg_b, cfg_t, batch,
+            const int wplan = choose_window_plan(p, k, (size_t)tick_dtype, lds_limit, cfg_b, cfg_t, batch,
                                                  mask_us, &sh_b, &sh_t, tabs.tab4_ok,
                                                  mask_out && !sh_mask_pass ? 1.22 : 1.0, &window_us);
             // (the mask's cost is left out of the comparison with the wave-column plan, which pays
@@ -575,6 +584,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     if (plan == CP_PLAN_AUTO && cp_out && !blevel_out && (use == CP_PLAN_WAVE_COLUMN || p.win_b.far_cap > 0))
         return CP_ERR_ARG;
     // several partitions in the lanes of a workgroup, both sweeps in one launch
+    const bool by_partition = out_layout == CP_OUT_PARTITION_MAJOR;
     LaneCfg lane_cfg;
     const int lane_sweeps = ((blevel_out || cp_out) ? 1 : 0) + (tlevel_out ? 1 : 0);
     bool lanes = false;
@@ -582,44 +592,51 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     if ((plan == CP_PLAN_AUTO || plan == CP_PLAN_LANE_WINDOW) && lane_sweeps > 0) {
         double lane_us = 0.0;
         lanes = choose_lanes(p, tabs, k, speeds, bandwidth, batch, tick_dtype, blevel_out || tlevel_out,
-                             out_layout == CP_OUT_PARTITION_MAJOR, lane_sweeps,
-                             device_window_lds_limit(), lane_cfg, &lane_us);
+                             by_partition, lane_sweeps, lds_limit, lane_cfg, &lane_us);
         if (lanes)
             lane_work = lane_work_bytes((blevel_out || cp_out) ? &p.lane_b : nullptr, tlevel_out ? &p.lane_t : nullptr, p.n,
                                         batch, lane_cfg.groups, lane_cfg.word);
         if (lanes && plan == CP_PLAN_AUTO) {
-            // against the plan chosen so far: its sweeps (side by side where they would share the launch),
-            // the device ids it gathers per sweep at about 1 us per MB, and the mask pass that its t sweep
-            // may save it
+            // against the plan chosen so far: its sweeps (side by side where they would share the launch), the
+            // device ids it gathers per sweep at about 1 us per MB, the launches it needs past two (1.5 us each),
+            // and the mask pass that its t sweep may save it
             const double mb = (double)p.n * batch * 1e-6;
-            const bool both = lane_sweeps == 2;
+            const double mask_pass_us = mask_out && by_partition
+                                            ? 5.0 + (double)p.n * batch * (2.0 * tick_dtype + 0.125) / kMaskPassBytesPerUs
+                                            : 0.0;
+            const bool both = lane_sweeps == 2, want_b = blevel_out || cp_out;
+            const bool rows = assign_layout == CP_ASSIGN_PARTITION_MAJOR &&
+                              ((uint64_t)p.n * (uint64_t)batch) % 16 == 0 && ((uintptr_t)assignments % 16) == 0;
             double other_us = column_plan_us(p, batch, (size_t)tick_dtype) * (both ? 1.0 : 0.5);
             if (use == CP_PLAN_RESIDENT_WINDOW) {
-                const bool by_rows = out_layout == CP_OUT_PARTITION_MAJOR;
-                const double b_us = crowded_window_sweep_us(p.win_b, cfg_b, batch, by_rows);
-                const double t_us = crowded_window_sweep_us(p.win_t, cfg_t, batch, by_rows);
+                const double b_us = crowded_window_sweep_us(p.win_b, cfg_b, batch, by_partition);
+                const double t_us = crowded_window_sweep_us(p.win_t, cfg_t, batch, by_partition);
                 WindowCfg x, y;
                 other_us = both ? b_us + t_us : (tlevel_out ? t_us : b_us);
-                if (both && out_layout == CP_OUT_PARTITION_MAJOR && tick_dtype == CP_TICK_I32 &&
-                    window_pair_config(p.win_b, p.win_t, k, device_window_lds_limit(), x, y)) {
+                bool side = false;
+                if (both && by_partition && tick_dtype == CP_TICK_I32 &&
+                    window_pair_config(p.win_b, p.win_t, k, lds_limit, x, y)) {
+                    side = true;
                     if (window_wg_per_cu(cfg_b) == 1.0 && window_wg_per_cu(cfg_t) == 1.0) other_us *= 0.66;
                     else if (2.0 * std::ceil((double)batch / 256.0) <= std::min(window_wg_per_cu(x), window_wg_per_cu(y)))
-                        other_us = 1.2 * std::max(b_us, t_us);
+                        other_us = 0.95 * std::max(b_us, t_us);
+                    else side = false;
                 }
+                const int launches_past_two = (side ? 1 : lane_sweeps) + (want_b && !(rows && p.win_b.direct_ok)) +
+                                              (tlevel_out && !(rows && p.win_t.direct_ok)) - 2;
+                other_us += 1.5 * launches_past_two;
+                if (!side && tick_dtype == CP_TICK_I32 && rows && p.win_t.direct_ok && p.win_t.smax >= 4) lane_us += mask_pass_us;
             } else if (use == CP_PLAN_SHARED_WINDOW_2 || use == CP_PLAN_SHARED_WINDOW_4) {
                 const int shared_by = use == CP_PLAN_SHARED_WINDOW_4 ? 4 : 2;
-                other_us = ((blevel_out || cp_out) ? shared_sweep_us(p.win_b, shared_by, batch) : 0.0) +
+                other_us = (want_b ? shared_sweep_us(p.win_b, shared_by, batch) : 0.0) +
                            (tlevel_out ? shared_sweep_us(p.win_t, shared_by, batch) : 0.0);
-                if (mask_out && out_layout == CP_OUT_PARTITION_MAJOR)
-                    lane_us += 5.0 + (double)p.n * batch * (2.0 * tick_dtype + 0.125) / kMaskPassBytesPerUs;
+                lane_us += mask_pass_us;
             }
             if (use != CP_PLAN_WAVE_COLUMN) {
-                const bool rows = assign_layout == CP_ASSIGN_PARTITION_MAJOR &&
-                                  ((uint64_t)p.n * (uint64_t)batch) % 16 == 0 && ((uintptr_t)assignments % 16) == 0;
                 other_us += mb * ((rows && p.win_b.direct_ok ? 0.0 : 1.0) + (rows && p.win_t.direct_ok ? 0.0 : 1.0)) *
                             (both ? 1.0 : 0.5);
             }
-            lanes = 5.0 + 0.7 * mb + lane_us < other_us &&
+            lanes = 1.5 + 0.7 * mb + lane_us < other_us &&
                     tables_bytes(k) + lane_work <= workspace_bytes;
         }
     }
@@ -630,11 +647,11 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const bool shared = use == CP_PLAN_SHARED_WINDOW_2 || use == CP_PLAN_SHARED_WINDOW_4;
     if (shared && plan != CP_PLAN_AUTO &&
         (!tabs.magic_ok || !shared_fits(p, k, (size_t)tick_dtype, use == CP_PLAN_SHARED_WINDOW_4 ? 4 : 2,
-                                        device_window_lds_limit(), &sh_b, &sh_t, tabs.tab4_ok)))
+                                        lds_limit, &sh_b, &sh_t, tabs.tab4_ok)))
         return CP_ERR_ARG;
     StreamCfg st_b, st_t, st_tm;
     const bool streamed = use == CP_PLAN_STREAMED_WINDOW;
-    if (streamed && (!tabs.magic_ok || !stream_fits(p, k, (size_t)tick_dtype, device_window_lds_limit(), &st_b, &st_t)))
+    if (streamed && (!tabs.magic_ok || !stream_fits(p, k, (size_t)tick_dtype, lds_limit, &st_b, &st_t)))
         return CP_ERR_ARG;
     const bool windowish = use == CP_PLAN_RESIDENT_WINDOW || shared || streamed || lanes;
     const bool columnish = !windowish;       // wave-column, or its persistent column-slice form
@@ -659,7 +676,6 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const size_t pperm_t_bytes = gather_t ? pperm_bytes(p, p.win_t, batch) : 0;
     need += pperm_b_bytes + pperm_t_bytes;
     if (lanes) need += lane_work;
-    const bool by_partition = out_layout == CP_OUT_PARTITION_MAJOR;
     const bool via_scratch = by_partition && columnish;
     const size_t scratch_at = need;
     if (via_scratch) need += 2 * column_scratch_bytes(p, batch, tick_dtype);
@@ -731,11 +747,11 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     bool fuse_mask = use == CP_PLAN_RESIDENT_WINDOW && by_partition && mask_out && direct_t &&
                      tick_dtype == CP_TICK_I32 && ((uintptr_t)blevel_out % 16) == 0 &&
                      ((uint64_t)p.n * (uint64_t)batch * 4) % 16 == 0 &&
-                     window_config(p.win_t, k, (size_t)tick_dtype, device_window_lds_limit(), cfg_tm, true);
+                     window_config(p.win_t, k, (size_t)tick_dtype, lds_limit, cfg_tm, true);
     // the streamed kernel: the same rule without the cost model (its workgroups are small either way)
     const bool fuse_mask_st = streamed && by_partition && mask_out && direct_t && p.win_t.smax >= 4 &&
                               ((uintptr_t)blevel_out % 16) == 0 && ((uint64_t)p.n * (uint64_t)batch * 4) % 16 == 0 &&
-                              stream_config(p.win_t, k, device_window_lds_limit() - kSharedStaticLds, true, st_tm);
+                              stream_config(p.win_t, k, lds_limit - kSharedStaticLds, true, st_tm);
     if (fuse_mask) {
         // The mask variant costs a little per slice (one more LDS read and a compare) and a fixed
         // amount per tick.  On wide ticks that is far less than a streaming pass over b and tl
@@ -760,7 +776,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     // more than the overlap gains, 4.9 against 3.8 ms)
     bool paired = use == CP_PLAN_RESIDENT_WINDOW && (blevel_out || cp_out) && tlevel_out && tick_dtype == CP_TICK_I32 &&
                   by_partition &&
-                  window_pair_config(p.win_b, p.win_t, k, device_window_lds_limit(), pr_b, pr_t);
+                  window_pair_config(p.win_b, p.win_t, k, lds_limit, pr_b, pr_t);
     // ... or where every workgroup of both sweeps finds room on the chip at once (small graphs,
     // moderate batches): then the two chains simply run side by side
     const bool alone = window_wg_per_cu(cfg_b) == 1.0 && window_wg_per_cu(cfg_t) == 1.0;
