@@ -121,7 +121,7 @@ struct LaneDir {
     int32_t far_cap = 0;     // far reads per tick, a multiple of 16; 0 = none anywhere
     int32_t far_count = 0;   // vertices some far read asks for
     size_t pos_off = 0;      // int32 [n] position of a vertex: the positions of a tick follow those of the last
-    int32_t ticks = 0, slots = 0, max_chunks = 0, max_units = 0, max_verts = 0, width = 0;
+    int32_t ticks = 0, slots = 0, max_chunks = 0, max_verts = 0, width = 0;
     int64_t units = 0;       // of all ticks
 };
 inline uint32_t lane_unit_bytes(int width) { return 64u * (1u + (uint32_t)width); }
@@ -142,6 +142,14 @@ struct Packed {
     int32_t max_width = 0;
     std::vector<uint8_t> blob;  // host image of the device blob
 };
+
+// Room for a graph's blob, made at once: growing it piece by piece copied it more often than it was written (121,000
+// vertices, 364,000 edges: 88 -> 60 ms, together with packets that are written in place).  A window packet takes up to
+// 10 bytes an edge and 700 a level, a lane packet 20 an edge, as a rule; pages that stay untouched cost nothing.
+inline size_t blob_room(int32_t n, int64_t m, int32_t L, bool narrow) {
+    const size_t per_edge = 4 + (narrow ? 4 + 10 + 20 : 8), per_vertex = 24 + 8 + (narrow ? 16 + 40 : 0);
+    return 2 * ((size_t)m * per_edge + (size_t)n * per_vertex + (size_t)L * (narrow ? 700 : 32)) + (1 << 18);
+}
 
 // Validate and pack.  Returns CP_OK or an error code.
 int pack_graph(int32_t n, int64_t m, int32_t L,

@@ -2,6 +2,7 @@
 // into the device image used by the two kernel families.  No GPU call here.
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <numeric>
 
@@ -391,69 +392,91 @@ bool pack_window_dir(BlobWriter &w, int32_t n, int32_t L, const int64_t *c, int6
     return true;
 }
 
+// Positions and ticks of the lane-window plan, made level by level as far as somebody asks: a graph whose ring turns
+// out too long costs its first levels, not all of them.  Positions go by level, inside a level by vertex number,
+// so that outputs are written along rows; a tick is a run of at most kLaneTickVerts vertices of a level, and about
+// kLaneTickBytes of packet.
+struct LaneTicks {
+    const ColumnDir &col;
+    const Csr &csr;
+    const int32_t *level_ptr, *level_vtx;
+    const bool forward;
+    const uint32_t row_bytes;            // of the packet, per sub-row
+    const int shift;                     // log2 of the entries per sub-row
+    std::unique_ptr<int32_t[]> order, pos, tick_of;      // filled for the levels made so far
+    std::vector<int32_t> begin, end;     // positions of the ticks made so far
+    size_t levels = 0;                   // made so far
+
+    LaneTicks(int32_t n, const ColumnDir &col_, const Csr &csr_, const int32_t *lp, const int32_t *lv, bool fwd, int width)
+        : col(col_), csr(csr_), level_ptr(lp), level_vtx(lv), forward(fwd), row_bytes(lane_unit_bytes(width) / kLaneUnit),
+          shift(width == 4 ? 2 : 1), order(new int32_t[(size_t)n]), pos(new int32_t[(size_t)n]),
+          tick_of(new int32_t[(size_t)n]) {}
+
+    int32_t degree(int32_t v) const { return csr.ptr[v + 1] - csr.ptr[v]; }
+    int32_t pieces(int32_t v) const { return std::max(1, (degree(v) + (1 << shift) - 1) >> shift); }
+
+    void next_level() {
+        const size_t l = forward ? levels : col.lvl_begin.size() - 1 - levels;
+        const int32_t first = col.lvl_begin[levels], count = col.lvl_count[levels];
+        int32_t *const to = order.get() + first;
+        std::copy(level_vtx + level_ptr[l], level_vtx + level_ptr[l + 1], to);
+        if (!std::is_sorted(to, to + count)) std::sort(to, to + count);
+        int64_t bytes = 0;
+        for (int32_t i = first; i < first + count; ++i) {
+            const int32_t v = order[i];
+            const int64_t add = 8 + (int64_t)pieces(v) * row_bytes;
+            if (i == first || i - begin.back() == kLaneTickVerts || bytes + add > kLaneTickBytes) {
+                begin.push_back(i);
+                end.push_back(i);
+                bytes = 0;
+            }
+            bytes += add;
+            end.back() = i + 1;
+            pos[v] = i;
+            tick_of[v] = (int32_t)begin.size() - 1;
+        }
+        ++levels;
+    }
+    // Makes ticks up to number s; false if there are fewer.
+    bool have(size_t s) {
+        while (begin.size() <= s && levels < col.lvl_begin.size()) next_level();
+        return s < begin.size();
+    }
+};
+
 // Lane-window packing for one direction (layout: see LaneDir).  Returns false if the ring of a
 // workgroup of 8 partitions would be too long.
 bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes, int width, const Csr &csr,
                    const int32_t *level_ptr, const int32_t *level_vtx, bool forward, const ColumnDir &col, LaneDir &dir) {
-    // Positions: by level, inside a level by vertex number, so that outputs are written along rows.
-    std::vector<int32_t> order((size_t)n), pos((size_t)n), slot((size_t)n);
-    for (size_t s = 0; s < col.lvl_begin.size(); ++s) {
-        const size_t l = forward ? s : col.lvl_begin.size() - 1 - s;
-        const auto to = order.begin() + col.lvl_begin[s];
-        std::copy(level_vtx + level_ptr[l], level_vtx + level_ptr[l + 1], to);
-        if (!std::is_sorted(to, to + col.lvl_count[s])) std::sort(to, to + col.lvl_count[s]);
-    }
+    LaneTicks ticks(n, col, csr, level_ptr, level_vtx, forward, width);
     const size_t row_bytes = (8 + 1) * word_bytes;
-    for (int32_t i = 0; i < n; ++i) pos[order[i]] = i;
-    auto degree = [&](int32_t i) { return csr.ptr[order[i] + 1] - csr.ptr[order[i]]; };
-
     const uint32_t unit_bytes = lane_unit_bytes(width);
-    auto pieces = [&](int32_t i) { return std::max(1, (degree(i) + width - 1) / width); };
-
-    // Ticks: runs of at most kLaneTickVerts vertices of a level, and about kLaneTickBytes of packet.
-    std::vector<int32_t> tick_a, tick_b;
-    for (size_t s = 0; s < col.lvl_begin.size(); ++s) {
-        const int32_t a = col.lvl_begin[s], b = a + col.lvl_count[s];
-        int32_t start = a;
-        int64_t bytes = 0;
-        for (int32_t i = a; i < b; ++i) {
-            const int64_t add = 8 + (int64_t)pieces(i) * unit_bytes / kLaneUnit;
-            if (i > start && (i - start == kLaneTickVerts || bytes + add > kLaneTickBytes)) {
-                tick_a.push_back(start);
-                tick_b.push_back(i);
-                start = i;
-                bytes = 0;
-            }
-            bytes += add;
-        }
-        if (b > start) {
-            tick_a.push_back(start);
-            tick_b.push_back(b);
-        }
-    }
-    const int32_t T = (int32_t)tick_a.size();
-    std::vector<int32_t> tick_of((size_t)n);
-    for (int32_t s = 0; s < T; ++s)
-        for (int32_t i = tick_a[s]; i < tick_b[s]; ++i) tick_of[order[i]] = s;
     // Ring: while tick s runs, the values its edges read and those of tick s - 1 (on their way to the
     // output) are live, and the device ids of the two ticks after s are written already.  far_ticks = 0:
     // every neighbour in the ring.  Returns false if that is too long, or a tick has too many far reads.
     int64_t need = 0;
-    std::vector<int32_t> far_seen((size_t)n, -1);      // last tick with a far read of the vertex
+    std::vector<int32_t> far_of_tick;
     auto ring_fits = [&](int32_t far_ticks) {
         need = 1;
         dir.far_cap = 0;
-        std::fill(far_seen.begin(), far_seen.end(), -1);
-        for (int32_t s = 0; s < T; ++s) {
-            int32_t oldest = tick_a[std::max(s - 1, 0)], far = 0;
-            for (int32_t i = tick_a[s]; i < tick_b[s]; ++i)
-                for (int32_t e = csr.ptr[order[i]]; e < csr.ptr[order[i] + 1]; ++e) {
+        for (int32_t s = 0; ticks.have((size_t)s); ++s) {
+            ticks.have((size_t)s + 2);
+            int32_t oldest = ticks.begin[std::max(s - 1, 0)];
+            far_of_tick.clear();
+            for (int32_t i = ticks.begin[s]; i < ticks.end[s]; ++i) {
+                const int32_t v = ticks.order[i];
+                for (int32_t e = csr.ptr[v]; e < csr.ptr[v + 1]; ++e) {
                     const int32_t u = csr.idx[e];
-                    if (far_ticks == 0 || s - tick_of[u] < far_ticks) oldest = std::min(oldest, pos[u]);
-                    else if (far_seen[u] != s) { far_seen[u] = s; ++far; }
+                    if (far_ticks == 0 || s - ticks.tick_of[u] < far_ticks) oldest = std::min(oldest, ticks.pos[u]);
+                    else far_of_tick.push_back(u);
                 }
-            need = std::max<int64_t>(need, (int64_t)tick_b[std::min(s + 2, T - 1)] - oldest);
-            dir.far_cap = std::max(dir.far_cap, (far + 15) / 16 * 16);
+            }
+            if (far_of_tick.size() > 16) {               // (up to 16 the cap is the same whatever repeats)
+                std::sort(far_of_tick.begin(), far_of_tick.end());
+                far_of_tick.erase(std::unique(far_of_tick.begin(), far_of_tick.end()), far_of_tick.end());
+            }
+            need = std::max<int64_t>(need, (int64_t)ticks.end[std::min<size_t>((size_t)s + 2, ticks.end.size() - 1)] - oldest);
+            dir.far_cap = std::max(dir.far_cap, ((int32_t)far_of_tick.size() + 15) / 16 * 16);
             if ((uint64_t)(need + 2 * dir.far_cap) * row_bytes > kLaneRingBytes || dir.far_cap > kLaneMaxFar) return false;
         }
         return true;
@@ -461,23 +484,26 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
     int32_t far_ticks = 0;
     if (!ring_fits(0)) {
         far_ticks = kLaneFarTicks;
-        while (far_ticks < T && !ring_fits(far_ticks)) {
+        while (!ring_fits(far_ticks)) {
             // a longer ring helps against too many far reads only
-            if (dir.far_cap <= kLaneMaxFar) return false;
+            if (dir.far_cap <= kLaneMaxFar || ticks.begin.size() <= (size_t)far_ticks) return false;
             far_ticks *= 2;
         }
-        if (far_ticks >= T) return false;
+        if (far_ticks >= (int32_t)ticks.begin.size()) return false;
     }
+    const int32_t T = (int32_t)ticks.begin.size();
+    const int32_t *const order = ticks.order.get(), *const tick_of = ticks.tick_of.get();
     dir.ticks = T;
     dir.slots = (int32_t)need;
     dir.width = width;
+    std::unique_ptr<int32_t[]> slot(new int32_t[(size_t)n]);
     for (int32_t i = 0, at = 0; i < n; ++i) {
         slot[order[i]] = at;
         if (++at == dir.slots) at = 0;
     }
 
     // vertices that far reads ask for, numbered in the order they are computed
-    std::vector<int32_t> far_no, far_list;
+    std::vector<int32_t> far_no, far_list, far_seen;
     if (far_ticks) {
         far_no.assign((size_t)n, -1);
         for (int32_t i = 0; i < n; ++i)
@@ -486,25 +512,37 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
         for (int32_t i = 0; i < n; ++i)
             if (far_no[order[i]] == 0) far_no[order[i]] = dir.far_count++;
         far_list.assign((size_t)T * dir.far_cap, 0);
-        std::fill(far_seen.begin(), far_seen.end(), -1);
+        far_seen.assign((size_t)n, -1);                  // last tick with a far read of the vertex
     }
     std::vector<int32_t> far_row(far_ticks ? (size_t)n : 0);     // row of the vertex among the current tick's far reads
-    std::vector<uint32_t> tab((size_t)std::max(T, 1), 0), stream;
-    stream.reserve((size_t)(csr.ptr[n] + n) * 4);
+    // what each tick takes of the stream, then the packets in place
+    std::vector<uint32_t> tab((size_t)std::max(T, 1), 0);
+    size_t total = 0;
     for (int32_t s = 0; s < T; ++s) {
-        const int32_t a = tick_a[s], b = tick_b[s];
         int64_t rows = 0;
-        for (int32_t i = a; i < b; ++i) rows += pieces(i);
+        uint32_t far_out = 0;
+        for (int32_t i = ticks.begin[s]; i < ticks.end[s]; ++i) {
+            rows += ticks.pieces(order[i]);
+            far_out += far_ticks && far_no[order[i]] >= 0;
+        }
         const int64_t units = (rows + 2 * kLaneUnit - 1) / (2 * kLaneUnit) * 2;
         if (units >= (1 << 14)) return false;
-        uint32_t far_out = 0, far_in = 0;
-        for (int32_t i = a; far_ticks && i < b; ++i) far_out += far_no[order[i]] >= 0;
-        const uint32_t bytes = (uint32_t)units * unit_bytes + 8u * (uint32_t)(b - a) + 4 * far_out, chunks = (bytes + 15) / 16;
-        const size_t base = stream.size();                  // in words
-        if (base / 4 + chunks >= (1ull << 31)) return false;
-        stream.resize(base + 4 * (size_t)chunks, 0);
-        tab[s] = (uint32_t)units | (uint32_t)(b - a) << 14 | far_out << 23;
-        uint32_t *const first_unit = stream.data() + base;
+        const uint32_t verts = (uint32_t)(ticks.end[s] - ticks.begin[s]);
+        const uint32_t chunks = ((uint32_t)units * unit_bytes + 8u * verts + 4 * far_out + 15) / 16;
+        tab[s] = (uint32_t)units | verts << 14 | far_out << 23;
+        total += chunks;
+        if (total >= (1ull << 31)) return false;
+        dir.units += units;
+        dir.max_chunks = std::max(dir.max_chunks, (int32_t)chunks);
+        dir.max_verts = std::max(dir.max_verts, (int32_t)verts);
+    }
+    dir.stream_off = w.reserve(16 * std::max<size_t>(total, 1));
+    uint32_t *packet = w.at<uint32_t>(dir.stream_off);
+    const uint32_t pad_from = (uint32_t)dir.slots;
+    for (int32_t s = 0; s < T; ++s) {
+        const int32_t a = ticks.begin[s], b = ticks.end[s];
+        const uint32_t units = tab[s] & 0x3fffu, far_out = tab[s] >> 23;
+        uint32_t far_in = 0;
         auto source = [&](int32_t u) {
             if (!far_ticks || s - tick_of[u] < far_ticks) return (uint32_t)slot[u];
             if (far_seen[u] != s) {
@@ -514,38 +552,33 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
             }
             return (uint32_t)(dir.slots + 2 + (s & 1) * dir.far_cap + far_row[u]);
         };
-        int64_t row = 0;
+        uint32_t row = 0;
         auto put_row = [&](uint32_t to, uint32_t cv, int32_t e, int32_t len) {
-            uint32_t *x = first_unit + (size_t)(row / kLaneUnit) * (unit_bytes / 4) + 2 * (row % kLaneUnit);
+            uint32_t *x = packet + (size_t)(row / kLaneUnit) * (unit_bytes / 4) + 2 * (row % kLaneUnit);
             x[0] = to;
             x[1] = cv;
             for (int j = 0; j < width; ++j) {
                 x += 2 * kLaneUnit;
-                x[0] = j < len ? source(csr.idx[e + j]) : (uint32_t)dir.slots;
+                x[0] = j < len ? source(csr.idx[e + j]) : pad_from;
                 x[1] = j < len ? (uint32_t)csr.wt[e + j] : 0;
             }
             ++row;
         };
         for (int32_t i = a; i < b; ++i) {
-            const int32_t v = order[i], d = degree(i);
+            const int32_t v = order[i], d = ticks.degree(v);
             for (int32_t j = 0; j == 0 || j < d; j += width) put_row((uint32_t)slot[v], (uint32_t)c[v], csr.ptr[v] + j, d - j);
         }
-        while (row < units * kLaneUnit) put_row((uint32_t)dir.slots + 1, 0, 0, 0);
-        uint32_t *verts = stream.data() + base + (size_t)units * unit_bytes / 4;
+        while (row < units * kLaneUnit) put_row(pad_from + 1, 0, 0, 0);
+        uint32_t *verts = packet + (size_t)units * unit_bytes / 4;
         for (int32_t i = a; i < b; ++i) {
             verts[2 * (i - a)] = (uint32_t)order[i];
             verts[2 * (i - a) + 1] = (uint32_t)c[order[i]];
         }
         uint32_t *out = verts + 2 * (b - a);
-        for (int32_t i = a; far_ticks && i < b; ++i)
+        for (int32_t i = a; far_out && i < b; ++i)
             if (far_no[order[i]] >= 0) *out++ = (uint32_t)slot[order[i]];
-        dir.units += units;
-        dir.max_chunks = std::max(dir.max_chunks, (int32_t)chunks);
-        dir.max_units = std::max(dir.max_units, (int32_t)units);
-        dir.max_verts = std::max(dir.max_verts, b - a);
+        packet += ((size_t)units * unit_bytes + 8u * (uint32_t)(b - a) + 4 * far_out + 15) / 16 * 4;
     }
-    dir.stream_off = w.reserve(4 * std::max<size_t>(stream.size(), 4));
-    std::memcpy(w.at<uint32_t>(dir.stream_off), stream.data(), 4 * stream.size());
     dir.tick_off = w.reserve(4 * tab.size());
     std::memcpy(w.at<uint32_t>(dir.tick_off), tab.data(), 4 * tab.size());
     if (far_ticks) {
@@ -553,7 +586,7 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
         std::memcpy(w.at<int32_t>(dir.far_off), far_list.data(), 4 * far_list.size());
     }
     dir.pos_off = w.reserve(4 * (size_t)n);
-    std::memcpy(w.at<int32_t>(dir.pos_off), pos.data(), 4 * (size_t)n);
+    std::memcpy(w.at<int32_t>(dir.pos_off), ticks.pos.get(), 4 * (size_t)n);
     return true;
 }
 
@@ -667,6 +700,7 @@ int pack_graph(int32_t n, int64_t m, int32_t L,
 
     try {
         P.blob.clear();
+        P.blob.reserve(blob_room(n, m, L, P.narrow));
         BlobWriter w(P.blob);
         pack_column_dir(w, n, m, P.narrow, succ, order_b, P.col_b);
         pack_column_dir(w, n, m, P.narrow, pred, order_t, P.col_t);

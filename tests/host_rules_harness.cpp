@@ -2,6 +2,7 @@
 // argv[1] names the check; exit status 0 = it holds, 1 = it does not (with a line that says where).
 #include <cstdio>
 #include <cstring>
+#include <string>
 #include <vector>
 
 #include "../paper_1711_01912_amd/csrc/launch.hpp"
@@ -110,8 +111,40 @@ static int rounded() {
     return 0;
 }
 
+// A graph's blob is allocated once.  argv[2]: the directory with the caller-side arrays.
+template <typename T>
+static std::vector<T> read_all(const std::string &name) {
+    std::vector<T> v;
+    FILE *f = std::fopen(name.c_str(), "rb");
+    if (!f) return v;
+    std::fseek(f, 0, SEEK_END);
+    v.resize((size_t)std::ftell(f) / sizeof(T));
+    std::fseek(f, 0, SEEK_SET);
+    if (!v.empty() && std::fread(v.data(), sizeof(T), v.size(), f) != v.size()) v.clear();
+    std::fclose(f);
+    return v;
+}
+
+static int room(const std::string &dir) {
+    auto i32 = [&](const char *name) { return read_all<int32_t>(dir + "/" + name + ".bin"); };
+    auto i64 = [&](const char *name) { return read_all<int64_t>(dir + "/" + name + ".bin"); };
+    const auto hdr = i64("hdr");
+    if (hdr.size() != 3) return 2;
+    const auto sp = i32("succ_ptr"), si = i32("succ_idx"), pp = i32("pred_ptr"), pi = i32("pred_idx"), pe = i32("pred_eid"),
+               lp = i32("level_ptr"), lv = i32("level_vtx");
+    const auto st = i64("succ_t"), c = i64("c");
+    Packed p;
+    if (pack_graph((int32_t)hdr[0], hdr[1], (int32_t)hdr[2], sp.data(), si.data(), st.data(), pp.data(), pi.data(),
+                   pe.data(), c.data(), lp.data(), lv.data(), p) != CP_OK)
+        return 2;
+    const size_t made = blob_room(p.n, p.m, p.L, p.narrow);
+    std::printf("blob %zu, room %zu, held %zu\n", p.blob.size(), made, p.blob.capacity());
+    return p.blob.size() > made || p.blob.capacity() != made;
+}
+
 int main(int argc, char **argv) {
     if (argc < 2) return 2;
+    if (argc > 2 && !std::strcmp(argv[1], "room")) return room(argv[2]);
     if (!std::strcmp(argv[1], "prepare")) return prepare();
     if (!std::strcmp(argv[1], "rounded")) return rounded();
     if (!std::strcmp(argv[1], "column")) return column();

@@ -5,6 +5,9 @@ import subprocess
 
 import pytest
 
+from test_packer_sanitized import _deep, _dump
+from workloads import make_workload
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1711_01912_amd", "csrc")
 
@@ -36,3 +39,19 @@ def test_wave_column_blocks_cover_the_rows_and_share_long_ones_out(harness):
 
 def test_rounded_cost_tables_are_exact_and_built_only_on_request(harness):
     _holds(harness, "rounded")
+
+
+@pytest.mark.parametrize("case", ["tiny", "mlp", "inception", "hubs", "sparse", "deep", "wide-weights"])
+def test_blob_is_allocated_once(harness, tmp_path, case):
+    if case == "hubs":
+        w = make_workload("comm_heavy", P=1, levels=5, width=600, hub_degree=300)
+    elif case == "sparse":
+        w = make_workload("large_sparse", P=1, levels=150, width=200)
+    elif case == "deep":
+        w = _deep(0)
+    else:
+        w = make_workload("tiny" if case == "wide-weights" else case, P=1)
+        if case == "wide-weights":
+            w.c = w.c * 2**36
+    _dump(w, str(tmp_path))
+    _holds(harness, "room", str(tmp_path))
