@@ -43,6 +43,10 @@ TRAFFIC_SOURCES = ("kernels.hip", "window_shared.hip", "graph.cpp", "api.hip", "
                    "device_math.hpp")     # the sweep kernels, the packet layout, the choice of plan and shape
 
 
+PLAN_NAMES = {1: "wave-column", 2: "resident-window", 3: "shared-window-2", 4: "shared-window-4", 5: "column-slice",
+              6: "streamed-window", 7: "lane-window"}
+
+
 def sources_digest():
     import hashlib
     h = hashlib.sha256()
@@ -78,7 +82,8 @@ def main():
     ap.add_argument("--warmup", type=int, default=3)
     ap.add_argument("--workload", default="large_sparse")
     ap.add_argument("--plan", type=int, default=0, help="0 auto, 1 wave-column, 2 resident-window, "
-                    "3 / 4 shared window with 2 / 4 partitions per workgroup, 5 column slices, 6 streamed window")
+                    "3 / 4 shared window with 2 / 4 partitions per workgroup, 5 column slices, 6 streamed window, "
+                    "7 lane window")
     ap.add_argument("--batch", type=int, default=0, help="override the workload's batch size")
     ap.add_argument("--print-sources-digest", action="store_true",
                     help="print the digest MEASURED_TRAFFIC is keyed by (after taking the HBM counters anew) and exit")
@@ -121,9 +126,9 @@ def main():
     a = torch.from_numpy(w.assignments).to(dev)
     P, n, m = w.P, w.n, w.m
     tdt = torch.int32 if T == 4 else torch.int64
-    plan_used = args.plan if args.plan else binding.choose_plan(g, P, w.speeds, w.bandwidth, T)
+    plan_asked = args.plan if args.plan else binding.choose_plan(g, P, w.speeds, w.bandwidth, T)
     if args.out_layout == "native":
-        out_layout = (cpe.OUT_VERTEX_MAJOR if plan_used in (cpe.PLAN_WAVE_COLUMN, cpe.PLAN_COLUMN_SLICE)
+        out_layout = (cpe.OUT_VERTEX_MAJOR if plan_asked in (cpe.PLAN_WAVE_COLUMN, cpe.PLAN_COLUMN_SLICE)
                       else cpe.OUT_PARTITION_MAJOR)
     else:
         out_layout = cpe.OUT_PARTITION_MAJOR if args.out_layout == "partition" else cpe.OUT_VERTEX_MAJOR
@@ -160,6 +165,7 @@ def main():
     t1 = time.perf_counter()
     assert int(out["status"].item()) == 0
     ms_per_step = (t1 - t0) * 1e3 / args.steps
+    plan_used = prof.plan(0)      # of the timed steps, all alike
 
     stages = {name: [] for name in binding.STAGE_NAMES}
     launches = (1, 1)
@@ -286,8 +292,7 @@ def main():
         "config": {"workload": args.workload, "n": n, "m": m, "L": w.L, "P": P, "k": w.k,
                    "tick_bytes": T, "max_out_degree": info["max_out_degree"],
                    "raw_path_bound": info["raw_path_bound"],
-                   "plan": {1: "wave-column", 2: "resident-window", 3: "shared-window-2", 4: "shared-window-4",
-                            5: "column-slice", 6: "streamed-window"}[plan_used],
+                   "plan": PLAN_NAMES[plan_used],
                    "out_layout": "vertex-major" if out_layout == cpe.OUT_VERTEX_MAJOR else "partition-major"},
         "stage_ms": stage_ms,
         "sweep_relaxations_per_s": sweeps * m * P / (b_ms * 1e-3),      # of the dominant kernel's stage

@@ -90,8 +90,8 @@ extern "C" {
 #define CP_PLAN_STREAMED_WINDOW  6   /* as 2, but the compute wavefronts fetch the graph themselves, two ticks ahead, into
                                         registers; LDS holds only what depends on the partition */
 #define CP_PLAN_LANE_WINDOW      7   /* as 2, but one workgroup = 4 or 8 partitions in the lanes of its wavefronts, both
-                                        sweeps in one launch; CP_PLAN_AUTO takes it by itself where it is the faster form
-                                        of the window plans (cp_eval_choose_plan then still names the plan it stands in for) */
+                                        sweeps in one launch; CP_PLAN_AUTO takes it in place of the plan it resolves to
+                                        where it is faster for the call (see cp_eval_choose_plan) */
 #define CP_PLAN_COLUMN_SLICE     5   /* the wave-column layout, but one persistent workgroup owns 64 partitions and
                                         walks all levels in one launch per sweep (never chosen by CP_PLAN_AUTO) */
 
@@ -127,7 +127,8 @@ typedef struct cp_graph_info {
     int32_t window_ticks_t;      /* ... and t-level sweep */
     int32_t window_slices_b;     /* slices of the widest tick, b-level sweep */
     int32_t window_slices_t;     /* ... and t-level sweep */
-    int32_t auto_plan;           /* plan CP_PLAN_AUTO resolves to for a batch of 256 (the choice is made per call) */
+    int32_t auto_plan;           /* plan CP_PLAN_AUTO resolves to for a batch of 256, in cp_eval_choose_plan's sense (the
+                                    choice is made per call) */
     int32_t uploaded;            /* 1 after cp_graph_upload */
     uint64_t blob_bytes;
 } cp_graph_info;
@@ -179,7 +180,10 @@ int cp_eval_workspace_bytes(const cp_graph *g, int32_t batch, int32_t k, int ass
 /*
  * The plan CP_PLAN_AUTO resolves to for this batch and cost model on the current
  * device (a caller may want to know it to ask for the layout that plan produces
- * directly).  Errors: as cp_eval's argument checks.
+ * directly, or whether CP can be had without b).  Where the lane-window plan is faster for
+ * the call at hand, which depends on its outputs, layouts and workspace, AUTO runs that one in
+ * its place, with the same results and the same refusals: it is never the answer here, and
+ * cp_profile_plan tells what a call ran.  Errors: as cp_eval's argument checks.
  */
 int cp_eval_choose_plan(const cp_graph *g, int32_t batch, int32_t k, const int64_t *speeds,
                         const int64_t *bandwidth, int tick_dtype, int *plan_out);
@@ -208,9 +212,9 @@ int cp_eval_choose_plan(const cp_graph *g, int32_t batch, int32_t k, const int64
  *   profile       NULL, or a profile whose next slot receives this call's stage timestamps
  *
  * Dependencies between outputs: mask_out needs cp_out, blevel_out and tlevel_out; cp_out needs
- * blevel_out unless the resident-window plan runs on a graph without far reads (info.window_far_b
- * == 0): it keeps a running maximum, so CP alone costs no output traffic (cp_eval_choose_plan tells
- * which plan CP_PLAN_AUTO takes).  CP_ERR_ARG otherwise.
+ * blevel_out unless a window plan (2, 3, 4, 6) runs on a graph without far reads (info.window_far_b
+ * == 0), or the lane-window plan is asked for by name: these keep a running maximum, so CP alone costs
+ * no output traffic (CP_PLAN_AUTO goes by the plan that cp_eval_choose_plan names).  CP_ERR_ARG otherwise.
  * Errors: CP_ERR_NULL, CP_ERR_SIZE, CP_ERR_SPEED, CP_ERR_BANDWIDTH, CP_ERR_OVERFLOW
  * (CP_TICK_I32 with a bound >= 2^31), CP_ERR_WORKSPACE, CP_ERR_STATE, CP_ERR_ARG, CP_ERR_HIP.
  */
@@ -239,7 +243,8 @@ int cp_eval(const cp_graph *g, int32_t batch, int32_t k,
  * writes partition-major outputs; the device ids in sweep order (about n * batch bytes per
  * sweep) when the resident-window plan cannot read them straight from the caller's rows
  * (vertex-major assignments, rows not 16-byte aligned, or a graph whose levels are
- * scattered over the vertex numbers).  A resident-window call on aligned partition-major
+ * scattered over the vertex numbers); the same and the copies of far reads for the lane-window plan, which
+ * CP_PLAN_AUTO leaves aside where they do not fit.  A resident-window call on aligned partition-major
  * rows needs the tables only.
  *
  * All calls on one GPU share that GPU's array: calls that may overlap in time on one GPU
@@ -463,6 +468,8 @@ int cp_profile_count(const cp_profile *p, int32_t *out);   /* slots filled so fa
  * launch ran both (its time is the b-level stage's). */
 int cp_profile_read(const cp_profile *p, int32_t slot, float ms_out[CP_NUM_STAGES],
                     int32_t sweep_launches[2]);
+/* CP_PLAN_* that the call in a filled slot ran. */
+int cp_profile_plan(const cp_profile *p, int32_t slot, int *plan_out);
 void cp_profile_destroy(cp_profile *p);
 
 /*

@@ -32,7 +32,7 @@ EXPORTS = (
     "cp_search_workspace_bytes", "cp_search", "cp_seed_workspace_bytes", "cp_seed_partition",
     "cp_simulate_workspace_bytes", "cp_simulate",
     "cp_profile_create", "cp_profile_reset",
-    "cp_profile_count", "cp_profile_read", "cp_profile_destroy", "cp_cost_magic",
+    "cp_profile_count", "cp_profile_read", "cp_profile_plan", "cp_profile_destroy", "cp_cost_magic",
     "cp_error_string", "cp_cost_compact", "cp_window_shape",
 )
 
@@ -137,6 +137,8 @@ def load_library():
     lib.cp_profile_count.argtypes = [vp, i32p]
     lib.cp_profile_read.restype = C.c_int
     lib.cp_profile_read.argtypes = [vp, C.c_int32, C.POINTER(C.c_float), i32p]
+    lib.cp_profile_plan.restype = C.c_int
+    lib.cp_profile_plan.argtypes = [vp, C.c_int32, C.POINTER(C.c_int)]
     lib.cp_profile_destroy.restype = None
     lib.cp_profile_destroy.argtypes = [vp]
     lib.cp_cost_magic.restype = C.c_int
@@ -292,6 +294,14 @@ class CpProfile:
             raise CpError(rc, "cp_profile_read")
         return {STAGE_NAMES[i]: float(ms[i]) for i in range(NUM_STAGES)}, (int(launches[0]), int(launches[1]))
 
+    def plan(self, slot: int) -> int:
+        """PLAN_* that the call in a filled slot ran."""
+        out = C.c_int(0)
+        rc = self._lib.cp_profile_plan(self._handle, int(slot), C.byref(out))
+        if rc:
+            raise CpError(rc, "cp_profile_plan")
+        return int(out.value)
+
     def close(self):
         if getattr(self, "_handle", None) is not None and self._handle:
             self._lib.cp_profile_destroy(self._handle)
@@ -317,7 +327,8 @@ def workspace_bytes(graph: CpGraph, batch: int, k: int, assign_layout=ASSIGN_PAR
 
 
 def choose_plan(graph: CpGraph, batch: int, speeds, bandwidth, tick_bytes=None) -> int:
-    """The plan PLAN_AUTO resolves to for this batch and cost model on the current device."""
+    """The plan PLAN_AUTO resolves to for this batch and cost model on the current device; where the lane-window plan
+    is faster for a call, it runs in this one's place (``CpProfile.plan`` tells)."""
     s = np.ascontiguousarray(speeds, dtype=np.int64)
     bw = np.ascontiguousarray(bandwidth, dtype=np.int64)
     if tick_bytes is None:

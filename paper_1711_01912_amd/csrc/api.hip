@@ -17,6 +17,7 @@ struct cp_profile {
     int32_t slots = 0, count = 0;
     std::vector<hipEvent_t> ev;          // slots * (CP_NUM_STAGES + 1)
     std::vector<int32_t> launches;       // slots * 2
+    std::vector<int32_t> plan;           // slots
 };
 
 namespace {
@@ -697,6 +698,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
         ev = profile->ev.data() + (size_t)profile->count * (CP_NUM_STAGES + 1);
         launches = profile->launches.data() + (size_t)profile->count * 2;
         launches[0] = launches[1] = 0;
+        profile->plan[(size_t)profile->count] = use;
         profile->count++;
     }
 #define CP_MARK(i)                                                              \
@@ -1234,6 +1236,7 @@ int cp_profile_create(int32_t slots, cp_profile **out) {
     try {
         p->ev.assign((size_t)slots * (CP_NUM_STAGES + 1), nullptr);
         p->launches.assign((size_t)slots * 2, 0);
+        p->plan.assign((size_t)slots, CP_PLAN_AUTO);
     } catch (const std::bad_alloc &) {
         delete p;
         return CP_ERR_ALLOC;
@@ -1270,6 +1273,13 @@ int cp_profile_read(const cp_profile *p, int32_t slot, float ms_out[CP_NUM_STAGE
         sweep_launches[0] = p->launches[(size_t)slot * 2];
         sweep_launches[1] = p->launches[(size_t)slot * 2 + 1];
     }
+    return CP_OK;
+}
+
+int cp_profile_plan(const cp_profile *p, int32_t slot, int *plan_out) {
+    if (!p || !plan_out) return CP_ERR_NULL;
+    if (slot < 0 || slot >= p->count) return CP_ERR_STATE;
+    *plan_out = p->plan[(size_t)slot];
     return CP_OK;
 }
 
