@@ -381,9 +381,10 @@ def cp_eval(graph: CpGraph, assignments, speeds, bandwidth, *, want=("cp", "b", 
     if "mask" in want:
         want |= {"cp", "b", "tl"}
     if "cp" in want and "b" not in want:
-        # CP alone: the resident-window plan needs no b array for it
+        # CP alone: the window plans need no b array for it, without far reads; the lane-window plan never does
         used = plan if plan != PLAN_AUTO else choose_plan(graph, batch, s, bw, tick_bytes)
-        if used not in (PLAN_RESIDENT_WINDOW, PLAN_SHARED_WINDOW_2, PLAN_SHARED_WINDOW_4, PLAN_STREAMED_WINDOW) or info["window_far_b"] > 0:
+        window = (PLAN_RESIDENT_WINDOW, PLAN_SHARED_WINDOW_2, PLAN_SHARED_WINDOW_4, PLAN_STREAMED_WINDOW)
+        if used != PLAN_LANE_WINDOW and (used not in window or info["window_far_b"] > 0):
             want.add("b")
     rows, cols = (n, batch) if out_layout == OUT_VERTEX_MAJOR else (batch, n)
     if "cp" in want and "cp" not in out:

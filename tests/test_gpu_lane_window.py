@@ -45,6 +45,7 @@ def _check(gpu, oracle, w, **kw):
         assert_equal_to_oracle(res, ref, f"layout {layout}, outputs {out_layout}")
     for want in (("cp",), ("tl",), ("b",)):       # one sweep alone
         res = run_gpu(w, gpu.PLAN_LANE_WINDOW, graph=g, out_layout=1, want=want, **kw)
+        assert set(res) == set(want)              # CP alone writes no b, with far reads neither
         for key in want:
             assert np.array_equal(res[key], ref[key]), key
     g.close()
