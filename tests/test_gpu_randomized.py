@@ -9,7 +9,7 @@ from workloads.dags import _finish
 
 pytestmark = pytest.mark.gpu
 
-PLANS = (1, 2, 3, 4, 5, 6)    # wave-column, resident window, shared window x2 / x4, column slices, streamed window
+PLANS = (1, 2, 3, 4, 5, 6, 7)    # wave-column, resident window, shared window x2 / x4, column slices, streamed, lane window
 
 
 @pytest.fixture(scope="module")
