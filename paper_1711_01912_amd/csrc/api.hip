@@ -286,7 +286,8 @@ double crowded_window_sweep_us(const WindowDir &d, const WindowCfg &c, int32_t b
 
 // The cheapest shape for this batch: true and its time if the lane-window kernel applies.
 bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, const int64_t *speeds, const int64_t *bandwidth,
-                  int32_t batch, int tick_bytes, bool with_out, bool by_partition, int sweeps, size_t lds_limit, LaneCfg &out, double *us_out) {
+                  int32_t batch, int tick_bytes, bool with_out, bool by_partition, int sweeps, size_t lds_limit,
+                  LaneCfg &out, double *us_out) {
     if (!p.have_lanes || k > kMagicMaxK) return false;
     // the multiply-shift forms go with 32-bit ring words, the rounded form with 64-bit ones
     const int word = p.lane_word == 4 && tabs.magic_ok ? 4 : 8;
@@ -494,7 +495,7 @@ int cp_eval_workspace_bytes(const cp_graph *g, int32_t batch, int32_t k, int ass
     // the lane-window plan regroups the device ids
     size_t lanes = 0;
     if ((plan == CP_PLAN_AUTO || plan == CP_PLAN_LANE_WINDOW) && g->packed.have_lanes && k <= kMagicMaxK)
-        for (int groups : {4, 8}) 
+        for (int groups : {4, 8})
             lanes = std::max(lanes, lane_work_bytes(&g->packed.lane_b, &g->packed.lane_t, g->packed.n, batch, groups, 8));
     *out_bytes = bytes + std::max({column, window, lanes});
     return CP_OK;

@@ -5,12 +5,12 @@
 // every partition pays the tick's chain of dependent LDS reads and its barrier for itself (19,800
 // vertices in 660 levels, 4,096 partitions: 1.6 ms per sweep, 0.78 us a tick, three rounds of
 // workgroups).  Here a workgroup owns G = 4 or 8 consecutive partitions, a wavefront relaxes
-// 64 / G sub-rows (runs of at most kLaneWidth edges of a vertex) for all of them at once, and the
+// 64 / G sub-rows (runs of at most LaneDir::width edges of a vertex) for all of them at once, and the
 // lanes of a partition group share the packet entry they read, so a narrow level fills the
 // lanes and the tick's chain is paid once per G partitions.  Both sweeps of a call run side by
 // side in one launch.  Whole calls, before -> now: 2,016 vertices in 195 levels, 1,024 partitions 300 ->
 // 105 us; 121,000 in 701 levels, 777 partitions, rows per vertex 2.84 -> 1.15 ms; 29,000 in 301 levels with
-// 64-bit ticks (a launch per level before), 320 partitions 3.65 -> 0.34 ms.  What bounds it: on narrow ticks
+// 64-bit ticks (a launch per level before), 320 partitions 3.65 -> 0.32 ms.  What bounds it: on narrow ticks
 // the chain of a tick (two LDS round trips, publication, barrier: about 0.3 us), on wide ones the vector
 // instructions of a compute unit (55 per item of 4 entries, about 0.05 us with what loaders and stores add).
 //
@@ -35,7 +35,7 @@
 //             those of tick t + 1 behind the ring.  A word is copied in the iteration after its tick, every
 //             store wavefront waits each iteration until its copies of kFarWait iterations ago have
 //             reached the L2, and the fetch, past the L1, is issued X + 1 iterations before the tick that
-//             reads it: a distance of kFarWait + X + 3 ticks or more is safe, kLaneFarTicks is that.
+//             reads it: a distance of kFarWait + X + 3 = 15 ticks or more is safe; kLaneFarTicks is 16.
 // A vertex with several sub-rows needs no care: words are published with LDS maxima into rows that hold
 // the device ids already.
 #include <hip/hip_runtime.h>
@@ -80,7 +80,7 @@ struct LaneArgs {
 };
 
 struct LaneShape {
-    int32_t nc, nlw, nsw, nfw; // compute, loader, store and far wavefronts
+    int32_t nc, nlw, nsw;      // compute, loader and store wavefronts; the others, if any, are far wavefronts
     uint32_t stage_off, stage_bytes, tab_off, ticks_off;
 };
 
@@ -498,7 +498,7 @@ int launch_lanes_k(const LaneArgs &b, const LaneArgs &t, const LaneCfg &cfg, int
             hipSuccess)
         return CP_ERR_HIP;
     LaneShape sh{};
-    sh.nc = cfg.nc; sh.nlw = cfg.nlw; sh.nsw = cfg.nsw; sh.nfw = cfg.nfw;
+    sh.nc = cfg.nc; sh.nlw = cfg.nlw; sh.nsw = cfg.nsw;
     sh.stage_off = (uint32_t)cfg.stage_off;
     sh.stage_bytes = (uint32_t)cfg.stage_bytes;
     sh.tab_off = (uint32_t)cfg.tab_off;
