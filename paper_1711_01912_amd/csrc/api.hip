@@ -609,7 +609,8 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
             const bool both = lane_sweeps == 2, want_b = blevel_out || cp_out;
             const bool rows = assign_layout == CP_ASSIGN_PARTITION_MAJOR &&
                               ((uint64_t)p.n * (uint64_t)batch) % 16 == 0 && ((uintptr_t)assignments % 16) == 0;
-            double other_us = column_plan_us(p, batch, (size_t)tick_dtype) * (both ? 1.0 : 0.5);
+            double other_us = 0.0;
+            if (use == CP_PLAN_WAVE_COLUMN) other_us = column_plan_us(p, batch, (size_t)tick_dtype) * (both ? 1.0 : 0.5);
             if (use == CP_PLAN_RESIDENT_WINDOW) {
                 const double b_us = crowded_window_sweep_us(p.win_b, cfg_b, batch, by_partition);
                 const double t_us = crowded_window_sweep_us(p.win_t, cfg_t, batch, by_partition);
