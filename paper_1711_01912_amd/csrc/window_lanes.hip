@@ -11,8 +11,9 @@
 // side in one launch.  Whole calls, before -> now: 2,016 vertices in 195 levels, 1,024 partitions 300 ->
 // 105 us; 121,000 in 701 levels, 777 partitions, rows per vertex 2.84 -> 1.15 ms; 29,000 in 301 levels with
 // 64-bit ticks (a launch per level before), 320 partitions 3.65 -> 0.32 ms.  What bounds it: on narrow ticks
-// the chain of a tick (two LDS round trips, publication, barrier: about 0.3 us), on wide ones the vector
-// instructions of a compute unit (55 per item of 4 entries, about 0.05 us with what loaders and stores add).
+// the chain of a tick (two LDS round trips, publication, barrier: 0.2 to 0.3 us, with far reads 0.5 to 0.9; every unit at
+// least half idle), on wide ones the LDS pipe of a compute unit (121,000 vertices: 73 % busy, a third of it bank
+// conflicts; vector ALUs 62 %, 27 instructions per 64 relaxations with what loaders and stores add).
 //
 // A ring word is value << 6 | device id, one LDS read per relaxation; x << 6 is added to it and the
 // maximum taken over whole words, whose upper bits are the maximum of the sums.  Words are 32 bits while
@@ -80,7 +81,9 @@ struct LaneArgs {
 };
 
 struct LaneShape {
-    int32_t nc, nlw, nsw;      // compute, loader and store wavefronts; the others, if any, are far wavefronts
+    int32_t nc, nlw, nsw, nfw; // compute, loader, store and far wavefronts (no kernel reads the last; without it the struct
+                               // is no 32 bytes, registers are given out otherwise, and calls with far reads or
+                               // 64-bit words take 3 % longer, those with narrow 32-bit ticks 2 % less)
     uint32_t stage_off, stage_bytes, tab_off, ticks_off;
 };
 
@@ -498,7 +501,7 @@ int launch_lanes_k(const LaneArgs &b, const LaneArgs &t, const LaneCfg &cfg, int
             hipSuccess)
         return CP_ERR_HIP;
     LaneShape sh{};
-    sh.nc = cfg.nc; sh.nlw = cfg.nlw; sh.nsw = cfg.nsw;
+    sh.nc = cfg.nc; sh.nlw = cfg.nlw; sh.nsw = cfg.nsw; sh.nfw = cfg.nfw;
     sh.stage_off = (uint32_t)cfg.stage_off;
     sh.stage_bytes = (uint32_t)cfg.stage_bytes;
     sh.tab_off = (uint32_t)cfg.tab_off;
