@@ -734,7 +734,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     s.magic = tabs.magic_ok;
     s.narrow = p.narrow;
     s.tick_bytes = tick_dtype;
-    s.n = p.n; s.m = p.m; s.P = batch; s.k = k; s.L = p.L; s.max_width = p.max_width;
+    s.n = p.n; s.P = batch; s.k = k; s.L = p.L; s.max_width = p.max_width;
     const uint32_t *d_tab4 = tabs.tab4_ok ? (const uint32_t *)(d_tab + table_entries(k) * 8) : nullptr;
     s.vert_tab4 = d_tab4 ? d_tab4 + 2 * kk : nullptr;
     s.pT = pT;

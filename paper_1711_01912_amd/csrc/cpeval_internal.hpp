@@ -52,6 +52,7 @@ struct ColumnDir {
     size_t lvl_off = 0;     // int32 [L][4]  {first position, hub rows, rows, 0} per level in sweep order
     // per level, in sweep order
     std::vector<int32_t> lvl_begin, lvl_hubs, lvl_count;
+    std::vector<int32_t> lvl_longest;    // edges of the longest row that is no hub row
 };
 
 // One sweep direction of the resident-window plan.  Vertices are renumbered by

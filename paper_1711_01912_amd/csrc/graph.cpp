@@ -46,6 +46,7 @@ void sweep_order(int32_t n, int32_t L, const int32_t *level_ptr, const int32_t *
     dir.lvl_begin.assign(L, 0);
     dir.lvl_hubs.assign(L, 0);
     dir.lvl_count.assign(L, 0);
+    dir.lvl_longest.assign(L, 0);
     int32_t pos = 0;
     for (int32_t s = 0; s < L; ++s) {
         int32_t l = forward ? s : L - 1 - s;
@@ -64,6 +65,7 @@ void sweep_order(int32_t n, int32_t L, const int32_t *level_ptr, const int32_t *
         dir.lvl_begin[s] = pos;
         dir.lvl_hubs[s] = hubs;
         dir.lvl_count[s] = b - a;
+        if (hubs < b - a) dir.lvl_longest[s] = ptr[order[pos + hubs] + 1] - ptr[order[pos + hubs]];
         pos += b - a;
     }
 }

@@ -141,7 +141,7 @@ struct ColumnArgs {
 // leaving the maximum in its inner loop without a condition took 2 - 6 % off every batch.
 template <int ROWS>
 __device__ __forceinline__ bool column_task(const ColumnArgs &a, int wave, int32_t &vi, int32_t &col) {
-    column_place((int32_t)blockIdx.x, ROWS > 1 ? wave : 0, a.deal, a.ncol, ROWS, vi, col);
+    column_place(blockIdx.x, ROWS > 1 ? (uint32_t)wave : 0u, a.deal, (uint32_t)a.ncol, ROWS, vi, col);
     const bool live = vi < a.count && col < a.ncol;
     if (!live) vi = col = 0;
     return live;
@@ -1126,10 +1126,9 @@ int launch_column_sweep_t(const SweepLaunch &s, hipStream_t st, int32_t *launche
     a.status = s.status;
     a.P = s.P; a.ncol = ncol; a.k = s.k;
     const int4 *rows = (const int4 *)(s.blob + dir.rows_off);
-    auto deal = [&](int32_t rows, int rows_per_block) {
+    auto deal = [&](int32_t rows, int rows_per_block, int32_t longest) {
         a.count = rows;
-        a.deal = column_deal(rows, ncol, rows_per_block,
-                             column_by_slices(rows, ncol, (int)sizeof(Tick), (double)s.m / std::max(s.n, 1)));
+        a.deal = column_deal(rows, ncol, rows_per_block, column_by_runs(longest, ncol));
         return column_blocks(a.deal, rows, ncol, rows_per_block);
     };
     int32_t count = 0;
@@ -1137,7 +1136,7 @@ int launch_column_sweep_t(const SweepLaunch &s, hipStream_t st, int32_t *launche
         const int32_t hubs = dir.lvl_hubs[l], total = dir.lvl_count[l];
         if (hubs > 0) {
             a.rows = rows + dir.lvl_begin[l];
-            const int64_t blocks = deal(hubs, 1);
+            const int64_t blocks = deal(hubs, 1, kHubDegree);
             const size_t lds_bytes = tab_bytes + sizeof(Tick) * 64 * kHubWaves;
             hipLaunchKernelGGL((column_level_kernel<Tick, WT, MAGIC, TSWEEP, true>),
                                dim3((unsigned)blocks), dim3(kHubWaves * 64), lds_bytes, st, a);
@@ -1145,7 +1144,7 @@ int launch_column_sweep_t(const SweepLaunch &s, hipStream_t st, int32_t *launche
         }
         if (total > hubs) {
             a.rows = rows + dir.lvl_begin[l] + hubs;
-            const int64_t blocks = deal(total - hubs, 4);
+            const int64_t blocks = deal(total - hubs, 4, dir.lvl_longest[l]);
             hipLaunchKernelGGL((column_level_kernel<Tick, WT, MAGIC, TSWEEP, false>),
                                dim3((unsigned)blocks), dim3(256), tab_bytes, st, a);
             ++count;

@@ -17,7 +17,6 @@ struct SweepLaunch {
     bool narrow = false;                // 32-bit weights in the blob
     int tick_bytes = 4;
     int32_t n = 0, P = 0, k = 0, L = 0, max_width = 0;
-    int64_t m = 0;
     const uint8_t *pT = nullptr;        // [n][P] device ids (wave-column)
     const uint8_t *assign = nullptr;    // caller's assignments (resident-window: input of the gather)
     const uint8_t *pperm = nullptr;     // [P][ticks*wpad] device ids in sweep order (resident-window)
@@ -96,31 +95,29 @@ inline unsigned prepare_blocks(int32_t words, int32_t cells) {
                                         std::min<int64_t>(kPrepareBlocks, ((int64_t)cells + 255) / 256)});
 }
 
-// Which row of a level and which 64 partitions (a slice) a wavefront of the wave-column kernel takes.
-//   by rows (parts = 0)  all slices of a row before the next one: the longest rows, which come first in a level,
-//                        start first.  Where the slices are a multiple of 4, an XCD also meets the same few of them
-//                        in every row.
-//   by slices            `parts` of a slice's blocks are dealt to the XCDs one by one, slice after slice, so that an
-//                        L2 keeps a slice's values while all rows read them.  Rows are sorted by length: a part takes
-//                        every parts-th block of rows (runs of rows gave one XCD all the long ones).
-// Measured over levels of 3 to 20,000 vertices and 24 to 200,000 partitions, all three outputs.  By slices gains
-// where their number is odd, a level's values outgrow the L2s and there are rows enough to use a slice up: 10,000 rows
-// of 12 edges, 17 slices 1.54 -> 1.32 ms; 5,000 of 3 edges, 17 slices 0.381 -> 0.366.  Elsewhere it loses: 30 rows,
-// 3,125 slices 0.51 -> 0.65 ms; 2,000 rows of 12 edges, 17 slices 0.43 -> 0.51; 10 or 14 slices +-4 %; 20,000
-// rows of 3 edges (a slice of 6.4 MB does not fit an L2), 17 slices 1.52 -> 1.61.
+// Which row of a level and which 64 partitions (a slice) a wavefront of the wave-column kernel takes.  Rows are sorted by
+// length, and blocks go round the 8 XCDs.
+//   by rows   (parts = 0) all slices of a row before the next one: the longest rows start first, and all XCDs share them
+//   by runs   slice after slice, a slice's blocks cut into `parts` runs that are dealt to the XCDs: an XCD's L2 keeps a
+//             slice's values while its rows read them, and the edges of its rows from slice to slice
+// By runs go launches of hub rows (all long, so that runs are even), and rows of up to kHubDegree edges with long ones
+// among them where the slices are few or one per XCD: those of a slice then share an L2.  With more slices, one
+// XCD would get all long rows.  Everything else goes by rows: t sweeps of the graphs below 1.05 to 1.3 times as fast as by runs.
+// Levels with one row in a hundred of a tenth of a level's edges, by rows -> by runs, b sweeps: 10,000 rows, 17 slices
+// 1,766 -> 1,347 us (hubs by runs), 6,500 rows, 5 slices 269 -> 257; 2,446 rows (244 edges, no hub rows) 1 slice 294 ->
+// 260, 4 slices 312 -> 256, 8 slices 308 -> 247, but 10 slices 328 -> 378, 17 slices 342 -> 507.
 #if defined(__HIPCC__)
 #define CP_HOST_DEVICE __host__ __device__ __forceinline__
 #else
 #define CP_HOST_DEVICE inline
 #endif
+constexpr int kColumnRunRow = 64;         // edges of a long row
 struct ColumnDeal { int32_t parts, part_blocks; };
-inline bool column_by_slices(int32_t rows, int32_t slices, int tick_bytes, double edges_per_row) {
-    const int64_t slice = (int64_t)rows * 64 * (tick_bytes + 1);
-    return slices % 2 == 1 && rows >= 3000 && slice * slices >= (12 << 20) &&
-           (slice <= (4 << 20) || edges_per_row >= 8.0);
+inline bool column_by_runs(int32_t longest_row, int32_t slices) {
+    return longest_row >= kHubDegree || (longest_row >= kColumnRunRow && (slices <= 4 || slices == 8));
 }
-inline ColumnDeal column_deal(int32_t rows, int32_t slices, int rows_per_block, bool by_slices) {
-    if (!by_slices) return ColumnDeal{0, 0};
+inline ColumnDeal column_deal(int32_t rows, int32_t slices, int rows_per_block, bool by_runs) {
+    if (!by_runs) return ColumnDeal{0, 0};
     const int32_t row_blocks = (rows + rows_per_block - 1) / rows_per_block;
     const int32_t even = slices % 8 == 0 ? 1 : (slices % 4 == 0 ? 2 : (slices % 2 == 0 ? 4 : 8));
     const int32_t parts = std::max(1, std::min(even, row_blocks));
@@ -130,19 +127,19 @@ inline int64_t column_blocks(const ColumnDeal &d, int32_t rows, int32_t slices, 
     if (!d.parts) return ((int64_t)rows * slices + rows_per_block - 1) / rows_per_block;
     return ((int64_t)slices * d.parts + 7) / 8 * 8 * d.part_blocks;
 }
-// Row and slice of a wavefront; either may lie past the end.
-CP_HOST_DEVICE void column_place(int32_t block, int wave, const ColumnDeal &d, int32_t slices, int rows_per_block,
-                                 int32_t &row, int32_t &slice) {
+// Row and slice of a wavefront; either may lie past the end.  (A grid holds fewer than 2^24 blocks of 256 threads.)
+CP_HOST_DEVICE void column_place(uint32_t block, uint32_t wave, const ColumnDeal &d, uint32_t slices,
+                                 uint32_t rows_per_block, int32_t &row, int32_t &slice) {
     if (!d.parts) {
-        const int64_t task = (int64_t)block * rows_per_block + wave;
+        const uint32_t task = block * rows_per_block + wave;
         row = (int32_t)(task / slices);
         slice = (int32_t)(task % slices);
         return;
     }
-    const int32_t i = block / 8;
-    const int32_t unit = i / d.part_blocks * 8 + block % 8;
-    row = (i % d.part_blocks * d.parts + unit % d.parts) * rows_per_block + wave;
-    slice = unit / d.parts;
+    const uint32_t parts = (uint32_t)d.parts, part_blocks = (uint32_t)d.part_blocks, i = block / 8;
+    const uint32_t unit = i / part_blocks * 8 + block % 8;
+    row = (int32_t)((unit % parts * part_blocks + i % part_blocks) * rows_per_block + wave);
+    slice = (int32_t)(unit / parts);
 }
 
 // Launch shape of the lane-window kernel, the same for both sweeps.

@@ -23,13 +23,13 @@ static int prepare() {
     return 0;
 }
 
-// Every row of every slice is taken once, in either order; by slices, the XCDs (block number modulo 8) get even shares
-// of rows that are sorted by length, the first one in fifty a hundred times as long as the others.
-static int column_order(int32_t rows, int32_t slices, int per_block, bool by_slices) {
-    const ColumnDeal d = column_deal(rows, slices, per_block, by_slices);
+// Every row of every slice is taken once, in either order; by runs, the XCDs (block number modulo 8) get even shares of
+// the rows, which are alike where that order is taken for any number of slices.
+static int column_rows(int32_t rows, int32_t slices, int per_block, bool by_runs) {
+    const ColumnDeal d = column_deal(rows, slices, per_block, by_runs);
     const int64_t blocks = column_blocks(d, rows, slices, per_block);
     std::vector<int> taken((size_t)rows * slices, 0);
-    double share[8] = {}, all = 0;
+    int64_t share[8] = {};
     for (int32_t b = 0; b < blocks; ++b)
         for (int wave = 0; wave < per_block; ++wave) {
             int32_t r, slice;
@@ -37,18 +37,15 @@ static int column_order(int32_t rows, int32_t slices, int per_block, bool by_sli
             if (r < 0 || slice < 0) return std::printf("below 0\n"), 1;
             if (r >= rows || slice >= slices) continue;
             ++taken[(size_t)r * slices + slice];
-            const double length = r < rows / 50 ? 100 : 1;
-            share[b % 8] += length;
-            all += length;
+            ++share[b % 8];
         }
     for (int x : taken)
         if (x != 1) return std::printf("slices %d rows %d: a row %d times\n", slices, rows, x), 1;
-    if (!by_slices) return 0;
-    // a part of a slice has at most one block of long rows more than another
+    if (!by_runs) return 0;
     const int64_t units = ((int64_t)slices * d.parts + 7) / 8, row_blocks = (rows + per_block - 1) / per_block;
-    const double most = *std::max_element(share, share + 8);
-    if (rows >= 1000 && most > all / 8 + units * per_block * 100.0)
-        return std::printf("slices %d rows %d: an XCD has %.0f of %.0f\n", slices, rows, most, all), 1;
+    const int64_t most = *std::max_element(share, share + 8);
+    if (most > units * d.part_blocks * per_block)
+        return std::printf("slices %d rows %d: an XCD has %lld rows\n", slices, rows, (long long)most), 1;
     // no more than the blocks of the rows, rounded up per part and per round of the XCDs
     if (blocks > slices * row_blocks + (int64_t)slices * d.parts + 8 * d.part_blocks)
         return std::printf("slices %d rows %d: %lld blocks\n", slices, rows, (long long)blocks), 1;
@@ -59,11 +56,11 @@ static int column() {
     for (int per_block : {1, 4})
         for (int32_t slices : {1, 2, 3, 4, 7, 8, 10, 17, 24})
             for (int32_t rows : {1, 3, 4, 5, 31, 32, 33, 1000, 4001})
-                for (bool by_slices : {false, true})
-                    if (column_order(rows, slices, per_block, by_slices)) return 1;
-    // few rows, an even number of slices and levels that the L2s hold: the longest rows first
-    if (column_by_slices(30, 3125, 4, 3) || column_by_slices(10000, 16, 4, 12) || column_by_slices(1031, 17, 4, 9) ||
-        column_by_slices(20000, 17, 4, 3) || !column_by_slices(10000, 17, 4, 12))
+                for (bool by_runs : {false, true})
+                    if (column_rows(rows, slices, per_block, by_runs)) return 1;
+    // rows of very different lengths stay in order where runs would give one XCD the long ones of many slices
+    if (!column_by_runs(kHubDegree, 17) || column_by_runs(255, 17) || column_by_runs(255, 5) || !column_by_runs(255, 1) ||
+        !column_by_runs(64, 8) || column_by_runs(63, 1))
         return std::printf("the rule\n"), 1;
     return 0;
 }

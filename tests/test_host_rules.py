@@ -33,7 +33,7 @@ def test_large_batches_are_cleared_by_as_many_threads(harness):
     _holds(harness, "prepare")
 
 
-def test_wave_column_blocks_cover_the_rows_and_share_long_ones_out(harness):
+def test_wave_column_blocks_cover_the_rows_and_leave_long_ones_in_order(harness):
     _holds(harness, "column")
 
 
