@@ -253,35 +253,59 @@ int choose_window_plan(const Packed &p, int32_t k, size_t tick_bytes, size_t lds
     return best;
 }
 
-// The lane-window kernel: both sweeps in one launch, a workgroup per sweep and G partitions.  A tick is a chain of
-// 0.2 us, 0.1 more with rows per partition; with far reads 0.2 us more and 0.003 per far read of the widest tick, and
-// 0.14 of its own with rows per partition (the store wavefronts wait for their copies behind those stores).  To the
-// chain every workgroup of a compute unit adds 0.04 us and its items, 0.042 us each, twice that with 64-bit words.
-// Fitted, with the model below, to 408 calls: 60 to 250,000 vertices, 8 to 1,900 ticks, 8 to 4,096 partitions, 2 to 50
-// devices, one sweep or both, either layout.  Over 414 others the plan is slower than the one it stands in for by
-// more than 3 % in 9 of the 339 calls it is chosen for (10 partitions of 84,000 vertices: 1.22 times), and all 414
-// take 1.82 times as long without it.  With one chain of 0.3 us for every shape it was 41 calls, up to 1.52 times:
-// batches of fewer than 1,000 partitions with far reads.
-double lane_sweep_us(const LaneDir &d, const LaneCfg &c, int32_t batch, int sweeps, bool by_partition) {
+// The lane-window kernel: both sweeps in one launch, a workgroup per sweep and G partitions.  A tick takes the longer of
+// two chains.
+//   compute   0.2 us, 0.05 more with rows per partition; with far reads 0.2 us more and 0.005 per far read of the widest
+//             tick, and 0.14 with rows per partition.  Without outputs (CP alone) 0.15 us, with far reads 0.18 more
+//             and 0.0015 per far read.  Every workgroup of a compute unit adds 0.04 us and its items:
+//             0.036 us each with 4 entries a sub-row, 0.03 with 2, twice that with 64-bit words.
+//   stores    0.32 us (rows per vertex 0.255) for each pair of pieces that a store wavefront writes one after the other,
+//             0.34 more with far reads, and 0.27 of what the workgroups add to the other chain.
+// Fitted, with the model below, to 1,100 calls: 60 to 250,000 vertices, 8 to 1,900 ticks, 8 to 4,096 partitions, 2 to 50
+// devices, one sweep or both, either layout.  Over 274 others the plan is slower than the one it stands in for by more
+// than 3 % in 5 calls, at most 1.08 times, and what it stands in for would have been passed over for it with a gain of
+// more than 3 % in 4.  With one chain of 0.3 us for every shape, 85 of 822 calls were slower, up to 1.52 times: batches
+// of fewer than 1,000 partitions with far reads above all.
+double lane_sweep_us(const LaneDir &d, const LaneCfg &c, int32_t n, int32_t batch, int sweeps, bool with_out,
+                     bool by_partition) {
     const double wgs = std::ceil((double)batch / c.groups) * sweeps;
     const double per_cu = std::max(1.0, std::floor(std::min((double)kLdsBudget / (double)(c.lds_bytes + 512),
                                                             (c.nfw > 0 && c.word == 8 ? 24.0 : 32.0) /
                                                                 (c.nc + c.nlw + c.nsw + c.nfw))));
+    const bool far = d.far_cap > 0;
     const double items = (double)d.units * c.groups / 8 / std::max(d.ticks, 1);      // per tick
-    const double chain = 0.2 + (by_partition ? 0.1 : 0.0) +
-                         (c.nfw > 0 ? 0.2 + 0.003 * d.far_cap + (by_partition ? 0.14 : 0.0) : 0.0);
-    const double each = 0.04 + items * 0.042 * (c.word == 8 ? 2.0 : 1.0);
+    const double each = 0.04 + items * (c.width == 2 ? 0.03 : 0.036) * (c.word == 8 ? 2.0 : 1.0);
+    double chain = 0.2 + (by_partition ? 0.05 : 0.0) +
+                   (far ? 0.2 + 0.005 * d.far_cap + (by_partition ? 0.14 : 0.0) : 0.0);
+    double stores = 0.0;
+    if (!with_out) {
+        chain = 0.15 + (far ? 0.18 + 0.0015 * d.far_cap : 0.0);
+    } else {
+        const double verts = (double)n / std::max(d.ticks, 1);
+        const double rows_at_once = std::max(1.0, 64.0 / std::exp2(std::ceil(std::log2(std::max(1.0, std::min(64.0, verts))))));
+        const double pairs = by_partition ? std::ceil(verts / 64.0) * std::ceil(c.groups / (2.0 * c.nsw * rows_at_once))
+                                          : std::ceil(verts * c.groups / (2.0 * c.nsw * 64.0));
+        stores = pairs * (by_partition ? 0.32 : 0.255) + (far ? 0.34 : 0.0);
+    }
+    auto tick = [&](double there) { return std::max(chain + there * each, stores + 0.27 * there * each); };
     const double full = std::floor(wgs / (256.0 * per_cu)), rest = std::ceil((wgs - full * 256.0 * per_cu) / 256.0);
-    return d.ticks * (full * (chain + per_cu * each) + (rest > 0.0 ? chain + rest * each : 0.0));
+    return d.ticks * (full * tick(per_cu) + (rest > 0.0 ? tick(rest) : 0.0));
 }
 
-// The resident-window kernel as the lane-window plan meets it: a chain of 0.63 us a tick, or, where its workgroups
-// crowd a compute unit, 0.09 us a slice whichever workgroup it belongs to, 1.3 times that with rows per vertex.
-// (window_sweep_us above, which ranks the window plans among each other, leaves the crowding out.)
+// The resident-window kernel as the lane-window plan meets it: a chain of 0.63 us a tick and 0.015 a slice, or, where its
+// workgroups crowd a compute unit, 0.083 us a slice whichever workgroup it belongs to, 1.16 times that with rows per
+// vertex.  (window_sweep_us above, which ranks the window plans among each other, leaves the crowding out.)
 double crowded_window_sweep_us(const WindowDir &d, const WindowCfg &c, int32_t batch, bool by_partition) {
     const double per_cu = window_wg_per_cu(c), wgs = std::ceil((double)batch / std::max(1, c.groups));
     const double rounds = std::ceil(wgs / (256.0 * per_cu)), there = std::min(per_cu, std::ceil(wgs / 256.0));
-    return rounds * d.ticks * std::max(0.63, 0.09 * d.smax * there * (by_partition ? 1.0 : 1.3));
+    return rounds * d.ticks * std::max(0.63 + 0.015 * d.smax, 0.083 * d.smax * there * (by_partition ? 1.0 : 1.16));
+}
+
+// The same where both sweeps run side by side in one launch: workgroups of either crowd a unit, 0.04 us a slice and
+// edge of a vertex (279 partitions, three slices of 2 edges 0.71 us a tick; 492, two slices of 4 edges 1.3).
+double side_window_sweep_us(const Packed &p, const WindowDir &d, int32_t batch) {
+    const double slice = 0.04 * std::max(1.0, (double)p.m / p.n);
+    return d.ticks * std::max(0.65 + 0.015 * d.smax, slice * d.smax * std::ceil(2.0 * batch / 256.0));
 }
 
 // The cheapest shape for this batch: true and its time if the lane-window kernel applies.
@@ -301,8 +325,8 @@ bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, const int6
         if (((int64_t)batch + groups - 1) / groups > 65535) continue;        // the grid's second dimension
         if (!lane_config(p.lane_b, p.lane_t, p.n, k, groups, word, with_out,
                          ((int64_t)batch + groups - 1) / groups * sweeps, lds_limit, c)) continue;
-        const double us = std::max(lane_sweep_us(p.lane_b, c, batch, sweeps, by_partition),
-                                   lane_sweep_us(p.lane_t, c, batch, sweeps, by_partition));
+        const double us = std::max(lane_sweep_us(p.lane_b, c, p.n, batch, sweeps, with_out, by_partition),
+                                   lane_sweep_us(p.lane_t, c, p.n, batch, sweeps, with_out, by_partition));
         if (!found || us < *us_out) {
             found = true;
             *us_out = us;
@@ -600,7 +624,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                                         batch, lane_cfg.groups, lane_cfg.word);
         if (lanes && plan == CP_PLAN_AUTO) {
             // against the plan chosen so far: its sweeps (side by side where they would share the launch), the
-            // device ids it gathers per sweep at about 1 us per MB, the launches it needs past two (1.5 us each),
+            // device ids it gathers per sweep at about 1 us per MB, the launches it needs past two (2.5 us each),
             // and the mask pass that its t sweep may save it
             const double mb = (double)p.n * batch * 1e-6;
             const double mask_pass_us = mask_out && by_partition
@@ -622,12 +646,12 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                     side = true;
                     if (window_wg_per_cu(cfg_b) == 1.0 && window_wg_per_cu(cfg_t) == 1.0) other_us *= 0.66;
                     else if (2.0 * std::ceil((double)batch / 256.0) <= std::min(window_wg_per_cu(x), window_wg_per_cu(y)))
-                        other_us = 0.95 * std::max(b_us, t_us);
+                        other_us = std::max(side_window_sweep_us(p, p.win_b, batch), side_window_sweep_us(p, p.win_t, batch));
                     else side = false;
                 }
                 const int launches_past_two = (side ? 1 : lane_sweeps) + (want_b && !(rows && p.win_b.direct_ok)) +
                                               (tlevel_out && !(rows && p.win_t.direct_ok)) - 2;
-                other_us += 1.5 * launches_past_two;
+                other_us += 2.5 * launches_past_two;
                 if (!side && tick_dtype == CP_TICK_I32 && rows && p.win_t.direct_ok && p.win_t.smax >= 4) lane_us += mask_pass_us;
             } else if (use == CP_PLAN_SHARED_WINDOW_2 || use == CP_PLAN_SHARED_WINDOW_4) {
                 const int shared_by = use == CP_PLAN_SHARED_WINDOW_4 ? 4 : 2;
@@ -639,7 +663,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                 other_us += mb * ((rows && p.win_b.direct_ok ? 0.0 : 1.0) + (rows && p.win_t.direct_ok ? 0.0 : 1.0)) *
                             (both ? 1.0 : 0.5);
             }
-            lanes = 1.5 + 0.7 * mb + lane_us < other_us &&
+            lanes = 1.0 + 0.7 * mb + lane_us < other_us &&
                     tables_bytes(k) + lane_work <= workspace_bytes;
         }
     }
