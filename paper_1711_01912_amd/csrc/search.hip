@@ -18,9 +18,9 @@
 // range of levels with a value, and the maxima of all levels come from one pass over the graph.
 // A step is then both sweeps of ONE partition, the walk of its path, and that pass, whatever
 // the number of candidates: 211,000 vertices in 1,000 levels on 16 devices, three moves of about
-// 5,000 candidates each take 4.3 ms, 32.2 ms when every candidate was evaluated by a sweep of its
-// own.  Per step: both sweeps 0.78 ms, the walk 0.47 ms (chains of dependent steps of one partition),
-// the pass over the graph 0.09 ms, the candidates 0.007 ms.
+// 5,000 candidates each take 4.0 ms, 32.2 ms when every candidate was evaluated by a sweep of its
+// own.  Per step: both sweeps 0.78 ms, the walk 0.43 ms (chains of dependent steps of one partition),
+// the pass over the graph 0.03 ms, the candidates 0.007 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
