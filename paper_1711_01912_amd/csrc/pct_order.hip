@@ -15,13 +15,13 @@
 // find each other, every lane reads its digit's counter, the last lane of a group moves it on.
 //
 // Partitions of at most 20,480 vertices with 32-bit keys are sorted by one workgroup each, entirely
-// inside LDS (the bucket kernel below with the whole partition as its bucket).
+// inside LDS (as a bucket is, the whole partition its bucket).
 //
 // Long partitions of 32-bit keys take a shorter way where they can: a pass on the LEADING 9
 // bits cuts a partition into 512 buckets, and a bucket of at most 4,096 or 8,192 items is then
-// sorted on the remaining bits entirely inside LDS by one workgroup (the same ranking, LDS to
-// LDS) and leaves as the finished list: an item crosses HBM three times (keys written, the
-// leading digit's scatter, the bucket sort) whatever the key length.  Whether every bucket fits
+// sorted on the remaining bits entirely inside LDS by one workgroup (LDS to
+// LDS, by bins where its keys are spread) and leaves as the finished list: an item crosses HBM three times (keys
+// written, the leading digit's scatter, the bucket sort) whatever the key length.  Whether every bucket fits
 // is only known on the device, after the scan of the leading digit's counts.  So both
 // continuations are launched -- the leading digit's scatter and the bucket sort, or the
 // ordinary passes from the low digit up -- and a flag the bucket check sets lets the kernels of
@@ -456,48 +456,211 @@ __global__ __launch_bounds__(kSortThreads) void pct_scatter_kernel(const Key *__
 // ---------------------------------------------------------------- buckets of the leading digit
 
 // a bucket is sorted by a workgroup of 256 or 512 threads, 16 items per thread at most
+constexpr int kLeftOverGrid = 2048;
 constexpr int kBucketCapSmall = 256 * kSortRounds, kBucketCapLarge = 512 * kSortRounds;     // 4,096 / 8,192 items
 
 __global__ void pct_flag_clear_kernel(uint32_t *flag) { *flag = 0; }
 
 // After the scan of the leading digit's counts, bucket d of partition q starts where tile 0's
 // run of digit d starts.  flag |= 1 if some bucket holds more than `cap` items.
-__global__ __launch_bounds__(kBuckets) void pct_bucket_check_kernel(const uint32_t *__restrict__ starts, int32_t n,
-                                                                    int32_t tiles, int32_t cap, uint32_t *flag) {
+// crowded[q] = 1 where 512 of the partition's keys, spread over its vertices, fall into common bins of
+// pct_bucket_bins_kernel (keys without their low `shift` bits) as they would with more than kBinAverage items in an average
+// item's bin: then ranking by digits is the faster way, and the bins would be tried in vain.
+constexpr int kBinMost = 96, kBinAverage = 32;
+__global__ __launch_bounds__(kBuckets) void pct_bucket_check_kernel(const uint32_t *__restrict__ starts,
+                                                                    const uint32_t *__restrict__ keys, int32_t n,
+                                                                    int32_t tiles, int32_t cap, int shift, uint32_t *flag,
+                                                                    int32_t *crowded, int32_t crowded_stride) {
+    constexpr int kTable = 4096;
+    __shared__ uint32_t table[kTable];
     const int32_t q = blockIdx.x, d = threadIdx.x;
     const uint32_t lo = starts[((int64_t)q * kBuckets + d) * tiles];
     const uint32_t hi = d + 1 < kBuckets ? starts[((int64_t)q * kBuckets + d + 1) * tiles] : (uint32_t)n;
+    const uint32_t x = keys[(int64_t)q * n + (int64_t)d * n / kBuckets] >> shift;
+    for (int i = d; i < kTable; i += kBuckets) table[i] = 0xffffffffu;
     // (one atomic per partition at most, none once the flag is up: they queue up on the one word)
     const int any = __syncthreads_or(hi - lo > (uint32_t)cap);
     if (any && threadIdx.x == 0 && *(volatile const uint32_t *)flag == 0) atomicOr(flag, 1u);
+    const uint32_t before = atomicExch(&table[x * 0x9e3779b1u >> 20], x);
+    const int pairs = __syncthreads_count(before == x);
+    if (threadIdx.x == 0)
+        crowded[(int64_t)q * crowded_stride] = (int64_t)pairs * n > (int64_t)kBuckets * kBuckets / 2 * kBinAverage ? 1 : 0;
 }
 
-// WHOLE: the "bucket" is a whole partition (at most kBucketThreads * kRounds vertices), its keys
-// in vertex order in keys_in, sorted on all `bits` key bits: short partitions need no pass over
-// HBM at all.
+// Inclusive sum over the lanes of a wavefront: inside rows of 16 by shifts, then a row's last lane
+// handed to the rows behind it.
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);     // row_shr 1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);     // row_shr 2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);     // row_shr 4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);     // row_shr 8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);    // row_bcast 15 into rows 1, 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);    // row_bcast 31 into rows 2, 3
+    return x;
+}
+
+// Items whose key bits spread them, sorted without ranking digit by digit: they are dealt to eight bins per
+// thread, in any order, by one returning LDS add each; then every item compares itself with the others of
+// its bin, the key's bits below the bin's and the vertex number as one word, which gives its place in the list.
+// An item costs some 50 instructions plus five for each other item that the fullest bin of its wavefront holds,
+// instead of the 130 per digit that ranking by ballots takes.  (val_bits: of a vertex number; both parts of the word
+// fit 32 bits.)  False, with nothing written, where a bin holds more than kBinMost items or (WHOLE: the items are a
+// partition's vertices in their order) 64 items, spread over the vertices, share their bins as they
+// would with more than kBinAverage items in an average item's bin: keys that repeat, or that differ in
+// their low bits only.
+constexpr int bin_bits(int threads) { return threads == 128 ? 10 : threads == 256 ? 11 : threads == 512 ? 12 : 13; }
+// 211,000 vertices, 512 partitions, buckets of 412 items: 1,325 -> 382 us (577 with 64-bit words, and no faster
+// with the next bucket's items loaded ahead): vector issue 58 %, the LDS pipe 40 %.  Whole partitions, the call:
+// 19,800 vertices, 4,096 partitions 1,194 -> 814 us; 5,271 vertices 313 -> 219.  Where one key has some 40
+// items (300 values of b, 16 devices, 211,000 vertices) bins and digits take the same time, and trying costs the call
+// up to 9 % (2.18 -> 2.38 ms).
+template <int kThreads, int kRounds, bool WHOLE>
+__device__ __forceinline__ bool sort_by_bins(const uint32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
+                                             int32_t *__restrict__ vals_out, int32_t items, int bits, int val_bits,
+                                             uint32_t *sorted, uint32_t *bins, uint32_t *wave_sum) {
+    constexpr int kWaves = kThreads / 64;
+    static_assert(kThreads * 8 == 1 << bin_bits(kThreads), "eight bins per thread");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int shift = max(0, bits - bin_bits(kThreads));
+    const uint32_t below = (1u << shift) - 1, bin_of = (1u << (bits - shift)) - 1;
+    uint32_t key[kRounds], rank[kRounds], bin[kRounds];
+    int32_t val[kRounds];
+    const bool sampled = WHOLE && items > kThreads;
+    uint32_t sample = 0;
+    if (sampled && wave == 0) sample = keys_in[(uint32_t)lane * (uint32_t)items / 64];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int32_t t = r * kThreads + tid;
+        if (t < items) {
+            key[r] = keys_in[t];
+            val[r] = WHOLE ? t : vals_in[t];
+        }
+    }
+    Counts4 *mine = (Counts4 *)(bins + tid * 8);
+    mine[0] = mine[1] = Counts4{};
+    __syncthreads();
+    if (sampled) {
+        if (wave == 0) {
+            // pairs in one bin: the sum of the places
+            const uint32_t b = sample >> shift & bin_of;
+            const uint32_t pairs = wave_inclusive_sum(atomicAdd(&bins[b], 1u));
+            bins[b] = 0;
+            if (lane == 63) wave_sum[0] = pairs;
+        }
+        __syncthreads();
+        if (wave_sum[0] * (uint32_t)items > 64 * 64 / 2 * kBinAverage) return false;
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+        if (r * kThreads + tid < items) rank[r] = atomicAdd(&bins[key[r] >> shift & bin_of], 1u);
+    __syncthreads();
+    Counts4 c[2] = {mine[0], mine[1]};
+    uint32_t most = 0, sum = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        most = max(most, c[j / 4].x[j % 4]);
+        sum += c[j / 4].x[j % 4];
+    }
+    const uint32_t inc = wave_inclusive_sum(sum);
+    const bool crowded = __ballot(most > (uint32_t)kBinMost) != 0;
+    if (lane == 63) wave_sum[wave] = crowded ? inc | 1u << 31 : inc;
+    __syncthreads();
+    uint32_t run = inc - sum, all = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        run += w < wave ? wave_sum[w] : 0u;
+        all |= wave_sum[w];
+    }
+    if (all >> 31) {
+        __syncthreads();                                  // (the caller goes on with the same LDS)
+        return false;
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t x = c[j / 4].x[j % 4];
+        c[j / 4].x[j % 4] = run | x << 16;                // start and length
+        run += x;
+    }
+    mine[0] = c[0];
+    mine[1] = c[1];
+    __syncthreads();
+    auto word_of = [&](uint32_t k, int32_t v) { return (k & below) << val_bits | (uint32_t)v; };
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+        if (r * kThreads + tid < items) {
+            bin[r] = bins[key[r] >> shift & bin_of];
+            sorted[(bin[r] & 0xffffu) + rank[r]] = word_of(key[r], val[r]);
+        }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+        if (r * kThreads + tid < items) {
+            const uint32_t first = bin[r] & 0xffffu, end = first + (bin[r] >> 16);
+            const uint32_t x = word_of(key[r], val[r]);
+            uint32_t place = first, j = first;
+            if (end - first > 1) {
+                for (; j + 4 <= end; j += 4) {
+                    const uint32_t a = sorted[j], b = sorted[j + 1], c = sorted[j + 2], d = sorted[j + 3];
+                    place += (a < x ? 1u : 0u) + (b < x ? 1u : 0u) + (c < x ? 1u : 0u) + (d < x ? 1u : 0u);
+                }
+                for (; j < end; ++j) place += sorted[j] < x ? 1u : 0u;
+            }
+            rank[r] = place;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+        if (r * kThreads + tid < items) sorted[rank[r]] = (uint32_t)val[r];
+    __syncthreads();
+    for (int32_t t = tid; t < items; t += kThreads) vals_out[t] = (int32_t)sorted[t];
+    return true;
+}
+
+// The buckets of the leading digit, by bins.  left[i] = 1 for those that pct_bucket_sort_kernel has to sort: of more
+// than eight items per thread, of a partition whose keys the sample of pct_bucket_check_kernel found in
+// common bins, or with a crowded bin after all.
+constexpr int kBinRounds = 8;
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_t *__restrict__ keys_in,
+                                                                   const int32_t *__restrict__ vals_in,
+                                                                   int32_t *__restrict__ vals_out, int32_t n,
+                                                                   int32_t tiles, int bits, int val_bits,
+                                                                   const uint32_t *__restrict__ starts, Gate gate,
+                                                                   const int32_t *__restrict__ crowded, int32_t crowded_stride,
+                                                                   uint32_t *left) {
+    __shared__ uint32_t sorted[kThreads * kBinRounds];
+    __shared__ __align__(16) uint32_t bins[kThreads * 8];
+    __shared__ uint32_t wave_sum[kThreads / 64];
+    const int32_t q = (int32_t)(blockIdx.x / kBuckets), d = (int32_t)(blockIdx.x % kBuckets);
+    // (both before the gate: the two round trips overlap)
+    const uint32_t lo = starts[((int64_t)q * kBuckets + d) * tiles];
+    const uint32_t hi = d + 1 == kBuckets ? (uint32_t)n : starts[((int64_t)q * kBuckets + d + 1) * tiles];
+    if (gate.closed()) return;
+    const int32_t items = (int32_t)(hi - lo);
+    const int64_t at = (int64_t)q * n + lo;
+    bool done = items <= 0;
+    if (!done && items <= kThreads * kBinRounds && crowded[(int64_t)q * crowded_stride] == 0)
+        done = sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits,
+                                                               val_bits, sorted, bins, wave_sum);
+    if (threadIdx.x == 0) left[blockIdx.x] = done ? 0u : 1u;
+}
+
 // One bucket, sorted on the low `bits` bits inside LDS: stable passes of 8 bits, each ranking
 // the items as the scatter kernel does (wavefront w owns items [w*1024, (w+1)*1024) of the
 // bucket in (round, lane) order) and moving keys and vertex numbers through one LDS buffer;
 // the vertex numbers of the last pass go straight out.
+// WHOLE: the "bucket" is a whole partition (at most kBucketThreads * kRounds vertices), its keys
+// in vertex order in keys_in, sorted on all `bits` key bits: short partitions need no pass over
+// HBM at all.
+// slot: kBucketThreads * kRounds words; cnt: 256 per wavefront
 template <int kBucketThreads, int kRounds, bool WHOLE>
-__global__ __launch_bounds__(kBucketThreads) void pct_bucket_sort_kernel(const uint32_t *__restrict__ keys_in,
-                                                                         const int32_t *__restrict__ vals_in,
-                                                                         int32_t *__restrict__ vals_out, int32_t n,
-                                                                         int32_t tiles, int bits,
-                                                                         const uint32_t *__restrict__ starts, Gate gate) {
-    constexpr int kWaves = kBucketThreads / 64, kRadix = 256, kBucketCap = kBucketThreads * kRounds;
-    extern __shared__ __align__(16) uint32_t slot[];      // kBucketCap keys, then vertex numbers, in sorted order
-    __shared__ uint32_t cnt[kWaves][kRadix];
+__device__ __forceinline__ void sort_bucket(const uint32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
+                                            int32_t *__restrict__ vals_out, int32_t items, int bits, uint32_t *slot,
+                                            uint32_t (*cnt)[256]) {
+    constexpr int kWaves = kBucketThreads / 64, kRadix = 256;
     __shared__ uint32_t wave_sum[kRadix / 64];
-    if (gate.closed()) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int32_t q = WHOLE ? (int32_t)blockIdx.x : (int32_t)(blockIdx.x / kBuckets);
-    const int32_t d = WHOLE ? 0 : (int32_t)(blockIdx.x % kBuckets);
-    const uint32_t lo = WHOLE ? 0u : starts[((int64_t)q * kBuckets + d) * tiles];
-    const uint32_t hi = WHOLE || d + 1 == kBuckets ? (uint32_t)n : starts[((int64_t)q * kBuckets + d + 1) * tiles];
-    const int32_t items = (int32_t)(hi - lo);
-    if (items <= 0 || items > kBucketCap) return;         // (larger buckets: the other continuation runs)
-    const int64_t at = (int64_t)q * n + lo;
     // rounds this bucket needs (the same for every wavefront: wavefront w owns items
     // [w * nr * 64, (w + 1) * nr * 64) of the bucket)
     const int nr = (items + kBucketThreads - 1) / kBucketThreads;
@@ -508,8 +671,8 @@ __global__ __launch_bounds__(kBucketThreads) void pct_bucket_sort_kernel(const u
     for (int r = 0; r < kRounds; ++r) {
         const int32_t t = wave * (nr * 64) + r * 64 + lane;
         const bool valid = r < nr && t < items;
-        key[r] = valid ? keys_in[at + t] : 0u;
-        val[r] = WHOLE ? t : (valid ? vals_in[at + t] : 0);       // WHOLE: the keys come in vertex order
+        key[r] = valid ? keys_in[t] : 0u;
+        val[r] = WHOLE ? t : (valid ? vals_in[t] : 0);       // WHOLE: the keys come in vertex order
     }
     for (int shift = 0; shift < bits; shift += 8) {
         const bool last = shift + 8 >= bits;
@@ -575,13 +738,57 @@ __global__ __launch_bounds__(kBucketThreads) void pct_bucket_sort_kernel(const u
         }
         __syncthreads();
         if (last) {
-            for (int32_t i = tid; i < items; i += kBucketThreads) vals_out[at + i] = (int32_t)slot[i];
+            for (int32_t i = tid; i < items; i += kBucketThreads) vals_out[i] = (int32_t)slot[i];
         } else {
 #pragma unroll
             for (int r = 0; r < kRounds; ++r) {
                 const int32_t t = wave * (nr * 64) + r * 64 + lane;
                 if (r < nr && t < items) val[r] = (int32_t)slot[t];
             }
+            __syncthreads();
+        }
+    }
+}
+
+// A whole partition per workgroup: by bins (BINS: the words fit 32 bits), else by digits.
+template <int kThreads, int kRounds, bool BINS>
+__global__ __launch_bounds__(kThreads) void pct_whole_sort_kernel(const uint32_t *__restrict__ keys_in,
+                                                                  int32_t *__restrict__ vals_out, int32_t n, int bits,
+                                                                  int val_bits) {
+    extern __shared__ __align__(16) uint32_t slot[];
+    __shared__ __align__(16) uint32_t counters[kThreads * (BINS ? 8 : 4)];
+    __shared__ uint32_t wave_sum[kThreads / 64];
+    const int64_t at = (int64_t)blockIdx.x * n;
+    if constexpr (BINS)
+        if (sort_by_bins<kThreads, kRounds, true>(keys_in + at, nullptr, vals_out + at, n, bits, val_bits, slot,
+                                                            counters, wave_sum))
+            return;
+    sort_bucket<kThreads, kRounds, true>(keys_in + at, nullptr, vals_out + at, n, bits, slot, (uint32_t (*)[256])counters);
+}
+
+// The buckets that pct_bucket_bins_kernel left, 64 after each other to a workgroup of a fixed grid.
+template <int kThreads>
+__global__ __launch_bounds__(kThreads, 6) void pct_bucket_sort_kernel(const uint32_t *__restrict__ keys_in,
+                                                                   const int32_t *__restrict__ vals_in,
+                                                                   int32_t *__restrict__ vals_out, int32_t n,
+                                                                   int32_t buckets, int32_t tiles, int bits,
+                                                                   const uint32_t *__restrict__ starts, Gate gate,
+                                                                   const uint32_t *__restrict__ left) {
+    __shared__ uint32_t slot[kThreads * kSortRounds], counters[kThreads / 64][256];
+    if (gate.closed()) return;
+    static_assert(kBuckets % 64 == 0, "no 64 buckets of two partitions");
+    for (int32_t i0 = blockIdx.x * 64; i0 < buckets; i0 += gridDim.x * 64) {
+        unsigned long long some = __ballot(left[i0 + (threadIdx.x & 63)] != 0);      // the same in every wavefront
+        const uint32_t q = (uint32_t)i0 / kBuckets;
+        for (; some != 0; some &= some - 1) {
+            const uint32_t d = (uint32_t)i0 % kBuckets + (uint32_t)__ffsll((long long)some) - 1;
+            const uint32_t lo = starts[((int64_t)q * kBuckets + d) * tiles];
+            const uint32_t hi = d + 1 == kBuckets ? (uint32_t)n : starts[((int64_t)q * kBuckets + d + 1) * tiles];
+            const int64_t at = (int64_t)q * n + lo;
+            const int32_t items = (int32_t)(hi - lo);
+            if (items <= kThreads * kSortRounds)          // (more: the flag is up)
+                sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot,
+                                                          counters);
             __syncthreads();
         }
     }
@@ -732,25 +939,42 @@ int run_bucket_sort(const PctOrderLaunch &s, const KeyArgs &a, hipStream_t st) {
     if (!s.b_by_partition) lead.count((const uint32_t *)s.keys_a);
     lead.scan();
     // the smaller workgroup (more of them per compute unit) where buckets of twice the average size fit it
-    const bool small = 2 * ((int64_t)s.n / kBuckets + 1) <= kBucketCapSmall;
-    hipLaunchKernelGGL(pct_bucket_check_kernel, dim3((unsigned)s.P), dim3(kBuckets), 0, st, s.counts, s.n, tiles,
-                       small ? kBucketCapSmall : kBucketCapLarge, flag);
+    const int32_t average = s.n / kBuckets + 1;
+    const bool small = 2 * (int64_t)average <= kBucketCapSmall;
+    const int threads = average <= 512 ? 128 : average <= 1024 ? 256 : 512;     // eight items a thread: twice the average
+    const int shift = std::max(0, rem - bin_bits(threads));
+    // (noted where the partition's list bounds will stand)
+    int32_t *crowded = s.seg_out;
+    hipLaunchKernelGGL(pct_bucket_check_kernel, dim3((unsigned)s.P), dim3(kBuckets), 0, st, s.counts,
+                       (const uint32_t *)s.keys_a, s.n, tiles, small ? kBucketCapSmall : kBucketCapLarge, shift, flag, crowded,
+                       s.k + 1);
     if (hipGetLastError() != hipSuccess) return CP_ERR_HIP;
-    const DigitPass<uint32_t, kLeadThreads, kBucketBits> lead_if_fit{s, st, rem, Gate{flag, 0u}};
+    const Gate fit{flag, 0u};
+    const DigitPass<uint32_t, kLeadThreads, kBucketBits> lead_if_fit{s, st, rem, fit};
     const int rc = lead_if_fit.scatter(/*first=*/true, /*last=*/false, (const uint32_t *)s.keys_a, (uint32_t *)s.keys_b,
                                        nullptr, s.vals_tmp);
     if (rc) return rc;
-    const dim3 bgrid((unsigned)((int64_t)s.P * kBuckets));
-    if (small)
-        hipLaunchKernelGGL((pct_bucket_sort_kernel<256, kSortRounds, false>), bgrid, dim3(256),
-                           (size_t)kBucketCapSmall * 4, st, (const uint32_t *)s.keys_b,
-                           (const int32_t *)s.vals_tmp, s.order_out, s.n, tiles, rem, (const uint32_t *)s.counts,
-                           Gate{flag, 0u});
-    else
-        hipLaunchKernelGGL((pct_bucket_sort_kernel<512, kSortRounds, false>), bgrid, dim3(512),
-                           (size_t)kBucketCapLarge * 4, st, (const uint32_t *)s.keys_b,
-                           (const int32_t *)s.vals_tmp, s.order_out, s.n, tiles, rem, (const uint32_t *)s.counts,
-                           Gate{flag, 0u});
+    // (what the bins leave is noted in keys_a, which nothing reads any more on this way)
+    uint32_t *left = (uint32_t *)s.keys_a;
+    const uint32_t *keys = (const uint32_t *)s.keys_b, *starts = s.counts;
+    const int32_t *vals = s.vals_tmp;
+    const int32_t all = s.P * kBuckets;
+    const int val_bits = 32 - __builtin_clz((unsigned)s.n - 1);
+    // (keys of 32 bits: shift is 13, 12 or 11 at most for up to 2^18, 2^19 or 2^20 vertices)
+    if (shift + val_bits > 32) return CP_ERR_ARG;
+#define CP_BINS(T)                                                                                                    \
+    hipLaunchKernelGGL(pct_bucket_bins_kernel<T>, dim3((unsigned)all), dim3(T), 0, st, keys, vals, s.order_out, s.n, tiles, \
+                       rem, val_bits, starts, fit, (const int32_t *)crowded, s.k + 1, left)
+    if (threads == 128) CP_BINS(128);
+    else if (threads == 256) CP_BINS(256);
+    else CP_BINS(512);
+#undef CP_BINS
+#define CP_LEFT(T)                                                                                                    \
+    hipLaunchKernelGGL(pct_bucket_sort_kernel<T>, dim3(kLeftOverGrid), dim3(T), 0, st, keys, vals, s.order_out, s.n, all, \
+                       tiles, rem, starts, fit, (const uint32_t *)left)
+    if (small) CP_LEFT(256);
+    else CP_LEFT(512);
+#undef CP_LEFT
     if (hipGetLastError() != hipSuccess) return CP_ERR_HIP;
     return run_sort<uint32_t, kSortThreadsLong, true>(s, st, Gate{flag, 1u});
 }
@@ -758,18 +982,24 @@ int run_bucket_sort(const PctOrderLaunch &s, const KeyArgs &a, hipStream_t st) {
 // Partitions of at most 20,480 vertices with 32-bit keys: one workgroup sorts a whole partition
 // inside LDS.
 constexpr int kWholeRoundsMax = 20, kWholeMax = kSortThreadsLong * kWholeRoundsMax;
-template <int THREADS, int ROUNDS>
-int launch_whole(const PctOrderLaunch &s, hipStream_t st) {
-    auto kern = pct_bucket_sort_kernel<THREADS, ROUNDS, true>;
+template <int THREADS, int ROUNDS, bool BINS>
+int launch_whole_as(const PctOrderLaunch &s, hipStream_t st, int val_bits) {
+    auto kern = pct_whole_sort_kernel<THREADS, ROUNDS, BINS>;
     const size_t lds = (size_t)THREADS * ROUNDS * 4;
-    // more than 64 KB of dynamic LDS has to be asked for
-    if (lds > 64 * 1024 &&
+    // more than 64 KB of LDS has to be asked for
+    if (lds + THREADS * 32 > 64 * 1024 &&
         hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return CP_ERR_HIP;
-    hipLaunchKernelGGL(kern, dim3((unsigned)s.P), dim3(THREADS), lds, st, (const uint32_t *)s.keys_a,
-                       (const int32_t *)nullptr, s.order_out, s.n, 0, s.key_bits, (const uint32_t *)nullptr,
-                       Gate{nullptr, 0u});
+    hipLaunchKernelGGL(kern, dim3((unsigned)s.P), dim3(THREADS), lds, st, (const uint32_t *)s.keys_a, s.order_out, s.n,
+                       s.key_bits, val_bits);
     return hip_status(hipGetLastError());
+}
+template <int THREADS, int ROUNDS>
+int launch_whole(const PctOrderLaunch &s, hipStream_t st) {
+    const int val_bits = 32 - __builtin_clz((unsigned)s.n);
+    return std::max(0, s.key_bits - bin_bits(THREADS)) + val_bits <= 32
+               ? launch_whole_as<THREADS, ROUNDS, true>(s, st, val_bits)
+               : launch_whole_as<THREADS, ROUNDS, false>(s, st, val_bits);
 }
 int run_whole_sort(const PctOrderLaunch &s, hipStream_t st) {
     if (s.n <= 256 * kSortRounds) return launch_whole<256, kSortRounds>(s, st);
