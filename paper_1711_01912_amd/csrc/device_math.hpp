@@ -46,6 +46,12 @@ __device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
 }
 
+// (the same where every lane is named: no register holds a value for the others)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_row(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+}
+
 template <int CTRL>
 __device__ __forceinline__ long long dpp_i64(long long x) {
     const uint32_t lo = dpp_u32<CTRL>((uint32_t)x);

@@ -381,8 +381,8 @@ struct SeedArgs {
     const int32_t *path;      // device-free critical path
     const int32_t *len;
     uint8_t *assign;          // [n]
-    int32_t n, k, fastest, magic;
-    Magic mg[kSeedMaxK];
+    int32_t n, k, fastest;
+    Magic mg[kSeedMaxK];         // where the graph and the speeds have them
     int64_t speed[kSeedMaxK];
 };
 
@@ -428,13 +428,13 @@ __device__ __forceinline__ uint32_t min_over_lanes_u32(uint32_t x) {
 // One batch of up to 64 vertices on relative 32-bit loads (see seed_greedy_kernel): lane j of
 // `dev` holds vertex j's device (0xff: not placed yet), of `cv` its c.  No branch but the one
 // that skips a placed vertex.
-template <bool MAGIC, bool WIDE>
+template <bool WIDE>
 __device__ __forceinline__ void seed_batch_u32(uint32_t &rel, int32_t &dev, uint32_t cv, int cnt, bool mine,
-                                               const Magic &mg, uint64_t sp, int lane) {
+                                               uint64_t sp, int lane) {
     for (int j = 0; j < cnt; ++j) {
         if (__builtin_amdgcn_readlane(dev, j) != 0xff) continue;            // on the critical path
         const uint32_t cj = (uint32_t)__builtin_amdgcn_readlane((int)cv, j);
-        const uint32_t w = MAGIC ? magic_div(cj, mg) : (uint32_t)plain_div((uint64_t)cj, sp);
+        const uint32_t w = (uint32_t)plain_div((uint64_t)cj, sp);
         const uint32_t val = mine ? rel + w : 0xffffffffu;
         const uint32_t best = min_over_lanes_u32<WIDE>(val);
         const int chosen = __ffsll((long long)__ballot(val == best)) - 1;  // lowest device on ties
@@ -443,44 +443,11 @@ __device__ __forceinline__ void seed_batch_u32(uint32_t &rel, int32_t &dev, uint
     }
 }
 
-// One batch on keys: (load - low) << BITS | device, so that the minimum names its device and the lowest one
-// wins a tie without a ballot.  With 16 devices or fewer every row of 16 lanes holds all of them and
-// does the same work, and the chain of a vertex is one addition, four register permutations and one
-// selection; with more, the rows' minima meet in scalar registers.  A vertex's execution times do not
-// depend on the chain and are computed beside it.  Bound by that chain on one wavefront: 211,000 vertices on
-// 16 devices 0.055 us each (0.114 with a ballot and a branch per vertex), the whole call 25.2 -> 13.1 ms.
-template <int BITS>
-__device__ __forceinline__ void seed_batch_keys(uint32_t &key, int32_t &dev, uint32_t cv, Magic mg, int lane) {
-    // the vertices still to be placed, packed into the first lanes: no test inside the chain
-    const unsigned long long open = __ballot(dev == 0xff);
-    const int cnt = __popcll(open), rank = __popcll(open & ((1ull << lane) - 1));
-    const bool mine = dev == 0xff;
-    const uint32_t packed = (uint32_t)__builtin_amdgcn_ds_permute(4 * (mine ? rank : 63 - (lane - rank)), (int)cv);
-    uint32_t chosen = 0;
-    auto one = [&](int j) {
-        const uint32_t cj = (uint32_t)__builtin_amdgcn_readlane((int)packed, j);
-        uint32_t w = magic_div(cj, mg);                // 0 in lanes without a device
-        asm("" : "+v"(w));                             // (else the shift is folded into the product in three steps)
-        const uint32_t val = (w << BITS) + key;
-        uint32_t best = val;
-        best = min(best, dpp_u32<0xB1>(best));
-        best = min(best, dpp_u32<0x4E>(best));
-        best = min(best, dpp_u32<0x141>(best));
-        best = min(best, dpp_u32<0x140>(best));
-        if (BITS > 4)
-            best = min(min((uint32_t)__builtin_amdgcn_readlane((int)best, 0), (uint32_t)__builtin_amdgcn_readlane((int)best, 16)),
-                       min((uint32_t)__builtin_amdgcn_readlane((int)best, 32), (uint32_t)__builtin_amdgcn_readlane((int)best, 48)));
-        key = val == best ? val : key;
-        chosen = lane == j ? best : chosen;
-    };
-    int j = 0;
-    for (; j + 8 <= cnt; j += 8) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) one(j + i);
-    }
-    for (; j < cnt; ++j) one(j);
-    const int32_t got = __shfl((int)chosen, rank);
-    if (mine) dev = got & ((1 << BITS) - 1);
+// Barrier that orders LDS only: the global loads of the wavefronts stay in flight across it.
+__device__ __forceinline__ void lds_only_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 __device__ __forceinline__ long long lane0_i64(long long x) {
@@ -495,27 +462,21 @@ __device__ __forceinline__ long long lane0_i64(long long x) {
 // to the smallest one, which stay below 2^32 - 1 through the batch when (largest - smallest
 // load) + 64 * (largest c of the batch) does -- an execution time is at most c.  The choices
 // are the same, a minimum and its ties do not move when every load loses the same amount.
+// (For speeds and costs without multiply-shift constants: seed_keys_kernel places the others.)
 template <typename WT>
 __global__ __launch_bounds__(64) void seed_greedy_kernel(SeedArgs a) {
     const int lane = threadIdx.x;
     const WT *c = (const WT *)a.c;
     const bool mine = lane < a.k;
-    const Magic mg = a.mg[mine ? lane : 0];
     const uint64_t sp = (uint64_t)a.speed[mine ? lane : 0];
-    auto cost = [&](uint64_t cv) -> long long {
-        return a.magic ? (long long)magic_div((uint32_t)cv, mg) : (long long)plain_div(cv, sp);
-    };
+    auto cost = [&](uint64_t cv) -> long long { return (long long)plain_div(cv, sp); };
     // the critical path is placed first: its execution times on the fastest device
     long long load = 0;
     {
-        const Magic mf = a.mg[a.fastest];
         const uint64_t sf = (uint64_t)a.speed[a.fastest];
         const int32_t len = *a.len;
         long long part = 0;
-        for (int32_t i = lane; i < len; i += 64) {
-            const uint64_t cv = (uint64_t)c[a.path[i]];
-            part += a.magic ? (long long)magic_div((uint32_t)cv, mf) : (long long)plain_div(cv, sf);
-        }
+        for (int32_t i = lane; i < len; i += 64) part += (long long)plain_div((uint64_t)c[a.path[i]], sf);
         for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
         if (lane == a.fastest) load = part;
     }
@@ -532,28 +493,10 @@ __global__ __launch_bounds__(64) void seed_greedy_kernel(SeedArgs a) {
         unsigned long long cmax = cv;
         for (int off = 32; off > 0; off >>= 1) cmax = max(cmax, (unsigned long long)__shfl_xor((long long)cmax, off));
         const bool narrow = cmax < (1ull << 32) && (unsigned long long)(high - low) + 64 * cmax < 0xffffffffull;
-        // ... and the same with the device number behind the load (every row of 16 lanes as lanes 0 .. 15)
-        const int bits = span <= 16 ? 4 : 6;
-        const bool keyed = a.magic && narrow &&
-                           (unsigned long long)(high - low) + 64 * cmax < (0xffffffffull >> bits);
-        if (keyed) {
-            const int d = bits == 4 ? lane & 15 : lane;
-            const bool here = d < a.k;
-            const Magic md = here ? a.mg[d] : Magic{0, 0};
-            const uint32_t at = (uint32_t)__shfl((int)(uint32_t)(load - low), d);
-            uint32_t key = here ? at << bits | (uint32_t)d : 0xffffffffu;
-            if (bits == 4) seed_batch_keys<4>(key, dev, (uint32_t)cv, md, lane);
-            else seed_batch_keys<6>(key, dev, (uint32_t)cv, md, lane);
-            if (mine) load = low + (long long)(key >> bits);
-        } else if (narrow) {
+        if (narrow) {
             uint32_t rel = mine ? (uint32_t)(load - low) : 0xffffffffu;
-            if (a.magic) {
-                if (span <= 16) seed_batch_u32<true, false>(rel, dev, (uint32_t)cv, cnt, mine, mg, sp, lane);
-                else seed_batch_u32<true, true>(rel, dev, (uint32_t)cv, cnt, mine, mg, sp, lane);
-            } else {
-                if (span <= 16) seed_batch_u32<false, false>(rel, dev, (uint32_t)cv, cnt, mine, mg, sp, lane);
-                else seed_batch_u32<false, true>(rel, dev, (uint32_t)cv, cnt, mine, mg, sp, lane);
-            }
+            if (span <= 16) seed_batch_u32<false>(rel, dev, (uint32_t)cv, cnt, mine, sp, lane);
+            else seed_batch_u32<true>(rel, dev, (uint32_t)cv, cnt, mine, sp, lane);
             if (mine) load = low + (long long)rel;
         } else {
             for (int j = 0; j < cnt; ++j) {
@@ -569,6 +512,218 @@ __global__ __launch_bounds__(64) void seed_greedy_kernel(SeedArgs a) {
             }
         }
         if (v < a.n) a.assign[v] = (uint8_t)dev;
+    }
+}
+
+// The same chain where execution times come from multiply-shift constants, with nothing but the chain on the wavefront
+// that walks it.  Its numbers are keys, (load - low) << BITS | device, so that a minimum names its device and the
+// lowest one wins a tie; every row of 16 lanes holds all devices, PER of them a lane (device r * 16 + lane).  A vertex
+// is an addition, four register permutations, a comparison and a selection.  Three wavefronts beside it read c and the
+// vertices still to be placed 64 at a time, two batches ahead, put the execution times of every device into
+// LDS and write the devices chosen a batch ago.  Loads leave the keys (64 bits, and return when they can) where
+// eight vertices might take them past 32 - BITS bits.
+// Bound by the chain and by what one wavefront issues, six to eight cycles an instruction and two wait states before
+// each permutation: 211,000 vertices on 16 devices 0.056 -> 0.038 us each, a tenth of it between the batches.  (A branch
+// of any kind between two vertices costs as much as half a vertex.  Two vertices at a time, the second one's choice
+// prepared for each outcome of the first, or both outcomes' keys added up ahead of the comparison: 4 % less and 4 % more.)
+template <int PER, int BITS>
+__global__ __launch_bounds__(256) void seed_keys_kernel(SeedArgs a) {
+    static_assert(PER << 4 == 1 << BITS, "BITS bits name a device");
+    constexpr int kBatch = 64, kCols = 16 * PER;
+    constexpr uint32_t kLimit = 0xffffffffu >> BITS, kDevice = (1u << BITS) - 1;
+    __shared__ __align__(16) uint32_t times[2 * kBatch + 8][kCols];              // (eight rows are read past the end)
+    __shared__ unsigned long long open_of[4];                                    // vertices to be placed, of four batches
+    __shared__ uint32_t cmax_of[4], chosen_of[2][16];                            // chosen: four devices a word
+    __shared__ Magic mg[kCols];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t *c = (const uint32_t *)a.c;
+    const int32_t batches = (a.n + kBatch - 1) / kBatch;
+    for (int i = tid; i < (2 * kBatch + 8) * kCols; i += 256) (&times[0][0])[i] = 0;
+    if (tid < kCols) mg[tid] = a.mg[tid];
+    __syncthreads();
+    if (wave == 0) {
+        __builtin_amdgcn_s_setprio(3);
+        const int d = lane & 15;
+        long long load[PER], base = 0;
+        uint32_t key[PER], bound = 0;        // bound: no key's load is larger
+        bool wide = true;
+        {
+            // the critical path is placed first: its execution times on the fastest device
+            const Magic mf = a.mg[a.fastest];
+            const int32_t len = *a.len;
+            long long part = 0;
+            for (int32_t i = lane; i < len; i += 64) part += (long long)magic_div(c[a.path[i]], mf);
+            for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+#pragma unroll
+            for (int r = 0; r < PER; ++r) {
+                load[r] = r * 16 + d == a.fastest ? part : 0;
+                key[r] = 0xffffffffu;
+            }
+        }
+        auto here = [&](int r) { return r * 16 + d < a.k; };
+        auto id = [&](int r) { return (uint32_t)(r * 16 + d); };
+        auto to_loads = [&]() {
+#pragma unroll
+            for (int r = 0; r < PER; ++r) load[r] = base + (long long)(key[r] >> BITS);
+            wide = true;
+        };
+        auto to_keys = [&](uint32_t more) {  // where `more` on top of the largest load still fits
+            long long low = LLONG_MAX, high = LLONG_MAX;
+#pragma unroll
+            for (int r = 0; r < PER; ++r) {
+                if (here(r) && load[r] < low) low = load[r];
+                if (here(r) && -load[r] < high) high = -load[r];
+            }
+            low = lane0_i64(min_over_lanes(low, 16));
+            high = -lane0_i64(min_over_lanes(high, 16));
+            if ((unsigned long long)(high - low) + more >= kLimit) return;
+#pragma unroll
+            for (int r = 0; r < PER; ++r)
+                key[r] = here(r) ? (uint32_t)(load[r] - low) << BITS | id(r) : 0xffffffffu;
+            base = low;
+            bound = (uint32_t)(high - low);
+            wide = false;
+        };
+        lds_only_barrier();                  // the first batch is there
+        for (int32_t b = 0; b <= batches; ++b) {
+            const int cnt = b < batches ? __popcll(open_of[b & 3]) : 0;
+            // (eight times the largest c, or a number no key has room for)
+            const uint32_t cmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)cmax_of[b & 3]);
+            const uint32_t more = cmax < kLimit / 8 ? 8 * cmax : kLimit;
+            const uint32_t *row = &times[(b & 1) * kBatch][d * PER];
+            uint32_t chosen = 0, packed[2];
+            // the winner's key
+            auto place = [&](const uint32_t (&w)[PER]) {
+                uint32_t val[PER], best;
+#pragma unroll
+                for (int r = 0; r < PER; ++r) {
+                    val[r] = (w[r] << BITS) + key[r];
+                    best = r ? min(best, val[r]) : val[r];
+                }
+                best = min(best, dpp_row<0xB1>(best));
+                best = min(best, dpp_row<0x4E>(best));
+                best = min(best, dpp_row<0x141>(best));
+                best = min(best, dpp_row<0x140>(best));
+#pragma unroll
+                for (int r = 0; r < PER; ++r) key[r] = val[r] == best ? val[r] : key[r];
+                return best;
+            };
+            auto note = [&](int j) { chosen = lane == j / 4 ? packed[0] : lane == j / 4 + 1 ? packed[1] : chosen; };
+            int j = 0;
+            if (!wide && (unsigned long long)bound + 8ull * more < kLimit) {
+                // the whole batch fits the keys: eight vertices after the other without a test between them
+                // (all reads of eight times at once: a wait for each would be an instruction for each)
+                uint32_t w[2][8][PER];
+                auto ask = [&](int at, uint32_t (&to)[8][PER]) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+#pragma unroll
+                        for (int r = 0; r < PER; ++r) to[i][r] = row[(at + i) * kCols + r];
+                };
+                auto eight = [&](const uint32_t (&w)[8][PER]) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) packed[i / 4] = __builtin_amdgcn_alignbit(place(w[i]), packed[i / 4], 8);
+                    note(j);
+                    j += 8;
+                };
+                ask(0, w[0]);
+                while (j + 16 <= cnt) {
+                    ask(j + 8, w[1]);
+                    eight(w[0]);
+                    ask(j + 8, w[0]);
+                    eight(w[1]);
+                }
+                if (j + 8 <= cnt) eight(w[0]);
+                bound += 8 * more;
+            }
+            for (; j < cnt; j += 8) {
+                uint32_t w[8][PER];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int r = 0; r < PER; ++r) w[i][r] = row[(j + i) * kCols + r];
+                const int some = min(8, cnt - j);
+                if (!wide && bound >= kLimit - more) to_loads();
+                if (wide) to_keys(more);
+                packed[0] = packed[1] = 0;
+                if (!wide) bound += more;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    uint32_t got = 0;
+                    if (i < some && !wide) {
+                        got = place(w[i]);
+                    } else if (i < some) {
+                        long long best = LLONG_MAX;
+#pragma unroll
+                        for (int r = 0; r < PER; ++r)
+                            if (here(r) && load[r] + (long long)w[i][r] < best) best = load[r] + (long long)w[i][r];
+                        best = lane0_i64(min_over_lanes(best, 16));
+                        bool found = false;
+#pragma unroll
+                        for (int r = 0; r < PER; ++r) {
+                            const uint32_t hit =
+                                (uint32_t)__ballot(here(r) && load[r] + (long long)w[i][r] == best) & 0xffffu;
+                            if (!found && hit) {
+                                got = (uint32_t)(r * 16 + __ffs((int)hit) - 1);
+                                found = true;
+                                if (id(r) == got) load[r] = best;
+                            }
+                        }
+                    }
+                    packed[i / 4] = __builtin_amdgcn_alignbit(got, packed[i / 4], 8);
+                }
+                note(j);
+            }
+            if (lane < 16) chosen_of[b & 1][lane] = chosen;
+            lds_only_barrier();
+        }
+    } else {
+        const int h = wave - 1;
+        uint32_t cv[4], dev[4];              // of the batches on their way, two of them asked for but not there yet
+        auto fetch = [&](int32_t b, uint32_t &cs, uint32_t &ds) {
+            const int32_t v = min(b * kBatch + lane, a.n - 1);
+            cs = c[v];
+            ds = a.assign[v];
+        };
+        auto stage = [&](int32_t b, uint32_t cs, uint32_t ds) {
+            const bool mine = ds == 0xff && b * kBatch + lane < a.n;
+            const unsigned long long open = __ballot(mine);
+            uint32_t *row = &times[(b & 1) * kBatch + __popcll(open & ((1ull << lane) - 1))][0];
+#pragma unroll
+            for (int i = 0; i < (kCols + 2) / 3; ++i) {
+                const int d = min(h + 3 * i, a.k - 1);   // (past the last device: its times once more)
+                const uint32_t w = magic_div(cs, mg[d]);
+                if (mine) row[(d & 15) * PER + (d >> 4)] = w;
+            }
+            if (h == 0) {
+                const uint32_t most = ~min_over_wave(~cs);
+                if (lane == 0) {
+                    open_of[b & 3] = open;
+                    cmax_of[b & 3] = most;
+                }
+            }
+        };
+        fetch(0, cv[0], dev[0]);
+        stage(0, cv[0], dev[0]);
+        fetch(1, cv[1], dev[1]);
+        fetch(2, cv[2], dev[2]);
+        lds_only_barrier();
+        for (int32_t b0 = 0; b0 <= batches; b0 += 4) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int32_t b = b0 + i;
+                if (b > batches) break;
+                fetch(b + 3, cv[(i + 3) % 4], dev[(i + 3) % 4]);
+                if (b + 1 < batches) stage(b + 1, cv[(i + 1) % 4], dev[(i + 1) % 4]);
+                if (h == 0 && b >= 1) {
+                    const unsigned long long open = open_of[(b - 1) & 3];
+                    const uint32_t at = (uint32_t)__popcll(open & ((1ull << lane) - 1));
+                    const uint32_t got = chosen_of[(b - 1) & 1][at / 4 & 15] >> (8 * (at % 4)) & kDevice;
+                    if (open >> lane & 1) a.assign[(b - 1) * kBatch + lane] = (uint8_t)got;
+                }
+                lds_only_barrier();
+            }
+        }
     }
 }
 
@@ -836,14 +991,17 @@ int cp_seed_partition(const cp_graph *g, int32_t k, const int64_t *speeds, void 
     a.fastest = 0;
     for (int d = 1; d < k; ++d)
         if (speeds[d] > speeds[a.fastest]) a.fastest = d;
-    a.magic = tabs.magic_ok ? 1 : 0;
     for (int d = 0; d < k; ++d) {
         a.mg[d] = tabs.magic[2 * (size_t)k * k + d];
         a.speed[d] = speeds[d];
     }
     hipLaunchKernelGGL(seed_mark_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
     hipLaunchKernelGGL(seed_path_kernel, dim3(64), dim3(256), 0, st, a);
-    if (p.narrow) hipLaunchKernelGGL(seed_greedy_kernel<uint32_t>, dim3(1), dim3(64), 0, st, a);
+    // (16 devices a register of the chain's wavefront)
+    if (tabs.magic_ok && k <= 16) hipLaunchKernelGGL((seed_keys_kernel<1, 4>), dim3(1), dim3(256), 0, st, a);
+    else if (tabs.magic_ok && k <= 32) hipLaunchKernelGGL((seed_keys_kernel<2, 5>), dim3(1), dim3(256), 0, st, a);
+    else if (tabs.magic_ok) hipLaunchKernelGGL((seed_keys_kernel<4, 6>), dim3(1), dim3(256), 0, st, a);
+    else if (p.narrow) hipLaunchKernelGGL(seed_greedy_kernel<uint32_t>, dim3(1), dim3(64), 0, st, a);
     else hipLaunchKernelGGL(seed_greedy_kernel<int64_t>, dim3(1), dim3(64), 0, st, a);
     return hipGetLastError() == hipSuccess ? CP_OK : CP_ERR_HIP;
 }
