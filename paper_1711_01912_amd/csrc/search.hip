@@ -729,7 +729,7 @@ __global__ __launch_bounds__(256) void seed_keys_kernel(SeedArgs a) {
 
 struct SearchLayout {
     size_t eval_ws = 0, b = 0, tl = 0, level = 0, over = 0, slot_at = 0, want = 0, mine = 0, slots = 0, path = 0,
-           small = 0, total = 0;
+           small = 0, total = 0, jumps = 0;
     size_t eval_bytes = 0;
     int rows_over = 1;       // rows of the level-range tables: ranges of 1, 2, 4, ... levels
     int tick = 4;
@@ -761,7 +761,8 @@ int search_layout(const cp_graph *g, int32_t k, SearchLayout &o) {
     o.slots = at;   at += align_up(L * sizeof(SlotBest));
     o.path = at;    at += align_up(L * sizeof(int32_t));
     o.small = at;   at += kAlign;        // StepResult, broken constraints
-    o.total = at;
+    o.total = at;                        // (the path's jumps are optional: an array of this size still serves)
+    o.jumps = path_by_jumps(info.n, 1, info.L) ? align_up(path_jump_words(info.n) * sizeof(int32_t)) : 0;
     return CP_OK;
 }
 
@@ -808,7 +809,7 @@ int cp_search_workspace_bytes(const cp_graph *g, int32_t k, int32_t chunk, size_
     SearchLayout lay;
     int rc = search_layout(g, k, lay);
     if (rc) return rc;
-    *out_bytes = lay.total;
+    *out_bytes = lay.total + lay.jumps;
     return CP_OK;
 }
 
@@ -869,6 +870,7 @@ int cp_search(const cp_graph *g, int32_t k, const int64_t *speeds, const int64_t
     a.n = info.n; a.L = info.L; a.k = k;
     a.rows_over = lay.rows_over;
     a.constrained = num_pairs > 0 || num_pins > 0;
+    int32_t *jumps = lay.jumps && workspace_bytes >= lay.total + lay.jumps ? (int32_t *)(ws + lay.total) : nullptr;
     const bool stepping = max_moves > 0 && k > 1;
     int32_t done = 0;
     int64_t seen = 0;
@@ -881,9 +883,9 @@ int cp_search(const cp_graph *g, int32_t k, const int64_t *speeds, const int64_t
                      lay.eval_bytes, stream, &a.res->cp, ws + lay.b, ws + lay.tl, nullptr, lay.tick, layout,
                      CP_PLAN_AUTO, &a.res->status[0], nullptr);
         if (rc) return rc;
-        rc = cp_critical_path(g, 1, k, assignment, CP_ASSIGN_PARTITION_MAJOR, speeds, bandwidth, ws + lay.b,
-                              &a.res->cp, lay.tick, layout, ws + lay.eval_ws, lay.eval_bytes, stream, info.L,
-                              (int32_t *)(ws + lay.path), &a.res->len, &a.res->status[1]);
+        rc = critical_path(g, 1, k, assignment, CP_ASSIGN_PARTITION_MAJOR, speeds, bandwidth, ws + lay.b,
+                           &a.res->cp, lay.tick, layout, ws + lay.eval_ws, lay.eval_bytes, stream, info.L,
+                           (int32_t *)(ws + lay.path), &a.res->len, &a.res->status[1], jumps);
         if (rc) return rc;
         if (stepping) {
             const int64_t cells = (int64_t)a.rows_over * a.L;
@@ -922,7 +924,7 @@ int cp_search(const cp_graph *g, int32_t k, const int64_t *speeds, const int64_t
     return CP_OK;
 }
 
-int cp_seed_workspace_bytes(const cp_graph *g, size_t *out_bytes) {
+static int seed_bytes(const cp_graph *g, size_t *out_bytes, size_t *jump_bytes) {
     if (!g || !out_bytes) return CP_ERR_NULL;
     cp_graph_info info;
     int rc = cp_graph_get_info(g, &info);
@@ -933,15 +935,23 @@ int cp_seed_workspace_bytes(const cp_graph *g, size_t *out_bytes) {
     if (rc) return rc;
     *out_bytes = align_up(eval) + align_up((size_t)info.n) + align_up((size_t)info.n * (size_t)info.min_tick_bytes) +
                  align_up((size_t)info.L * sizeof(int32_t)) + kAlign;
+    *jump_bytes = path_by_jumps(info.n, 1, info.L) ? align_up(path_jump_words(info.n) * sizeof(int32_t)) : 0;
     return CP_OK;
+}
+
+int cp_seed_workspace_bytes(const cp_graph *g, size_t *out_bytes) {
+    size_t jump_bytes = 0;
+    const int rc = seed_bytes(g, out_bytes, &jump_bytes);
+    if (rc == CP_OK) *out_bytes += jump_bytes;
+    return rc;
 }
 
 int cp_seed_partition(const cp_graph *g, int32_t k, const int64_t *speeds, void *workspace, size_t workspace_bytes,
                       void *stream, uint8_t *assignment_out, int32_t *status_out) {
     if (!g || !speeds || !workspace || !assignment_out || !status_out) return CP_ERR_NULL;
     if (k < 1 || k > kSeedMaxK) return CP_ERR_SIZE;
-    size_t need = 0;
-    int rc = cp_seed_workspace_bytes(g, &need);
+    size_t need = 0, jump_bytes = 0;         // (the path's jumps are optional: an array of `need` bytes still serves)
+    int rc = seed_bytes(g, &need, &jump_bytes);
     if (rc) return rc;
     if (((uintptr_t)workspace % kAlign) != 0 || workspace_bytes < need) return CP_ERR_WORKSPACE;
     cp_graph_info info;
@@ -978,8 +988,9 @@ int cp_seed_partition(const cp_graph *g, int32_t k, const int64_t *speeds, void 
     rc = cp_eval(g, 1, 1, d_one, CP_ASSIGN_PARTITION_MAJOR, &unit, &unit, ws, align_up(eval), stream, d_cp, d_b,
                  nullptr, nullptr, T, CP_OUT_VERTEX_MAJOR, CP_PLAN_AUTO, status_out, nullptr);
     if (rc) return rc;
-    rc = cp_critical_path(g, 1, 1, d_one, CP_ASSIGN_PARTITION_MAJOR, &unit, &unit, d_b, d_cp, T,
-                          CP_OUT_VERTEX_MAJOR, ws, align_up(eval), stream, info.L, d_path, d_len, status_out);
+    int32_t *jumps = jump_bytes && workspace_bytes >= need + jump_bytes ? (int32_t *)(ws + need) : nullptr;
+    rc = critical_path(g, 1, 1, d_one, CP_ASSIGN_PARTITION_MAJOR, &unit, &unit, d_b, d_cp, T, CP_OUT_VERTEX_MAJOR, ws,
+                       align_up(eval), stream, info.L, d_path, d_len, status_out, jumps);
     if (rc) return rc;
     SeedArgs a{};
     a.c = (const uint8_t *)g->device_blob + p.c_off;
