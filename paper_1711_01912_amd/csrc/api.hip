@@ -482,8 +482,10 @@ int critical_path(const cp_graph *g, int32_t batch, int32_t k, const uint8_t *as
     s.edge_tab = d_tab;
     s.vert_tab = d_tab + 2 * (size_t)k * k * 8;
     s.status = status_out;
-    return launch_critical_path(s, (const int32_t *)(s.blob + p.sources_off), p.info.num_sources, cp,
-                                max_len, path_out, len_out, jumps, stream);
+    // the tables are all that a call needs of its workspace; the rest takes the records if they fit
+    const bool room = (workspace_bytes - tables_bytes(k)) / (kPathRecordWords * 4) >= (size_t)p.n;
+    return launch_critical_path(s, (const int32_t *)(s.blob + p.sources_off), p.info.num_sources, cp, max_len, path_out,
+                                len_out, jumps, room ? (uint32_t *)(d_tab + tables_bytes(k)) : nullptr, stream);
 }
 
 }  // namespace cpeval

@@ -410,9 +410,10 @@ struct PathArgs {
     const int32_t *sources;
     int32_t nsrc;
     const uint8_t *assign;
-    int64_t a_stride_p, a_stride_v;
+    int64_t a_stride_p, b_sq;
     const void *b;           // ticks; b(v, q) sits at v * b_sv + q * b_sq
-    int64_t b_sv, b_sq;
+    uint32_t a_stride_v, b_sv;   // 32 bits: an offset is one multiply-add (and leaves the loads beside each other:
+                                 // of 64 bits, the second address took a register that waits for the first load)
     const int64_t *cp;       // [P]
     const void *edge_tab;    // b-sweep orientation: row = device of the edge's source vertex
     const void *vert_tab;
@@ -424,7 +425,7 @@ struct PathArgs {
 
 // The lowest-numbered source whose b is CP, of those this wavefront looks at, or 0x7fffffff: eight in flight a lane.
 template <typename Tick>
-__device__ __forceinline__ uint32_t lowest_start(const PathArgs &a, const Tick *b, int64_t bsv, long long cp, int tid,
+__device__ __forceinline__ uint32_t lowest_start(const PathArgs &a, const Tick *b, uint32_t bsv, long long cp, int tid,
                                                  int nt) {
     uint32_t low = 0x7fffffff;
     for (int32_t i = tid; i < a.nsrc; i += 8 * nt) {
@@ -433,7 +434,7 @@ __device__ __forceinline__ uint32_t lowest_start(const PathArgs &a, const Tick *
 #pragma unroll
         for (int j = 0; j < 8; ++j) src[j] = a.sources[min(i + j * nt, a.nsrc - 1)];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) bs[j] = (long long)b[(int64_t)src[j] * bsv];
+        for (int j = 0; j < 8; ++j) bs[j] = (long long)b[(uint64_t)(uint32_t)src[j] * bsv];
 #pragma unroll
         for (int j = 0; j < 8; ++j) low = bs[j] == cp ? min(low, (uint32_t)src[j]) : low;
     }
@@ -448,6 +449,8 @@ __device__ __forceinline__ uint32_t lowest_start(const PathArgs &a, const Tick *
 // global load less per step of the walk).
 // The workgroup's wavefronts look for the start together, eight sources in flight per lane; the first one walks.
 // (One wavefront with one source in flight per lane spent more on 10,000 sources than on the walk.)
+// The path is stored 64 vertices at a time and offsets are 32-bit products: a store per step and an address that held up
+// the second load of a pair were a sixth of the walk (777 partitions, paths of 329 vertices: 525 -> 448 us).
 template <typename Tick, typename WT, bool MAGIC, bool LDS_TAB>
 __global__ __launch_bounds__(kPathThreads) void critical_path_kernel(PathArgs a) {
     extern __shared__ __align__(16) uint64_t path_lds[];
@@ -456,7 +459,7 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_kernel(PathArgs a)
     const int32_t q = blockIdx.x;
     const int32_t k = a.k;
     const Tick *b = (const Tick *)a.b + (int64_t)q * a.b_sq;
-    const int64_t bsv = a.b_sv;
+    const uint32_t asv = a.a_stride_v, bsv = a.b_sv;
     const uint8_t *row = a.assign + (int64_t)q * a.a_stride_p;
     const WT *wt = (const WT *)a.wt;
     const WT *cw = (const WT *)a.c;
@@ -490,16 +493,17 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_kernel(PathArgs a)
     Tick bv = 0;
     int32_t e0 = 0, e1 = 0;
     if (v != 0x7fffffff) {
-        pv = row[(int64_t)v * a.a_stride_v];
+        pv = row[(uint64_t)(uint32_t)v * asv];
         cv = cw[v];
-        bv = b[(int64_t)v * bsv];
+        bv = b[(uint64_t)(uint32_t)v * bsv];
         e0 = a.ptr[v];
         e1 = a.ptr[v + 1];
     }
     bool bad_id = false;
-    int32_t len = 0;
+    int32_t len = 0, step = 0;
     while (v != 0x7fffffff && len < a.max_len) {
-        if (lane == 0) path[len] = v;
+        step = lane == (len & 63) ? v : step;            // (a store per vertex is waited for with the loads behind it)
+        if ((len & 63) == 63) path[len - 63 + lane] = step;
         ++len;
         if (pv >= (uint32_t)k) { bad_id = true; pv = 0; }
         const Tick wv = MAGIC ? (Tick)magic_div((uint32_t)cv, vtab_m[pv])
@@ -513,8 +517,8 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_kernel(PathArgs a)
         for (int32_t e = e0 + lane; e < e1; e += 64) {
             const int32_t u = a.idx[e];
             const WT te = wt[e];
-            const uint32_t pu_raw = row[(int64_t)u * a.a_stride_v];
-            const Tick bu = b[(int64_t)u * bsv];
+            const uint32_t pu_raw = row[(uint64_t)(uint32_t)u * asv];
+            const Tick bu = b[(uint64_t)(uint32_t)u * bsv];
             const WT cu = cw[u];
             const int32_t u0 = a.ptr[u], u1 = a.ptr[u + 1];
             const uint32_t pu = min(pu_raw, (uint32_t)(k - 1));
@@ -537,6 +541,127 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_kernel(PathArgs a)
         }
         v = (int32_t)best;
     }
+    if (lane < (len & 63)) path[(len & ~63) + lane] = step;
+    if (bad_id) *a.status = CP_STATUS_BAD_DEVICE_ID;
+    if (lane == 0) a.len[q] = len;
+}
+
+// The walk with one round of loads per path vertex instead of two.  path_records_kernel lays out, once a call, what the
+// walk reads of a vertex as one 64-byte record: c, the number of its out-edges, and up to seven of them as (head, t).  A
+// step asks for the candidates' b and devices and for the candidates' records together; the winner's record then names
+// the next candidates.  (Before, the winner's edges were asked for only when it had won.)  Vertices
+// of more than seven edges take the edges out of the CSR and their winner's record in a round of its own.
+// Bound by the latency of that one round, b and the device ids from HBM or the last cache, 0.9 us a path vertex: 777
+// partitions, 121,000 vertices in 701 levels (paths of 329): 448 -> 306 us and 10 for the records; 300 partitions,
+// 240,000 vertices in 2,000 levels (1,027): 1,045 -> 764 and 16.
+constexpr int kRecordEdges = 7;
+
+__global__ __launch_bounds__(256) void path_records_kernel(PathArgs a, int32_t n, uint32_t *__restrict__ records) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int32_t v = (int32_t)(i >> 4);
+    const int w = (int)(i & 15);
+    if (v >= n) return;
+    const int32_t e0 = a.ptr[v], e1 = a.ptr[v + 1], e = e0 + (w - 2) / 2;
+    uint32_t x = 0;                       // (an edge that is not there names vertex 0: its loads are in range)
+    if (w == 0) x = ((const uint32_t *)a.c)[v];
+    else if (w == 1) x = (uint32_t)(e1 - e0);
+    else if (e < e1) x = (w & 1) ? ((const uint32_t *)a.wt)[e] : (uint32_t)a.idx[e];
+    records[i] = x;
+}
+
+template <typename Tick>
+__global__ __launch_bounds__(kPathThreads) void critical_path_records_kernel(PathArgs a, const uint32_t *__restrict__ records) {
+    extern __shared__ __align__(16) uint64_t path_lds[];
+    __shared__ uint32_t starts[kPathThreads / 64];
+    const int lane = threadIdx.x & 63, tid = threadIdx.x, nt = blockDim.x;
+    const int32_t q = blockIdx.x;
+    const int32_t k = a.k;
+    const Tick *b = (const Tick *)a.b + (int64_t)q * a.b_sq;
+    const uint32_t asv = a.a_stride_v, bsv = a.b_sv;
+    const uint8_t *row = a.assign + (int64_t)q * a.a_stride_p;
+    const uint32_t *wt = (const uint32_t *)a.wt;
+    const uint64_t *ge = (const uint64_t *)a.edge_tab, *gv = (const uint64_t *)a.vert_tab;
+    for (int i = tid; i < k * k; i += nt) path_lds[i] = ge[i];
+    for (int i = tid; i < k; i += nt) path_lds[k * k + i] = gv[i];
+    const Magic *etab = (const Magic *)path_lds, *vtab = etab + k * k;
+    int32_t *path = a.path + (int64_t)q * a.max_len;
+    for (int i = tid; i < a.max_len; i += nt) path[i] = -1;
+    uint32_t low = lowest_start(a, b, bsv, a.cp[q], tid, nt);
+    if (lane == 0) starts[tid >> 6] = low;
+    __syncthreads();                         // (the tables are in LDS, and the row is cleared, too)
+    if (tid >= 64) return;
+    for (int i = 1; i < nt >> 6; ++i) low = min(low, starts[i]);
+    low = (uint32_t)__builtin_amdgcn_readfirstlane((int)low);
+
+    const int word = lane & 15, part = lane >> 4;        // four records a load, sixteen lanes each
+    auto load_record = [&](uint32_t v) { return records[(size_t)v * 16 + word]; };
+    auto from = [&](uint32_t rec, int at) { return (uint32_t)__builtin_amdgcn_ds_bpermute(at * 4, (int)rec); };
+    int32_t v = (int32_t)low;
+    uint32_t pv = 0, rec = 0;                // rec: the current vertex's record, in the sixteen lanes from `base` on
+    int base = 0;
+    Tick bv = 0;
+    if (v != 0x7fffffff) {
+        pv = row[(uint64_t)(uint32_t)v * asv];
+        bv = b[(uint64_t)(uint32_t)v * bsv];
+        rec = load_record((uint32_t)v);
+    }
+    bool bad_id = false;
+    int32_t len = 0, step = 0;
+    while (v != 0x7fffffff && len < a.max_len) {
+        step = lane == (len & 63) ? v : step;            // (a store per vertex is waited for with the loads behind it)
+        if ((len & 63) == 63) path[len - 63 + lane] = step;
+        ++len;
+        const uint32_t cv = (uint32_t)__builtin_amdgcn_readlane((int)rec, base);
+        const int32_t deg = __builtin_amdgcn_readlane((int)rec, base + 1);
+        if (pv >= (uint32_t)k) { bad_id = true; pv = 0; }
+        const Magic *costs = etab + pv * k;
+        auto fits = [&](uint32_t p_raw, uint32_t te, Tick bu, Tick rest) {
+            return (Tick)magic_div(te, costs[min(p_raw, (uint32_t)(k - 1))]) + bu == rest;
+        };
+        uint32_t next = 0x7fffffff, n_p = 0;             // this lane's best successor, its device and b
+        Tick n_b = 0;
+        if (deg <= kRecordEdges) {
+            // (lanes past the last edge repeat it)
+            const int own = base + 2 + 2 * min(lane, max(deg - 1, 0));
+            const uint32_t u = from(rec, own), te = from(rec, own + 1);
+            const uint32_t u0 = from(rec, base + 2 + 2 * part), u1 = from(rec, base + 2 + 2 * min(4 + part, kRecordEdges - 1));
+            n_p = row[(uint64_t)u * asv];
+            n_b = b[(uint64_t)u * bsv];
+            const uint32_t rec0 = load_record(u0);
+            uint32_t rec1 = 0;
+            if (deg > 4) rec1 = load_record(u1);
+            const Tick rest = bv - (Tick)magic_div(cv, vtab[pv]);
+            if (lane < deg && fits(n_p, te, n_b, rest)) next = u;
+            const uint32_t best = min_over_wave(next);
+            v = (int32_t)best;
+            const int won = __ffsll((long long)__ballot(next == best)) - 1;
+            if (best != 0x7fffffffu) {
+                pv = wave_bcast<uint32_t>(n_p, won);
+                bv = wave_bcast<Tick>(n_b, won);
+                rec = won < 4 ? rec0 : rec1;
+                base = 16 * (won & 3);
+            }
+        } else {
+            const Tick rest = bv - (Tick)magic_div(cv, vtab[pv]);
+            const int32_t e0 = a.ptr[v];
+            for (int32_t e = e0 + lane; e < e0 + deg; e += 64) {
+                const uint32_t u = (uint32_t)a.idx[e];
+                const uint32_t pu = row[(uint64_t)(uint32_t)u * asv];
+                const Tick bu = b[(uint64_t)(uint32_t)u * bsv];
+                if (fits(pu, wt[e], bu, rest) && u < next) { next = u; n_p = pu; n_b = bu; }
+            }
+            const uint32_t best = min_over_wave(next);
+            v = (int32_t)best;
+            if (best != 0x7fffffffu) {
+                const int won = __ffsll((long long)__ballot(next == best)) - 1;
+                pv = wave_bcast<uint32_t>(n_p, won);
+                bv = wave_bcast<Tick>(n_b, won);
+                rec = load_record(best);
+                base = 0;
+            }
+        }
+    }
+    if (lane < (len & 63)) path[(len & ~63) + lane] = step;
     if (bad_id) *a.status = CP_STATUS_BAD_DEVICE_ID;
     if (lane == 0) a.len[q] = len;
 }
@@ -545,7 +670,7 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_kernel(PathArgs a)
 // names the vertex the path would take from it, all at once; three rounds of "the next one's next one" make
 // that a jump of eight; one lane then jumps, and every landing is filled up to the following one by a thread of
 // its own.  A path vertex costs an eighth of one dependent load instead of two dependent rounds of them:
-// 211,000 vertices in 1,000 levels 605 us walked, 50 by jumps (8 + 3 x 5 + 27); a million in 2,000: 1,270 and 118.
+// 211,000 vertices in 1,000 levels 555 us walked, 50 by jumps (8 + 3 x 5 + 27); a million in 2,000: 1,145 and 118.
 // The entry n stands for "the path has ended" and leads to itself.
 constexpr int kPathJump = 8;
 
@@ -1598,7 +1723,8 @@ int launch_cp_sources(const int32_t *sources, int32_t nsrc, const void *b, int32
         }                                                                                            \
     } while (0)
 int launch_critical_path(const SweepLaunch &s, const int32_t *sources, int32_t nsrc, const int64_t *cp,
-                         int32_t max_len, int32_t *path, int32_t *len, int32_t *jumps, void *stream) {
+                         int32_t max_len, int32_t *path, int32_t *len, int32_t *jumps, uint32_t *records,
+                         void *stream) {
     const ColumnDir &dir = *s.dir;
     PathArgs a{};
     a.ptr = (const int32_t *)(s.blob + dir.ptr_off);
@@ -1640,6 +1766,15 @@ int launch_critical_path(const SweepLaunch &s, const int32_t *sources, int32_t n
     const size_t lds = lds_tab ? ((size_t)s.k * s.k + s.k) * 8 : 0;
     // one wavefront where that many sources leave the others nothing to do
     const dim3 grid((unsigned)s.P), block((unsigned)(nsrc > 512 ? kPathThreads : 64));
+    if (records && s.magic && lds_tab && path_by_records(s.n, s.L)) {
+        const dim3 words((unsigned)(((int64_t)s.n * kPathRecordWords + 255) / 256));
+        hipLaunchKernelGGL(path_records_kernel, words, dim3(256), 0, st, a, s.n, records);
+        if (s.tick_bytes == 4)
+            hipLaunchKernelGGL(critical_path_records_kernel<int32_t>, grid, block, lds, st, a, records);
+        else
+            hipLaunchKernelGGL(critical_path_records_kernel<int64_t>, grid, block, lds, st, a, records);
+        return hip_ok(hipGetLastError());
+    }
 #define CP_PATH(TICK, WT, MAGIC)                                                                            \
     do {                                                                                                    \
         if (lds_tab) hipLaunchKernelGGL((critical_path_kernel<TICK, WT, MAGIC, true>), grid, block, lds, st, a); \

@@ -232,14 +232,21 @@ int launch_zero_words(uint64_t *dst, int64_t words, void *stream);
 int launch_ranks(const void *b, const void *tl, const void *c, bool narrow, int tick_bytes, int32_t n,
                  int64_t *up, int64_t *down, int64_t *total, void *stream);
 // jumps: scratch of path_jump_words(n) words for one partition's path by jumps, or null.
+// records: scratch of n records of kPathRecordWords words, on a 64-byte boundary, for the walk over records, or null.
+constexpr size_t kPathRecordWords = 16;
 int launch_critical_path(const SweepLaunch &s, const int32_t *sources, int32_t nsrc, const int64_t *cp,
-                         int32_t max_len, int32_t *path, int32_t *len, int32_t *jumps, void *stream);
+                         int32_t max_len, int32_t *path, int32_t *len, int32_t *jumps, uint32_t *records,
+                         void *stream);
 inline size_t path_jump_words(int32_t n) { return 3 * ((size_t)n + 1); }
 // The jumps are four more launches and read the whole graph once (45 us a million vertices) where the walk pays
-// two round trips, 0.4 to 0.7 us, per path vertex: many levels, and not too many vertices to one.  Walked and by
-// jumps: 128 levels of 300 vertices 50 and 26 us, of 4,000 97 and 63.
+// its round trips, 1 us, per path vertex: many levels, and not too many vertices to one.  Walked and by jumps: 128
+// levels of 300 vertices 42 and 26 us, of 4,000 90 and 63, 300 of 3,000 190 and 93.
 inline bool path_by_jumps(int32_t n, int32_t P, int32_t L) { return P == 1 && L >= 128 && n / L < 4096; }
-// cp_critical_path with that scratch; with it, what lies behind the path in path_out stays as it was.
+// Records are one more launch, which reads the graph and writes 64 bytes a vertex (5 us at 60,000 vertices, 16 at 240,000),
+// and save a tenth to a half of a microsecond per path vertex.  Without and with: 195 levels of 65 vertices 107 and
+// 105 us, 256 of 900 163 and 114, 300 of 300 131 and 98, 1,000 of 60 406 and 304.
+inline bool path_by_records(int32_t n, int32_t L) { return L >= 256 && n / L < 1024; }
+// cp_critical_path with scratch for the jumps or null; with it, what lies behind the path in path_out stays as it was.
 int critical_path(const cp_graph *g, int32_t batch, int32_t k, const uint8_t *assignments, int assign_layout,
                   const int64_t *speeds, const int64_t *bandwidth, const void *blevel, const int64_t *cp,
                   int tick_dtype, int b_layout, void *workspace, size_t workspace_bytes, void *stream,
