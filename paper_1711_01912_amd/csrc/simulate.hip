@@ -160,9 +160,15 @@ __device__ __forceinline__ long long load_b(const uint8_t *bq, int32_t z, int64_
 // the open inputs, which every edge of a started vertex asks for.  kAll (6 bytes more): the ready times and the
 // inboxes too; then nothing that two lanes exchange is in memory, and a step waits for no store.  Measured
 // against the state in memory: 5,271 vertices, 50 devices, 4,096 partitions (16 wavefronts
-// per compute unit, owners and inputs kept) 5.73 -> 4.55 ms; 1,124 vertices, 26 devices, 1,957 partitions (all
+// per compute unit, owners and inputs kept; 3.93 with the near inbox below) 5.73 -> 4.55 ms; 1,124 vertices, 26 devices, 1,957 partitions (all
 // kept) 1.83 -> 0.90 ms.
 enum Resident { kNothing, kOwnersAndInputs, kAll };
+
+// kOwnersAndInputs: the first two vertices handed to a device in a step wait in LDS, the others in its inbox in memory,
+// which then costs most steps neither a store to wait for nor a round trip (5,271 vertices, 50 devices, 4,096
+// partitions: PCT 4.46 -> 3.93 ms, FIFO 3.88 -> 3.40).  Two, because the static LDS then still is kSimStaticLds; 16 bits,
+// because state in LDS means at most 43,690 vertices.
+constexpr int32_t kNearInbox = 2;
 
 struct SimArgs {
     const int32_t *ptr;        // successor CSR over original ids
@@ -199,6 +205,7 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
     __shared__ int32_t count[64];      // vertices per device, then vertices handed to the device so far
     __shared__ int32_t seg[64];        // first slot of the device's segment
     __shared__ int32_t gbad[64];       // per group: a device id >= k was seen
+    __shared__ uint16_t near_in[64][kNearInbox];       // kOwnersAndInputs: the first vertices handed over in a step
     const int lane = threadIdx.x;
     const int32_t n = a.n, k = a.k;
     // with k <= 32 devices a wavefront can hold up to 64 / k partitions side by side: group g =
@@ -286,6 +293,7 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
                 const uint32_t d = owner(v);
                 const int32_t pos = atomicAdd(&count[first + d], 1);
                 if (KEEP == kAll) l_inbox[seg[first + d] + pos] = (uint16_t)v;
+                else if (KEEP == kOwnersAndInputs && pos < kNearInbox) near_in[d][pos] = (uint16_t)v;
                 else inbox_store(inbox + seg[first + d] + pos, v);
             }
         }
@@ -319,6 +327,7 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
         const int to = (KEEP != kNothing ? 0 : first) + (int)d;    // idle lanes help with wide rows: not their first
         const int32_t pos = atomicAdd(&count[to], 1);
         if (KEEP == kAll) l_inbox[seg[to] + pos] = (uint16_t)z;
+        else if (KEEP == kOwnersAndInputs && pos < kNearInbox) near_in[to][pos] = (uint16_t)z;
         else inbox_store(inbox + seg[to] + pos, z);
     };
     // every step with work left starts at least one vertex in every unfinished group, so
@@ -326,6 +335,10 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
     for (int64_t step = 0; step <= n; ++step) {
         if (alive) {   // vertices handed to this device since its last step, four loads in flight at a time
             const int32_t have = count[lane];
+            if (KEEP == kOwnersAndInputs) {            // what is handed over in a step is numbered from 0
+                taken = 0;
+                count[lane] = 0;
+            }
             while (taken < have) {
                 const int32_t cnt = min(4, have - taken);
                 int32_t z[4];
@@ -333,7 +346,9 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int32_t at = taken + min(j, cnt - 1);
-                    z[j] = KEEP == kAll ? (int32_t)l_inbox[base + at] : inbox_load(my_inbox + at);
+                    if (KEEP == kAll) z[j] = (int32_t)l_inbox[base + at];
+                    else if (KEEP == kOwnersAndInputs && at < kNearInbox) z[j] = (int32_t)near_in[lane][at];
+                    else z[j] = inbox_load(my_inbox + at);
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
