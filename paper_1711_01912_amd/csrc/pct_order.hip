@@ -456,7 +456,6 @@ __global__ __launch_bounds__(kSortThreads) void pct_scatter_kernel(const Key *__
 // ---------------------------------------------------------------- buckets of the leading digit
 
 // a bucket is sorted by a workgroup of 256 or 512 threads, 16 items per thread at most
-constexpr int kLeftOverGrid = 2048;
 constexpr int kBucketCapSmall = 256 * kSortRounds, kBucketCapLarge = 512 * kSortRounds;     // 4,096 / 8,192 items
 
 __global__ void pct_flag_clear_kernel(uint32_t *flag) { *flag = 0; }
@@ -657,10 +656,10 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
 template <int kBucketThreads, int kRounds, bool WHOLE>
 __device__ __forceinline__ void sort_bucket(const uint32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
                                             int32_t *__restrict__ vals_out, int32_t items, int bits, uint32_t *slot,
-                                            uint32_t (*cnt)[256]) {
+                                            uint32_t (*cnt)[256], int tid) {
     constexpr int kWaves = kBucketThreads / 64, kRadix = 256;
     __shared__ uint32_t wave_sum[kRadix / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     // rounds this bucket needs (the same for every wavefront: wavefront w owns items
     // [w * nr * 64, (w + 1) * nr * 64) of the bucket)
     const int nr = (items + kBucketThreads - 1) / kBucketThreads;
@@ -763,34 +762,42 @@ __global__ __launch_bounds__(kThreads) void pct_whole_sort_kernel(const uint32_t
         if (sort_by_bins<kThreads, kRounds, true>(keys_in + at, nullptr, vals_out + at, n, bits, val_bits, slot,
                                                             counters, wave_sum))
             return;
-    sort_bucket<kThreads, kRounds, true>(keys_in + at, nullptr, vals_out + at, n, bits, slot, (uint32_t (*)[256])counters);
+    sort_bucket<kThreads, kRounds, true>(keys_in + at, nullptr, vals_out + at, n, bits, slot, (uint32_t (*)[256])counters, threadIdx.x);
 }
 
-// The buckets that pct_bucket_bins_kernel left, 64 after each other to a workgroup of a fixed grid.
+// The buckets that pct_bucket_bins_kernel left, out of `each` neighbours (of one partition) per workgroup.
+// (Six wavefronts a SIMD, and the thread's number new in every round: else the loop keeps every address that follows from
+// it, 110 registers, or spills some; so 77 and no scratch.)
 template <int kThreads>
 __global__ __launch_bounds__(kThreads, 6) void pct_bucket_sort_kernel(const uint32_t *__restrict__ keys_in,
                                                                    const int32_t *__restrict__ vals_in,
-                                                                   int32_t *__restrict__ vals_out, int32_t n,
-                                                                   int32_t buckets, int32_t tiles, int bits,
+                                                                   int32_t *__restrict__ vals_out, int32_t n, int32_t each,
+                                                                   int32_t tiles, int bits,
                                                                    const uint32_t *__restrict__ starts, Gate gate,
                                                                    const uint32_t *__restrict__ left) {
     __shared__ uint32_t slot[kThreads * kSortRounds], counters[kThreads / 64][256];
     if (gate.closed()) return;
-    static_assert(kBuckets % 64 == 0, "no 64 buckets of two partitions");
-    for (int32_t i0 = blockIdx.x * 64; i0 < buckets; i0 += gridDim.x * 64) {
-        unsigned long long some = __ballot(left[i0 + (threadIdx.x & 63)] != 0);      // the same in every wavefront
-        const uint32_t q = (uint32_t)i0 / kBuckets;
-        for (; some != 0; some &= some - 1) {
-            const uint32_t d = (uint32_t)i0 % kBuckets + (uint32_t)__ffsll((long long)some) - 1;
-            const uint32_t lo = starts[((int64_t)q * kBuckets + d) * tiles];
-            const uint32_t hi = d + 1 == kBuckets ? (uint32_t)n : starts[((int64_t)q * kBuckets + d + 1) * tiles];
-            const int64_t at = (int64_t)q * n + lo;
-            const int32_t items = (int32_t)(hi - lo);
-            if (items <= kThreads * kSortRounds)          // (more: the flag is up)
-                sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot,
-                                                          counters);
-            __syncthreads();
-        }
+    // (turned by one neighbourhood from partition to partition: workgroups go round the eight XCDs, and the digits in use
+    // are the same in all partitions; of 9 devices, 19 in every 32: 2,480 us by eights, so 990)
+    const uint32_t per = (uint32_t)(kBuckets / each), q = blockIdx.x / per;
+    const uint32_t i0 = q * kBuckets + (blockIdx.x + q) % per * (uint32_t)each;
+    const int lane = threadIdx.x & 63;
+    const bool mine = lane < each;
+    uint32_t bound = (uint32_t)n;                         // where bucket i0 + lane starts
+    if (lane <= each && i0 % kBuckets + lane < kBuckets) bound = starts[(int64_t)(i0 + lane) * tiles];
+    unsigned long long some = __ballot(mine && left[i0 + (mine ? lane : 0)] != 0);      // the same in every wavefront
+    for (; some != 0; some &= some - 1) {
+        int tid = threadIdx.x;
+        asm("" : "+v"(tid));
+        __builtin_assume(tid >= 0 && tid < kThreads);
+        const int i = __ffsll((long long)some) - 1;
+        const uint32_t lo = __builtin_amdgcn_readlane(bound, i), hi = __builtin_amdgcn_readlane(bound, i + 1);
+        const int64_t at = (int64_t)q * n + lo;
+        const int32_t items = (int32_t)(hi - lo);
+        if (items <= kThreads * kSortRounds)              // (more: the flag is up)
+            sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters,
+                                                      tid);
+        __syncthreads();
     }
 }
 
@@ -969,9 +976,11 @@ int run_bucket_sort(const PctOrderLaunch &s, const KeyArgs &a, hipStream_t st) {
     else if (threads == 256) CP_BINS(256);
     else CP_BINS(512);
 #undef CP_BINS
+    const int32_t each = left_over_each(all);
+    static_assert(kBuckets % kLeftOverMost == 0, "no neighbours of two partitions");
 #define CP_LEFT(T)                                                                                                    \
-    hipLaunchKernelGGL(pct_bucket_sort_kernel<T>, dim3(kLeftOverGrid), dim3(T), 0, st, keys, vals, s.order_out, s.n, all, \
-                       tiles, rem, starts, fit, (const uint32_t *)left)
+    hipLaunchKernelGGL(pct_bucket_sort_kernel<T>, dim3((unsigned)(all / each)), dim3(T), 0, st, keys, vals, s.order_out, \
+                       s.n, each, tiles, rem, starts, fit, (const uint32_t *)left)
     if (small) CP_LEFT(256);
     else CP_LEFT(512);
 #undef CP_LEFT

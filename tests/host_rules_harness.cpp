@@ -108,6 +108,17 @@ static int rounded() {
     return 0;
 }
 
+// Buckets that are left to be ranked are sorted by as many workgroups as there are buckets, or by enough to fill the GPU
+// several times over.
+static int left_over() {
+    for (int64_t partitions : {1, 2, 7, 8, 31, 32, 33, 63, 64, 100, 128, 200, 511, 512, 1000, 4000000}) {
+        const int32_t buckets = (int32_t)(512 * partitions), each = left_over_each(buckets);
+        if (each < 1 || each > 16 || 512 % each || (each > 1 && buckets / each < 8192))
+            return std::printf("%d buckets, %d each\n", buckets, each), 1;
+    }
+    return 0;
+}
+
 // A graph's blob is allocated once.  argv[2]: the directory with the caller-side arrays.
 template <typename T>
 static std::vector<T> read_all(const std::string &name) {
@@ -145,5 +156,6 @@ int main(int argc, char **argv) {
     if (!std::strcmp(argv[1], "prepare")) return prepare();
     if (!std::strcmp(argv[1], "rounded")) return rounded();
     if (!std::strcmp(argv[1], "column")) return column();
+    if (!std::strcmp(argv[1], "left-over")) return left_over();
     return 2;
 }

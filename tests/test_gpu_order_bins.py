@@ -59,3 +59,25 @@ def test_lists_by_bins(gpu, oracle, n, kind, k, top):
         assert np.array_equal(seg.cpu().numpy(), ref_seg)
         assert np.array_equal(order.cpu().numpy(), ref_order)
     g.close()
+
+
+@pytest.mark.parametrize("P", [32, 65, 128, 257])
+def test_left_buckets_among_others(gpu, oracle, P):
+    """Two, four, eight and sixteen neighbouring buckets per workgroup: crowded partitions between spread ones, empty digits (9 of
+    16 devices) and, in one partition, full buckets beside nearly empty ones."""
+    import torch
+    n, k, top = 65_537, 9, 3_000_000
+    rng = np.random.default_rng(P)
+    n, level, src, dst = random_layered_dag(rng, [n // 2, n - n // 2], 1, 1, 1)
+    w = T._custom("left", n, src, dst, np.ones(len(src), dtype=np.int64), np.ones(n, dtype=np.int64), [1] * k,
+                  np.ones((k, k), dtype=np.int64), rng.integers(0, k, (P, n), dtype=np.uint8), level)
+    b = rng.integers(0, top + 1, (P, n), dtype=np.int32)
+    b[::3] = b[::3] // 150_000 * 150_000                     # 21 values
+    b[1] = np.where(rng.random(n) < 0.4, top // 2 + b[1] // 1000, b[1])
+    ref_order, ref_seg = oracle.pct_order(k, w.assignments, b.astype(np.int64), threads=8)
+    g = gpu.CpGraph.from_workload(w, device="cuda:0")
+    order, seg = gpu.cp_pct_order(g, torch.from_numpy(w.assignments).to("cuda:0"), k, torch.from_numpy(b).to("cuda:0"),
+                                  max_b=top, b_layout=1)
+    assert np.array_equal(seg.cpu().numpy(), ref_seg)
+    assert np.array_equal(order.cpu().numpy(), ref_order)
+    g.close()

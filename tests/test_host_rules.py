@@ -41,6 +41,10 @@ def test_rounded_cost_tables_are_exact_and_built_only_on_request(harness):
     _holds(harness, "rounded")
 
 
+def test_left_over_buckets_are_shared_out_over_the_gpu(harness):
+    _holds(harness, "left-over")
+
+
 @pytest.mark.parametrize("case", ["tiny", "mlp", "inception", "hubs", "sparse", "deep", "wide-weights"])
 def test_blob_is_allocated_once(harness, tmp_path, case):
     if case == "hubs":
