@@ -631,7 +631,8 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
     __shared__ uint32_t sorted[kThreads * kBinRounds];
     __shared__ __align__(16) uint32_t bins[kThreads * 8];
     __shared__ uint32_t wave_sum[kThreads / 64];
-    const int32_t q = (int32_t)(blockIdx.x / kBuckets), d = (int32_t)(blockIdx.x % kBuckets);
+    // (turned by one digit from partition to partition, as in pct_bucket_sort_kernel)
+    const int32_t q = (int32_t)(blockIdx.x / kBuckets), d = (int32_t)((blockIdx.x + (uint32_t)q) % kBuckets);
     // (both before the gate: the two round trips overlap)
     const uint32_t lo = starts[((int64_t)q * kBuckets + d) * tiles];
     const uint32_t hi = d + 1 == kBuckets ? (uint32_t)n : starts[((int64_t)q * kBuckets + d + 1) * tiles];
@@ -642,7 +643,7 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
     if (!done && items <= kThreads * kBinRounds && crowded[(int64_t)q * crowded_stride] == 0)
         done = sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits,
                                                                val_bits, sorted, bins, wave_sum);
-    if (threadIdx.x == 0) left[blockIdx.x] = done ? 0u : 1u;
+    if (threadIdx.x == 0) left[(int64_t)q * kBuckets + d] = done ? 0u : 1u;
 }
 
 // One bucket, sorted on the low `bits` bits inside LDS: stable passes of 8 bits, each ranking
@@ -946,9 +947,8 @@ int run_bucket_sort(const PctOrderLaunch &s, const KeyArgs &a, hipStream_t st) {
     if (!s.b_by_partition) lead.count((const uint32_t *)s.keys_a);
     lead.scan();
     // the smaller workgroup (more of them per compute unit) where buckets of twice the average size fit it
-    const int32_t average = s.n / kBuckets + 1;
-    const bool small = 2 * (int64_t)average <= kBucketCapSmall;
-    const int threads = average <= 512 ? 128 : average <= 1024 ? 256 : 512;     // eight items a thread: twice the average
+    const bool small = 2 * ((int64_t)s.n / kBuckets + 1) <= kBucketCapSmall;
+    const int threads = bucket_threads(s.n, s.k, s.b_bits, rem, s.max_b);
     const int shift = std::max(0, rem - bin_bits(threads));
     // (noted where the partition's list bounds will stand)
     int32_t *crowded = s.seg_out;
@@ -967,7 +967,7 @@ int run_bucket_sort(const PctOrderLaunch &s, const KeyArgs &a, hipStream_t st) {
     const int32_t *vals = s.vals_tmp;
     const int32_t all = s.P * kBuckets;
     const int val_bits = 32 - __builtin_clz((unsigned)s.n - 1);
-    // (keys of 32 bits: shift is 13, 12 or 11 at most for up to 2^18, 2^19 or 2^20 vertices)
+    // (keys of 32 bits: shift is 13, 12 or 11 at most for up to 2^18, 2^19 or 2^20 vertices, less for larger workgroups)
     if (shift + val_bits > 32) return CP_ERR_ARG;
 #define CP_BINS(T)                                                                                                    \
     hipLaunchKernelGGL(pct_bucket_bins_kernel<T>, dim3((unsigned)all), dim3(T), 0, st, keys, vals, s.order_out, s.n, tiles, \

@@ -119,6 +119,26 @@ static int left_over() {
     return 0;
 }
 
+// The workgroups that take the buckets of a partition's keys hold 1.4 times the average of those in use, up to 4,096 items.
+static int bucket_sizes() {
+    for (int32_t n : {65536, 70000, 211000, 250000, 262143, 480000, 1048576})
+        for (int32_t k : {1, 2, 3, 5, 9, 16, 17, 33, 50, 64, 100, 255})
+            for (int64_t max_b : {131072ll, 262143ll, 1000000ll, 1048576ll, 2100000ll, 4194303ll, 5000000ll, 16777215ll}) {
+                const int bb = 64 - __builtin_clzll((uint64_t)max_b), kb = k > 1 ? 32 - __builtin_clz((unsigned)k - 1) : 0;
+                const int rem = bb + kb - 9;
+                if (bb + kb > 32 || bb + kb <= 17) continue;
+                std::vector<char> in(512, 0);
+                for (int64_t dev = 0; dev < k; ++dev)
+                    for (int64_t x = 0; x <= max_b; x = x < max_b && x + (1ll << rem) > max_b ? max_b : x + (1ll << rem))
+                        in[(size_t)((dev << bb | x) >> rem)] = 1;
+                const int64_t used = std::count(in.begin(), in.end(), 1), threads = bucket_threads(n, k, bb, rem, max_b);
+                if (8 * threads < std::min<int64_t>(4096, n / used * 7 / 5) || (threads > 128 && 4 * threads >= n / used * 7 / 5 + 7) || (threads != 128 && threads != 256 && threads != 512))
+                    return std::printf("n %d k %d max_b %lld: %lld digits, %lld threads\n", n, k, (long long)max_b,
+                                       (long long)used, (long long)threads), 1;
+            }
+    return 0;
+}
+
 // A graph's blob is allocated once.  argv[2]: the directory with the caller-side arrays.
 template <typename T>
 static std::vector<T> read_all(const std::string &name) {
@@ -157,5 +177,6 @@ int main(int argc, char **argv) {
     if (!std::strcmp(argv[1], "rounded")) return rounded();
     if (!std::strcmp(argv[1], "column")) return column();
     if (!std::strcmp(argv[1], "left-over")) return left_over();
+    if (!std::strcmp(argv[1], "bucket-sizes")) return bucket_sizes();
     return 2;
 }

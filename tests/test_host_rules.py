@@ -45,6 +45,10 @@ def test_left_over_buckets_are_shared_out_over_the_gpu(harness):
     _holds(harness, "left-over")
 
 
+def test_bins_hold_the_buckets_in_use(harness):
+    _holds(harness, "bucket-sizes")
+
+
 @pytest.mark.parametrize("case", ["tiny", "mlp", "inception", "hubs", "sparse", "deep", "wide-weights"])
 def test_blob_is_allocated_once(harness, tmp_path, case):
     if case == "hubs":
