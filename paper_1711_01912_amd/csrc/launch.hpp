@@ -206,6 +206,15 @@ inline int32_t left_over_each(int32_t buckets) {
     while (each < kLeftOverMost && buckets / (2 * each) >= 8192) each *= 2;
     return each;
 }
+// The same for the bins, most of whose buckets have work: four where 16,384 workgroups remain.  262,144 buckets of partitions
+// that the sample found crowded: 65 us one by one, 41, 22 and 12 by twos, fours and eights; with work, 16 devices: 477, 369,
+// 361 and 357; with work for the odd partition only (300 values of b): 168, 132, 141 and 158.
+constexpr int32_t kBinsMost = 4;
+inline int32_t bins_each(int32_t buckets) {
+    int32_t each = 1;
+    while (each < kBinsMost && buckets / (2 * each) >= 16384) each *= 2;
+    return each;
+}
 // Threads of the workgroup that deals a bucket to bins, eight items each: the smallest for 1.4 times the average of the
 // buckets in use (layered graphs of 211,000 to 480,000 vertices: the fullest holds 1.14 to 1.38 of it).  In use are the
 // leading digits (keys without their low `rem` bits) that a device number below k and a max_b - b of max_b at most can

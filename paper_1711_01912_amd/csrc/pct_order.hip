@@ -616,14 +616,14 @@ __device__ __forceinline__ bool sort_by_bins(const uint32_t *__restrict__ keys_i
     return true;
 }
 
-// The buckets of the leading digit, by bins.  left[i] = 1 for those that pct_bucket_sort_kernel has to sort: of more
+// The buckets of the leading digit, by bins, `each` neighbours per workgroup.  left[i] = 1 for those that pct_bucket_sort_kernel has to sort: of more
 // than eight items per thread, of a partition whose keys the sample of pct_bucket_check_kernel found in
 // common bins, or with a crowded bin after all.
 constexpr int kBinRounds = 8;
 template <int kThreads>
 __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_t *__restrict__ keys_in,
                                                                    const int32_t *__restrict__ vals_in,
-                                                                   int32_t *__restrict__ vals_out, int32_t n,
+                                                                   int32_t *__restrict__ vals_out, int32_t n, int32_t each,
                                                                    int32_t tiles, int bits, int val_bits,
                                                                    const uint32_t *__restrict__ starts, Gate gate,
                                                                    const int32_t *__restrict__ crowded, int32_t crowded_stride,
@@ -631,19 +631,27 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
     __shared__ uint32_t sorted[kThreads * kBinRounds];
     __shared__ __align__(16) uint32_t bins[kThreads * 8];
     __shared__ uint32_t wave_sum[kThreads / 64];
-    // (turned by one digit from partition to partition, as in pct_bucket_sort_kernel)
-    const int32_t q = (int32_t)(blockIdx.x / kBuckets), d = (int32_t)((blockIdx.x + (uint32_t)q) % kBuckets);
-    // (both before the gate: the two round trips overlap)
-    const uint32_t lo = starts[((int64_t)q * kBuckets + d) * tiles];
-    const uint32_t hi = d + 1 == kBuckets ? (uint32_t)n : starts[((int64_t)q * kBuckets + d + 1) * tiles];
+    // (neighbours turned from partition to partition, as in pct_bucket_sort_kernel)
+    const uint32_t per = (uint32_t)(kBuckets / each), q = blockIdx.x / per, d0 = (blockIdx.x + q) % per * (uint32_t)each;
+    const int lane = threadIdx.x & 63;
+    uint32_t bound = (uint32_t)n;                         // where bucket d0 + lane starts
+    if (lane <= each && d0 + lane < kBuckets) bound = starts[((int64_t)q * kBuckets + d0 + lane) * tiles];
     if (gate.closed()) return;
-    const int32_t items = (int32_t)(hi - lo);
-    const int64_t at = (int64_t)q * n + lo;
-    bool done = items <= 0;
-    if (!done && items <= kThreads * kBinRounds && crowded[(int64_t)q * crowded_stride] == 0)
-        done = sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits,
-                                                               val_bits, sorted, bins, wave_sum);
-    if (threadIdx.x == 0) left[(int64_t)q * kBuckets + d] = done ? 0u : 1u;
+    left += (int64_t)q * kBuckets + d0;
+    if (crowded[(int64_t)q * crowded_stride] != 0) {
+        if ((int)threadIdx.x < each) left[threadIdx.x] = 1u;
+        return;
+    }
+    for (int i = 0; i < each; ++i) {
+        const uint32_t lo = __builtin_amdgcn_readlane(bound, i), hi = __builtin_amdgcn_readlane(bound, i + 1);
+        const int32_t items = (int32_t)(hi - lo);
+        const int64_t at = (int64_t)q * n + lo;
+        bool done = items <= 0;
+        if (!done && items <= kThreads * kBinRounds)
+            done = sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits,
+                                                                   val_bits, sorted, bins, wave_sum);
+        if (threadIdx.x == 0) left[i] = done ? 0u : 1u;
+    }
 }
 
 // One bucket, sorted on the low `bits` bits inside LDS: stable passes of 8 bits, each ranking
@@ -969,8 +977,9 @@ int run_bucket_sort(const PctOrderLaunch &s, const KeyArgs &a, hipStream_t st) {
     const int val_bits = 32 - __builtin_clz((unsigned)s.n - 1);
     // (keys of 32 bits: shift is 13, 12 or 11 at most for up to 2^18, 2^19 or 2^20 vertices, less for larger workgroups)
     if (shift + val_bits > 32) return CP_ERR_ARG;
+    const int32_t dealt = bins_each(all);
 #define CP_BINS(T)                                                                                                    \
-    hipLaunchKernelGGL(pct_bucket_bins_kernel<T>, dim3((unsigned)all), dim3(T), 0, st, keys, vals, s.order_out, s.n, tiles, \
+    hipLaunchKernelGGL(pct_bucket_bins_kernel<T>, dim3((unsigned)(all / dealt)), dim3(T), 0, st, keys, vals, s.order_out, s.n, dealt, tiles, \
                        rem, val_bits, starts, fit, (const int32_t *)crowded, s.k + 1, left)
     if (threads == 128) CP_BINS(128);
     else if (threads == 256) CP_BINS(256);

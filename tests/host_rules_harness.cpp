@@ -115,6 +115,10 @@ static int left_over() {
         const int32_t buckets = (int32_t)(512 * partitions), each = left_over_each(buckets);
         if (each < 1 || each > 16 || 512 % each || (each > 1 && buckets / each < 8192))
             return std::printf("%d buckets, %d each\n", buckets, each), 1;
+        const int32_t dealt = bins_each(buckets);
+        if (dealt < 1 || dealt > 4 || 512 % dealt || (dealt > 1 && buckets / dealt < 16384) ||
+            (dealt < 4 && buckets / dealt > 32768))
+            return std::printf("%d buckets, %d dealt\n", buckets, dealt), 1;
     }
     return 0;
 }
