@@ -639,7 +639,8 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
     if (gate.closed()) return;
     left += (int64_t)q * kBuckets + d0;
     if (crowded[(int64_t)q * crowded_stride] != 0) {
-        if ((int)threadIdx.x < each) left[threadIdx.x] = 1u;
+        const uint32_t next = __shfl_down(bound, 1);
+        if ((int)threadIdx.x < each) left[threadIdx.x] = next != bound ? 1u : 0u;
         return;
     }
     for (int i = 0; i < each; ++i) {
