@@ -195,24 +195,33 @@ struct PctOrderLaunch {
     int32_t *order_out = nullptr, *seg_out = nullptr, *status = nullptr;
 };
 size_t pct_counts_bytes(int32_t n, int32_t P);
-// Neighbouring buckets of the leading digit that one workgroup looks through for those that are left to the ranking by
-// ballots.  One while they are few: left buckets lie beside each other, and a workgroup sorts its own one after the other.
-// More where 8,192 workgroups remain, because one that finds none costs as much as a whole one: 262,144 buckets, none left,
-// 65 us one by one (128 threads each), 22 by eights, 14 by sixteens.  Ranked, 211,000 vertices, 512 partitions, 9 devices: one by one 1,470 us,
-// by sixteens 1,080, by thirty-twos 1,130; 70,000 vertices, 3 devices: 695, 671 and 869.
+// Buckets of the leading digit that one workgroup looks through for those that are left to the ranking by ballots, which it
+// sorts one after the other: one while they are few, up to sixteen where 8,192 workgroups remain, because one that finds
+// none costs as much as a whole one (262,144 buckets, none left: 65 us one by one, 14 by sixteens).  All in use left, ranked
+// one by one / so: 211,000 vertices on 3 devices, 32 partitions 63 / 69 us, 128 partitions 234 / 233; on 16 devices, 512
+// partitions 1,900 / 1,385.  (Fixed workgroups, 1,792 that share all buckets out in turn: 93, 278 and 1,603.)
 constexpr int32_t kLeftOverMost = 16;
 inline int32_t left_over_each(int32_t buckets) {
     int32_t each = 1;
     while (each < kLeftOverMost && buckets / (2 * each) >= 8192) each *= 2;
     return each;
 }
-// The same for the bins, most of whose buckets have work: four where 16,384 workgroups remain.  262,144 buckets of partitions
-// that the sample found crowded: 65 us one by one, 41, 22 and 12 by twos, fours and eights; with work, 16 devices: 477, 369,
-// 361 and 357; with work for the odd partition only (300 values of b): 168, 132, 141 and 158.
+// The bucket of its partition that a workgroup looks at as its t-th: far apart, and turned from partition to partition and
+// from one to the next, because left buckets lie beside each other, the digits in use are the same in all partitions
+// (of 9 devices, 19 in every 32) and workgroups go round the eight XCDs.
+template <int kAll>
+CP_HOST_DEVICE uint32_t left_over_bucket(uint32_t workgroup, uint32_t t, int32_t each) {
+    const uint32_t per = (uint32_t)(kAll / each), q = workgroup / per;
+    return t * per + (workgroup + q + t * 79) % per;
+}
+// Neighbouring buckets that one workgroup deals to bins: four where 8,192 workgroups remain, because one whose partition is
+// crowded costs as much as a whole one.  262,144 buckets, all crowded: 65 us one by one, 41, 22 and 12 by twos, fours and
+// eights; with work, 16 devices: 477, 369, 361 and 357; with work for the odd partition only (300 values of b): 168, 132,
+// 141 and 158.  16,384 buckets, all crowded: 11 one by one, 6.7 by twos.
 constexpr int32_t kBinsMost = 4;
 inline int32_t bins_each(int32_t buckets) {
     int32_t each = 1;
-    while (each < kBinsMost && buckets / (2 * each) >= 16384) each *= 2;
+    while (each < kBinsMost && buckets / (2 * each) >= 8192) each *= 2;
     return each;
 }
 // Threads of the workgroup that deals a bucket to bins, eight items each: the smallest for 1.4 times the average of the

@@ -616,9 +616,9 @@ __device__ __forceinline__ bool sort_by_bins(const uint32_t *__restrict__ keys_i
     return true;
 }
 
-// The buckets of the leading digit, by bins, `each` neighbours per workgroup.  left[i] = 1 for those that pct_bucket_sort_kernel has to sort: of more
-// than eight items per thread, of a partition whose keys the sample of pct_bucket_check_kernel found in
-// common bins, or with a crowded bin after all.
+// The buckets of the leading digit, by bins, `each` neighbours per workgroup.  left[i] = 1 for those that
+// pct_bucket_sort_kernel has to sort: of more than eight items per thread, of a partition whose keys the sample of
+// pct_bucket_check_kernel found in common bins, or with a crowded bin after all.
 constexpr int kBinRounds = 8;
 template <int kThreads>
 __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_t *__restrict__ keys_in,
@@ -631,7 +631,8 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
     __shared__ uint32_t sorted[kThreads * kBinRounds];
     __shared__ __align__(16) uint32_t bins[kThreads * 8];
     __shared__ uint32_t wave_sum[kThreads / 64];
-    // (neighbours turned from partition to partition, as in pct_bucket_sort_kernel)
+    // (turned by one neighbourhood from partition to partition: workgroups go round the eight XCDs, and the digits in use
+    // are the same in all partitions; of 9 devices, 19 in every 32: 884 us one by one, so 568)
     const uint32_t per = (uint32_t)(kBuckets / each), q = blockIdx.x / per, d0 = (blockIdx.x + q) % per * (uint32_t)each;
     const int lane = threadIdx.x & 63;
     uint32_t bound = (uint32_t)n;                         // where bucket d0 + lane starts
@@ -775,7 +776,7 @@ __global__ __launch_bounds__(kThreads) void pct_whole_sort_kernel(const uint32_t
     sort_bucket<kThreads, kRounds, true>(keys_in + at, nullptr, vals_out + at, n, bits, slot, (uint32_t (*)[256])counters, threadIdx.x);
 }
 
-// The buckets that pct_bucket_bins_kernel left, out of `each` neighbours (of one partition) per workgroup.
+// The buckets that pct_bucket_bins_kernel left, out of the `each` that a workgroup looks at (left_over_bucket).
 // (Six wavefronts a SIMD, and the thread's number new in every round: else the loop keeps every address that follows from
 // it, 110 registers, or spills some; so 77 and no scratch.)
 template <int kThreads>
@@ -787,26 +788,27 @@ __global__ __launch_bounds__(kThreads, 6) void pct_bucket_sort_kernel(const uint
                                                                    const uint32_t *__restrict__ left) {
     __shared__ uint32_t slot[kThreads * kSortRounds], counters[kThreads / 64][256];
     if (gate.closed()) return;
-    // (turned by one neighbourhood from partition to partition: workgroups go round the eight XCDs, and the digits in use
-    // are the same in all partitions; of 9 devices, 19 in every 32: 2,480 us by eights, so 990)
-    const uint32_t per = (uint32_t)(kBuckets / each), q = blockIdx.x / per;
-    const uint32_t i0 = q * kBuckets + (blockIdx.x + q) % per * (uint32_t)each;
-    const int lane = threadIdx.x & 63;
-    const bool mine = lane < each;
-    uint32_t bound = (uint32_t)n;                         // where bucket i0 + lane starts
-    if (lane <= each && i0 % kBuckets + lane < kBuckets) bound = starts[(int64_t)(i0 + lane) * tiles];
-    unsigned long long some = __ballot(mine && left[i0 + (mine ? lane : 0)] != 0);      // the same in every wavefront
+    const uint32_t q = blockIdx.x / (uint32_t)(kBuckets / each);
+    uint32_t lo = 0, hi = 0;
+    if ((int)(threadIdx.x & 63) < each) {
+        const uint32_t d = left_over_bucket<kBuckets>(blockIdx.x, threadIdx.x & 63, each);
+        const int64_t i = (int64_t)q * kBuckets + d;
+        if (left[i] != 0) {
+            lo = starts[i * tiles];
+            hi = d + 1 == kBuckets ? (uint32_t)n : starts[(i + 1) * tiles];
+        }
+    }
+    if (hi - lo > kThreads * kSortRounds) hi = lo;        // (more: the flag is up)
+    unsigned long long some = __ballot(hi > lo);          // the same in every wavefront
     for (; some != 0; some &= some - 1) {
         int tid = threadIdx.x;
         asm("" : "+v"(tid));
         __builtin_assume(tid >= 0 && tid < kThreads);
-        const int i = __ffsll((long long)some) - 1;
-        const uint32_t lo = __builtin_amdgcn_readlane(bound, i), hi = __builtin_amdgcn_readlane(bound, i + 1);
-        const int64_t at = (int64_t)q * n + lo;
-        const int32_t items = (int32_t)(hi - lo);
-        if (items <= kThreads * kSortRounds)              // (more: the flag is up)
-            sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters,
-                                                      tid);
+        const int which = __ffsll((long long)some) - 1;
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)lo, which);
+        const int32_t items = (int32_t)((uint32_t)__builtin_amdgcn_readlane((int)hi, which) - first);
+        const int64_t at = (int64_t)q * n + first;
+        sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters, tid);
         __syncthreads();
     }
 }
@@ -987,7 +989,6 @@ int run_bucket_sort(const PctOrderLaunch &s, const KeyArgs &a, hipStream_t st) {
     else CP_BINS(512);
 #undef CP_BINS
     const int32_t each = left_over_each(all);
-    static_assert(kBuckets % kLeftOverMost == 0, "no neighbours of two partitions");
 #define CP_LEFT(T)                                                                                                    \
     hipLaunchKernelGGL(pct_bucket_sort_kernel<T>, dim3((unsigned)(all / each)), dim3(T), 0, st, keys, vals, s.order_out, \
                        s.n, each, tiles, rem, starts, fit, (const uint32_t *)left)

@@ -108,16 +108,29 @@ static int rounded() {
     return 0;
 }
 
-// Buckets that are left to be ranked are sorted by as many workgroups as there are buckets, or by enough to fill the GPU
-// several times over.
+// Buckets that are left to be ranked: each is looked at once, by as many workgroups as there are buckets or by thousands,
+// and a run of digits that all partitions use falls to the XCDs in even shares.
 static int left_over() {
-    for (int64_t partitions : {1, 2, 7, 8, 31, 32, 33, 63, 64, 100, 128, 200, 511, 512, 1000, 4000000}) {
-        const int32_t buckets = (int32_t)(512 * partitions), each = left_over_each(buckets);
+    for (int32_t partitions : {1, 2, 3, 7, 31, 32, 33, 64, 100, 129, 257, 512}) {
+        const int32_t buckets = 512 * partitions, each = left_over_each(buckets);
         if (each < 1 || each > 16 || 512 % each || (each > 1 && buckets / each < 8192))
             return std::printf("%d buckets, %d each\n", buckets, each), 1;
+        std::vector<int> taken((size_t)buckets, 0);
+        int64_t share[8] = {};
+        for (int32_t b = 0; b < buckets / each; ++b)
+            for (int32_t t = 0; t < each; ++t) {
+                const uint32_t d = left_over_bucket<512>((uint32_t)b, (uint32_t)t, each);
+                if (d >= 512) return std::printf("digit %u\n", d), 1;
+                ++taken[(size_t)(b / (512 / each)) * 512 + d];
+                share[b % 8] += d % 32 < 19;
+            }
+        for (int x : taken)
+            if (x != 1) return std::printf("%d buckets: one %d times\n", buckets, x), 1;
+        if (partitions >= 8 && *std::max_element(share, share + 8) > 1.1 * (buckets * 19 / 32 / 8))
+            return std::printf("%d buckets: an XCD has too many\n", buckets), 1;
         const int32_t dealt = bins_each(buckets);
-        if (dealt < 1 || dealt > 4 || 512 % dealt || (dealt > 1 && buckets / dealt < 16384) ||
-            (dealt < 4 && buckets / dealt > 32768))
+        if (dealt < 1 || dealt > 4 || 512 % dealt || (dealt > 1 && buckets / dealt < 8192) ||
+            (dealt < 4 && buckets / dealt > 16384))
             return std::printf("%d buckets, %d dealt\n", buckets, dealt), 1;
     }
     return 0;
