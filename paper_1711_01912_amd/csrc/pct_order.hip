@@ -66,9 +66,14 @@ struct KeyArgs {
     int64_t a_stride_p, a_stride_v;
     void *keys;               // Key [P][n]
     int32_t *status;
+    uint32_t *flag;           // of the bucket path, cleared here (a launch less), or null
     int64_t max_b;
     int32_t n, P, k, bb;
 };
+
+__device__ __forceinline__ void clear_flag(const KeyArgs &a) {
+    if (a.flag != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *a.flag = 0;
+}
 
 // A kernel launched for one of two continuations returns at once when the device-side flag
 // says the other one runs (flag == nullptr: always runs).  Uniform for the whole grid.
@@ -83,6 +88,7 @@ struct Gate {
 template <typename Tick, typename Key>
 __global__ __launch_bounds__(256) void pct_keys_kernel(KeyArgs a) {
     __shared__ Key tile[64][65];
+    clear_flag(a);
     const int lane = threadIdx.x & 63, row0 = threadIdx.x >> 6;
     const int64_t v0 = (int64_t)blockIdx.x * 64, q0 = (int64_t)blockIdx.y * 64;
     const Tick *b = (const Tick *)a.b;
@@ -123,6 +129,7 @@ __global__ __launch_bounds__(256) void pct_keys_kernel(KeyArgs a) {
 // The same from b laid out [P][n]: no transpose, one key per thread.
 template <typename Tick, typename Key>
 __global__ __launch_bounds__(256) void pct_keys_rows_kernel(KeyArgs a) {
+    clear_flag(a);
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= a.n) return;
     bool bad_b = false, bad_id = false;
@@ -207,6 +214,7 @@ __global__ __launch_bounds__(kLeadThreads) void pct_keys_count_kernel(KeyArgs a,
     constexpr int kRadix = 1 << kBucketBits, kTile = kLeadThreads * kSortRounds;
     constexpr int kQuadRounds = kSortRounds / 4;
     __shared__ Histogram<kLeadThreads, kRadix> hist;
+    clear_flag(a);
     const int tid = threadIdx.x;
     const int32_t tile = (int32_t)(blockIdx.x % (uint32_t)tiles), q = (int32_t)(blockIdx.x / (uint32_t)tiles);
     hist.clear(tid);
@@ -457,8 +465,6 @@ __global__ __launch_bounds__(kSortThreads) void pct_scatter_kernel(const Key *__
 
 // a bucket is sorted by a workgroup of 256 or 512 threads, 16 items per thread at most
 constexpr int kBucketCapSmall = 256 * kSortRounds, kBucketCapLarge = 512 * kSortRounds;     // 4,096 / 8,192 items
-
-__global__ void pct_flag_clear_kernel(uint32_t *flag) { *flag = 0; }
 
 // After the scan of the leading digit's counts, bucket d of partition q starts where tile 0's
 // run of digit d starts.  flag |= 1 if some bucket holds more than `cap` items.
@@ -934,11 +940,11 @@ void launch_keys(const PctOrderLaunch &s, const KeyArgs &a, hipStream_t st) {
 // leading digit's scatter and the buckets sorted inside LDS (flag 0), or the ordinary passes
 // from the untouched keys (flag 1).  With rows of b per partition one kernel writes the keys
 // and counts their leading digit.
-int run_bucket_sort(const PctOrderLaunch &s, const KeyArgs &a, hipStream_t st) {
+int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     constexpr int kTile = kLeadThreads * kSortRounds;
     const int32_t tiles = (s.n + kTile - 1) / kTile;
     uint32_t *flag = s.counts + (size_t)s.P * kMaxRadix * (size_t)tiles;     // behind the counts
-    hipLaunchKernelGGL(pct_flag_clear_kernel, dim3(1), dim3(1), 0, st, flag);
+    a.flag = flag;
     const int rem = s.key_bits - kBucketBits;
     if (s.b_by_partition) {
         const dim3 grid((unsigned)((int64_t)tiles * s.P)), block(kLeadThreads);
