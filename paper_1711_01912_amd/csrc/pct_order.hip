@@ -468,28 +468,42 @@ constexpr int kBucketCapSmall = 256 * kSortRounds, kBucketCapLarge = 512 * kSort
 
 // After the scan of the leading digit's counts, bucket d of partition q starts where tile 0's
 // run of digit d starts.  flag |= 1 if some bucket holds more than `cap` items.
-// crowded[q] = 1 where 512 of the partition's keys, spread over its vertices, fall into common bins of
+// crowded[q] = 1 where 512 * kEach of the partition's keys, spread over its vertices, fall into common bins of
 // pct_bucket_bins_kernel (keys without their low `shift` bits) as they would with more than kBinAverage items in an average
-// item's bin: then ranking by digits is the faster way, and the bins would be tried in vain.
-constexpr int kBinMost = 96, kBinAverage = 32;
+// item's bin: then ranking by digits is the faster way, and the bins would be tried in vain.  Few partitions are sampled
+// more finely, because the call then takes as long as the one that was misjudged (a million vertices on 16 devices in 66
+// items a bin, of 512 samples one partition in 14 passed for spread; 8 partitions: 231 us, 203 with 2,048).
+constexpr int kBinMost = 96, kBinAverage = 32, kFineSamples = 128;
+template <int kEach>
 __global__ __launch_bounds__(kBuckets) void pct_bucket_check_kernel(const uint32_t *__restrict__ starts,
                                                                     const uint32_t *__restrict__ keys, int32_t n,
                                                                     int32_t tiles, int32_t cap, int shift, uint32_t *flag,
                                                                     int32_t *crowded, int32_t crowded_stride) {
-    constexpr int kTable = 4096;
-    __shared__ uint32_t table[kTable];
+    constexpr int kTableBits = kEach > 1 ? 13 : 12, kSamples = kBuckets * kEach;
+    __shared__ uint32_t table[1 << kTableBits], wave_pairs[kBuckets / 64];
     const int32_t q = blockIdx.x, d = threadIdx.x;
     const uint32_t lo = starts[((int64_t)q * kBuckets + d) * tiles];
     const uint32_t hi = d + 1 < kBuckets ? starts[((int64_t)q * kBuckets + d + 1) * tiles] : (uint32_t)n;
-    const uint32_t x = keys[(int64_t)q * n + (int64_t)d * n / kBuckets] >> shift;
-    for (int i = d; i < kTable; i += kBuckets) table[i] = 0xffffffffu;
+    uint32_t x[kEach];
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) x[j] = keys[(int64_t)q * n + (int64_t)(j * kBuckets + d) * n / kSamples] >> shift;
+    for (int i = d; i < 1 << kTableBits; i += kBuckets) table[i] = 0xffffffffu;
     // (one atomic per partition at most, none once the flag is up: they queue up on the one word)
     const int any = __syncthreads_or(hi - lo > (uint32_t)cap);
     if (any && threadIdx.x == 0 && *(volatile const uint32_t *)flag == 0) atomicOr(flag, 1u);
-    const uint32_t before = atomicExch(&table[x * 0x9e3779b1u >> 20], x);
-    const int pairs = __syncthreads_count(before == x);
-    if (threadIdx.x == 0)
-        crowded[(int64_t)q * crowded_stride] = (int64_t)pairs * n > (int64_t)kBuckets * kBuckets / 2 * kBinAverage ? 1 : 0;
+    uint32_t before[kEach];
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) before[j] = atomicExch(&table[x[j] * 0x9e3779b1u >> (32 - kTableBits)], x[j]);
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) mine += (uint32_t)__popcll(__ballot(before[j] == x[j]));
+    if (d % 64 == 0) wave_pairs[d / 64] = mine;
+    __syncthreads();
+    int pairs = 0;
+#pragma unroll
+    for (int w = 0; w < kBuckets / 64; ++w) pairs += (int)wave_pairs[w];
+    if (d == 0)
+        crowded[(int64_t)q * crowded_stride] = (int64_t)pairs * n > (int64_t)kSamples * kSamples / 2 * kBinAverage ? 1 : 0;
 }
 
 // Inclusive sum over the lanes of a wavefront: inside rows of 16 by shifts, then a row's last lane
@@ -969,9 +983,9 @@ int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     const int shift = std::max(0, rem - bin_bits(threads));
     // (noted where the partition's list bounds will stand)
     int32_t *crowded = s.seg_out;
-    hipLaunchKernelGGL(pct_bucket_check_kernel, dim3((unsigned)s.P), dim3(kBuckets), 0, st, s.counts,
-                       (const uint32_t *)s.keys_a, s.n, tiles, small ? kBucketCapSmall : kBucketCapLarge, shift, flag, crowded,
-                       s.k + 1);
+    auto check = s.P <= kFineSamples ? pct_bucket_check_kernel<4> : pct_bucket_check_kernel<1>;
+    hipLaunchKernelGGL(check, dim3((unsigned)s.P), dim3(kBuckets), 0, st, s.counts, (const uint32_t *)s.keys_a, s.n, tiles,
+                       small ? kBucketCapSmall : kBucketCapLarge, shift, flag, crowded, s.k + 1);
     if (hipGetLastError() != hipSuccess) return CP_ERR_HIP;
     const Gate fit{flag, 0u};
     const DigitPass<uint32_t, kLeadThreads, kBucketBits> lead_if_fit{s, st, rem, fit};

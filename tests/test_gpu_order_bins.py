@@ -61,12 +61,13 @@ def test_lists_by_bins(gpu, oracle, n, kind, k, top):
     g.close()
 
 
-@pytest.mark.parametrize("P", [32, 65, 128, 257])
-def test_left_buckets_among_others(gpu, oracle, P):
-    """Two, four, eight and sixteen neighbouring buckets per workgroup: crowded partitions between spread ones, empty digits (9 of
+@pytest.mark.parametrize("n,P", [(65_537, 17), (65_537, 32), (65_537, 65), (65_537, 128), (65_537, 257), (262_145, 17),
+                                 (524_801, 20)])
+def test_left_buckets_among_others(gpu, oracle, n, P):
+    """One to sixteen buckets per workgroup of the ranking, one to four of the bins, which have 128, 256 or 512 threads: crowded partitions between spread ones, empty digits (9 of
     16 devices) and, in one partition, full buckets beside nearly empty ones."""
     import torch
-    n, k, top = 65_537, 9, 3_000_000
+    k, top = 9, 3_000_000
     rng = np.random.default_rng(P)
     n, level, src, dst = random_layered_dag(rng, [n // 2, n - n // 2], 1, 1, 1)
     w = T._custom("left", n, src, dst, np.ones(len(src), dtype=np.int64), np.ones(n, dtype=np.int64), [1] * k,
