@@ -796,6 +796,37 @@ __global__ __launch_bounds__(kThreads) void pct_whole_sort_kernel(const uint32_t
     sort_bucket<kThreads, kRounds, true>(keys_in + at, nullptr, vals_out + at, n, bits, slot, (uint32_t (*)[256])counters, threadIdx.x);
 }
 
+// Both in one launch, a bucket per workgroup, for at most kBothMost partitions: their calls are a row of launches of a few
+// microseconds, and a second one for what the bins leave would cost them as much as the bins save.  Beyond, the bins want
+// smaller workgroups than the ranking has registers and LDS for.  250,000 vertices, in one launch and in two: 8 partitions,
+// spread keys 78 and 80 us, 300 values of b 98 and 103 (103 and 95 before there were bins); 32 partitions 143 and 137, 197
+// and 210 (235 and 196); 64 partitions 245 and 214, 344 and 324.
+constexpr int32_t kBothMost = 16;
+template <int kThreads>
+__global__ __launch_bounds__(kThreads, 6) void pct_bucket_kernel(const uint32_t *__restrict__ keys_in,
+                                                              const int32_t *__restrict__ vals_in,
+                                                              int32_t *__restrict__ vals_out, int32_t n, int32_t tiles, int bits,
+                                                              int val_bits, const uint32_t *__restrict__ starts, Gate gate,
+                                                              const int32_t *__restrict__ crowded, int32_t crowded_stride) {
+    // sorted words and bins, or the ranking's slots
+    __shared__ __align__(16) uint32_t slot[kThreads * kSortRounds], counters[kThreads / 64][256], wave_sum[kThreads / 64];
+    static_assert(kSortRounds == kBinRounds + 8, "eight bins per thread behind the sorted words");
+    const uint32_t q = blockIdx.x / kBuckets, d = (blockIdx.x + q) % kBuckets;    // (turned, as in pct_bucket_bins_kernel)
+    const uint32_t *at_bucket = starts + ((int64_t)q * kBuckets + d) * tiles;
+    const uint32_t lo = at_bucket[0], hi = d + 1 == kBuckets ? (uint32_t)n : at_bucket[tiles];
+    const bool bins = crowded[(int64_t)q * crowded_stride] == 0;
+    if (gate.closed()) return;
+    const int32_t items = (int32_t)(hi - lo);
+    if (items <= 0 || items > kThreads * kSortRounds) return;                      // (more: the flag is up)
+    const int64_t at = (int64_t)q * n + lo;
+    if (bins && items <= kThreads * kBinRounds &&
+        sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, val_bits, slot,
+                                                   slot + kThreads * kBinRounds, wave_sum))
+        return;
+    sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters,
+                                              threadIdx.x);
+}
+
 // The buckets that pct_bucket_bins_kernel left, out of the `each` that a workgroup looks at (left_over_bucket).
 // (Six wavefronts a SIMD, and the thread's number new in every round: else the loop keeps every address that follows from
 // it, 110 registers, or spills some; so 77 and no scratch.)
@@ -979,7 +1010,9 @@ int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     lead.scan();
     // the smaller workgroup (more of them per compute unit) where buckets of twice the average size fit it
     const bool small = 2 * ((int64_t)s.n / kBuckets + 1) <= kBucketCapSmall;
-    const int threads = bucket_threads(s.n, s.k, s.b_bits, rem, s.max_b);
+    const bool both = s.P <= kBothMost;
+    const int for_bins = bucket_threads(s.n, s.k, s.b_bits, rem, s.max_b);
+    const int threads = both ? (small && for_bins <= 256 ? 256 : 512) : for_bins;
     const int shift = std::max(0, rem - bin_bits(threads));
     // (noted where the partition's list bounds will stand)
     int32_t *crowded = s.seg_out;
@@ -1001,6 +1034,16 @@ int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     // (keys of 32 bits: shift is 13, 12 or 11 at most for up to 2^18, 2^19 or 2^20 vertices, less for larger workgroups)
     if (shift + val_bits > 32) return CP_ERR_ARG;
     const int32_t dealt = bins_each(all);
+    if (both) {
+#define CP_BOTH(T)                                                                                                    \
+    hipLaunchKernelGGL(pct_bucket_kernel<T>, dim3((unsigned)all), dim3(T), 0, st, keys, vals, s.order_out, s.n, tiles, rem, \
+                       val_bits, starts, fit, (const int32_t *)crowded, s.k + 1)
+        if (threads == 256) CP_BOTH(256);
+        else CP_BOTH(512);
+#undef CP_BOTH
+        if (hipGetLastError() != hipSuccess) return CP_ERR_HIP;
+        return run_sort<uint32_t, kSortThreadsLong, true>(s, st, Gate{flag, 1u});
+    }
 #define CP_BINS(T)                                                                                                    \
     hipLaunchKernelGGL(pct_bucket_bins_kernel<T>, dim3((unsigned)(all / dealt)), dim3(T), 0, st, keys, vals, s.order_out, s.n, dealt, tiles, \
                        rem, val_bits, starts, fit, (const int32_t *)crowded, s.k + 1, left)
