@@ -524,55 +524,73 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
 // An item costs some 50 instructions plus five for each other item that the fullest bin of its wavefront holds,
 // instead of the 130 per digit that ranking by ballots takes.  (val_bits: of a vertex number; both parts of the word
 // fit 32 bits.)  False, with nothing written, where a bin holds more than kBinMost items or (WHOLE: the items are a
-// partition's vertices in their order) 64 items, spread over the vertices, share their bins as they
-// would with more than kBinAverage items in an average item's bin: keys that repeat, or that differ in
-// their low bits only.
+// partition's vertices in their order, their keys loaded as sort_bucket wants them) one item per thread, out of all parts
+// of the list, shares its bin as it would with more than kBinAverage items in an average item's bin: keys that repeat, or
+// that differ in their low bits only.
 constexpr int bin_bits(int threads) { return threads == 128 ? 10 : threads == 256 ? 11 : threads == 512 ? 12 : 13; }
-// 211,000 vertices, 512 partitions, buckets of 412 items: 1,325 -> 382 us (577 with 64-bit words, and no faster
-// with the next bucket's items loaded ahead): vector issue 58 %, the LDS pipe 40 %.  Whole partitions, the call:
-// 19,800 vertices, 4,096 partitions 1,194 -> 814 us; 5,271 vertices 313 -> 219.  Where one key has some 40
-// items (300 values of b, 16 devices, 211,000 vertices) bins and digits take the same time, and trying costs the call
-// up to 9 % (2.18 -> 2.38 ms).
+// 211,000 vertices, 512 partitions, buckets of 412 items, ranked and by bins: 1,325 -> 361 us.  Whole partitions, the call:
+// 19,000 vertices, 512 partitions 154 -> 83 us; 5,000 vertices, 3,000 partitions 186 -> 96.  Keys that repeat are found out
+// by the sample and pay for it: whole partitions 2 - 3 us, 3 to 8 % of the call; longer ones 0 - 2 us up to 16
+// partitions, 4 to 8 % of a call of 32 to 128, nothing beyond.
 template <int kThreads, int kRounds, bool WHOLE>
 __device__ __forceinline__ bool sort_by_bins(const uint32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
                                              int32_t *__restrict__ vals_out, int32_t items, int bits, int val_bits,
-                                             uint32_t *sorted, uint32_t *bins, uint32_t *wave_sum) {
+                                             uint32_t *sorted, uint32_t *bins, uint32_t *wave_sum,
+                                             uint32_t (&key)[kRounds]) {
     constexpr int kWaves = kThreads / 64;
     static_assert(kThreads * 8 == 1 << bin_bits(kThreads), "eight bins per thread");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int shift = max(0, bits - bin_bits(kThreads));
     const uint32_t below = (1u << shift) - 1, bin_of = (1u << (bits - shift)) - 1;
-    uint32_t key[kRounds], rank[kRounds], bin[kRounds];
+    const int nr = WHOLE ? (items + kThreads - 1) / kThreads : kRounds;
+    auto at = [&](int r) -> int32_t { return WHOLE ? wave * (nr * 64) + r * 64 + lane : r * kThreads + tid; };
+    auto valid = [&](int r) { return (!WHOLE || r < nr) && at(r) < items; };
+    uint32_t rank[kRounds], bin[kRounds];
     int32_t val[kRounds];
-    const bool sampled = WHOLE && items > kThreads;
-    uint32_t sample = 0;
-    if (sampled && wave == 0) sample = keys_in[(uint32_t)lane * (uint32_t)items / 64];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const int32_t t = r * kThreads + tid;
-        if (t < items) {
-            key[r] = keys_in[t];
-            val[r] = WHOLE ? t : vals_in[t];
+        if (WHOLE) {
+            val[r] = at(r);
+        } else if (valid(r)) {
+            key[r] = keys_in[at(r)];
+            val[r] = vals_in[at(r)];
         }
     }
     Counts4 *mine = (Counts4 *)(bins + tid * 8);
     mine[0] = mine[1] = Counts4{};
     __syncthreads();
-    if (sampled) {
-        if (wave == 0) {
-            // pairs in one bin: the sum of the places
-            const uint32_t b = sample >> shift & bin_of;
-            const uint32_t pairs = wave_inclusive_sum(atomicAdd(&bins[b], 1u));
-            bins[b] = 0;
-            if (lane == 63) wave_sum[0] = pairs;
+    int early = -1;                                       // the round whose item has been dealt already
+    if (WHOLE && items > kThreads) {
+        // (a thread of the last wavefronts may have no such item)
+        const int r0 = tid % nr;
+        uint32_t sample = 0, got = 0;
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) sample = r == r0 ? key[r] : sample;
+        if (at(r0) < items) {
+            got = atomicAdd(&bins[sample >> shift & bin_of], 1u);
+            early = r0;
+        }
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) rank[r] = got;
+        // pairs in one bin: the sum of the places
+        const uint32_t pairs = wave_inclusive_sum(got), some = (uint32_t)__popcll(__ballot(early >= 0));
+        if (lane == 63) {
+            wave_sum[wave] = pairs;
+            wave_sum[kWaves + wave] = some;
         }
         __syncthreads();
-        if (wave_sum[0] * (uint32_t)items > 64 * 64 / 2 * kBinAverage) return false;
+        uint64_t all_pairs = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            all_pairs += wave_sum[w];
+            all += wave_sum[kWaves + w];
+        }
+        if (all_pairs * (uint32_t)items > all * all / 2 * kBinAverage) return false;
         __syncthreads();
     }
 #pragma unroll
     for (int r = 0; r < kRounds; ++r)
-        if (r * kThreads + tid < items) rank[r] = atomicAdd(&bins[key[r] >> shift & bin_of], 1u);
+        if (valid(r) && r != early) rank[r] = atomicAdd(&bins[key[r] >> shift & bin_of], 1u);
     __syncthreads();
     Counts4 c[2] = {mine[0], mine[1]};
     uint32_t most = 0, sum = 0;
@@ -607,14 +625,14 @@ __device__ __forceinline__ bool sort_by_bins(const uint32_t *__restrict__ keys_i
     auto word_of = [&](uint32_t k, int32_t v) { return (k & below) << val_bits | (uint32_t)v; };
 #pragma unroll
     for (int r = 0; r < kRounds; ++r)
-        if (r * kThreads + tid < items) {
+        if (valid(r)) {
             bin[r] = bins[key[r] >> shift & bin_of];
             sorted[(bin[r] & 0xffffu) + rank[r]] = word_of(key[r], val[r]);
         }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kRounds; ++r)
-        if (r * kThreads + tid < items) {
+        if (valid(r)) {
             const uint32_t first = bin[r] & 0xffffu, end = first + (bin[r] >> 16);
             const uint32_t x = word_of(key[r], val[r]);
             uint32_t place = first, j = first;
@@ -630,7 +648,7 @@ __device__ __forceinline__ bool sort_by_bins(const uint32_t *__restrict__ keys_i
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kRounds; ++r)
-        if (r * kThreads + tid < items) sorted[rank[r]] = (uint32_t)val[r];
+        if (valid(r)) sorted[rank[r]] = (uint32_t)val[r];
     __syncthreads();
     for (int32_t t = tid; t < items; t += kThreads) vals_out[t] = (int32_t)sorted[t];
     return true;
@@ -651,6 +669,7 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
     __shared__ uint32_t sorted[kThreads * kBinRounds];
     __shared__ __align__(16) uint32_t bins[kThreads * 8];
     __shared__ uint32_t wave_sum[kThreads / 64];
+    uint32_t key[kBinRounds];
     // (turned by one neighbourhood from partition to partition: workgroups go round the eight XCDs, and the digits in use
     // are the same in all partitions; of 9 devices, 19 in every 32: 884 us one by one, so 568)
     const uint32_t per = (uint32_t)(kBuckets / each), q = blockIdx.x / per, d0 = (blockIdx.x + q) % per * (uint32_t)each;
@@ -671,7 +690,7 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
         bool done = items <= 0;
         if (!done && items <= kThreads * kBinRounds)
             done = sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits,
-                                                                   val_bits, sorted, bins, wave_sum);
+                                                                   val_bits, sorted, bins, wave_sum, key);
         if (threadIdx.x == 0) left[i] = done ? 0u : 1u;
     }
 }
@@ -681,13 +700,13 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
 // bucket in (round, lane) order) and moving keys and vertex numbers through one LDS buffer;
 // the vertex numbers of the last pass go straight out.
 // WHOLE: the "bucket" is a whole partition (at most kBucketThreads * kRounds vertices), its keys
-// in vertex order in keys_in, sorted on all `bits` key bits: short partitions need no pass over
+// in vertex order and already in `key`, sorted on all `bits` key bits: short partitions need no pass over
 // HBM at all.
 // slot: kBucketThreads * kRounds words; cnt: 256 per wavefront
 template <int kBucketThreads, int kRounds, bool WHOLE>
 __device__ __forceinline__ void sort_bucket(const uint32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
                                             int32_t *__restrict__ vals_out, int32_t items, int bits, uint32_t *slot,
-                                            uint32_t (*cnt)[256], int tid) {
+                                            uint32_t (*cnt)[256], int tid, uint32_t (&key)[kRounds]) {
     constexpr int kWaves = kBucketThreads / 64, kRadix = 256;
     __shared__ uint32_t wave_sum[kRadix / 64];
     const int lane = tid & 63, wave = tid >> 6;
@@ -695,14 +714,14 @@ __device__ __forceinline__ void sort_bucket(const uint32_t *__restrict__ keys_in
     // [w * nr * 64, (w + 1) * nr * 64) of the bucket)
     const int nr = (items + kBucketThreads - 1) / kBucketThreads;
 
-    uint32_t key[kRounds], loc[kRounds];
+    uint32_t loc[kRounds];
     int32_t val[kRounds];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
         const int32_t t = wave * (nr * 64) + r * 64 + lane;
         const bool valid = r < nr && t < items;
-        key[r] = valid ? keys_in[t] : 0u;
-        val[r] = WHOLE ? t : (valid ? vals_in[t] : 0);       // WHOLE: the keys come in vertex order
+        if (!WHOLE) key[r] = valid ? keys_in[t] : 0u;
+        val[r] = WHOLE ? t : (valid ? vals_in[t] : 0);
     }
     for (int shift = 0; shift < bits; shift += 8) {
         const bool last = shift + 8 >= bits;
@@ -780,20 +799,41 @@ __device__ __forceinline__ void sort_bucket(const uint32_t *__restrict__ keys_in
     }
 }
 
-// A whole partition per workgroup: by bins (BINS: the words fit 32 bits), else by digits.
+// A whole partition per workgroup: by bins (BINS: the words fit 32 bits), else by digits.  (80 registers are six
+// wavefronts a SIMD: with 89 a unit had two workgroups of 512 threads instead of three.)
 template <int kThreads, int kRounds, bool BINS>
-__global__ __launch_bounds__(kThreads) void pct_whole_sort_kernel(const uint32_t *__restrict__ keys_in,
+__global__ __launch_bounds__(kThreads, kThreads == 1024 ? 4 : 6) void pct_whole_sort_kernel(const uint32_t *__restrict__ keys_in,
                                                                   int32_t *__restrict__ vals_out, int32_t n, int bits,
                                                                   int val_bits) {
     extern __shared__ __align__(16) uint32_t slot[];
     __shared__ __align__(16) uint32_t counters[kThreads * (BINS ? 8 : 4)];
-    __shared__ uint32_t wave_sum[kThreads / 64];
+    __shared__ uint32_t wave_sum[2 * (kThreads / 64)];
     const int64_t at = (int64_t)blockIdx.x * n;
-    if constexpr (BINS)
-        if (sort_by_bins<kThreads, kRounds, true>(keys_in + at, nullptr, vals_out + at, n, bits, val_bits, slot,
-                                                            counters, wave_sum))
+    const int nr = (n + kThreads - 1) / kThreads;
+    uint32_t key[kRounds];
+    const uint32_t *mine = keys_in + at;
+    int tid = threadIdx.x;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {                   // (as sort_bucket deals them out)
+        const int32_t t = (threadIdx.x >> 6) * (nr * 64) + r * 64 + (threadIdx.x & 63);
+        key[r] = r < nr && t < n ? mine[t] : 0u;
+    }
+    if constexpr (BINS) {
+        if (sort_by_bins<kThreads, kRounds, true>(nullptr, nullptr, vals_out + at, n, bits, val_bits, slot, counters,
+                                                   wave_sum, key))
             return;
-    sort_bucket<kThreads, kRounds, true>(keys_in + at, nullptr, vals_out + at, n, bits, slot, (uint32_t (*)[256])counters, threadIdx.x);
+        if (kThreads == 512) {   // (again: kept through the bins they would cost spills, or a workgroup per compute unit)
+            asm("" : "+v"(tid), "+s"(mine));
+            __builtin_assume(tid >= 0 && tid < kThreads);
+#pragma unroll
+            for (int r = 0; r < kRounds; ++r) {
+                const int32_t t = (tid >> 6) * (nr * 64) + r * 64 + (tid & 63);
+                key[r] = r < nr && t < n ? mine[t] : 0u;
+            }
+        }
+    }
+    sort_bucket<kThreads, kRounds, true>(nullptr, nullptr, vals_out + at, n, bits, slot, (uint32_t (*)[256])counters, tid,
+                                         key);
 }
 
 // Both in one launch, a bucket per workgroup, for at most kBothMost partitions: their calls are a row of launches of a few
@@ -816,15 +856,16 @@ __global__ __launch_bounds__(kThreads, 6) void pct_bucket_kernel(const uint32_t 
     const uint32_t lo = at_bucket[0], hi = d + 1 == kBuckets ? (uint32_t)n : at_bucket[tiles];
     const bool bins = crowded[(int64_t)q * crowded_stride] == 0;
     if (gate.closed()) return;
+    uint32_t few[kBinRounds], key[kSortRounds];
     const int32_t items = (int32_t)(hi - lo);
     if (items <= 0 || items > kThreads * kSortRounds) return;                      // (more: the flag is up)
     const int64_t at = (int64_t)q * n + lo;
     if (bins && items <= kThreads * kBinRounds &&
         sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, val_bits, slot,
-                                                   slot + kThreads * kBinRounds, wave_sum))
+                                                   slot + kThreads * kBinRounds, wave_sum, few))
         return;
     sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters,
-                                              threadIdx.x);
+                                              threadIdx.x, key);
 }
 
 // The buckets that pct_bucket_bins_kernel left, out of the `each` that a workgroup looks at (left_over_bucket).
@@ -859,7 +900,9 @@ __global__ __launch_bounds__(kThreads, 6) void pct_bucket_sort_kernel(const uint
         const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)lo, which);
         const int32_t items = (int32_t)((uint32_t)__builtin_amdgcn_readlane((int)hi, which) - first);
         const int64_t at = (int64_t)q * n + first;
-        sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters, tid);
+        uint32_t key[kSortRounds];
+        sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters, tid,
+                                                  key);
         __syncthreads();
     }
 }
