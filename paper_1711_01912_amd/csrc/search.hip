@@ -520,8 +520,8 @@ __global__ __launch_bounds__(64) void seed_greedy_kernel(SeedArgs a) {
 // lowest one wins a tie; every row of 16 lanes holds all devices, PER of them a lane (device r * 16 + lane).  A vertex
 // is an addition, four register permutations, a comparison and a selection.  Three wavefronts beside it read c and the
 // vertices still to be placed 64 at a time, two batches ahead, put the execution times of every device into
-// LDS and write the devices chosen a batch ago.  Loads leave the keys (64 bits, and return when they can) where
-// eight vertices might take them past 32 - BITS bits.
+// LDS and write the devices chosen a batch ago.  Where a batch might take a load past 32 - BITS bits above the lowest, its
+// loads are 32 bits relative to that without a device number, and past 32 bits they are 64; ties are then told by ballots.
 // Bound by the chain and by what one wavefront issues, six to eight cycles an instruction and two wait states before
 // each permutation: 211,000 vertices on 16 devices 0.056 -> 0.038 us each, a tenth of it between the batches.  (A branch
 // of any kind between two vertices costs as much as half a vertex.  Two vertices at a time, the second one's choice
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(256) void seed_keys_kernel(SeedArgs a) {
         const int d = lane & 15;
         long long load[PER], base = 0;
         uint32_t key[PER], bound = 0;        // bound: no key's load is larger
-        bool wide = true;
+        enum { kKeys, kLoads32, kLoads64 } form = kLoads64;
         {
             // the critical path is placed first: its execution times on the fastest device
             const Magic mf = a.mg[a.fastest];
@@ -562,12 +562,72 @@ __global__ __launch_bounds__(256) void seed_keys_kernel(SeedArgs a) {
         }
         auto here = [&](int r) { return r * 16 + d < a.k; };
         auto id = [&](int r) { return (uint32_t)(r * 16 + d); };
-        auto to_loads = [&]() {
-#pragma unroll
-            for (int r = 0; r < PER; ++r) load[r] = base + (long long)(key[r] >> BITS);
-            wide = true;
+        auto min_of_row = [&](uint32_t best) {
+            best = min(best, dpp_row<0xB1>(best));
+            best = min(best, dpp_row<0x4E>(best));
+            best = min(best, dpp_row<0x141>(best));
+            return min(best, dpp_row<0x140>(best));
         };
-        auto to_keys = [&](uint32_t more) {  // where `more` on top of the largest load still fits
+        // the lowest device for which `hit` is true (of one row: all rows are alike)
+        auto lowest = [&](auto hit) {
+            if constexpr (PER <= 2) {
+                uint32_t hits = (uint32_t)__ballot(hit(0)) & 0xffffu;
+                if (PER == 2) hits |= (uint32_t)__ballot(hit(PER - 1)) << 16;
+                return (uint32_t)(__ffs((int)hits) - 1);
+            } else {
+                unsigned long long hits = 0;
+#pragma unroll
+                for (int r = 0; r < PER; ++r) hits |= (unsigned long long)((uint32_t)__ballot(hit(r)) & 0xffffu) << (16 * r);
+                return (uint32_t)(__ffsll((long long)hits) - 1);
+            }
+        };
+        // One vertex: its execution times to its device.  In keys: the winner's key.
+        auto place_keys = [&](const uint32_t (&w)[PER]) {
+            uint32_t val[PER], best = 0;
+#pragma unroll
+            for (int r = 0; r < PER; ++r) {
+                val[r] = (w[r] << BITS) + key[r];
+                best = r ? min(best, val[r]) : val[r];
+            }
+            best = min_of_row(best);
+#pragma unroll
+            for (int r = 0; r < PER; ++r) key[r] = val[r] == best ? val[r] : key[r];
+            return best;
+        };
+        auto place_32 = [&](const uint32_t (&w)[PER]) {
+            uint32_t val[PER], best = 0;
+#pragma unroll
+            for (int r = 0; r < PER; ++r) {
+                val[r] = w[r] + key[r];
+                best = r ? min(best, val[r]) : val[r];
+            }
+            best = min_of_row(best);
+            const uint32_t got = lowest([&](int r) { return val[r] == best; });
+#pragma unroll
+            for (int r = 0; r < PER; ++r) key[r] = id(r) == got ? best : key[r];
+            return got;
+        };
+        auto place_64 = [&](const uint32_t (&w)[PER]) {
+            long long val[PER], best = LLONG_MAX;
+#pragma unroll
+            for (int r = 0; r < PER; ++r) {
+                val[r] = here(r) ? load[r] + (long long)w[r] : LLONG_MAX;
+                best = val[r] < best ? val[r] : best;
+            }
+            best = lane0_i64(min_over_lanes(best, 16));
+            const uint32_t got = lowest([&](int r) { return val[r] == best; });
+#pragma unroll
+            for (int r = 0; r < PER; ++r) load[r] = id(r) == got ? best : load[r];
+            return got;
+        };
+        // loads of 64 bits, and from them the shortest form in which a load can grow by `room`
+        auto choose_form = [&](unsigned long long room) {
+#pragma unroll
+            for (int r = 0; r < PER; ++r)
+                load[r] = form == kKeys ? base + (long long)(key[r] >> BITS)
+                                        : form == kLoads32 ? base + (long long)key[r] : load[r];
+            form = kLoads64;
+            if (room >= 0xffffffffull) return;
             long long low = LLONG_MAX, high = LLONG_MAX;
 #pragma unroll
             for (int r = 0; r < PER; ++r) {
@@ -576,104 +636,75 @@ __global__ __launch_bounds__(256) void seed_keys_kernel(SeedArgs a) {
             }
             low = lane0_i64(min_over_lanes(low, 16));
             high = -lane0_i64(min_over_lanes(high, 16));
-            if ((unsigned long long)(high - low) + more >= kLimit) return;
+            const unsigned long long most = (unsigned long long)(high - low) + room;
+            if (most >= 0xffffffffull) return;
+            form = most < kLimit ? kKeys : kLoads32;
 #pragma unroll
-            for (int r = 0; r < PER; ++r)
-                key[r] = here(r) ? (uint32_t)(load[r] - low) << BITS | id(r) : 0xffffffffu;
+            for (int r = 0; r < PER; ++r) {
+                const uint32_t rel = (uint32_t)(load[r] - low);
+                key[r] = !here(r) ? 0xffffffffu : form == kKeys ? rel << BITS | id(r) : rel;
+            }
             base = low;
             bound = (uint32_t)(high - low);
-            wide = false;
         };
         lds_only_barrier();                  // the first batch is there
         for (int32_t b = 0; b <= batches; ++b) {
-            const int cnt = b < batches ? __popcll(open_of[b & 3]) : 0;
-            // (eight times the largest c, or a number no key has room for)
-            const uint32_t cmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)cmax_of[b & 3]);
-            const uint32_t more = cmax < kLimit / 8 ? 8 * cmax : kLimit;
             const uint32_t *row = &times[(b & 1) * kBatch][d * PER];
-            uint32_t chosen = 0, packed[2];
-            // the winner's key
-            auto place = [&](const uint32_t (&w)[PER]) {
-                uint32_t val[PER], best;
+            uint32_t w[2][8][PER], chosen = 0;
+            auto ask = [&](int at, uint32_t (&to)[8][PER]) {
 #pragma unroll
-                for (int r = 0; r < PER; ++r) {
-                    val[r] = (w[r] << BITS) + key[r];
-                    best = r ? min(best, val[r]) : val[r];
-                }
-                best = min(best, dpp_row<0xB1>(best));
-                best = min(best, dpp_row<0x4E>(best));
-                best = min(best, dpp_row<0x141>(best));
-                best = min(best, dpp_row<0x140>(best));
+                for (int i = 0; i < 8; ++i)
 #pragma unroll
-                for (int r = 0; r < PER; ++r) key[r] = val[r] == best ? val[r] : key[r];
-                return best;
+                    for (int r = 0; r < PER; ++r) to[i][r] = row[(at + i) * kCols + r];
             };
-            auto note = [&](int j) { chosen = lane == j / 4 ? packed[0] : lane == j / 4 + 1 ? packed[1] : chosen; };
-            int j = 0;
-            if (!wide && (unsigned long long)bound + 8ull * more < kLimit) {
-                // the whole batch fits the keys: eight vertices after the other without a test between them
-                // (all reads of eight times at once: a wait for each would be an instruction for each)
-                uint32_t w[2][8][PER];
-                auto ask = [&](int at, uint32_t (&to)[8][PER]) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-#pragma unroll
-                        for (int r = 0; r < PER; ++r) to[i][r] = row[(at + i) * kCols + r];
+            ask(0, w[0]);
+            const int cnt = b < batches ? __popcll(open_of[b & 3]) : 0;
+            const unsigned long long room =
+                (unsigned long long)kBatch * (uint32_t)__builtin_amdgcn_readfirstlane((int)cmax_of[b & 3]);
+            // (a shorter form is looked for once a batch, where its numbers could hold the batch at all)
+            const bool stays = form == kKeys ? bound + room < kLimit
+                               : form == kLoads32 ? room >= kLimit && bound + room < 0xffffffffull : room >= 0xffffffffull;
+            if (cnt > 0 && !stays) choose_form(room);
+            if (form != kLoads64) bound += cnt > 0 ? (uint32_t)room : 0u;
+            // eight vertices after the other without a test between them, all their reads at once (a wait for each would
+            // be an instruction for each), then those that are left
+            auto place_all = [&](auto place) {
+                uint32_t packed[2] = {0, 0};
+                int j = 0;
+                auto note = [&]() {
+                    chosen = lane == j / 4 ? packed[0] : chosen;
+                    chosen = lane == j / 4 + 1 ? packed[1] : chosen;
+                    j += 8;
                 };
                 auto eight = [&](const uint32_t (&w)[8][PER]) {
 #pragma unroll
                     for (int i = 0; i < 8; ++i) packed[i / 4] = __builtin_amdgcn_alignbit(place(w[i]), packed[i / 4], 8);
-                    note(j);
-                    j += 8;
+                    note();
                 };
-                ask(0, w[0]);
                 while (j + 16 <= cnt) {
                     ask(j + 8, w[1]);
                     eight(w[0]);
                     ask(j + 8, w[0]);
                     eight(w[1]);
                 }
-                if (j + 8 <= cnt) eight(w[0]);
-                bound += 8 * more;
-            }
-            for (; j < cnt; j += 8) {
-                uint32_t w[8][PER];
+                if (j + 8 <= cnt) {
+                    ask(j + 8, w[1]);
+                    eight(w[0]);
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
+                    for (int i = 0; i < 8; ++i)
 #pragma unroll
-                    for (int r = 0; r < PER; ++r) w[i][r] = row[(j + i) * kCols + r];
-                const int some = min(8, cnt - j);
-                if (!wide && bound >= kLimit - more) to_loads();
-                if (wide) to_keys(more);
-                packed[0] = packed[1] = 0;
-                if (!wide) bound += more;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    uint32_t got = 0;
-                    if (i < some && !wide) {
-                        got = place(w[i]);
-                    } else if (i < some) {
-                        long long best = LLONG_MAX;
-#pragma unroll
-                        for (int r = 0; r < PER; ++r)
-                            if (here(r) && load[r] + (long long)w[i][r] < best) best = load[r] + (long long)w[i][r];
-                        best = lane0_i64(min_over_lanes(best, 16));
-                        bool found = false;
-#pragma unroll
-                        for (int r = 0; r < PER; ++r) {
-                            const uint32_t hit =
-                                (uint32_t)__ballot(here(r) && load[r] + (long long)w[i][r] == best) & 0xffffu;
-                            if (!found && hit) {
-                                got = (uint32_t)(r * 16 + __ffs((int)hit) - 1);
-                                found = true;
-                                if (id(r) == got) load[r] = best;
-                            }
-                        }
-                    }
-                    packed[i / 4] = __builtin_amdgcn_alignbit(got, packed[i / 4], 8);
+                        for (int r = 0; r < PER; ++r) w[0][i][r] = w[1][i][r];
                 }
-                note(j);
-            }
+                if (j < cnt) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        packed[i / 4] = __builtin_amdgcn_alignbit(j + i < cnt ? place(w[0][i]) : 0u, packed[i / 4], 8);
+                    note();
+                }
+            };
+            if (form == kKeys) place_all(place_keys);
+            else if (form == kLoads32) place_all(place_32);
+            else place_all(place_64);
             if (lane < 16) chosen_of[b & 1][lane] = chosen;
             lds_only_barrier();
         }
