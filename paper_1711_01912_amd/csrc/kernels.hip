@@ -554,8 +554,11 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_kernel(PathArgs a)
 // The walk with one round of loads per path vertex instead of two.  path_records_kernel lays out, once a call, what the
 // walk reads of a vertex as one 64-byte record: c, the number of its out-edges, and up to seven of them as (head, t).  A
 // step asks for the candidates' b and devices and for the candidates' records together; the winner's record then names
-// the next candidates.  (Before, the winner's edges were asked for only when it had won.)  Vertices
-// of more than seven edges take the edges out of the CSR and their winner's record in a round of its own.
+// the next candidates.  (Before, the winner's edges were asked for only when it had won.)  The record of a vertex of more
+// than seven edges names its first one instead; its step takes the edges out of the CSR, and beside the candidates' b and
+// devices their c and row bounds, so that a winner of many edges again needs no record, and no such step more rounds
+// than over the CSR (120,000 vertices of up to 40 edges in 400 levels, 777 partitions: 639 us with the winner's record
+// and row bounds in rounds of their own, so 545; where rows are that long on average the CSR is taken, 511).
 // Bound by the latency of that one round, b and the device ids from HBM or the last cache, 0.9 us a path vertex: 777
 // partitions, 121,000 vertices in 701 levels (paths of 329): 448 -> 306 us and 10 for the records; 300 partitions,
 // 240,000 vertices in 2,000 levels (1,027): 1,045 -> 764 and 16.
@@ -570,6 +573,7 @@ __global__ __launch_bounds__(256) void path_records_kernel(PathArgs a, int32_t n
     uint32_t x = 0;                       // (an edge that is not there names vertex 0: its loads are in range)
     if (w == 0) x = ((const uint32_t *)a.c)[v];
     else if (w == 1) x = (uint32_t)(e1 - e0);
+    else if (e1 - e0 > kRecordEdges) x = w == 2 ? (uint32_t)e0 : 0;
     else if (e < e1) x = (w & 1) ? ((const uint32_t *)a.wt)[e] : (uint32_t)a.idx[e];
     records[i] = x;
 }
@@ -584,7 +588,7 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_records_kernel(Pat
     const Tick *b = (const Tick *)a.b + (int64_t)q * a.b_sq;
     const uint32_t asv = a.a_stride_v, bsv = a.b_sv;
     const uint8_t *row = a.assign + (int64_t)q * a.a_stride_p;
-    const uint32_t *wt = (const uint32_t *)a.wt;
+    const uint32_t *wt = (const uint32_t *)a.wt, *c = (const uint32_t *)a.c;
     const uint64_t *ge = (const uint64_t *)a.edge_tab, *gv = (const uint64_t *)a.vert_tab;
     for (int i = tid; i < k * k; i += nt) path_lds[i] = ge[i];
     for (int i = tid; i < k; i += nt) path_lds[k * k + i] = gv[i];
@@ -610,14 +614,20 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_records_kernel(Pat
         bv = b[(uint64_t)(uint32_t)v * bsv];
         rec = load_record((uint32_t)v);
     }
+    uint32_t cv = 0;                         // the current vertex's c, out-edges and, of more than a record's, the first one
+    int32_t deg = 0, first = 0;
+    auto read_record = [&]() {
+        cv = (uint32_t)__builtin_amdgcn_readlane((int)rec, base);
+        deg = __builtin_amdgcn_readlane((int)rec, base + 1);
+        first = __builtin_amdgcn_readlane((int)rec, base + 2);
+    };
+    read_record();
     bool bad_id = false;
     int32_t len = 0, step = 0;
     while (v != 0x7fffffff && len < a.max_len) {
         step = lane == (len & 63) ? v : step;            // (a store per vertex is waited for with the loads behind it)
         if ((len & 63) == 63) path[len - 63 + lane] = step;
         ++len;
-        const uint32_t cv = (uint32_t)__builtin_amdgcn_readlane((int)rec, base);
-        const int32_t deg = __builtin_amdgcn_readlane((int)rec, base + 1);
         if (pv >= (uint32_t)k) { bad_id = true; pv = 0; }
         const Magic *costs = etab + pv * k;
         auto fits = [&](uint32_t p_raw, uint32_t te, Tick bu, Tick rest) {
@@ -645,15 +655,23 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_records_kernel(Pat
                 bv = wave_bcast<Tick>(n_b, won);
                 rec = won < 4 ? rec0 : rec1;
                 base = 16 * (won & 3);
+                read_record();
             }
         } else {
             const Tick rest = bv - (Tick)magic_div(cv, vtab[pv]);
-            const int32_t e0 = a.ptr[v];
-            for (int32_t e = e0 + lane; e < e0 + deg; e += 64) {
+            uint32_t n_c = 0;
+            int32_t n_first = 0, n_deg = 0;
+            for (int32_t e = first + lane; e < first + deg; e += 64) {
                 const uint32_t u = (uint32_t)a.idx[e];
-                const uint32_t pu = row[(uint64_t)(uint32_t)u * asv];
-                const Tick bu = b[(uint64_t)(uint32_t)u * bsv];
-                if (fits(pu, wt[e], bu, rest) && u < next) { next = u; n_p = pu; n_b = bu; }
+                const uint32_t te = wt[e];
+                const uint32_t pu = row[(uint64_t)u * asv];
+                const Tick bu = b[(uint64_t)u * bsv];
+                const uint32_t cu = c[u];
+                const int32_t u0 = a.ptr[u], u1 = a.ptr[u + 1];
+                if (fits(pu, te, bu, rest) && u < next) {
+                    next = u; n_p = pu; n_b = bu;
+                    n_c = cu; n_first = u0; n_deg = u1 - u0;
+                }
             }
             const uint32_t best = min_over_wave(next);
             v = (int32_t)best;
@@ -661,8 +679,13 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_records_kernel(Pat
                 const int won = __ffsll((long long)__ballot(next == best)) - 1;
                 pv = wave_bcast<uint32_t>(n_p, won);
                 bv = wave_bcast<Tick>(n_b, won);
-                rec = load_record(best);
-                base = 0;
+                cv = wave_bcast<uint32_t>(n_c, won);
+                first = wave_bcast<int32_t>(n_first, won);
+                deg = wave_bcast<int32_t>(n_deg, won);
+                if (deg <= kRecordEdges) {
+                    rec = load_record(best);
+                    base = 0;
+                }
             }
         }
     }
@@ -1771,7 +1794,7 @@ int launch_critical_path(const SweepLaunch &s, const int32_t *sources, int32_t n
     const size_t lds = lds_tab ? ((size_t)s.k * s.k + s.k) * 8 : 0;
     // one wavefront where that many sources leave the others nothing to do
     const dim3 grid((unsigned)s.P), block((unsigned)(nsrc > 512 ? kPathThreads : 64));
-    if (records && s.magic && lds_tab && path_by_records(s.n, s.L)) {
+    if (records && s.magic && lds_tab && path_by_records(s.n, s.m, s.L)) {
         const dim3 words((unsigned)(((int64_t)s.n * kPathRecordWords + 255) / 256));
         hipLaunchKernelGGL(path_records_kernel, words, dim3(256), 0, st, a, s.n, records);
         if (s.tick_bytes == 4)

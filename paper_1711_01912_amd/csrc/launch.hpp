@@ -17,6 +17,7 @@ struct SweepLaunch {
     bool narrow = false;                // 32-bit weights in the blob
     int tick_bytes = 4;
     int32_t n = 0, P = 0, k = 0, L = 0, max_width = 0;
+    int64_t m = 0;                      // critical-path walk only
     const uint8_t *pT = nullptr;        // [n][P] device ids (wave-column)
     const uint8_t *assign = nullptr;    // caller's assignments (resident-window: input of the gather)
     const uint8_t *pperm = nullptr;     // [P][ticks*wpad] device ids in sweep order (resident-window)
@@ -284,8 +285,9 @@ inline size_t path_jump_words(int32_t n) { return 3 * ((size_t)n + 1); }
 inline bool path_by_jumps(int32_t n, int32_t P, int32_t L) { return P == 1 && L >= 128 && n / L < 4096; }
 // Records are one more launch, which reads the graph and writes 64 bytes a vertex (5 us at 60,000 vertices, 16 at 240,000),
 // and save a tenth to a half of a microsecond per path vertex.  Without and with: 195 levels of 65 vertices 107 and
-// 105 us, 256 of 900 163 and 114, 300 of 300 131 and 98, 1,000 of 60 406 and 304.
-inline bool path_by_records(int32_t n, int32_t L) { return L >= 256 && n / L < 1024; }
+// 105 us, 256 of 900 163 and 114, 300 of 300 131 and 98, 1,000 of 60 406 and 304.  Not where most rows are longer than
+// a record: 400 levels of 300 vertices with 20 edges each, 24 partitions, 225 and 341 us.
+inline bool path_by_records(int32_t n, int64_t m, int32_t L) { return L >= 256 && n / L < 1024 && m / n <= 5; }
 // cp_critical_path with scratch for the jumps or null; with it, what lies behind the path in path_out stays as it was.
 int critical_path(const cp_graph *g, int32_t batch, int32_t k, const uint8_t *assignments, int assign_layout,
                   const int64_t *speeds, const int64_t *bandwidth, const void *blevel, const int64_t *cp,

@@ -1,4 +1,5 @@
-"""cp_critical_path's two walks, over records (256 levels and more, room in the workspace) and over the CSR: path lengths
+"""cp_critical_path's two walks, over records (256 levels and more, five edges a vertex at most, room in the workspace) and
+over the CSR: path lengths
 around the 64 vertices that are stored together, out-degrees around the seven edges of a record, both tick widths and
 layouts, weights without multiply-shift constants."""
 import numpy as np
@@ -70,6 +71,24 @@ def test_degrees(gpu, oracle, degree):
     level[2 * len(at) * width] = 2 * len(at)
     w = T._custom("degrees", n, src[order], dst[order], rng.integers(0, 4, len(src)), rng.integers(0, 3, n), [1, 2, 5],
                   rng.integers(1, 4, (3, 3)), rng.integers(0, 3, (7, n), dtype=np.uint8), level)
+    _check(gpu, oracle, w)
+
+
+@pytest.mark.parametrize("rich", [(8, 12), (7, 9), (60, 70), (1, 100)])
+def test_long_rows_after_each_other(gpu, oracle, rich):
+    """Paths through rows of more than a record's seven edges: one after the other, before and after short rows."""
+    rng = np.random.default_rng(rich[0])
+    levels, width = 270, 120
+    n = levels * width
+    deg = np.where(np.arange(n) % width < 4, rng.integers(rich[0], rich[1] + 1, n), rng.integers(0, 3, n))
+    deg[-width:] = 0
+    src = np.repeat(np.arange(n), deg)
+    # half of the edges go to the four rich vertices of the next level
+    dst = (src // width + 1) * width + np.where(rng.random(len(src)) < 0.5, rng.integers(0, 4, len(src)),
+                                                rng.integers(0, width, len(src)))
+    w = T._custom("rich", n, src, dst, rng.integers(0, 40, len(src)), rng.integers(0, 30, n), [1, 2, 3],
+                  rng.integers(1, 4, (3, 3)), rng.integers(0, 3, (9, n), dtype=np.uint8), np.arange(n) // width)
+    assert len(src) <= 5 * n
     _check(gpu, oracle, w)
 
 
