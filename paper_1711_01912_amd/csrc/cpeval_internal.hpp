@@ -141,6 +141,7 @@ struct Packed {
     int32_t lane_word = 4;      // bytes of a ring word of the lane-window plan
     LaneDir lane_b, lane_t;
     int32_t max_width = 0;
+    int32_t hops = 0;           // L times the mean of 1 / (levels an edge climbs)
     std::vector<uint8_t> blob;  // host image of the device blob
 };
 

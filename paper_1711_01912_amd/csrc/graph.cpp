@@ -634,8 +634,13 @@ int pack_graph(int32_t n, int64_t m, int32_t L,
             level[v] = l;
         }
     }
-    for (int64_t e = 0; e < m; ++e)
-        if (level[edge_src[e]] >= level[succ_idx[e]]) return CP_ERR_LEVELS;
+    double per_level = 0;
+    for (int64_t e = 0; e < m; ++e) {
+        const int32_t climbs = level[succ_idx[e]] - level[edge_src[e]];
+        if (climbs <= 0) return CP_ERR_LEVELS;
+        per_level += 1.0 / climbs;
+    }
+    out.hops = m > 0 ? (int32_t)(L * (per_level / (double)m)) : 0;
 
     int64_t max_c = 0, max_t = 0;
     for (int32_t v = 0; v < n; ++v) {

@@ -1775,7 +1775,7 @@ int launch_critical_path(const SweepLaunch &s, const int32_t *sources, int32_t n
     a.status = s.status;
     a.P = s.P; a.k = s.k; a.max_len = max_len;
     hipStream_t st = (hipStream_t)stream;
-    if (jumps && path_by_jumps(s.n, s.P, s.L)) {
+    if (jumps && path_by_jumps(s.n, s.P, s.L, s.hops)) {
         int32_t *next = jumps, *two = next + s.n + 1, *four = two + s.n + 1;
         const dim3 vertices((unsigned)((s.n + 256) / 256));          // (and the entry n)
 #define CP_PATH(TICK, WT, MAGIC)                                                                              \
@@ -1794,7 +1794,7 @@ int launch_critical_path(const SweepLaunch &s, const int32_t *sources, int32_t n
     const size_t lds = lds_tab ? ((size_t)s.k * s.k + s.k) * 8 : 0;
     // one wavefront where that many sources leave the others nothing to do
     const dim3 grid((unsigned)s.P), block((unsigned)(nsrc > 512 ? kPathThreads : 64));
-    if (records && s.magic && lds_tab && path_by_records(s.n, s.m, s.L)) {
+    if (records && s.magic && lds_tab && path_by_records(s.n, s.m, s.L, s.hops)) {
         const dim3 words((unsigned)(((int64_t)s.n * kPathRecordWords + 255) / 256));
         hipLaunchKernelGGL(path_records_kernel, words, dim3(256), 0, st, a, s.n, records);
         if (s.tick_bytes == 4)

@@ -17,7 +17,8 @@ struct SweepLaunch {
     bool narrow = false;                // 32-bit weights in the blob
     int tick_bytes = 4;
     int32_t n = 0, P = 0, k = 0, L = 0, max_width = 0;
-    int64_t m = 0;                      // critical-path walk only
+    int64_t m = 0;                      // critical-path walk only, and Packed::hops
+    int32_t hops = 0;
     const uint8_t *pT = nullptr;        // [n][P] device ids (wave-column)
     const uint8_t *assign = nullptr;    // caller's assignments (resident-window: input of the gather)
     const uint8_t *pperm = nullptr;     // [P][ticks*wpad] device ids in sweep order (resident-window)
@@ -279,15 +280,23 @@ int launch_critical_path(const SweepLaunch &s, const int32_t *sources, int32_t n
                          int32_t max_len, int32_t *path, int32_t *len, int32_t *jumps, uint32_t *records,
                          void *stream);
 inline size_t path_jump_words(int32_t n) { return 3 * ((size_t)n + 1); }
+// Both rules ask for levels and for hops: a critical path has about as many vertices as L over the levels that its edges
+// climb, and it takes the short ones (measured: 13 to 25 vertices for 5 to 29 hops, 323 for 288, 749 for 587).  A path of
+// some 20 vertices through 300 levels is walked before the records are written.
 // The jumps are four more launches and read the whole graph once (45 us a million vertices) where the walk pays
-// its round trips, 1 us, per path vertex: many levels, and not too many vertices to one.  Walked and by jumps: 128
-// levels of 300 vertices 42 and 26 us, of 4,000 90 and 63, 300 of 3,000 190 and 93.
-inline bool path_by_jumps(int32_t n, int32_t P, int32_t L) { return P == 1 && L >= 128 && n / L < 4096; }
+// its round trips, half a microsecond to one, per path vertex: many levels, and not too many vertices to one.  Walked and
+// by jumps: 128 levels of 300 vertices 42 and 26 us, of 4,000 90 and 63, 300 of 3,000 190 and 93.
+inline bool path_by_jumps(int32_t n, int32_t P, int32_t L, int32_t hops) {
+    return P == 1 && L >= 128 && n / L < 4096 && hops >= 32;
+}
 // Records are one more launch, which reads the graph and writes 64 bytes a vertex (5 us at 60,000 vertices, 16 at 240,000),
 // and save a tenth to a half of a microsecond per path vertex.  Without and with: 195 levels of 65 vertices 107 and
-// 105 us, 256 of 900 163 and 114, 300 of 300 131 and 98, 1,000 of 60 406 and 304.  Not where most rows are longer than
-// a record: 400 levels of 300 vertices with 20 edges each, 24 partitions, 225 and 341 us.
-inline bool path_by_records(int32_t n, int64_t m, int32_t L) { return L >= 256 && n / L < 1024 && m / n <= 5; }
+// 105 us, 256 of 900 163 and 114, 300 of 300 131 and 98, 1,000 of 60 406 and 304; edges of up to 299 levels, 300 of 1,000,
+// 74 and 78.  Not where most rows are longer than a record: 400 levels of 300 vertices with 20 edges each, 24 partitions,
+// 225 and 341 us.
+inline bool path_by_records(int32_t n, int64_t m, int32_t L, int32_t hops) {
+    return L >= 256 && n / L < 1024 && m / n <= 5 && hops >= 64;
+}
 // cp_critical_path with scratch for the jumps or null; with it, what lies behind the path in path_out stays as it was.
 int critical_path(const cp_graph *g, int32_t batch, int32_t k, const uint8_t *assignments, int assign_layout,
                   const int64_t *speeds, const int64_t *bandwidth, const void *blevel, const int64_t *cp,

@@ -793,7 +793,7 @@ int search_layout(const cp_graph *g, int32_t k, SearchLayout &o) {
     o.path = at;    at += align_up(L * sizeof(int32_t));
     o.small = at;   at += kAlign;        // StepResult, broken constraints
     o.total = at;                        // (the path's jumps are optional: an array of this size still serves)
-    o.jumps = path_by_jumps(info.n, 1, info.L) ? align_up(path_jump_words(info.n) * sizeof(int32_t)) : 0;
+    o.jumps = path_by_jumps(info.n, 1, info.L, g->packed.hops) ? align_up(path_jump_words(info.n) * sizeof(int32_t)) : 0;
     return CP_OK;
 }
 
@@ -966,7 +966,7 @@ static int seed_bytes(const cp_graph *g, size_t *out_bytes, size_t *jump_bytes) 
     if (rc) return rc;
     *out_bytes = align_up(eval) + align_up((size_t)info.n) + align_up((size_t)info.n * (size_t)info.min_tick_bytes) +
                  align_up((size_t)info.L * sizeof(int32_t)) + kAlign;
-    *jump_bytes = path_by_jumps(info.n, 1, info.L) ? align_up(path_jump_words(info.n) * sizeof(int32_t)) : 0;
+    *jump_bytes = path_by_jumps(info.n, 1, info.L, g->packed.hops) ? align_up(path_jump_words(info.n) * sizeof(int32_t)) : 0;
     return CP_OK;
 }
 

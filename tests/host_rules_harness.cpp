@@ -187,9 +187,30 @@ static int room(const std::string &dir) {
     return p.blob.size() > made || p.blob.capacity() != made;
 }
 
+// A path by records or jumps only where it can be long: `wanted` says which of the two the packed graph of argv[2] gets.
+static int paths(const std::string &dir, const std::string &wanted) {
+    auto i32 = [&](const char *name) { return read_all<int32_t>(dir + "/" + name + ".bin"); };
+    auto i64 = [&](const char *name) { return read_all<int64_t>(dir + "/" + name + ".bin"); };
+    const auto hdr = i64("hdr");
+    if (hdr.size() != 3) return 2;
+    const auto sp = i32("succ_ptr"), si = i32("succ_idx"), pp = i32("pred_ptr"), pi = i32("pred_idx"), pe = i32("pred_eid"),
+               lp = i32("level_ptr"), lv = i32("level_vtx");
+    const auto st = i64("succ_t"), c = i64("c");
+    Packed p;
+    if (pack_graph((int32_t)hdr[0], hdr[1], (int32_t)hdr[2], sp.data(), si.data(), st.data(), pp.data(), pi.data(),
+                   pe.data(), c.data(), lp.data(), lv.data(), p) != CP_OK)
+        return 2;
+    std::string got = path_by_records(p.n, p.m, p.L, p.hops) ? "records" : "csr";
+    if (path_by_jumps(p.n, 1, p.L, p.hops)) got += "+jumps";
+    if (path_by_jumps(p.n, 2, p.L, p.hops)) got += "+jumps of a batch";
+    std::printf("%s, hops %d of %d\n", got.c_str(), p.hops, p.L);
+    return got != wanted;
+}
+
 int main(int argc, char **argv) {
     if (argc < 2) return 2;
     if (argc > 2 && !std::strcmp(argv[1], "room")) return room(argv[2]);
+    if (argc > 3 && !std::strcmp(argv[1], "paths")) return paths(argv[2], argv[3]);
     if (!std::strcmp(argv[1], "prepare")) return prepare();
     if (!std::strcmp(argv[1], "rounded")) return rounded();
     if (!std::strcmp(argv[1], "column")) return column();

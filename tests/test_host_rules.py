@@ -3,10 +3,12 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 from test_packer_sanitized import _deep, _dump
-from workloads import make_workload
+from workloads import build_csr, make_workload, random_layered_dag
+from workloads.dags import _finish
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1711_01912_amd", "csrc")
@@ -63,3 +65,20 @@ def test_blob_is_allocated_once(harness, tmp_path, case):
             w.c = w.c * 2**36
     _dump(w, str(tmp_path))
     _holds(harness, "room", str(tmp_path))
+
+
+@pytest.mark.parametrize("widths,deg,span,wanted", [
+    ([30] * 260, 3, 4, "records+jumps"),
+    ([1] * 256, 1, 1, "records+jumps"),
+    ([30] * 255, 3, 4, "csr+jumps"),
+    ([30] * 127, 3, 4, "csr"),
+    ([10] * 260, 20, 4, "csr+jumps"),            # rows longer than a record
+    ([30] * 260, 3, 200, "csr"),                 # paths of a dozen vertices
+])
+def test_long_paths_only_by_records_and_jumps(harness, tmp_path, widths, deg, span, wanted):
+    rng = np.random.default_rng(len(widths) + span)
+    n, level, src, dst = random_layered_dag(rng, widths, 1, deg, span)
+    csr = build_csr(n, src, dst, rng.integers(1, 100, len(src)), level)
+    w = _finish("paths", csr, rng.integers(1, 60, n), 2, np.ones(2), np.ones((2, 2)), np.zeros((1, n), dtype=np.uint8))
+    _dump(w, str(tmp_path))
+    _holds(harness, "paths", str(tmp_path), wanted)
