@@ -32,7 +32,7 @@ namespace {
 
 constexpr uint32_t kNever = 0xffffffffu;
 constexpr size_t kSimWaves = 32;         // wavefronts a compute unit holds
-constexpr size_t kSimStaticLds = 1024;   // static LDS of a wavefront, rounded up
+constexpr size_t kSimStaticLds = 1024;   // static LDS of a wavefront with a near inbox, the most there is
 constexpr int kWideRow = 32;      // out-edges from which a started vertex's row is shared out over the wavefront
 
 // All lanes of a partition sit in one wavefront, so everything they exchange passes through
@@ -40,8 +40,10 @@ constexpr int kWideRow = 32;      // out-edges from which a started vertex's row
 // release at device scope would write the L2 back on every step).  Ready times and open-input
 // counts are only changed by read-modify-write atomics, which execute in the L2 and leave the
 // L1 stale: a ready time is read back with a load of device scope, which goes past the L1.
-// Inbox slots are written once with ordinary stores and read afterwards by another lane of
-// the wavefront.
+// Inbox slots are written with ordinary stores and read afterwards by another lane of the wavefront; where the
+// first of a step wait in LDS they are written again every step.  Either is safe because one wavefront writes and reads
+// them: its accesses to an address keep their order in its compute unit's L1, which writes through, and step_fence
+// waits for the stores before the next step's loads.
 __device__ __forceinline__ int32_t l2_read(int32_t *p) {
     // a device-scope load goes past the L1 like the atomics do, and unlike an atomic it writes nothing
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -162,13 +164,17 @@ __device__ __forceinline__ long long load_b(const uint8_t *bq, int32_t z, int64_
 // against the state in memory: 5,271 vertices, 50 devices, 4,096 partitions (16 wavefronts
 // per compute unit, owners and inputs kept; 3.93 with the near inbox below) 5.73 -> 4.55 ms; 1,124 vertices, 26 devices, 1,957 partitions (all
 // kept) 1.83 -> 0.90 ms.
-enum Resident { kNothing, kOwnersAndInputs, kAll };
+enum Resident { kNothing, kOwnersAndInputs, kNearInboxToo, kAll };
 
-// kOwnersAndInputs: the first two vertices handed to a device in a step wait in LDS, the others in its inbox in memory,
+// kNearInboxToo: the first two vertices handed to a device in a step wait in LDS, the others in its inbox in memory,
 // which then costs most steps neither a store to wait for nor a round trip (5,271 vertices, 50 devices, 4,096
-// partitions: PCT 4.46 -> 3.93 ms, FIFO 3.88 -> 3.40).  Two, because the static LDS then still is kSimStaticLds; 16 bits,
-// because state in LDS means at most 43,690 vertices.
+// partitions: PCT 4.46 -> 3.93 ms, FIFO 3.88 -> 3.40).  From kNearFrom wavefronts a compute unit on: one alone finds its
+// inbox in the L1 (24,000 vertices, 8 devices: 64 and 256 partitions 1.02 times as long with it, 512 as long,
+// 1,024 0.98, on 50 devices 0.96).  Two, because the static LDS then still is kSimStaticLds; 16 bits, because state in LDS
+// means at most 43,690 vertices.
+constexpr size_t kNearFrom = 3;
 constexpr int32_t kNearInbox = 2;
+static_assert(3 * 64 * sizeof(int32_t) + 64 * kNearInbox * sizeof(uint16_t) <= kSimStaticLds, "fits() counts on it");
 
 struct SimArgs {
     const int32_t *ptr;        // successor CSR over original ids
@@ -202,10 +208,10 @@ struct SimArgs {
 template <typename WT, bool MAGIC, bool PCT, int KEEP>
 __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
     extern __shared__ uint32_t sim_lds[];
-    __shared__ int32_t count[64];      // vertices per device, then vertices handed to the device so far
+    __shared__ int32_t count[64];      // vertices per device, then handed to it so far (kNearInboxToo: in this step)
     __shared__ int32_t seg[64];        // first slot of the device's segment
     __shared__ int32_t gbad[64];       // per group: a device id >= k was seen
-    __shared__ uint16_t near_in[64][kNearInbox];       // kOwnersAndInputs: the first vertices handed over in a step
+    __shared__ uint16_t near_in[64][kNearInbox];       // kNearInboxToo: the first vertices handed over in a step
     const int lane = threadIdx.x;
     const int32_t n = a.n, k = a.k;
     // with k <= 32 devices a wavefront can hold up to 64 / k partitions side by side: group g =
@@ -293,7 +299,7 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
                 const uint32_t d = owner(v);
                 const int32_t pos = atomicAdd(&count[first + d], 1);
                 if (KEEP == kAll) l_inbox[seg[first + d] + pos] = (uint16_t)v;
-                else if (KEEP == kOwnersAndInputs && pos < kNearInbox) near_in[d][pos] = (uint16_t)v;
+                else if (KEEP == kNearInboxToo && pos < kNearInbox) near_in[d][pos] = (uint16_t)v;
                 else inbox_store(inbox + seg[first + d] + pos, v);
             }
         }
@@ -327,7 +333,7 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
         const int to = (KEEP != kNothing ? 0 : first) + (int)d;    // idle lanes help with wide rows: not their first
         const int32_t pos = atomicAdd(&count[to], 1);
         if (KEEP == kAll) l_inbox[seg[to] + pos] = (uint16_t)z;
-        else if (KEEP == kOwnersAndInputs && pos < kNearInbox) near_in[to][pos] = (uint16_t)z;
+        else if (KEEP == kNearInboxToo && pos < kNearInbox) near_in[to][pos] = (uint16_t)z;
         else inbox_store(inbox + seg[to] + pos, z);
     };
     // every step with work left starts at least one vertex in every unfinished group, so
@@ -335,7 +341,7 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
     for (int64_t step = 0; step <= n; ++step) {
         if (alive) {   // vertices handed to this device since its last step, four loads in flight at a time
             const int32_t have = count[lane];
-            if (KEEP == kOwnersAndInputs) {            // what is handed over in a step is numbered from 0
+            if (KEEP == kNearInboxToo) {            // what is handed over in a step is numbered from 0
                 taken = 0;
                 count[lane] = 0;
             }
@@ -347,7 +353,7 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
                 for (int j = 0; j < 4; ++j) {
                     const int32_t at = taken + min(j, cnt - 1);
                     if (KEEP == kAll) z[j] = (int32_t)l_inbox[base + at];
-                    else if (KEEP == kOwnersAndInputs && at < kNearInbox) z[j] = (int32_t)near_in[lane][at];
+                    else if (KEEP == kNearInboxToo && at < kNearInbox) z[j] = (int32_t)near_in[lane][at];
                     else z[j] = inbox_load(my_inbox + at);
                 }
 #pragma unroll
@@ -595,14 +601,16 @@ int launch_simulate(const SimulateLaunch &s, void *stream) {
     int keep = kNothing;
     if (groups == 1 && s.max_in_degree <= 255) {
         if (s.n <= 65535 && fits(all)) keep = kAll;
-        else if (fits(owners)) keep = kOwnersAndInputs;
+        else if (fits(owners)) keep = there < kNearFrom ? kOwnersAndInputs : kNearInboxToo;
     }
-    const size_t lds = keep == kAll ? all : (keep == kOwnersAndInputs ? owners : 0);
+    const size_t lds = keep == kAll ? all : (keep != kNothing ? owners : 0);
     const dim3 grid((unsigned)((s.P + groups - 1) / groups)), block(64);
 #define CP_SIM_K(WT, MAGIC, PCT)                                                                                    \
     do {                                                                                                            \
         if (keep == kAll)                                                                                           \
             hipLaunchKernelGGL((simulate_kernel<WT, MAGIC, PCT, kAll>), grid, block, lds, st, a);                   \
+        else if (keep == kNearInboxToo)                                                                             \
+            hipLaunchKernelGGL((simulate_kernel<WT, MAGIC, PCT, kNearInboxToo>), grid, block, lds, st, a);          \
         else if (keep == kOwnersAndInputs)                                                                          \
             hipLaunchKernelGGL((simulate_kernel<WT, MAGIC, PCT, kOwnersAndInputs>), grid, block, lds, st, a);       \
         else                                                                                                        \
