@@ -101,3 +101,25 @@ def test_long_rows_after_each_other(gpu, oracle, rich):
 ])
 def test_paths_equal_the_oracles(gpu, oracle, widths, deg, span, k, c_hi, t_hi):
     _check(gpu, oracle, _random(len(widths) + k, widths, deg, span, k, c_hi, t_hi))
+
+
+@pytest.mark.parametrize("room", [True, False])
+@pytest.mark.parametrize("where", [0, 100, 299])
+def test_a_device_id_too_large_is_reported(gpu, where, room):
+    """On the path of a chain, over records and over the CSR: reported, and the call returns.  All vertices are on the last
+    device, whose costs a larger id is given, so that the path reaches it."""
+    import torch
+    n, k = 300, 3
+    src, dst = np.arange(n - 1), np.arange(1, n)
+    w = T._custom("bad-id", n, src, dst, np.full(n - 1, 5), np.full(n, 2), [1] * k, np.ones((k, k), dtype=np.int64),
+                  np.full((2, n), k - 1, dtype=np.uint8), np.arange(n))
+    g = gpu.CpGraph.from_workload(w, device="cuda:0")
+    a = torch.from_numpy(w.assignments).to("cuda:0")
+    out = gpu.cp_eval(g, a, w.speeds, w.bandwidth, want=("cp", "b"), out_layout=1)
+    ws = torch.empty(4096 + (64 * n if room else 0), dtype=torch.uint8, device="cuda:0")
+    paths, lens = gpu.cp_critical_path(g, a, w.speeds, w.bandwidth, out["b"], out["cp"], b_layout=1, workspace=ws)
+    assert lens.tolist() == [n, n]
+    a[1, where] = k
+    with pytest.raises(ValueError):
+        gpu.cp_critical_path(g, a, w.speeds, w.bandwidth, out["b"], out["cp"], b_layout=1, workspace=ws)
+    g.close()
