@@ -614,20 +614,14 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_records_kernel(Pat
         bv = b[(uint64_t)(uint32_t)v * bsv];
         rec = load_record((uint32_t)v);
     }
-    uint32_t cv = 0;                         // the current vertex's c, out-edges and, of more than a record's, the first one
-    int32_t deg = 0, first = 0;
-    auto read_record = [&]() {
-        cv = (uint32_t)__builtin_amdgcn_readlane((int)rec, base);
-        deg = __builtin_amdgcn_readlane((int)rec, base + 1);
-        first = __builtin_amdgcn_readlane((int)rec, base + 2);
-    };
-    read_record();
     bool bad_id = false;
     int32_t len = 0, step = 0;
     while (v != 0x7fffffff && len < a.max_len) {
         step = lane == (len & 63) ? v : step;            // (a store per vertex is waited for with the loads behind it)
         if ((len & 63) == 63) path[len - 63 + lane] = step;
         ++len;
+        const uint32_t cv = (uint32_t)__builtin_amdgcn_readlane((int)rec, base);
+        const int32_t deg = __builtin_amdgcn_readlane((int)rec, base + 1);
         if (pv >= (uint32_t)k) { bad_id = true; pv = 0; }
         const Magic *costs = etab + pv * k;
         auto fits = [&](uint32_t p_raw, uint32_t te, Tick bu, Tick rest) {
@@ -635,7 +629,7 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_records_kernel(Pat
         };
         uint32_t next = 0x7fffffff, n_p = 0;             // this lane's best successor, its device and b
         Tick n_b = 0;
-        if (deg <= kRecordEdges) {
+        if (__builtin_expect(deg <= kRecordEdges, 1)) {
             // (lanes past the last edge repeat it)
             const int own = base + 2 + 2 * min(lane, max(deg - 1, 0));
             const uint32_t u = from(rec, own), te = from(rec, own + 1);
@@ -655,12 +649,12 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_records_kernel(Pat
                 bv = wave_bcast<Tick>(n_b, won);
                 rec = won < 4 ? rec0 : rec1;
                 base = 16 * (won & 3);
-                read_record();
             }
         } else {
             const Tick rest = bv - (Tick)magic_div(cv, vtab[pv]);
             uint32_t n_c = 0;
             int32_t n_first = 0, n_deg = 0;
+            const int32_t first = __builtin_amdgcn_readlane((int)rec, base + 2);
             for (int32_t e = first + lane; e < first + deg; e += 64) {
                 const uint32_t u = (uint32_t)a.idx[e];
                 const uint32_t te = wt[e];
@@ -679,13 +673,12 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_records_kernel(Pat
                 const int won = __ffsll((long long)__ballot(next == best)) - 1;
                 pv = wave_bcast<uint32_t>(n_p, won);
                 bv = wave_bcast<Tick>(n_b, won);
-                cv = wave_bcast<uint32_t>(n_c, won);
-                first = wave_bcast<int32_t>(n_first, won);
-                deg = wave_bcast<int32_t>(n_deg, won);
-                if (deg <= kRecordEdges) {
-                    rec = load_record(best);
-                    base = 0;
-                }
+                base = 0;
+                // (what the record of a long row says is known already)
+                const uint32_t c0 = wave_bcast<uint32_t>(n_c, won);
+                const int32_t e0 = wave_bcast<int32_t>(n_first, won), edges = wave_bcast<int32_t>(n_deg, won);
+                if (edges <= kRecordEdges) rec = load_record(best);
+                else rec = lane == 0 ? c0 : (uint32_t)(lane == 1 ? edges : e0);
             }
         }
     }
