@@ -232,9 +232,12 @@ inline int32_t bins_each(int32_t buckets) {
 // have: a quarter of the 512 where both lie just above a power of two, and sized by all 512 the bins left every bucket of
 // 211,000 vertices on 9 or 33 devices to the ranking.  9 devices, 512 partitions: bins 150 us in vain and 1,080 of ranking,
 // then bins of 256 threads for all, 570.  A size too large costs too (16 devices, 320 digits: 128 threads 500, 256 680).
-inline int bucket_threads(int32_t n, int32_t k, int b_bits, int rem, int64_t max_b) {
+inline int64_t bucket_average(int32_t n, int32_t k, int b_bits, int rem, int64_t max_b) {
     const int64_t used = rem >= b_bits ? ((int64_t)(k - 1) >> (rem - b_bits)) + 1 : k * ((max_b >> rem) + 1);
-    const int64_t wanted = (n / used + 1) * 7 / 5;
+    return n / used + 1;
+}
+inline int bucket_threads(int32_t n, int32_t k, int b_bits, int rem, int64_t max_b) {
+    const int64_t wanted = bucket_average(n, k, b_bits, rem, max_b) * 7 / 5;
     return wanted <= 8 * 128 ? 128 : wanted <= 8 * 256 ? 256 : 512;
 }
 int32_t pct_sort_tiles(int32_t n);

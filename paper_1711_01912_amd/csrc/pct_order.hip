@@ -530,8 +530,9 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
 constexpr int bin_bits(int threads) { return threads == 128 ? 10 : threads == 256 ? 11 : threads == 512 ? 12 : 13; }
 // 211,000 vertices, 512 partitions, buckets of 412 items, ranked and by bins: 1,325 -> 361 us.  Whole partitions, the call:
 // 19,000 vertices, 512 partitions 154 -> 83 us; 5,000 vertices, 3,000 partitions 186 -> 96.  Keys that repeat are found out
-// by the sample and pay for it: whole partitions 2 - 3 us, 3 to 8 % of the call; longer ones 0 - 2 us up to 16
-// partitions, 4 to 8 % of a call of 32 to 128, nothing beyond.
+// by the sample and pay for it: whole partitions 2 - 3 us, 3 to 8 % of the call; longer ones 0 - 2 us in one launch
+// (bins_and_ranking_in_one), in two 3 to 8 % of a call of up to 128 partitions and nothing beyond; most where buckets want
+// 512 threads (480,000 vertices, 9 devices, 300 values of b: 8 partitions 120 -> 136 us, 32 303 -> 324, 64 539 -> 509).
 template <int kThreads, int kRounds, bool WHOLE>
 __device__ __forceinline__ bool sort_by_bins(const uint32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
                                              int32_t *__restrict__ vals_out, int32_t items, int bits, int val_bits,
@@ -836,12 +837,20 @@ __global__ __launch_bounds__(kThreads, kThreads == 1024 ? 4 : 6) void pct_whole_
                                          key);
 }
 
-// Both in one launch, a bucket per workgroup, for at most kBothMost partitions: their calls are a row of launches of a few
-// microseconds, and a second one for what the bins leave would cost them as much as the bins save.  Beyond, the bins want
-// smaller workgroups than the ranking has registers and LDS for.  250,000 vertices, in one launch and in two: 8 partitions,
-// spread keys 78 and 80 us, 300 values of b 98 and 103 (103 and 95 before there were bins); 32 partitions 143 and 137, 197
-// and 210 (235 and 196); 64 partitions 245 and 214, 344 and 324.
-constexpr int32_t kBothMost = 16;
+// Both in one launch, a bucket per workgroup, for few partitions: their calls are a row of launches of a few microseconds,
+// and a second one for what the bins leave would cost them as much as the bins save.  Up to 24 partitions, up to 48
+// where the bins want the ranking's workgroup of 256 anyway (smaller ones want more of them on a compute unit than the
+// ranking has registers and LDS for), and up to 16 where they want the larger one, in which the ranking is slower.  Ranked as
+// before there were bins / in two launches / in one, us; spread keys, then 300 values of b:
+//   211,000 vertices,  3 devices, 17, 48, 64 partitions: 104 / 96 / 90, 188 / 156 / 150, 246 / 200 / 198;
+//                                                        104 / 115 / 105, 189 / 204 / 191, 246 / 258 / 250
+//                      9 devices: 122 / 98 / 92, 236 / 154 / 155, 310 / 194 / 205; 124 / 134 / 125, 240 / 252 / 240, 315 / 296 / 314
+//                     16 devices, 17, 24, 32: 139 / 100 / 97, 175 / 116 / 115, 216 / 126 / 138;
+//                                             139 / 150 / 143, 175 / 188 / 180, 216 / 216 / 223
+//   900,000 vertices,  3 devices, 8 (workgroups of 512): 142 / 133 / 129; 206 / 213 / 210
+inline bool bins_and_ranking_in_one(int32_t P, int for_bins, int threads) {
+    return P <= (threads == 512 ? 16 : for_bins > 128 ? 48 : 24);
+}
 template <int kThreads>
 __global__ __launch_bounds__(kThreads, 6) void pct_bucket_kernel(const uint32_t *__restrict__ keys_in,
                                                               const int32_t *__restrict__ vals_in,
@@ -1053,9 +1062,12 @@ int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     lead.scan();
     // the smaller workgroup (more of them per compute unit) where buckets of twice the average size fit it
     const bool small = 2 * ((int64_t)s.n / kBuckets + 1) <= kBucketCapSmall;
-    const bool both = s.P <= kBothMost;
     const int for_bins = bucket_threads(s.n, s.k, s.b_bits, rem, s.max_b);
-    const int threads = both ? (small && for_bins <= 256 ? 256 : 512) : for_bins;
+    // (a bucket that the bins do not hold after all is ranked by the same workgroup: an eighth to spare will do)
+    const int64_t average = bucket_average(s.n, s.k, s.b_bits, rem, s.max_b);
+    const int in_one = small && average * 8 / 7 <= 256 * kBinRounds ? 256 : 512;
+    const bool both = bins_and_ranking_in_one(s.P, for_bins, in_one);
+    const int threads = both ? in_one : for_bins;
     const int shift = std::max(0, rem - bin_bits(threads));
     // (noted where the partition's list bounds will stand)
     int32_t *crowded = s.seg_out;

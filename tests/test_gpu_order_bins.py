@@ -62,10 +62,11 @@ def test_lists_by_bins(gpu, oracle, n, kind, k, top):
 
 
 @pytest.mark.parametrize("n,P", [(65_537, 17), (65_537, 32), (65_537, 65), (65_537, 128), (65_537, 257), (262_145, 17),
-                                 (524_801, 20)])
+                                 (524_801, 20), (65_537, 24), (65_537, 25), (524_801, 48), (524_801, 49)])
 def test_left_buckets_among_others(gpu, oracle, n, P):
-    """One to sixteen buckets per workgroup of the ranking, one to four of the bins, which have 128, 256 or 512 threads: crowded partitions between spread ones, empty digits (9 of
-    16 devices) and, in one partition, full buckets beside nearly empty ones."""
+    """One to sixteen buckets per workgroup of the ranking, one to four of the bins, which have 128, 256 or 512 threads, and
+    both in one launch: crowded partitions between spread ones, empty digits (9 of 16 devices) and, in one partition, full
+    buckets beside nearly empty ones."""
     import torch
     k, top = 9, 3_000_000
     rng = np.random.default_rng(P)
