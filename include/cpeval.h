@@ -270,7 +270,10 @@ int cp_eval_static(const cp_graph *g, int32_t batch, int32_t k,
  *   assignments, assign_layout, speeds, bandwidth   as for cp_eval (same values as the
  *                 call that produced blevel and cp)
  *   blevel        device ticks laid out per b_layout (CP_OUT_*), cp device int64 [batch]: outputs of cp_eval
- *   workspace     device, 256-byte aligned, >= cp_eval_workspace_bytes for this batch and k
+ *   workspace     device, 256-byte aligned, >= cp_eval_workspace_bytes for this batch and k.  Graphs of 256 levels and
+ *                 more, of up to 1,024 vertices each and up to five edges a vertex, are walked faster, with the same
+ *                 result, where it holds 64 bytes a vertex behind the 12 k (2 k + 1) bytes, rounded up to 256, of the
+ *                 tables; that many bytes do from a few dozen partitions on, and a larger workspace may be handed over
  *   max_len       row length of path_out, >= the graph's number of levels L
  *   path_out      device int32 [batch][max_len]; unused tail = -1
  *   len_out       device int32 [batch]: vertices on the path
@@ -393,8 +396,9 @@ int cp_simulate(const cp_graph *g, int32_t batch, int32_t k,
  * smallest load(d) + ceil(c(v) / s[d]) (lowest number on ties), load(d) being the summed
  * execution times of the vertices already on d, the path included (the strategy's load
  * equation in integer ticks).  Memory capacities are not modelled.  The load rule is a
- * chain of n dependent choices: it runs on one wavefront: 0.06 microseconds a vertex with
- * 16 devices or fewer, 0.085 with up to 64, and up to 0.24 where the loads of 64 vertices spread over more than 26 bits.
+ * chain of n dependent choices on one wavefront: 0.037 microseconds a vertex with 16 devices or fewer, 0.046 with up
+ * to 32 and 0.067 with up to 64; about twice that where 64 vertices may part the loads by more than 28, 27 or 26 bits,
+ * 0.30 to 0.38 from 32 bits on, and 0.46 to 0.54 where c or speeds have no multiply-shift constants (cp_cost_magic).
  * Only enqueues work on `stream`.
  *
  *   k <= 64, speeds host int64 [k]

@@ -560,7 +560,7 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_kernel(PathArgs a)
 // than over the CSR (120,000 vertices of up to 40 edges in 400 levels, 777 partitions: 639 us with the winner's record
 // and row bounds in rounds of their own, so 545; where rows are that long on average the CSR is taken, 511).
 // Bound by the latency of that one round, b and the device ids from HBM or the last cache, 0.9 us a path vertex: 777
-// partitions, 121,000 vertices in 701 levels (paths of 329): 448 -> 306 us and 10 for the records; 300 partitions,
+// partitions, 121,000 vertices in 701 levels (paths of 329): 448 -> 303 us and 11 for the records; 300 partitions,
 // 240,000 vertices in 2,000 levels (1,027): 1,045 -> 764 and 16.
 constexpr int kRecordEdges = 7;
 

@@ -528,7 +528,8 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
 // of the list, shares its bin as it would with more than kBinAverage items in an average item's bin: keys that repeat, or
 // that differ in their low bits only.
 constexpr int bin_bits(int threads) { return threads == 128 ? 10 : threads == 256 ? 11 : threads == 512 ? 12 : 13; }
-// 211,000 vertices, 512 partitions, buckets of 412 items, ranked and by bins: 1,325 -> 361 us.  Whole partitions, the call:
+// 211,000 vertices, 512 partitions, 16 devices, ranked and by bins: 1,325 -> 315 us, bound by vector issue (83 %; the LDS pipe
+// is busy 64 % of the time, half of that with bank conflicts).  Whole partitions, the call:
 // 19,000 vertices, 512 partitions 154 -> 83 us; 5,000 vertices, 3,000 partitions 186 -> 96.  Keys that repeat are found out
 // by the sample and pay for it: whole partitions 2 - 3 us, 3 to 8 % of the call; longer ones 0 - 2 us in one launch
 // (bins_and_ranking_in_one), in two 3 to 8 % of a call of up to 128 partitions and nothing beyond; most where buckets want

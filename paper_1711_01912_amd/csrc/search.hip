@@ -18,9 +18,9 @@
 // range of levels with a value, and the maxima of all levels come from one pass over the graph.
 // A step is then both sweeps of ONE partition, the walk of its path, and that pass, whatever
 // the number of candidates: 211,000 vertices in 1,000 levels on 16 devices, three moves of about
-// 5,000 candidates each take 4.0 ms, 32.2 ms when every candidate was evaluated by a sweep of its
-// own.  Per step: both sweeps 0.78 ms, the walk 0.43 ms (chains of dependent steps of one partition),
-// the pass over the graph 0.03 ms, the candidates 0.007 ms.
+// 5,000 candidates each take 2.9 ms, 32.2 ms when every candidate was evaluated by a sweep of its
+// own.  Per step: both sweeps 0.78 ms (chains of dependent steps of one partition), the path by jumps
+// 0.045 ms, the pass over the graph 0.03 ms, the candidates 0.007 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -518,12 +518,13 @@ __global__ __launch_bounds__(64) void seed_greedy_kernel(SeedArgs a) {
 // The same chain where execution times come from multiply-shift constants, with nothing but the chain on the wavefront
 // that walks it.  Its numbers are keys, (load - low) << BITS | device, so that a minimum names its device and the
 // lowest one wins a tie; every row of 16 lanes holds all devices, PER of them a lane (device r * 16 + lane).  A vertex
-// is an addition, four register permutations, a comparison and a selection.  Three wavefronts beside it read c and the
+// is an addition, four minima over register permutations, a comparison and a selection.  Three wavefronts beside it read c and the
 // vertices still to be placed 64 at a time, two batches ahead, put the execution times of every device into
 // LDS and write the devices chosen a batch ago.  Where a batch might take a load past 32 - BITS bits above the lowest, its
 // loads are 32 bits relative to that without a device number, and past 32 bits they are 64; ties are then told by ballots.
-// Bound by the chain and by what one wavefront issues, six to eight cycles an instruction and two wait states before
-// each permutation: 211,000 vertices on 16 devices 0.056 -> 0.038 us each, a tenth of it between the batches.  (A branch
+// Bound by that chain, 88 cycles a vertex (the unit's busy cycles over the vertices): 211,000 vertices on 16 devices 0.056 ->
+// 0.037 us each, 32 devices 0.046, 50 0.067; c up to 2^26 (32-bit loads) 0.070, 0.094 and 0.15, up to 2^31 (64) 0.30, 0.35 and
+// 0.38 (0.32, 0.37 and 0.39 with all of a call's work on one wavefront).  (A branch
 // of any kind between two vertices costs as much as half a vertex.  Two vertices at a time, the second one's choice
 // prepared for each outcome of the first, or both outcomes' keys added up ahead of the comparison: 4 % less and 4 % more.)
 template <int PER, int BITS>

@@ -11,8 +11,8 @@
 // side in one launch.  Whole calls, before -> now: 2,016 vertices in 195 levels, 1,024 partitions 300 ->
 // 105 us; 121,000 in 701 levels, 777 partitions, rows per vertex 2.84 -> 1.15 ms; 29,000 in 301 levels with
 // 64-bit ticks (a launch per level before), 320 partitions 3.65 -> 0.32 ms.  What bounds it: on narrow ticks
-// the chain of a tick (two LDS round trips, publication, barrier: 0.2 to 0.3 us, with far reads 0.5 to 0.9; every unit at
-// least half idle), on wide ones the LDS pipe of a compute unit (121,000 vertices: 72 % busy, a third of it bank
+// the chain of a tick (two LDS round trips, publication, barrier: 0.2 to 0.3 us; with far reads, 660 levels, 1.0 us with one
+// workgroup on a compute unit, 1.3, 1.7 and 2.4 with two, three and four, no part of the unit busy a third of the time), on wide ones the LDS pipe of a compute unit (121,000 vertices: 72 % busy, a third of it bank
 // conflicts; vector ALUs 62 %, 27 instructions per 64 relaxations with what loaders and stores add).
 //
 // A ring word is value << 6 | device id, one LDS read per relaxation; x << 6 is added to it and the
