@@ -94,6 +94,9 @@ extern "C" {
                                         where it is faster for the call (see cp_eval_choose_plan) */
 #define CP_PLAN_COLUMN_SLICE     5   /* the wave-column layout, but one persistent workgroup owns 64 partitions and
                                         walks all levels in one launch per sweep (never chosen by CP_PLAN_AUTO) */
+#define CP_PLAN_CHAIN            8   /* only told by cp_profile_plan, never accepted: what CP_PLAN_AUTO may run for up to 64
+                                        partitions of a graph of many levels.  One workgroup = one sweep of one partition,
+                                        behind a launch that writes what every edge costs under it */
 
 /* stages of one cp_eval call, in the order they run; also the index into cp_profile_read's output */
 #define CP_STAGE_PREP    0   /* clear outputs, cost tables, assignment transpose */
@@ -183,7 +186,7 @@ int cp_eval_workspace_bytes(const cp_graph *g, int32_t batch, int32_t k, int ass
  * directly, or whether CP can be had without b).  Where the lane-window plan is faster for
  * the call at hand, which depends on its outputs, layouts and workspace, AUTO runs that one in
  * its place, with the same results and the same refusals: it is never the answer here, and
- * cp_profile_plan tells what a call ran.  Errors: as cp_eval's argument checks.
+ * cp_profile_plan tells what a call ran; the same holds for CP_PLAN_CHAIN.  Errors: as cp_eval's argument checks.
  */
 int cp_eval_choose_plan(const cp_graph *g, int32_t batch, int32_t k, const int64_t *speeds,
                         const int64_t *bandwidth, int tick_dtype, int *plan_out);
@@ -243,7 +246,8 @@ int cp_eval(const cp_graph *g, int32_t batch, int32_t k,
  * writes partition-major outputs; the device ids in sweep order (about n * batch bytes per
  * sweep) when the resident-window plan cannot read them straight from the caller's rows
  * (vertex-major assignments, rows not 16-byte aligned, or a graph whose levels are
- * scattered over the vertex numbers); the same and the copies of far reads for the lane-window plan, which
+ * scattered over the vertex numbers); the same and the copies of far reads for the lane-window plan, and
+ * what every edge costs (20 bytes for up to four of a vertex) for CP_PLAN_CHAIN, which
  * CP_PLAN_AUTO leaves aside where they do not fit.  A resident-window call on aligned partition-major
  * rows needs the tables only.
  *

@@ -11,6 +11,7 @@ from .binding import (  # noqa: F401
     OUT_PARTITION_MAJOR,
     OUT_VERTEX_MAJOR,
     PLAN_AUTO,
+    PLAN_CHAIN,
     PLAN_COLUMN_SLICE,
     PLAN_LANE_WINDOW,
     PLAN_RESIDENT_WINDOW,

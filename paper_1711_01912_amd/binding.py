@@ -21,6 +21,7 @@ ASSIGN_PARTITION_MAJOR, ASSIGN_VERTEX_MAJOR = 0, 1
 OUT_VERTEX_MAJOR, OUT_PARTITION_MAJOR = 0, 1
 PLAN_AUTO, PLAN_WAVE_COLUMN, PLAN_RESIDENT_WINDOW, PLAN_SHARED_WINDOW_2, PLAN_SHARED_WINDOW_4 = 0, 1, 2, 3, 4
 PLAN_COLUMN_SLICE, PLAN_STREAMED_WINDOW, PLAN_LANE_WINDOW = 5, 6, 7
+PLAN_CHAIN = 8     # only told by CpProfile.plan
 NUM_STAGES = 5
 STAGE_NAMES = ("prep", "blevel", "cp", "tlevel", "mask")
 STATUS_BAD_DEVICE_ID = 1

@@ -336,6 +336,29 @@ bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, const int6
     return found;
 }
 
+// The chain sweep: a workgroup per sweep and partition, behind a launch that writes what every edge costs.  Up to 64
+// partitions (measured up to there).
+constexpr int32_t kChainMostPartitions = 64;
+// No edge's cost and its vertex's execution time together reach 2^16.
+bool chain_cost16(const Packed &p, int32_t k, const int64_t *speeds, const int64_t *bandwidth) {
+    int64_t slowest = speeds[0], narrowest = INT64_MAX;
+    for (int32_t i = 0; i < k; ++i) {
+        slowest = std::min(slowest, speeds[i]);
+        for (int32_t j = 0; j < k; ++j)
+            if (i != j) narrowest = std::min(narrowest, bandwidth[(size_t)i * k + j]);
+    }
+    return p.info.max_c / slowest + 1 + (k > 1 ? p.info.max_t / narrowest + 1 : 0) < 1 << 16;
+}
+// Fitted to 70 calls (300 to 1,500 levels of 20 to 600 vertices, 1 to 64 partitions): a tick 0.1 us and 0.016 a wavefront, 0.05
+// more with 64-bit words; the launch that writes the costs 8 (or, with 32 bits each, 13) us for a million lanes of
+// ticks and partitions; rows per vertex 10 us for a million outputs.
+double chain_us(const Packed &p, int32_t batch, int sweeps, bool cost16, bool by_partition) {
+    const double lanes = (double)p.chain_width * ((double)p.chain_b.ticks + p.chain_t.ticks) / 2 * sweeps * batch;
+    const double tick = 0.1 + 0.016 * (p.chain_width / kWave) + (p.info.min_tick_bytes == 8 ? 0.05 : 0.0);
+    return 18.0 + lanes * (cost16 ? 8e-6 : 13e-6) + std::max(p.chain_b.ticks, p.chain_t.ticks) * tick +
+           (by_partition ? 0.0 : (double)p.n * batch * sweeps * 10e-6);
+}
+
 size_t tables_bytes(int32_t k) { return align_up(table_words(k) * 8); }
 
 // One call's tables as they lie in device memory: the 8-byte entries (multiply-shift constants,
@@ -549,8 +572,9 @@ int cp_graph_upload(cp_graph *g, void *device_blob, size_t blob_bytes, void *str
 
 void cp_graph_destroy(cp_graph *g) { delete g; }
 
-int cp_eval_workspace_bytes(const cp_graph *g, int32_t batch, int32_t k, int assign_layout,
-                            int plan, int out_layout, int tick_dtype, size_t *out_bytes) {
+// with_chain: room for the chain sweep too, without which the call goes another way
+static int eval_bytes(const cp_graph *g, int32_t batch, int32_t k, int assign_layout, int plan, int out_layout,
+                      int tick_dtype, bool with_chain, size_t *out_bytes) {
     if (!out_bytes) return CP_ERR_NULL;
     int rc = check_eval_sizes(g, batch, k, assign_layout, plan);
     if (rc) return rc;
@@ -576,8 +600,16 @@ int cp_eval_workspace_bytes(const cp_graph *g, int32_t batch, int32_t k, int ass
     if ((plan == CP_PLAN_AUTO || plan == CP_PLAN_LANE_WINDOW) && g->packed.have_lanes && k <= kMagicMaxK)
         for (int groups : {4, 8})
             lanes = std::max(lanes, lane_work_bytes(&g->packed.lane_b, &g->packed.lane_t, g->packed.n, batch, groups, 8));
-    *out_bytes = bytes + std::max({column, window, lanes});
+    size_t chain = 0;
+    if (with_chain && plan == CP_PLAN_AUTO && g->packed.have_chain && batch <= kChainMostPartitions)
+        chain = chain_work_bytes(&g->packed.chain_b, &g->packed.chain_t, g->packed.chain_width, batch, false);
+    *out_bytes = bytes + std::max({column, window, lanes, chain});
     return CP_OK;
+}
+
+int cp_eval_workspace_bytes(const cp_graph *g, int32_t batch, int32_t k, int assign_layout,
+                            int plan, int out_layout, int tick_dtype, size_t *out_bytes) {
+    return eval_bytes(g, batch, k, assign_layout, plan, out_layout, tick_dtype, true, out_bytes);
 }
 
 int cp_eval_choose_plan(const cp_graph *g, int32_t batch, int32_t k, const int64_t *speeds,
@@ -615,7 +647,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                     void *workspace, size_t workspace_bytes, void *stream,
                     int64_t *cp_out, void *blevel_out, void *tlevel_out, uint64_t *mask_out,
                     int tick_dtype, int out_layout, int plan, int32_t *status_out, cp_profile *profile,
-                    bool tables_by_kernel) {
+                    bool tables_by_kernel, uint8_t *chain_scratch = nullptr, size_t chain_scratch_bytes = 0) {
     int rc = check_eval_sizes(g, batch, k, assign_layout, plan);
     if (rc) return rc;
     if (!assignments || !speeds || !bandwidth || !workspace || !status_out) return CP_ERR_NULL;
@@ -670,6 +702,13 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const int lane_sweeps = ((blevel_out || cp_out) ? 1 : 0) + (tlevel_out ? 1 : 0);
     bool lanes = false;
     size_t lane_work = 0;
+    // a few partitions, each sweep of each by a workgroup of its own
+    const bool chain_fits = plan == CP_PLAN_AUTO && lane_sweeps > 0 && p.have_chain && batch <= kChainMostPartitions &&
+                            std::max(chain_lds_bytes(p.chain_b, p.info.min_tick_bytes),
+                                     chain_lds_bytes(p.chain_t, p.info.min_tick_bytes)) <= lds_limit &&
+                            (by_partition || batch * tick_dtype <= 256);      // (its output offsets take 24 bits by 8)
+    const bool cost16 = chain_fits && chain_cost16(p, k, speeds, bandwidth);
+    bool chain = false;
     if ((plan == CP_PLAN_AUTO || plan == CP_PLAN_LANE_WINDOW) && lane_sweeps > 0) {
         double lane_us = 0.0;
         lanes = choose_lanes(p, tabs, k, speeds, bandwidth, batch, tick_dtype, blevel_out || tlevel_out,
@@ -677,7 +716,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
         if (lanes)
             lane_work = lane_work_bytes((blevel_out || cp_out) ? &p.lane_b : nullptr, tlevel_out ? &p.lane_t : nullptr, p.n,
                                         batch, lane_cfg.groups, lane_cfg.word);
-        if (lanes && plan == CP_PLAN_AUTO) {
+        if ((lanes || chain_fits) && plan == CP_PLAN_AUTO) {
             // against the plan chosen so far: its sweeps (side by side where they would share the launch), the
             // device ids it gathers per sweep at about 1 us per MB, the launches it needs past two (2.5 us each),
             // and the mask pass that its t sweep may save it
@@ -718,12 +757,24 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                 other_us += mb * ((rows && p.win_b.direct_ok ? 0.0 : 1.0) + (rows && p.win_t.direct_ok ? 0.0 : 1.0)) *
                             (both ? 1.0 : 0.5);
             }
-            lanes = 1.0 + 0.7 * mb + lane_us < other_us &&
+            lanes = lanes && 1.0 + 0.7 * mb + lane_us < other_us &&
                     tables_bytes(k) + lane_work <= workspace_bytes;
+            if (chain_fits) {
+                const size_t work = chain_work_bytes((blevel_out || cp_out) ? &p.chain_b : nullptr,
+                                                     tlevel_out ? &p.chain_t : nullptr, p.chain_width, batch, cost16);
+                if (!chain_scratch) {
+                    chain_scratch = (uint8_t *)workspace + tables_bytes(k);
+                    chain_scratch_bytes = workspace_bytes - std::min(workspace_bytes, tables_bytes(k));
+                }
+                chain = work <= chain_scratch_bytes && tables_bytes(k) <= workspace_bytes &&
+                        chain_us(p, batch, lane_sweeps, cost16, by_partition) < (lanes ? 1.0 + 0.7 * mb + lane_us : other_us);
+                lanes = lanes && !chain;
+            }
         }
     }
     if (plan == CP_PLAN_LANE_WINDOW && !lanes) return CP_ERR_ARG;
     if (lanes) use = CP_PLAN_LANE_WINDOW;
+    if (chain) use = CP_PLAN_CHAIN;
     if (use == CP_PLAN_RESIDENT_WINDOW && !can_window) return CP_ERR_ARG;
     // several partitions per workgroup behind one graph stream
     const bool shared = use == CP_PLAN_SHARED_WINDOW_2 || use == CP_PLAN_SHARED_WINDOW_4;
@@ -735,11 +786,11 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const bool streamed = use == CP_PLAN_STREAMED_WINDOW;
     if (streamed && (!tabs.magic_ok || !stream_fits(p, k, (size_t)tick_dtype, lds_limit, &st_b, &st_t)))
         return CP_ERR_ARG;
-    const bool windowish = use == CP_PLAN_RESIDENT_WINDOW || shared || streamed || lanes;
+    const bool windowish = use == CP_PLAN_RESIDENT_WINDOW || shared || streamed || lanes || chain;
     const bool columnish = !windowish;       // wave-column, or its persistent column-slice form
     if (use == CP_PLAN_COLUMN_SLICE && (!tabs.magic_ok || k > kMagicMaxK)) return CP_ERR_ARG;
     // the wave-column plan reads CP off the stored b-levels; the window sweeps keep a running maximum
-    if (cp_out && !blevel_out && (!windowish || (!lanes && p.win_b.far_cap > 0))) return CP_ERR_ARG;
+    if (cp_out && !blevel_out && (!windowish || (!lanes && !chain && p.win_b.far_cap > 0))) return CP_ERR_ARG;
 
     // Device ids reach the resident-window sweep either straight from the caller's rows
     // (16-byte loads: the rows must be contiguous, and whole-buffer size and base must be
@@ -747,8 +798,8 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const bool rows_ok = assign_layout == CP_ASSIGN_PARTITION_MAJOR &&
                          ((uint64_t)p.n * (uint64_t)batch) % 16 == 0 && ((uintptr_t)assignments % 16) == 0;
     const bool direct_b = rows_ok && p.win_b.direct_ok, direct_t = rows_ok && p.win_t.direct_ok;
-    const bool gather_b = windowish && !lanes && (blevel_out || cp_out) && !direct_b;
-    const bool gather_t = windowish && !lanes && tlevel_out && !direct_t;
+    const bool gather_b = windowish && !lanes && !chain && (blevel_out || cp_out) && !direct_b;
+    const bool gather_t = windowish && !lanes && !chain && tlevel_out && !direct_t;
 
     // workspace: only what this call uses (cp_eval_workspace_bytes is an upper bound over
     // every way the call may go)
@@ -891,21 +942,26 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
 
     // ---- stage: b-level sweep
     CP_MARK(CP_STAGE_BLEVEL);
-    if (lanes) {
+    if (lanes || chain) {
+        s.dir = &p.col_b;
         s.edge_tab = d_tab;
         s.edge_tab4 = d_tab4;
         s.val = blevel_out;
         s.cp_out = cp_out;
         SweepLaunch t = s;
         t.tsweep = true;
+        t.dir = &p.col_t;
         t.edge_tab = d_tab + kk * 8;
         t.edge_tab4 = d_tab4 ? d_tab4 + kk : nullptr;
         t.val = tlevel_out;
         t.cp_out = nullptr;
-        rc = launch_window_lanes(s, t, p.lane_b, p.lane_t, lane_cfg, blevel_out || cp_out, tlevel_out != nullptr,
-                                 d_tab + tables_bytes(k), stream);
+        const bool want_b = blevel_out || cp_out;
+        rc = chain ? launch_chain(s, t, p.chain_b, p.chain_t, p.chain_width, p.info.min_tick_bytes, cost16, want_b,
+                                  tlevel_out != nullptr, chain_scratch, stream)
+                   : launch_window_lanes(s, t, p.lane_b, p.lane_t, lane_cfg, want_b, tlevel_out != nullptr,
+                                         d_tab + tables_bytes(k), stream);
         if (rc) return rc;
-        if (launches) launches[0] = 1;
+        if (launches) launches[chain && !want_b ? 1 : 0] = 1;
     } else if (blevel_out || cp_out) {
         s.tsweep = false;
         s.dir = &p.col_b;
@@ -958,7 +1014,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
 
     // ---- stage: t-level sweep
     CP_MARK(CP_STAGE_TLEVEL);
-    if (tlevel_out && !paired && !lanes) {
+    if (tlevel_out && !paired && !lanes && !chain) {
         s.tsweep = true;
         s.dir = &p.col_t;
         s.win = &p.win_t;
@@ -1007,6 +1063,31 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
 #undef CP_MARK
     return CP_OK;
 }
+
+}  // extern "C"
+
+namespace cpeval {
+
+size_t eval_chain_bytes(const cp_graph *g, bool both) {
+    const Packed &p = g->packed;
+    return p.have_chain ? chain_work_bytes(&p.chain_b, both ? &p.chain_t : nullptr, p.chain_width, 1, false) : 0;
+}
+
+int eval_one(const cp_graph *g, int32_t k, const uint8_t *assignment, const int64_t *speeds, const int64_t *bandwidth,
+             void *workspace, size_t workspace_bytes, void *stream, int64_t *cp_out, void *blevel_out, void *tlevel_out,
+             int tick_dtype, int out_layout, int32_t *status_out, uint8_t *chain_scratch, size_t chain_scratch_bytes) {
+    return eval_run(g, 1, k, assignment, CP_ASSIGN_PARTITION_MAJOR, speeds, bandwidth, workspace, workspace_bytes, stream,
+                    cp_out, blevel_out, tlevel_out, nullptr, tick_dtype, out_layout, CP_PLAN_AUTO, status_out, nullptr,
+                    /*tables_by_kernel=*/false, chain_scratch, chain_scratch_bytes);
+}
+
+int eval_one_bytes(const cp_graph *g, int32_t k, int out_layout, int tick_dtype, size_t *out_bytes) {
+    return eval_bytes(g, 1, k, CP_ASSIGN_PARTITION_MAJOR, CP_PLAN_AUTO, out_layout, tick_dtype, false, out_bytes);
+}
+
+}  // namespace cpeval
+
+extern "C" {
 
 int cp_eval(const cp_graph *g, int32_t batch, int32_t k,
             const uint8_t *assignments, int assign_layout,

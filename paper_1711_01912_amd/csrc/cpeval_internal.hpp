@@ -127,6 +127,29 @@ struct LaneDir {
 };
 inline uint32_t lane_unit_bytes(int width) { return 64u * (1u + (uint32_t)width); }
 
+// One sweep direction of the chain sweep (chain_sweep.hip).  A row is a vertex with its edges, four a lane in a group of 1, 2,
+// 4, 8 or 16 lanes; one of more than kChainRow edges is put together from rows with kChainRow of them each, in a stage of
+// its level before its own.  Rows are numbered as they are computed; a stage is one or more ticks of `chain_width` lanes.
+//   units     per lane {ring slots of the neighbours, 16 bits each, two words; ring slot written | log2 of the row's lanes
+//             << 16 | the same of the widest row in the wavefront << 20; vertex for the first lane of its row, else
+//             2^32 - 1}.  An edge that a lane does not have reads slot `slots`; lanes that are not the first of a
+//             row write slots behind it, one a lane
+//   edges     per lane {first edge in the CSR, the top bit set where the row is put together from others and its edges cost
+//             nothing; vertex, the top bit set in the rows that one is put together from, which leave w out}, {0, 2^32 - 1}
+//             for lanes without a row
+// Behind the ticks come one or more empty ones that are run through, to a multiple of kChainAhead in all, and kChainAhead
+// that are only read.
+struct ChainDir {
+    size_t unit_off = 0;     // uint32 [ticks][width][4]
+    size_t edge_off = 0;     // uint32 [ticks][width][2]
+    int32_t ticks = 0, slots = 0;
+};
+constexpr int kChainAhead = 8;           // ticks a lane's records are read ahead
+constexpr int32_t kChainRow = 64;        // edges of a row
+constexpr uint32_t kChainNobody = 0xffffffffu;
+constexpr int32_t kChainLevels = 256;    // levels from which a graph is packed for it
+constexpr size_t kChainLdsBytes = 152 * 1024;
+
 struct Packed {
     int32_t n = 0, L = 0;
     int64_t m = 0;
@@ -140,6 +163,9 @@ struct Packed {
     bool have_lanes = false;
     int32_t lane_word = 4;      // bytes of a ring word of the lane-window plan
     LaneDir lane_b, lane_t;
+    bool have_chain = false;
+    int32_t chain_width = 0;    // lanes of a workgroup of the chain sweep
+    ChainDir chain_b, chain_t;
     int32_t max_width = 0;
     int32_t hops = 0;           // L times the mean of 1 / (levels an edge climbs)
     std::vector<uint8_t> blob;  // host image of the device blob
@@ -150,7 +176,9 @@ struct Packed {
 // 10 bytes an edge and 700 a level, a lane packet 20 an edge, as a rule; pages that stay untouched cost nothing.
 inline size_t blob_room(int32_t n, int64_t m, int32_t L, bool narrow) {
     const size_t per_edge = 4 + (narrow ? 4 + 10 + 20 : 8), per_vertex = 24 + 8 + (narrow ? 16 + 40 : 0);
-    return 2 * ((size_t)m * per_edge + (size_t)n * per_vertex + (size_t)L * (narrow ? 700 : 32)) + (1 << 18);
+    // (a lane of the chain sweep takes 24 bytes: one a vertex and one for every four edges, or a few more)
+    const size_t chain = narrow && L >= kChainLevels ? 2 * 24 * ((size_t)n + (size_t)m / 4 + 64 * (size_t)L) : 0;
+    return 2 * ((size_t)m * per_edge + (size_t)n * per_vertex + (size_t)L * (narrow ? 700 : 32)) + (1 << 18) + chain;
 }
 
 // Validate and pack.  Returns CP_OK or an error code.

@@ -592,6 +592,154 @@ bool pack_lane_dir(BlobWriter &w, int32_t n, const int64_t *c, size_t word_bytes
     return true;
 }
 
+// Rows of the chain sweep in one direction (see ChainDir), level by level in sweep order, and inside a level stage by stage:
+// a vertex of more than kChainRow edges is put together from rows of the stages before its own.
+struct ChainRows {
+    struct Row {
+        int32_t vertex;
+        int32_t first, count;    // its edges in the CSR, or, `joins`, the rows that it is put together from
+        int8_t lanes_log2;
+        bool joins, part;        // part: a later row is put together from it
+    };
+    std::vector<Row> rows;
+    std::vector<int32_t> begin, lanes;       // of the stages: first row (and the end of the last one), lanes that its rows take
+    std::vector<int32_t> row_of;             // row of a vertex
+
+    ChainRows(int32_t n, int32_t L, const Csr &csr, const int32_t *level_ptr, const int32_t *level_vtx, bool forward)
+        : row_of((size_t)n) {
+        rows.reserve((size_t)n);
+        std::vector<Row> now, later;
+        for (int32_t s = 0; s < L; ++s) {
+            const int32_t l = forward ? s : L - 1 - s;
+            now.clear();
+            for (int32_t i = level_ptr[l]; i < level_ptr[l + 1]; ++i) {
+                const int32_t v = level_vtx[i], d = csr.ptr[v + 1] - csr.ptr[v];
+                int8_t lg = 0;
+                while (4 << lg < std::min(d, kChainRow)) ++lg;
+                now.push_back({v, csr.ptr[v], d, lg, false, false});
+            }
+            for (; !now.empty(); now.swap(later)) put_stage(now, later);
+        }
+        begin.push_back((int32_t)rows.size());
+    }
+
+  private:
+    // Parts first, then rows of most lanes: the lanes of a row are an aligned group.
+    void put_stage(const std::vector<Row> &now, std::vector<Row> &later) {
+        constexpr int8_t kMost = 4;
+        static_assert(4 << kMost == kChainRow, "a row's lanes hold four edges each");
+        begin.push_back((int32_t)rows.size());
+        int32_t taken = 0, of[kMost + 1] = {};
+        later.clear();
+        for (const Row &r : now) {
+            if (r.count <= kChainRow) {
+                ++of[r.lanes_log2];
+                continue;
+            }
+            const int32_t parts = (r.count + kChainRow - 1) / kChainRow;
+            int8_t lg = 0;
+            while (4 << lg < std::min(parts, kChainRow)) ++lg;
+            later.push_back({r.vertex, (int32_t)rows.size(), parts, lg, true, false});
+            for (int32_t i = 0; i < parts; ++i)
+                rows.push_back({r.vertex, r.first + i * kChainRow, std::min(kChainRow, r.count - i * kChainRow), kMost,
+                                r.joins, true});
+            taken += parts << kMost;
+        }
+        int32_t at[kMost + 1];
+        int32_t next = (int32_t)rows.size();
+        for (int lg = kMost; lg >= 0; --lg) {
+            at[lg] = next;
+            next += of[lg];
+            taken += of[lg] << lg;
+        }
+        rows.resize((size_t)next);
+        for (const Row &r : now) {
+            if (r.count > kChainRow) continue;
+            const int32_t to = at[r.lanes_log2]++;
+            rows[to] = r;
+            row_of[r.vertex] = to;
+        }
+        lanes.push_back(taken);
+    }
+};
+
+// Lanes of a workgroup for these stages: a tick costs 0.1 us and 0.016 a wavefront, whether its lanes are filled or not.
+int32_t chain_width(const ChainRows &b, const ChainRows &t) {
+    int32_t best = 0;
+    double best_us = 0;
+    for (int32_t waves : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
+        double us = 0;
+        for (const ChainRows *r : {&b, &t}) {
+            int64_t ticks = 0;
+            for (int32_t u : r->lanes) ticks += (u + 64 * waves - 1) / (64 * waves);
+            us = std::max(us, (double)ticks * (0.1 + 0.016 * waves));
+        }
+        if (best == 0 || us < best_us) {
+            best_us = us;
+            best = 64 * waves;
+        }
+    }
+    return best;
+}
+
+// Packing of one direction for the chain sweep (layout: see ChainDir).  Returns false if its ring would be too long.
+bool pack_chain_dir(BlobWriter &w, size_t word_bytes, const Csr &csr, const ChainRows &r, int32_t width, ChainDir &dir) {
+    int64_t ticks = 0, all = 0;
+    int32_t far = 0;
+    for (int32_t u : r.lanes) {
+        ticks += (u + width - 1) / width;
+        all += u;
+    }
+    for (int32_t i = 0; i < (int32_t)r.rows.size(); ++i) {
+        const ChainRows::Row &x = r.rows[i];
+        if (x.joins && x.count > 0) far = std::max(far, i - x.first);
+        else
+            for (int32_t e = x.first; e < x.first + x.count; ++e) far = std::max(far, i - r.row_of[csr.idx[e]]);
+    }
+    const int64_t slots = (int64_t)far + 2 * std::min<int64_t>(width, (int64_t)r.rows.size());
+    if ((size_t)(slots + 1 + kWave) * word_bytes > kChainLdsBytes) return false;
+    ticks = (ticks + 1 + kChainAhead - 1) / kChainAhead * kChainAhead + kChainAhead;
+    if (ticks * width >= (int64_t)1 << 27 || ticks * width > 8 * all + (1 << 20)) return false;
+    dir.ticks = (int32_t)ticks;
+    dir.slots = (int32_t)slots;
+    dir.unit_off = w.reserve((size_t)ticks * width * 16);
+    dir.edge_off = w.reserve((size_t)ticks * width * 8);
+    uint32_t *const units = w.at<uint32_t>(dir.unit_off), *const edges = w.at<uint32_t>(dir.edge_off);
+    const uint32_t none = (uint32_t)slots;
+    int64_t at = 0;                          // units so far
+    uint32_t steps = 0;                      // of the wavefront at hand: its first row has the most lanes
+    auto put = [&](uint32_t slot, uint32_t lg, uint32_t leads, uint32_t first, uint32_t vertex) {
+        uint32_t *u = units + 4 * at, *x = edges + 2 * at;
+        if (at % kWave == 0) steps = lg;
+        u[0] = u[1] = none | none << 16;
+        u[2] = (slot == none ? none + 1 + (uint32_t)(at % kWave) : slot) | lg << 16 | steps << 20;
+        u[3] = leads;
+        x[0] = first;
+        x[1] = vertex;
+        ++at;
+        return (uint16_t *)u;
+    };
+    for (size_t s = 0; s < r.lanes.size(); ++s) {
+        for (int32_t i = r.begin[s]; i < r.begin[s + 1]; ++i) {
+            const ChainRows::Row &x = r.rows[i];
+            const uint32_t flags = (uint32_t)x.vertex | (x.part ? 1u << 31 : 0);
+            for (int32_t j = 0; j < 1 << x.lanes_log2; ++j) {
+                const int32_t first = x.first + 4 * j;
+                uint16_t *u = put(j == 0 ? (uint32_t)(i % (int32_t)slots) : none, (uint32_t)x.lanes_log2,
+                                  j == 0 && !x.part ? (uint32_t)x.vertex : kChainNobody,
+                                  (uint32_t)first | (x.joins ? 1u << 31 : 0), flags);
+                for (int32_t e = 0; e < std::min(4, x.count - 4 * j); ++e) {
+                    const int32_t from = x.joins ? first + e : r.row_of[csr.idx[first + e]];
+                    u[e] = (uint16_t)(from % (int32_t)slots);
+                }
+            }
+        }
+        while (at % width) put(none, 0, kChainNobody, 0, kChainNobody);
+    }
+    while (at < ticks * width) put(none, 0, kChainNobody, 0, kChainNobody);
+    return true;
+}
+
 }  // namespace
 
 int pack_graph(int32_t n, int64_t m, int32_t L,
@@ -745,6 +893,15 @@ int pack_graph(int32_t n, int64_t m, int32_t L,
             P.have_lanes = pack_lane_dir(w, n, c, (size_t)P.lane_word, width, succ, level_ptr, level_vtx, false, P.col_b, P.lane_b) &&
                            pack_lane_dir(w, n, c, (size_t)P.lane_word, width, pred, level_ptr, level_vtx, true, P.col_t, P.lane_t);
             if (!P.have_lanes) P.blob.resize(mark);
+        }
+        P.have_chain = false;
+        if (L >= kChainLevels && n < (1 << 24) - 1 && (uint64_t)max_c + (uint64_t)max_t < (1ull << 32)) {
+            const size_t mark = P.blob.size(), word = (size_t)info.min_tick_bytes;
+            const ChainRows rows_b(n, L, succ, level_ptr, level_vtx, false), rows_t(n, L, pred, level_ptr, level_vtx, true);
+            P.chain_width = chain_width(rows_b, rows_t);
+            P.have_chain = pack_chain_dir(w, word, succ, rows_b, P.chain_width, P.chain_b) &&
+                           pack_chain_dir(w, word, pred, rows_t, P.chain_width, P.chain_t);
+            if (!P.have_chain) P.blob.resize(mark);
         }
         P.blob.resize(align_up(P.blob.size()));
     } catch (const std::bad_alloc &) {

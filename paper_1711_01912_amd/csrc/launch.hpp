@@ -161,6 +161,13 @@ size_t lane_work_bytes(const LaneDir *db, const LaneDir *dt, int32_t n, int32_t 
 int launch_window_lanes(const SweepLaunch &sb, const SweepLaunch &st, const LaneDir &db, const LaneDir &dt,
                         const LaneCfg &cfg, bool want_b, bool want_t, uint8_t *ids, void *stream);
 
+// The chain sweep of a few partitions (null: not that sweep): what a call's costs take, LDS of a workgroup, the launches.
+// cost16: no edge's cost and its vertex's w together reach 2^16.
+size_t chain_work_bytes(const ChainDir *db, const ChainDir *dt, int32_t width, int32_t P, bool cost16);
+size_t chain_lds_bytes(const ChainDir &d, int word_bytes);
+int launch_chain(const SweepLaunch &sb, const SweepLaunch &st, const ChainDir &db, const ChainDir &dt, int32_t width,
+                 int word_bytes, bool cost16, bool want_b, bool want_t, uint8_t *work, void *stream);
+
 // False if the direction cannot run under `lds_limit` bytes of LDS.
 // with_mask: the t sweep also stages the tick's b values and writes the mask.
 bool window_config(const WindowDir &d, int32_t k, size_t tick_bytes, size_t lds_limit, WindowCfg &out,
@@ -300,6 +307,13 @@ inline bool path_by_jumps(int32_t n, int32_t P, int32_t L, int32_t hops) {
 inline bool path_by_records(int32_t n, int64_t m, int32_t L, int32_t hops) {
     return L >= 256 && n / L < 1024 && m / n <= 5 && hops >= 64;
 }
+// cp_eval of one partition (CP_PLAN_AUTO) with scratch of its own for the chain sweep (eval_chain_bytes), or null;
+// `workspace` as for a call that goes without it (eval_one_bytes).
+size_t eval_chain_bytes(const cp_graph *g, bool both);
+int eval_one_bytes(const cp_graph *g, int32_t k, int out_layout, int tick_dtype, size_t *out_bytes);
+int eval_one(const cp_graph *g, int32_t k, const uint8_t *assignment, const int64_t *speeds, const int64_t *bandwidth,
+             void *workspace, size_t workspace_bytes, void *stream, int64_t *cp_out, void *blevel_out, void *tlevel_out,
+             int tick_dtype, int out_layout, int32_t *status_out, uint8_t *chain_scratch, size_t chain_scratch_bytes);
 // cp_critical_path with scratch for the jumps or null; with it, what lies behind the path in path_out stays as it was.
 int critical_path(const cp_graph *g, int32_t batch, int32_t k, const uint8_t *assignments, int assign_layout,
                   const int64_t *speeds, const int64_t *bandwidth, const void *blevel, const int64_t *cp,

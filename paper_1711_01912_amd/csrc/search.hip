@@ -761,7 +761,7 @@ __global__ __launch_bounds__(256) void seed_keys_kernel(SeedArgs a) {
 
 struct SearchLayout {
     size_t eval_ws = 0, b = 0, tl = 0, level = 0, over = 0, slot_at = 0, want = 0, mine = 0, slots = 0, path = 0,
-           small = 0, total = 0, jumps = 0;
+           small = 0, total = 0, jumps = 0, chain = 0;
     size_t eval_bytes = 0;
     int rows_over = 1;       // rows of the level-range tables: ranges of 1, 2, 4, ... levels
     int tick = 4;
@@ -775,7 +775,7 @@ int search_layout(const cp_graph *g, int32_t k, SearchLayout &o) {
     // one row of outputs is the same in either layout; room for whichever way the call goes
     for (int layout : {CP_OUT_VERTEX_MAJOR, CP_OUT_PARTITION_MAJOR}) {
         size_t ws = 0;
-        rc = cp_eval_workspace_bytes(g, 1, k, CP_ASSIGN_PARTITION_MAJOR, CP_PLAN_AUTO, layout, o.tick, &ws);
+        rc = eval_one_bytes(g, k, layout, o.tick, &ws);
         if (rc) return rc;
         o.eval_bytes = std::max(o.eval_bytes, align_up(ws));
     }
@@ -793,8 +793,9 @@ int search_layout(const cp_graph *g, int32_t k, SearchLayout &o) {
     o.slots = at;   at += align_up(L * sizeof(SlotBest));
     o.path = at;    at += align_up(L * sizeof(int32_t));
     o.small = at;   at += kAlign;        // StepResult, broken constraints
-    o.total = at;                        // (the path's jumps are optional: an array of this size still serves)
+    o.total = at;           // (the path's jumps and the chain sweep's costs are optional: an array of this size still serves)
     o.jumps = path_by_jumps(info.n, 1, info.L, g->packed.hops) ? align_up(path_jump_words(info.n) * sizeof(int32_t)) : 0;
+    o.chain = eval_chain_bytes(g, true);
     return CP_OK;
 }
 
@@ -841,7 +842,7 @@ int cp_search_workspace_bytes(const cp_graph *g, int32_t k, int32_t chunk, size_
     SearchLayout lay;
     int rc = search_layout(g, k, lay);
     if (rc) return rc;
-    *out_bytes = lay.total + lay.jumps;
+    *out_bytes = lay.total + lay.jumps + lay.chain;
     return CP_OK;
 }
 
@@ -903,6 +904,7 @@ int cp_search(const cp_graph *g, int32_t k, const int64_t *speeds, const int64_t
     a.rows_over = lay.rows_over;
     a.constrained = num_pairs > 0 || num_pins > 0;
     int32_t *jumps = lay.jumps && workspace_bytes >= lay.total + lay.jumps ? (int32_t *)(ws + lay.total) : nullptr;
+    uint8_t *chain = lay.chain && workspace_bytes >= lay.total + lay.jumps + lay.chain ? ws + lay.total + lay.jumps : nullptr;
     const bool stepping = max_moves > 0 && k > 1;
     int32_t done = 0;
     int64_t seen = 0;
@@ -911,9 +913,8 @@ int cp_search(const cp_graph *g, int32_t k, const int64_t *speeds, const int64_t
         hipLaunchKernelGGL(level_kernel, dim3((unsigned)((info.n + 255) / 256)), dim3(256), 0, st, a);
     for (;;) {
         // the current partition: CP, both levels, one critical path
-        rc = cp_eval(g, 1, k, assignment, CP_ASSIGN_PARTITION_MAJOR, speeds, bandwidth, ws + lay.eval_ws,
-                     lay.eval_bytes, stream, &a.res->cp, ws + lay.b, ws + lay.tl, nullptr, lay.tick, layout,
-                     CP_PLAN_AUTO, &a.res->status[0], nullptr);
+        rc = eval_one(g, k, assignment, speeds, bandwidth, ws + lay.eval_ws, lay.eval_bytes, stream, &a.res->cp,
+                      ws + lay.b, ws + lay.tl, lay.tick, layout, &a.res->status[0], chain, lay.chain);
         if (rc) return rc;
         rc = critical_path(g, 1, k, assignment, CP_ASSIGN_PARTITION_MAJOR, speeds, bandwidth, ws + lay.b,
                            &a.res->cp, lay.tick, layout, ws + lay.eval_ws, lay.eval_bytes, stream, info.L,
@@ -956,25 +957,25 @@ int cp_search(const cp_graph *g, int32_t k, const int64_t *speeds, const int64_t
     return CP_OK;
 }
 
-static int seed_bytes(const cp_graph *g, size_t *out_bytes, size_t *jump_bytes) {
+static int seed_bytes(const cp_graph *g, size_t *out_bytes, size_t *jump_bytes, size_t *chain_bytes) {
     if (!g || !out_bytes) return CP_ERR_NULL;
     cp_graph_info info;
     int rc = cp_graph_get_info(g, &info);
     if (rc) return rc;
     size_t eval = 0;
-    rc = cp_eval_workspace_bytes(g, 1, 1, CP_ASSIGN_PARTITION_MAJOR, CP_PLAN_AUTO, CP_OUT_VERTEX_MAJOR,
-                                 info.min_tick_bytes, &eval);
+    rc = eval_one_bytes(g, 1, CP_OUT_VERTEX_MAJOR, info.min_tick_bytes, &eval);
     if (rc) return rc;
     *out_bytes = align_up(eval) + align_up((size_t)info.n) + align_up((size_t)info.n * (size_t)info.min_tick_bytes) +
                  align_up((size_t)info.L * sizeof(int32_t)) + kAlign;
     *jump_bytes = path_by_jumps(info.n, 1, info.L, g->packed.hops) ? align_up(path_jump_words(info.n) * sizeof(int32_t)) : 0;
+    *chain_bytes = eval_chain_bytes(g, false);
     return CP_OK;
 }
 
 int cp_seed_workspace_bytes(const cp_graph *g, size_t *out_bytes) {
-    size_t jump_bytes = 0;
-    const int rc = seed_bytes(g, out_bytes, &jump_bytes);
-    if (rc == CP_OK) *out_bytes += jump_bytes;
+    size_t jump_bytes = 0, chain_bytes = 0;
+    const int rc = seed_bytes(g, out_bytes, &jump_bytes, &chain_bytes);
+    if (rc == CP_OK) *out_bytes += jump_bytes + chain_bytes;
     return rc;
 }
 
@@ -982,8 +983,8 @@ int cp_seed_partition(const cp_graph *g, int32_t k, const int64_t *speeds, void 
                       void *stream, uint8_t *assignment_out, int32_t *status_out) {
     if (!g || !speeds || !workspace || !assignment_out || !status_out) return CP_ERR_NULL;
     if (k < 1 || k > kSeedMaxK) return CP_ERR_SIZE;
-    size_t need = 0, jump_bytes = 0;         // (the path's jumps are optional: an array of `need` bytes still serves)
-    int rc = seed_bytes(g, &need, &jump_bytes);
+    size_t need = 0, jump_bytes = 0, chain_bytes = 0;        // (only `need` bytes are asked for)
+    int rc = seed_bytes(g, &need, &jump_bytes, &chain_bytes);
     if (rc) return rc;
     if (((uintptr_t)workspace % kAlign) != 0 || workspace_bytes < need) return CP_ERR_WORKSPACE;
     cp_graph_info info;
@@ -1000,8 +1001,7 @@ int cp_seed_partition(const cp_graph *g, int32_t k, const int64_t *speeds, void 
     }
     if (rc) return rc;
     size_t eval = 0;
-    rc = cp_eval_workspace_bytes(g, 1, 1, CP_ASSIGN_PARTITION_MAJOR, CP_PLAN_AUTO, CP_OUT_VERTEX_MAJOR,
-                                 info.min_tick_bytes, &eval);
+    rc = eval_one_bytes(g, 1, CP_OUT_VERTEX_MAJOR, info.min_tick_bytes, &eval);
     if (rc) return rc;
     const size_t n = (size_t)info.n;
     const int T = info.min_tick_bytes;
@@ -1017,8 +1017,9 @@ int cp_seed_partition(const cp_graph *g, int32_t k, const int64_t *speeds, void 
     rc = launch_zero_bytes(d_one, (int64_t)n, stream);
     if (rc) return rc;
     const int64_t unit = 1;
-    rc = cp_eval(g, 1, 1, d_one, CP_ASSIGN_PARTITION_MAJOR, &unit, &unit, ws, align_up(eval), stream, d_cp, d_b,
-                 nullptr, nullptr, T, CP_OUT_VERTEX_MAJOR, CP_PLAN_AUTO, status_out, nullptr);
+    uint8_t *chain = chain_bytes && workspace_bytes >= need + jump_bytes + chain_bytes ? ws + need + jump_bytes : nullptr;
+    rc = eval_one(g, 1, d_one, &unit, &unit, ws, align_up(eval), stream, d_cp, d_b, nullptr, T, CP_OUT_VERTEX_MAJOR,
+                  status_out, chain, chain_bytes);
     if (rc) return rc;
     int32_t *jumps = jump_bytes && workspace_bytes >= need + jump_bytes ? (int32_t *)(ws + need) : nullptr;
     rc = critical_path(g, 1, 1, d_one, CP_ASSIGN_PARTITION_MAJOR, &unit, &unit, d_b, d_cp, T, CP_OUT_VERTEX_MAJOR, ws,
