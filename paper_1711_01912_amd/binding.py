@@ -21,7 +21,7 @@ ASSIGN_PARTITION_MAJOR, ASSIGN_VERTEX_MAJOR = 0, 1
 OUT_VERTEX_MAJOR, OUT_PARTITION_MAJOR = 0, 1
 PLAN_AUTO, PLAN_WAVE_COLUMN, PLAN_RESIDENT_WINDOW, PLAN_SHARED_WINDOW_2, PLAN_SHARED_WINDOW_4 = 0, 1, 2, 3, 4
 PLAN_COLUMN_SLICE, PLAN_STREAMED_WINDOW, PLAN_LANE_WINDOW = 5, 6, 7
-PLAN_CHAIN = 8     # only told by CpProfile.plan
+PLAN_CHAIN, PLAN_WHOLE = 8, 9     # only told by CpProfile.plan
 NUM_STAGES = 5
 STAGE_NAMES = ("prep", "blevel", "cp", "tlevel", "mask")
 STATUS_BAD_DEVICE_ID = 1
@@ -95,10 +95,10 @@ def load_library():
     lib.cp_eval_choose_plan.restype = C.c_int
     lib.cp_eval_choose_plan.argtypes = [vp, C.c_int32, C.c_int32, i64p, i64p, C.c_int, C.POINTER(C.c_int)]
     lib.cp_eval.restype = C.c_int
-    lib.cp_eval.argtypes = [vp, C.c_int32, C.c_int32, vp, C.c_int, i64p, i64p, vp, C.c_size_t, vp,
+    lib.cp_eval.argtypes = [vp, C.c_int32, C.c_int32, vp, C.c_int, vp, vp, vp, C.c_size_t, vp,
                             vp, vp, vp, vp, C.c_int, C.c_int, C.c_int, vp, vp]
     lib.cp_eval_static.restype = C.c_int
-    lib.cp_eval_static.argtypes = [vp, C.c_int32, C.c_int32, vp, C.c_int, i64p, i64p, vp,
+    lib.cp_eval_static.argtypes = [vp, C.c_int32, C.c_int32, vp, C.c_int, vp, vp, vp,
                                    vp, vp, vp, vp, C.c_int, C.c_int, C.c_int, vp]
     lib.cp_critical_path.restype = C.c_int
     lib.cp_critical_path.argtypes = [vp, C.c_int32, C.c_int32, vp, C.c_int, i64p, i64p, vp, vp, C.c_int, C.c_int,
@@ -213,6 +213,10 @@ class CpGraph:
         if rc:
             self._handle = C.c_void_p()
             raise CpError(rc, "cp_graph_create")
+        # what a graph is from its creation on (`info` asks the library and makes a dict of 27 entries: a quarter of a
+        # small call's time in Python)
+        info = self.info
+        self._n, self._L, self._min_tick_bytes = info["n"], info["L"], info["min_tick_bytes"]
         if device is not None:
             self.upload(device)
 
@@ -319,7 +323,7 @@ def workspace_bytes(graph: CpGraph, batch: int, k: int, assign_layout=ASSIGN_PAR
                     plan=PLAN_AUTO, out_layout=OUT_VERTEX_MAJOR, tick_bytes=None) -> int:
     out = C.c_size_t(0)
     if tick_bytes is None:
-        tick_bytes = graph.info["min_tick_bytes"]
+        tick_bytes = graph._min_tick_bytes
     rc = load_library().cp_eval_workspace_bytes(graph._handle, int(batch), int(k), int(assign_layout),
                                                 int(plan), int(out_layout), int(tick_bytes), C.byref(out))
     if rc:
@@ -360,8 +364,7 @@ def cp_eval(graph: CpGraph, assignments, speeds, bandwidth, *, want=("cp", "b", 
     """
     import torch
     lib = load_library()
-    info = graph.info
-    n = info["n"]
+    n = graph._n
     assert assignments.is_cuda and assignments.dtype == torch.uint8 and assignments.is_contiguous()
     if assign_layout == ASSIGN_PARTITION_MAJOR:
         batch = int(assignments.shape[0])
@@ -374,7 +377,7 @@ def cp_eval(graph: CpGraph, assignments, speeds, bandwidth, *, want=("cp", "b", 
     k = int(s.shape[0])
     assert bw.shape == (k, k)
     if tick_bytes is None:
-        tick_bytes = info["min_tick_bytes"]
+        tick_bytes = graph._min_tick_bytes
     tdt = torch.int32 if tick_bytes == 4 else torch.int64
     dev = assignments.device
     out = dict(out) if out else {}
@@ -385,7 +388,7 @@ def cp_eval(graph: CpGraph, assignments, speeds, bandwidth, *, want=("cp", "b", 
         # CP alone: the window plans need no b array for it, without far reads; the lane-window plan never does
         used = plan if plan != PLAN_AUTO else choose_plan(graph, batch, s, bw, tick_bytes)
         window = (PLAN_RESIDENT_WINDOW, PLAN_SHARED_WINDOW_2, PLAN_SHARED_WINDOW_4, PLAN_STREAMED_WINDOW)
-        if used != PLAN_LANE_WINDOW and (used not in window or info["window_far_b"] > 0):
+        if used != PLAN_LANE_WINDOW and (used not in window or graph.info["window_far_b"] > 0):
             want.add("b")
     rows, cols = (n, batch) if out_layout == OUT_VERTEX_MAJOR else (batch, n)
     if "cp" in want and "cp" not in out:
@@ -398,25 +401,25 @@ def cp_eval(graph: CpGraph, assignments, speeds, bandwidth, *, want=("cp", "b", 
         out["mask"] = torch.empty((rows, (cols + 63) // 64), dtype=torch.int64, device=dev)
     if "status" not in out:
         out["status"] = torch.empty(1, dtype=torch.int32, device=dev)
-    ptr = lambda key: C.c_void_p(out[key].data_ptr()) if key in want else C.c_void_p()
+    # (addresses as plain numbers: a ctypes object for each would be a quarter of a small call's time in Python)
+    ptr = lambda key: out[key].data_ptr() if key in want else None
+    costs = s.ctypes.data, bw.ctypes.data
     if static:
         assert workspace is None and profile is None
-        rc = lib.cp_eval_static(graph._handle, batch, k, C.c_void_p(assignments.data_ptr()), int(assign_layout),
-                                _np_ptr(s, C.c_int64), _np_ptr(bw, C.c_int64), _stream_ptr(stream),
+        rc = lib.cp_eval_static(graph._handle, batch, k, assignments.data_ptr(), int(assign_layout),
+                                *costs, _stream_ptr(stream),
                                 ptr("cp"), ptr("b"), ptr("tl"), ptr("mask"), int(tick_bytes), int(out_layout),
-                                int(plan), C.c_void_p(out["status"].data_ptr()))
+                                int(plan), out["status"].data_ptr())
         if rc:
             raise CpError(rc, "cp_eval_static")
     else:
         if workspace is None:
             workspace = torch.empty(workspace_bytes(graph, batch, k, assign_layout, plan, out_layout, tick_bytes),
                                     dtype=torch.uint8, device=dev)
-        rc = lib.cp_eval(graph._handle, batch, k, C.c_void_p(assignments.data_ptr()), int(assign_layout),
-                         _np_ptr(s, C.c_int64), _np_ptr(bw, C.c_int64),
-                         C.c_void_p(workspace.data_ptr()), C.c_size_t(workspace.numel()), _stream_ptr(stream),
+        rc = lib.cp_eval(graph._handle, batch, k, assignments.data_ptr(), int(assign_layout),
+                         *costs, workspace.data_ptr(), workspace.numel(), _stream_ptr(stream),
                          ptr("cp"), ptr("b"), ptr("tl"), ptr("mask"), int(tick_bytes), int(out_layout), int(plan),
-                         C.c_void_p(out["status"].data_ptr()),
-                         C.c_void_p(profile._handle.value) if profile is not None else C.c_void_p())
+                         out["status"].data_ptr(), profile._handle.value if profile is not None else None)
         if rc:
             raise CpError(rc, "cp_eval")
         out["_workspace"] = workspace  # keep it alive until the caller drops the result
@@ -444,13 +447,12 @@ def cp_critical_path(graph: CpGraph, assignments, speeds, bandwidth, b, cp, *,
     lengths int32 [batch])."""
     import torch
     lib = load_library()
-    info = graph.info
     s = np.ascontiguousarray(speeds, dtype=np.int64)
     bw = np.ascontiguousarray(bandwidth, dtype=np.int64)
     k = int(s.shape[0])
     batch = int(cp.shape[0])
     dev = assignments.device
-    max_len = info["L"]
+    max_len = graph._L
     paths = torch.empty((batch, max_len), dtype=torch.int32, device=dev)
     lens = torch.empty(batch, dtype=torch.int32, device=dev)
     status = torch.empty(1, dtype=torch.int32, device=dev)
@@ -482,7 +484,7 @@ def cp_pct_order(graph: CpGraph, assignments, k: int, b, *, max_b: int = 0,
     assignments.  Returns (order int32 [batch][n], seg int32 [batch][k+1])."""
     import torch
     lib = load_library()
-    n = graph.info["n"]
+    n = graph._n
     batch = int(b.shape[1] if b_layout == OUT_VERTEX_MAJOR else b.shape[0])
     dev = b.device
     if workspace is None:
@@ -565,7 +567,7 @@ def cp_simulate(graph: CpGraph, assignments, speeds, bandwidth, policy, *, b=Non
     import torch
     lib = load_library()
     dev = assignments.device
-    n = graph.info["n"]
+    n = graph._n
     batch = int(assignments.shape[0] if assign_layout == ASSIGN_PARTITION_MAJOR else assignments.shape[1])
     s = np.ascontiguousarray(speeds, dtype=np.int64)
     bw = np.ascontiguousarray(bandwidth, dtype=np.int64)
@@ -674,7 +676,7 @@ def cp_ranks(graph: CpGraph, *, stream=None):
     import torch
     lib = load_library()
     dev = graph.blob.device
-    n = graph.info["n"]
+    n = graph._n
     need = C.c_size_t(0)
     rc = lib.cp_ranks_workspace_bytes(graph._handle, C.byref(need))
     if rc:
