@@ -44,7 +44,7 @@ TRAFFIC_SOURCES = ("kernels.hip", "window_shared.hip", "window_lanes.hip", "grap
 
 
 PLAN_NAMES = {1: "wave-column", 2: "resident-window", 3: "shared-window-2", 4: "shared-window-4", 5: "column-slice",
-              6: "streamed-window", 7: "lane-window", 8: "chain"}
+              6: "streamed-window", 7: "lane-window", 8: "chain", 9: "whole-graph"}
 
 
 def sources_digest():

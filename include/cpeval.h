@@ -97,6 +97,8 @@ extern "C" {
 #define CP_PLAN_CHAIN            8   /* only told by cp_profile_plan, never accepted: what CP_PLAN_AUTO may run for up to 64
                                         partitions of a graph of many levels.  One workgroup = one sweep of one partition,
                                         behind a launch that writes what every edge costs under it */
+#define CP_PLAN_WHOLE            9   /* only told by cp_profile_plan as well: CP_PLAN_AUTO's way with small graphs.  One workgroup =
+                                        4 or 8 partitions, all values in LDS; a call is one launch, or two */
 
 /* stages of one cp_eval call, in the order they run; also the index into cp_profile_read's output */
 #define CP_STAGE_PREP    0   /* clear outputs, cost tables, assignment transpose */
@@ -186,7 +188,7 @@ int cp_eval_workspace_bytes(const cp_graph *g, int32_t batch, int32_t k, int ass
  * directly, or whether CP can be had without b).  Where the lane-window plan is faster for
  * the call at hand, which depends on its outputs, layouts and workspace, AUTO runs that one in
  * its place, with the same results and the same refusals: it is never the answer here, and
- * cp_profile_plan tells what a call ran; the same holds for CP_PLAN_CHAIN.  Errors: as cp_eval's argument checks.
+ * cp_profile_plan tells what a call ran; the same holds for CP_PLAN_CHAIN and CP_PLAN_WHOLE.  Errors: as cp_eval's argument checks.
  */
 int cp_eval_choose_plan(const cp_graph *g, int32_t batch, int32_t k, const int64_t *speeds,
                         const int64_t *bandwidth, int tick_dtype, int *plan_out);

@@ -19,6 +19,7 @@ from .binding import (  # noqa: F401
     PLAN_STREAMED_WINDOW,
     PLAN_SHARED_WINDOW_4,
     PLAN_WAVE_COLUMN,
+    PLAN_WHOLE,
     POLICY_FIFO,
     POLICY_PCT,
     cost_compact,

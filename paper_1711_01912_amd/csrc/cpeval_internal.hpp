@@ -150,6 +150,20 @@ constexpr uint32_t kChainNobody = 0xffffffffu;
 constexpr int32_t kChainLevels = 256;    // levels from which a graph is packed for it
 constexpr size_t kChainLdsBytes = 152 * 1024;
 
+// The whole-graph sweep (whole_sweep.hip).  A unit is up to four edges of a vertex, 32 bytes:
+//   {neighbours, 16 bits each, two words; vertex; c} {t of the edges}
+// An edge that a unit does not have names vertex n, with t = 0; units without a vertex are of vertex n + 1.  A tick is
+// `units_a_tick` units of one level; both sweeps have as many ticks, a multiple of kWholeAhead, and kWholeAhead empty ones
+// behind them that are only read.
+struct WholeDir {
+    size_t units_b = 0, units_t = 0;         // [ticks + kWholeAhead][units_a_tick]
+    int32_t ticks = 0, units_a_tick = 0;
+};
+constexpr int kWholeAhead = 4;
+// Two groups of 4 partitions on a compute unit.  Larger graphs, which leave it to one, are slower than under the lane-window plan:
+// 3,600 vertices in 60 levels, 8 and 4,096 partitions 57 and 224 us against 45 and 168.
+constexpr int32_t kWholeVertices = 2048;
+
 struct Packed {
     int32_t n = 0, L = 0;
     int64_t m = 0;
@@ -163,6 +177,8 @@ struct Packed {
     bool have_lanes = false;
     int32_t lane_word = 4;      // bytes of a ring word of the lane-window plan
     LaneDir lane_b, lane_t;
+    bool have_whole = false;
+    WholeDir whole;
     bool have_chain = false;
     int32_t chain_width = 0;    // lanes of a workgroup of the chain sweep
     ChainDir chain_b, chain_t;
@@ -178,7 +194,9 @@ inline size_t blob_room(int32_t n, int64_t m, int32_t L, bool narrow) {
     const size_t per_edge = 4 + (narrow ? 4 + 10 + 20 : 8), per_vertex = 24 + 8 + (narrow ? 16 + 40 : 0);
     // (a lane of the chain sweep takes 24 bytes: one a vertex and one for every four edges, or a few more)
     const size_t chain = narrow && L >= kChainLevels ? 2 * 24 * ((size_t)n + (size_t)m / 4 + 64 * (size_t)L) : 0;
-    return 2 * ((size_t)m * per_edge + (size_t)n * per_vertex + (size_t)L * (narrow ? 700 : 32)) + (1 << 18) + chain;
+    // (a unit of the whole-graph sweep 32, and up to 64 units a tick of a level)
+    const size_t whole = narrow && n <= kWholeVertices ? 2 * 32 * ((size_t)n + (size_t)m / 4 + 64 * (size_t)L + 512) : 0;
+    return 2 * ((size_t)m * per_edge + (size_t)n * per_vertex + (size_t)L * (narrow ? 700 : 32)) + (1 << 18) + chain + whole;
 }
 
 // Validate and pack.  Returns CP_OK or an error code.

@@ -706,6 +706,12 @@ bool pack_chain_dir(BlobWriter &w, size_t word_bytes, const Csr &csr, const Chai
     dir.edge_off = w.reserve((size_t)ticks * width * 8);
     uint32_t *const units = w.at<uint32_t>(dir.unit_off), *const edges = w.at<uint32_t>(dir.edge_off);
     const uint32_t none = (uint32_t)slots;
+    // ring slots of the rows, and of the vertices (one look at an edge's neighbour instead of two and a division)
+    std::unique_ptr<uint16_t[]> slot_of(new uint16_t[r.rows.size()]), slot_at(new uint16_t[r.row_of.size()]);
+    for (size_t i = 0, at = 0; i < r.rows.size(); ++i, at = at + 1 == (size_t)slots ? 0 : at + 1) {
+        slot_of[i] = (uint16_t)at;
+        if (!r.rows[i].part) slot_at[r.rows[i].vertex] = (uint16_t)at;
+    }
     int64_t at = 0;                          // units so far
     uint32_t steps = 0;                      // of the wavefront at hand: its first row has the most lanes
     auto put = [&](uint32_t slot, uint32_t lg, uint32_t leads, uint32_t first, uint32_t vertex) {
@@ -725,19 +731,79 @@ bool pack_chain_dir(BlobWriter &w, size_t word_bytes, const Csr &csr, const Chai
             const uint32_t flags = (uint32_t)x.vertex | (x.part ? 1u << 31 : 0);
             for (int32_t j = 0; j < 1 << x.lanes_log2; ++j) {
                 const int32_t first = x.first + 4 * j;
-                uint16_t *u = put(j == 0 ? (uint32_t)(i % (int32_t)slots) : none, (uint32_t)x.lanes_log2,
+                uint16_t *u = put(j == 0 ? (uint32_t)slot_of[i] : none, (uint32_t)x.lanes_log2,
                                   j == 0 && !x.part ? (uint32_t)x.vertex : kChainNobody,
                                   (uint32_t)first | (x.joins ? 1u << 31 : 0), flags);
-                for (int32_t e = 0; e < std::min(4, x.count - 4 * j); ++e) {
-                    const int32_t from = x.joins ? first + e : r.row_of[csr.idx[first + e]];
-                    u[e] = (uint16_t)(from % (int32_t)slots);
-                }
+                const int32_t cnt = std::min(4, x.count - 4 * j);
+                for (int32_t e = 0; e < cnt; ++e) u[e] = x.joins ? slot_of[first + e] : slot_at[csr.idx[first + e]];
             }
         }
         while (at % width) put(none, 0, kChainNobody, 0, kChainNobody);
     }
     while (at < ticks * width) put(none, 0, kChainNobody, 0, kChainNobody);
     return true;
+}
+
+// Packing for the whole-graph sweep (layout: see WholeDir).
+void pack_whole(BlobWriter &w, int32_t n, int32_t L, const int64_t *c, const Csr &succ, const Csr &pred,
+                const int32_t *level_ptr, const int32_t *level_vtx, WholeDir &dir) {
+    const Csr *csr[2] = {&succ, &pred};
+    std::vector<int32_t> units[2];           // of the levels
+    for (int i = 0; i < 2; ++i)
+        for (int32_t l = 0; l < L; ++l) {
+            int32_t count = 0;
+            for (int32_t j = level_ptr[l]; j < level_ptr[l + 1]; ++j)
+                count += std::max(1, (csr[i]->ptr[level_vtx[j] + 1] - csr[i]->ptr[level_vtx[j]] + 3) / 4);
+            units[i].push_back(count);
+        }
+    // units of a tick: a tick costs 0.28 us, and 0.006 for every unit past 32, whether it is filled or not
+    double best_us = 0;
+    for (int32_t a_tick : {8, 16, 32, 48, 64}) {
+        int64_t ticks = 0;
+        for (int i = 0; i < 2; ++i) {
+            int64_t sum = 0;
+            for (int32_t u : units[i]) sum += (u + a_tick - 1) / a_tick;
+            ticks = std::max(ticks, sum);
+        }
+        const double us = (double)ticks * (0.28 + 0.006 * std::max(0, a_tick - 32));
+        if (dir.units_a_tick == 0 || us < best_us) {
+            best_us = us;
+            dir.units_a_tick = a_tick;
+            dir.ticks = (int32_t)((ticks + kWholeAhead - 1) / kWholeAhead * kWholeAhead);
+        }
+    }
+    const int64_t room = (int64_t)(dir.ticks + kWholeAhead) * dir.units_a_tick;
+    for (int i = 0; i < 2; ++i) {
+        const size_t off = w.reserve((size_t)room * 32);
+        (i ? dir.units_t : dir.units_b) = off;
+        uint32_t *to = w.at<uint32_t>(off), *const end = to + room * 8;
+        const uint32_t none = (uint32_t)n | (uint32_t)n << 16;
+        auto put = [&](uint32_t v, uint32_t cv) {
+            uint32_t *u = to;
+            u[0] = u[1] = none;
+            u[2] = v;
+            u[3] = cv;
+            u[4] = u[5] = u[6] = u[7] = 0;
+            to += 8;
+            return u;
+        };
+        for (int32_t s = 0; s < L; ++s) {
+            const int32_t l = i ? s : L - 1 - s;
+            for (int32_t j = level_ptr[l]; j < level_ptr[l + 1]; ++j) {
+                const int32_t v = level_vtx[j], e0 = csr[i]->ptr[v], e1 = csr[i]->ptr[v + 1];
+                for (int32_t e = e0; e < e1 || e == e0; e += 4) {
+                    uint32_t *u = put((uint32_t)v, (uint32_t)c[v]);
+                    for (int32_t x = 0; x < std::min(4, e1 - e); ++x) {
+                        ((uint16_t *)u)[x] = (uint16_t)csr[i]->idx[e + x];
+                        u[4 + x] = (uint32_t)csr[i]->wt[e + x];
+                    }
+                }
+            }
+            for (int32_t pad = (dir.units_a_tick - units[i][l] % dir.units_a_tick) % dir.units_a_tick; pad > 0; --pad)
+                put((uint32_t)n + 1, 0);
+        }
+        while (to < end) put((uint32_t)n + 1, 0);
+    }
 }
 
 }  // namespace
@@ -894,6 +960,9 @@ int pack_graph(int32_t n, int64_t m, int32_t L,
                            pack_lane_dir(w, n, c, (size_t)P.lane_word, width, pred, level_ptr, level_vtx, true, P.col_t, P.lane_t);
             if (!P.have_lanes) P.blob.resize(mark);
         }
+        P.have_whole = P.narrow && n <= kWholeVertices && u0 < (1ull << (64 - kLaneIdBits));
+        P.whole = WholeDir{};
+        if (P.have_whole) pack_whole(w, n, L, c, succ, pred, level_ptr, level_vtx, P.whole);
         P.have_chain = false;
         if (L >= kChainLevels && n < (1 << 24) - 1 && (uint64_t)max_c + (uint64_t)max_t < (1ull << 32)) {
             const size_t mark = P.blob.size(), word = (size_t)info.min_tick_bytes;

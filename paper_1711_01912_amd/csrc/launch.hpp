@@ -168,6 +168,21 @@ size_t chain_lds_bytes(const ChainDir &d, int word_bytes);
 int launch_chain(const SweepLaunch &sb, const SweepLaunch &st, const ChainDir &db, const ChainDir &dt, int32_t width,
                  int word_bytes, bool cost16, bool want_b, bool want_t, uint8_t *work, void *stream);
 
+// The whole-graph sweep.
+constexpr int kWholeTableWords = 880;        // 3.4 KB of cost tables among a kernel's arguments
+struct WholeCfg {
+    int groups = 0, word = 0, threads = 0;   // partitions per workgroup, bytes of a ring word, lanes of a workgroup
+    bool tab4 = false;
+    size_t lds_bytes = 0, table_bytes = 0;   // ... of edge and vertex entries
+};
+// False if a workgroup of `groups` partitions and that many sweeps does not fit `lds_limit` bytes of LDS or 1,024 lanes.
+bool whole_config(const WholeDir &d, int32_t n, int32_t k, int groups, int word_bytes, bool tab4, int sweeps,
+                  size_t lds_limit, WholeCfg &out);
+// table: cfg.table_bytes of edge and vertex entries that go with the launch, or null: they are in device memory.
+// check_all: the launch writes the status itself; else it has been cleared, and cp_out as well.
+int launch_whole(const SweepLaunch &sb, const SweepLaunch &st, const WholeDir &d, const WholeCfg &cfg, bool want_b,
+                 bool want_t, bool by_partition, const void *table, bool check_all, void *stream);
+
 // False if the direction cannot run under `lds_limit` bytes of LDS.
 // with_mask: the t sweep also stages the tick's b values and writes the mask.
 bool window_config(const WindowDir &d, int32_t k, size_t tick_bytes, size_t lds_limit, WindowCfg &out,

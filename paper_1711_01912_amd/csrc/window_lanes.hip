@@ -87,27 +87,6 @@ struct LaneShape {
     uint32_t stage_off, stage_bytes, tab_off, ticks_off;
 };
 
-// The cost tables' three forms: 8-byte multiply-shift entries, the same with the remainder looked at, and
-// 4-byte entries.  A table read by 64 lanes is the kernel's most expensive LDS access (random rows): 4-byte
-// entries are taken where they are exact, and the remainder form where nothing else is, with 64-bit words.
-enum Form { kMagic8, kRound8, kMagic4 };
-template <int FORM> struct TabOf { typedef Magic type; };
-template <> struct TabOf<kMagic4> { typedef uint32_t type; };
-
-template <int FORM>
-__device__ __forceinline__ uint32_t div_by(uint32_t x, typename TabOf<FORM>::type m) {
-    if constexpr (FORM == kRound8) return round_div(x, m);
-    else return magic_div(x, m);
-}
-
-// value + (x << 6) as one shift-and-add: the compiler would otherwise fold the shift into the product's
-// upper half, which takes three instructions
-template <typename Word>
-__device__ __forceinline__ Word add_shifted(Word value, uint32_t x) {
-    asm("" : "+v"(x));
-    return value + ((Word)x << kLaneIdBits);
-}
-
 __device__ __forceinline__ uint32_t tick_units(uint32_t word) { return word & 0x3fffu; }
 __device__ __forceinline__ uint32_t tick_verts(uint32_t word) { return word >> 14 & 0x1ffu; }
 __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
