@@ -120,6 +120,8 @@ int static_scratch(void **out) {
     return CP_OK;
 }
 
+constexpr uint64_t kWholeCheckBytes = 64 * 1024;       // ids that one workgroup looks at
+
 constexpr size_t kWindowLdsLimit = kLdsBudget - 256;   // room for the kernel's static LDS
 constexpr size_t kSharedStaticLds = 512;               // static LDS of the shared-window and streamed kernels beyond that
 
@@ -357,6 +359,40 @@ double chain_us(const Packed &p, int32_t batch, int sweeps, bool cost16, bool by
     const double tick = 0.1 + 0.016 * (p.chain_width / kWave) + (p.info.min_tick_bytes == 8 ? 0.05 : 0.0);
     return 18.0 + lanes * (cost16 ? 8e-6 : 13e-6) + std::max(p.chain_b.ticks, p.chain_t.ticks) * tick +
            (by_partition ? 0.0 : (double)p.n * batch * sweeps * 10e-6);
+}
+
+// Fitted to 100 calls (64 to 3,600 vertices, 8 to 300 levels, 8 to 4,096 partitions), with what the launch itself takes: a
+// tick 0.27 us, 0.03 more for every wavefront past four on a compute unit; ids and outputs 0.08 us (rows per vertex 0.23) for
+// every vertex and partition that a lane has of them.  A fifth more where the workgroups take turns on a compute unit (1,800
+// vertices in 300 levels, 4,096 partitions 190 us against the lane-window plan's 179).
+double whole_us(const Packed &p, const WholeCfg &c, int32_t batch, bool by_partition) {
+    const double wgs = std::ceil((double)batch / c.groups), waves = (double)c.threads / kWave;
+    const double per_cu = std::max(1.0, std::floor(std::min((double)kLdsBudget / (double)(c.lds_bytes + 256), 32.0 / waves)));
+    const double there = std::min(per_cu, std::ceil(wgs / 256.0)), rounds = std::ceil(wgs / (256.0 * per_cu));
+    return 9.0 + rounds * (rounds > 1.0 ? 1.2 : 1.0) *
+                     ((double)p.n * c.groups / c.threads * (by_partition ? 0.08 : 0.23) +
+                      p.whole.ticks * (0.27 + 0.03 * std::max(0.0, there * waves - 4.0)));
+}
+
+// The whole-graph sweep: a shape for this call, if there is one.
+bool choose_whole(const Packed &p, const CostTables &tabs, int32_t k, const int64_t *speeds, const int64_t *bandwidth,
+                  int32_t batch, bool mask, bool by_partition, int sweeps, size_t lds_limit, WholeCfg &out, double *us_out) {
+    if (!p.have_whole || k > kMagicMaxK) return false;
+    const int word = p.lane_word == 4 && tabs.magic_ok ? 4 : 8;
+    if (word == 8 && !round_fits(k, speeds, bandwidth, p.info.max_c, p.info.max_t)) return false;
+    bool found = false;
+    for (int groups : {4, 8}) {
+        if (groups == 4 && mask && !by_partition) continue;        // (a workgroup writes whole bytes of a vertex's mask)
+        WholeCfg c;
+        if (!whole_config(p.whole, p.n, k, groups, word, word == 4 && tabs.tab4_ok, sweeps, lds_limit, c)) continue;
+        const double us = whole_us(p, c, batch, by_partition);
+        if (!found || us < *us_out) {
+            found = true;
+            *us_out = us;
+            out = c;
+        }
+    }
+    return found;
 }
 
 size_t tables_bytes(int32_t k) { return align_up(table_words(k) * 8); }
@@ -709,6 +745,12 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                             (by_partition || batch * tick_dtype <= 256);      // (its output offsets take 24 bits by 8)
     const bool cost16 = chain_fits && chain_cost16(p, k, speeds, bandwidth);
     bool chain = false;
+    // a small graph, everything in one launch
+    WholeCfg whole_cfg;
+    double whole_us_of = 0.0;
+    bool whole = plan == CP_PLAN_AUTO && lane_sweeps > 0 &&
+                 choose_whole(p, tabs, k, speeds, bandwidth, batch, mask_out != nullptr, by_partition, lane_sweeps, lds_limit,
+                              whole_cfg, &whole_us_of);
     if ((plan == CP_PLAN_AUTO || plan == CP_PLAN_LANE_WINDOW) && lane_sweeps > 0) {
         double lane_us = 0.0;
         lanes = choose_lanes(p, tabs, k, speeds, bandwidth, batch, tick_dtype, blevel_out || tlevel_out,
@@ -716,7 +758,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
         if (lanes)
             lane_work = lane_work_bytes((blevel_out || cp_out) ? &p.lane_b : nullptr, tlevel_out ? &p.lane_t : nullptr, p.n,
                                         batch, lane_cfg.groups, lane_cfg.word);
-        if ((lanes || chain_fits) && plan == CP_PLAN_AUTO) {
+        if ((lanes || chain_fits || whole) && plan == CP_PLAN_AUTO) {
             // against the plan chosen so far: its sweeps (side by side where they would share the launch), the
             // device ids it gathers per sweep at about 1 us per MB, the launches it needs past two (2.5 us each),
             // and the mask pass that its t sweep may save it
@@ -759,6 +801,11 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
             }
             lanes = lanes && 1.0 + 0.7 * mb + lane_us < other_us &&
                     tables_bytes(k) + lane_work <= workspace_bytes;
+            if (whole) {
+                // (the other plans' launches take 15 us)
+                whole = whole_us_of < 15.0 + (lanes ? 1.0 + 0.7 * mb + lane_us : other_us);
+                lanes = lanes && !whole;
+            }
             if (chain_fits) {
                 const size_t work = chain_work_bytes((blevel_out || cp_out) ? &p.chain_b : nullptr,
                                                      tlevel_out ? &p.chain_t : nullptr, p.chain_width, batch, cost16);
@@ -767,14 +814,17 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                     chain_scratch_bytes = workspace_bytes - std::min(workspace_bytes, tables_bytes(k));
                 }
                 chain = work <= chain_scratch_bytes && tables_bytes(k) <= workspace_bytes &&
-                        chain_us(p, batch, lane_sweeps, cost16, by_partition) < (lanes ? 1.0 + 0.7 * mb + lane_us : other_us);
+                        chain_us(p, batch, lane_sweeps, cost16, by_partition) <
+                            (whole ? whole_us_of : lanes ? 1.0 + 0.7 * mb + lane_us : other_us);
                 lanes = lanes && !chain;
+                whole = whole && !chain;
             }
         }
     }
     if (plan == CP_PLAN_LANE_WINDOW && !lanes) return CP_ERR_ARG;
     if (lanes) use = CP_PLAN_LANE_WINDOW;
     if (chain) use = CP_PLAN_CHAIN;
+    if (whole) use = CP_PLAN_WHOLE;
     if (use == CP_PLAN_RESIDENT_WINDOW && !can_window) return CP_ERR_ARG;
     // several partitions per workgroup behind one graph stream
     const bool shared = use == CP_PLAN_SHARED_WINDOW_2 || use == CP_PLAN_SHARED_WINDOW_4;
@@ -786,11 +836,11 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const bool streamed = use == CP_PLAN_STREAMED_WINDOW;
     if (streamed && (!tabs.magic_ok || !stream_fits(p, k, (size_t)tick_dtype, lds_limit, &st_b, &st_t)))
         return CP_ERR_ARG;
-    const bool windowish = use == CP_PLAN_RESIDENT_WINDOW || shared || streamed || lanes || chain;
+    const bool windowish = use == CP_PLAN_RESIDENT_WINDOW || shared || streamed || lanes || chain || whole;
     const bool columnish = !windowish;       // wave-column, or its persistent column-slice form
     if (use == CP_PLAN_COLUMN_SLICE && (!tabs.magic_ok || k > kMagicMaxK)) return CP_ERR_ARG;
     // the wave-column plan reads CP off the stored b-levels; the window sweeps keep a running maximum
-    if (cp_out && !blevel_out && (!windowish || (!lanes && !chain && p.win_b.far_cap > 0))) return CP_ERR_ARG;
+    if (cp_out && !blevel_out && (!windowish || (!lanes && !chain && !whole && p.win_b.far_cap > 0))) return CP_ERR_ARG;
 
     // Device ids reach the resident-window sweep either straight from the caller's rows
     // (16-byte loads: the rows must be contiguous, and whole-buffer size and base must be
@@ -798,8 +848,8 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const bool rows_ok = assign_layout == CP_ASSIGN_PARTITION_MAJOR &&
                          ((uint64_t)p.n * (uint64_t)batch) % 16 == 0 && ((uintptr_t)assignments % 16) == 0;
     const bool direct_b = rows_ok && p.win_b.direct_ok, direct_t = rows_ok && p.win_t.direct_ok;
-    const bool gather_b = windowish && !lanes && !chain && (blevel_out || cp_out) && !direct_b;
-    const bool gather_t = windowish && !lanes && !chain && tlevel_out && !direct_t;
+    const bool gather_b = windowish && !lanes && !chain && !whole && (blevel_out || cp_out) && !direct_b;
+    const bool gather_t = windowish && !lanes && !chain && !whole && tlevel_out && !direct_t;
 
     // workspace: only what this call uses (cp_eval_workspace_bytes is an upper bound over
     // every way the call may go)
@@ -843,13 +893,19 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     std::vector<uint64_t> tab_img;
     try {
         std::vector<Magic> round;
-        if (lanes && lane_cfg.word == 8) build_round_table(k, speeds, bandwidth, round);
+        if ((lanes && lane_cfg.word == 8) || (whole && whole_cfg.word == 8)) build_round_table(k, speeds, bandwidth, round);
         tab_img = table_image(tabs, k, round);
     } catch (const std::bad_alloc &) {
         return CP_ERR_ALLOC;
     }
-    rc = prepare_call(tab_img.data(), tab_img.size(), d_tab, cp_out, batch, status_out, st, tables_by_kernel);
-    if (rc) return rc;
+    // A call of few ids on few devices needs no launch before the whole-graph sweep's: its tables go with that one, which looks
+    // at all ids in its first workgroup, so that nothing has to be cleared.
+    const bool all_in_one = whole && whole_cfg.table_bytes <= (size_t)kWholeTableWords * 4 &&
+                            (uint64_t)p.n * (uint64_t)batch <= kWholeCheckBytes && ((uintptr_t)assignments % 16) == 0;
+    if (!all_in_one) {
+        rc = prepare_call(tab_img.data(), tab_img.size(), d_tab, cp_out, batch, status_out, st, tables_by_kernel);
+        if (rc) return rc;
+    }
     const uint8_t *pT = assignments;
     if (need_pT) {
         rc = launch_transpose(assignments, d_pT, p.n, batch, stream);
@@ -942,7 +998,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
 
     // ---- stage: b-level sweep
     CP_MARK(CP_STAGE_BLEVEL);
-    if (lanes || chain) {
+    if (lanes || chain || whole) {
         s.dir = &p.col_b;
         s.edge_tab = d_tab;
         s.edge_tab4 = d_tab4;
@@ -956,10 +1012,29 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
         t.val = tlevel_out;
         t.cp_out = nullptr;
         const bool want_b = blevel_out || cp_out;
-        rc = chain ? launch_chain(s, t, p.chain_b, p.chain_t, p.chain_width, p.info.min_tick_bytes, cost16, want_b,
-                                  tlevel_out != nullptr, chain_scratch, stream)
-                   : launch_window_lanes(s, t, p.lane_b, p.lane_t, lane_cfg, want_b, tlevel_out != nullptr,
-                                         d_tab + tables_bytes(k), stream);
+        if (whole) {
+            s.mask_out = mask_out;
+            // edge entries of the b sweep, then the vertices', as the image has them
+            std::vector<uint8_t> table;
+            if (all_in_one) {
+                const size_t entry = whole_cfg.tab4 ? 4 : 8;
+                const uint8_t *from = (const uint8_t *)tab_img.data() + (whole_cfg.tab4 ? table_entries(k) * 8 : 0);
+                try {
+                    table.assign(from, from + kk * entry);
+                    table.insert(table.end(), from + 2 * kk * entry, from + (2 * kk + k) * entry);
+                } catch (const std::bad_alloc &) {
+                    return CP_ERR_ALLOC;
+                }
+            }
+            rc = launch_whole(s, t, p.whole, whole_cfg, want_b, tlevel_out != nullptr, by_partition,
+                              all_in_one ? table.data() : nullptr, all_in_one, stream);
+        } else if (chain) {
+            rc = launch_chain(s, t, p.chain_b, p.chain_t, p.chain_width, p.info.min_tick_bytes, cost16, want_b,
+                              tlevel_out != nullptr, chain_scratch, stream);
+        } else {
+            rc = launch_window_lanes(s, t, p.lane_b, p.lane_t, lane_cfg, want_b, tlevel_out != nullptr,
+                                     d_tab + tables_bytes(k), stream);
+        }
         if (rc) return rc;
         if (launches) launches[chain && !want_b ? 1 : 0] = 1;
     } else if (blevel_out || cp_out) {
@@ -1014,7 +1089,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
 
     // ---- stage: t-level sweep
     CP_MARK(CP_STAGE_TLEVEL);
-    if (tlevel_out && !paired && !lanes && !chain) {
+    if (tlevel_out && !paired && !lanes && !chain && !whole) {
         s.tsweep = true;
         s.dir = &p.col_t;
         s.win = &p.win_t;
@@ -1055,7 +1130,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
 
     // ---- stage: mask
     CP_MARK(CP_STAGE_MASK);
-    if (mask_out && !fuse_mask) {
+    if (mask_out && !fuse_mask && !whole) {
         rc = launch_mask(blevel_out, tlevel_out, cp_out, p.n, batch, tick_dtype, by_partition, mask_out, stream);
         if (rc) return rc;
     }
