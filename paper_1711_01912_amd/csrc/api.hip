@@ -399,10 +399,11 @@ size_t tables_bytes(int32_t k) { return align_up(table_words(k) * 8); }
 
 // One call's tables as they lie in device memory: the 8-byte entries (multiply-shift constants,
 // or plain divisors), then, where they exist, the 4-byte entries.
-std::vector<uint64_t> table_image(const CostTables &tabs, int32_t k, const std::vector<Magic> &round) {
+std::vector<uint64_t> table_image(const CostTables &tabs, int32_t k, const std::vector<Magic> &round,
+                                  const std::vector<double> &inverse = {}) {
     std::vector<uint64_t> img(table_words(k), 0);
     const size_t entries = table_entries(k);
-    const void *from = !round.empty() ? (const void *)round.data()
+    const void *from = !inverse.empty() ? (const void *)inverse.data() : !round.empty() ? (const void *)round.data()
                                       : (tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data());
     std::memcpy(img.data(), from, entries * 8);
     if (tabs.tab4_ok) std::memcpy(img.data() + entries, tabs.tab4.data(), entries * 4);
@@ -873,6 +874,10 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     void *col_t = via_scratch && tlevel_out ? (void *)(ws + scratch_at + column_scratch_bytes(p, batch, tick_dtype))
                                             : tlevel_out;
 
+    const bool column4 = use == CP_PLAN_WAVE_COLUMN && column4_fits(p.n, p.L, batch, k, p.narrow, tick_dtype) &&
+                         ((uintptr_t)col_b % 16) == 0 && ((uintptr_t)col_t % 16) == 0 &&
+                         (need_pT || ((uintptr_t)assignments % 4) == 0);
+
     hipStream_t st = (hipStream_t)stream;
     hipEvent_t *ev = nullptr;
     int32_t *launches = nullptr;
@@ -893,8 +898,10 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     std::vector<uint64_t> tab_img;
     try {
         std::vector<Magic> round;
+        std::vector<double> inverse;
+        if (column4) build_inverse_table(k, speeds, bandwidth, inverse);
         if ((lanes && lane_cfg.word == 8) || (whole && whole_cfg.word == 8)) build_round_table(k, speeds, bandwidth, round);
-        tab_img = table_image(tabs, k, round);
+        tab_img = table_image(tabs, k, round, inverse);
     } catch (const std::bad_alloc &) {
         return CP_ERR_ALLOC;
     }
@@ -1069,6 +1076,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                 if (launches) launches[0] = 1;
             } else {
                 rc = use == CP_PLAN_RESIDENT_WINDOW ? launch_window_sweep(s, cfg_b, stream, launches)
+                     : column4                      ? launch_column4(s, stream, launches)
                                                     : launch_column_sweep(s, stream, launches);
             }
         }
@@ -1118,6 +1126,8 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
             } else {
                 rc = use == CP_PLAN_RESIDENT_WINDOW
                          ? launch_window_sweep(s, fuse_mask ? cfg_tm : cfg_t, stream, launches ? launches + 1 : nullptr)
+                     : column4
+                         ? launch_column4(s, stream, launches ? launches + 1 : nullptr)
                          : launch_column_sweep(s, stream, launches ? launches + 1 : nullptr);
             }
         }

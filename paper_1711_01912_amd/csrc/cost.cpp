@@ -107,4 +107,14 @@ void build_round_table(int32_t k, const int64_t *speeds, const int64_t *bandwidt
     }
 }
 
+void build_inverse_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<double> &out) {
+    const size_t kk = (size_t)k * k;
+    out.assign(table_entries(k), 0.0);
+    for (size_t i = 0; i < (size_t)k; ++i) {
+        for (size_t j = 0; j < (size_t)k; ++j)
+            if (i != j) out[i * k + j] = out[kk + j * k + i] = 1.0 / (double)bandwidth[i * k + j];
+        out[2 * kk + i] = 1.0 / (double)speeds[i];
+    }
+}
+
 }  // namespace cpeval

@@ -13,6 +13,7 @@ namespace cpeval {
 constexpr int kWave = 64;              // wavefront width on gfx950
 constexpr int kHubDegree = 256;        // wave-column plan: rows this long get a whole workgroup
 constexpr int kHubWaves = 16;          // ... of this many wavefronts
+constexpr int kColumnSplit = 24;       // ... and, four partitions a lane, rows this long a wavefront
 constexpr int kMagicMaxK = 64;         // multiply-shift tables are staged in LDS up to this many devices
 constexpr size_t kAlign = 256;
 constexpr size_t kLdsBudget = 160 * 1024;   // LDS per workgroup on gfx950
@@ -53,6 +54,7 @@ struct ColumnDir {
     // per level, in sweep order
     std::vector<int32_t> lvl_begin, lvl_hubs, lvl_count;
     std::vector<int32_t> lvl_longest;    // edges of the longest row that is no hub row
+    std::vector<int32_t> lvl_split;      // rows of kColumnSplit edges or more that are no hub rows
 };
 
 // One sweep direction of the resident-window plan.  Vertices are renumbered by
@@ -236,6 +238,9 @@ int build_cost_tables(int32_t k, const int64_t *speeds, const int64_t *bandwidth
 // ring words reads it: the other calls do not pay for it (92 against 69 us of host time at 50 devices).
 bool round_fits(int32_t k, const int64_t *speeds, const int64_t *bandwidth, int64_t max_c, int64_t max_t);
 void build_round_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<Magic> &out);
+
+// 1 / divisor as doubles, 0 for a free transfer; same layout.  For kernels that divide by one rounded multiply-add (inverse_div).
+void build_inverse_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<double> &out);
 
 inline size_t table_entries(int32_t k) { return (size_t)2 * k * k + k; }
 // 64-bit words of one call's tables in device memory: the 8-byte entries, then the 4-byte ones

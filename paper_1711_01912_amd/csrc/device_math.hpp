@@ -34,6 +34,22 @@ __device__ __forceinline__ uint32_t round_div(uint32_t a, Magic mg) {
     return q + (nn - q * (mg.dm1 + 1u) > mg.dm1 ? 1u : 0u);
 }
 
+// ceil(a/d) as one multiply-add of doubles rounded up: a - 1/2 lies between two multiples of 1/d next to a/d, adding 1.5 * 2^52
+// makes the rounding one to whole numbers (also below 0: a = 0, d = 1), and they end up in the low word.  Exact for every 32-bit a and every divisor:
+// 1/d and the product are off by 2^-52 of a/d at most, the margin is 1/(2d).  inverse = 0 (a free transfer) yields 0.  One
+// instruction of four cycles where the multiply-shift forms take three, one of them a 64-bit product at a quarter of that
+// rate.  `base` is 1.5 * 2^52 from round_up_doubles, which sets the wavefront's rounding of doubles: whatever uses it comes after.
+// (Set behind the compiler's back, which would set it back in front of every operation on doubles.)
+__device__ __forceinline__ double round_up_doubles() {
+    double base = 6755399441055744.0;
+    asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 1" : "+v"(base));
+    return base;
+}
+__device__ __forceinline__ double less_half(uint32_t a) { return (double)a - 0.5; }      // (exact)
+__device__ __forceinline__ uint32_t inverse_div(double a_less_half, double inverse, double base) {
+    return (uint32_t)(uint64_t)__double_as_longlong(__builtin_fma(a_less_half, inverse, base));
+}
+
 // ceil(a/d) by division; d = 0 marks a free transfer.
 __device__ __forceinline__ uint64_t plain_div(uint64_t a, uint64_t d) {
     return d ? (a + d - 1) / d : 0;

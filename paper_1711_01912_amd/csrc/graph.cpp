@@ -47,6 +47,7 @@ void sweep_order(int32_t n, int32_t L, const int32_t *level_ptr, const int32_t *
     dir.lvl_hubs.assign(L, 0);
     dir.lvl_count.assign(L, 0);
     dir.lvl_longest.assign(L, 0);
+    dir.lvl_split.assign(L, 0);
     int32_t pos = 0;
     for (int32_t s = 0; s < L; ++s) {
         int32_t l = forward ? s : L - 1 - s;
@@ -62,6 +63,9 @@ void sweep_order(int32_t n, int32_t L, const int32_t *level_ptr, const int32_t *
             if (ptr[v + 1] - ptr[v] < kHubDegree) break;
             ++hubs;
         }
+        int32_t split = hubs;
+        while (split < b - a && ptr[order[pos + split] + 1] - ptr[order[pos + split]] >= kColumnSplit) ++split;
+        dir.lvl_split[s] = split - hubs;
         dir.lvl_begin[s] = pos;
         dir.lvl_hubs[s] = hubs;
         dir.lvl_count[s] = b - a;

@@ -133,6 +133,7 @@ struct ColumnArgs {
     const void *vert_tab;   // Magic[k] or int64[k]
     int32_t *status;
     int32_t P, ncol, k, count;
+    int32_t split;          // column4_kernel: rows that a wavefront takes alone, the first ones
     ColumnDeal deal;
 };
 
@@ -257,6 +258,140 @@ __global__ __launch_bounds__(HUB ? kHubWaves * 64 : 256) void column_level_kerne
                              : (Tick)plain_div((uint64_t)cv, (uint64_t)vtab_g[pv]);
         ticks_of(v)[uq] = TSWEEP ? acc : (Tick)(acc + w);
     }
+}
+
+// The same for 32-bit ticks and P a multiple of four: four partitions a lane (ids as one word, ticks as one 16-byte load), 16
+// lanes for a row's 64 partitions.  A wavefront takes four rows, or one of kColumnSplit edges and more, or its share of a
+// hub's, every fourth edge in each quarter of the lanes.  Cost tables hold inverses (inverse_div), in the t sweep an edge's
+// beside its source's.  A relaxation is five vector instructions in the b sweep and six in the t sweep, sixteen before.
+// 200,000 vertices in 20 levels with hubs, 1,024 partitions: t sweep 1,819 -> 1,168 us, b sweep 1,100 -> 588 and its hubs 945 ->
+// 799, which is 5 bytes an edge and partition at 10.8, 4.9 and 12 TB/s: the values come from the Infinity Cache.
+template <bool TSWEEP, bool HUB>
+__global__ __launch_bounds__(HUB ? kHubWaves * 64 : 256, 8) void column4_kernel(ColumnArgs a) {
+    extern __shared__ uint4 lds16[];
+    const double base = round_up_doubles();
+    const int tid = threadIdx.x, lane = tid & 63, part = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int k = a.k;
+    const uint32_t P = (uint32_t)a.P;
+    int32_t vi, col;
+    column_place(blockIdx.x, HUB ? 0u : (uint32_t)wave, a.deal, (uint32_t)a.ncol, HUB ? 1 : 4, vi, col);
+    const bool split = HUB || vi < a.split;      // the lanes' quarters share a row
+    if (!split) vi = a.split + 4 * (vi - a.split) + part;
+    const bool task_live = vi < a.count && col < a.ncol;
+    if (!task_live) vi = col = 0;
+    const int4 rec = a.rows[vi];
+    const uint32_t q = (uint32_t)col * 64 + (uint32_t)(lane & 15) * 4;
+    const bool live = task_live && q < P;
+    const uint32_t qc = live ? q : 0;
+    const uint32_t *wt = (const uint32_t *)a.wt, *cw = (const uint32_t *)a.c;
+    const uint32_t own_at = __umul24((uint32_t)rec.x, P) + qc;           // n and P below 2^24, n * P below 2^30
+    const uint32_t own_ids = *(const uint32_t *)(a.pT + own_at), own_c = cw[rec.x];
+    int32_t e0 = rec.y, e1 = live ? rec.z : rec.y;
+    if (HUB) {                           // this wavefront's share of the row
+        const int32_t len = e1 - e0, chunk = (len + kHubWaves - 1) / kHubWaves;
+        e0 = min(e1, e0 + wave * chunk);
+        e1 = min(e1, e0 + chunk);
+    }
+    const int32_t step = split ? 4 : 1;
+    if (split) e0 += part;
+    // four neighbours at a time; past the row's end its last one again, which changes no maximum.  The next four are
+    // looked up while these are on their way.
+    uint32_t next_u[kColumnUnroll], next_t[kColumnUnroll];
+    auto look_up = [&](int32_t e) {
+#pragma unroll
+        for (int i = 0; i < kColumnUnroll; ++i) {
+            const uint32_t at = (uint32_t)max(min(e + i * step, e1 - 1), 0);
+            next_u[i] = (uint32_t)a.idx[at];
+            next_t[i] = wt[at];
+        }
+    };
+    if (e0 < e1) look_up(e0);
+    double *etab = (double *)lds16, *vtab = etab + (TSWEEP ? 2 : 1) * k * k;
+    {
+        const double *e = (const double *)a.edge_tab, *vt = (const double *)a.vert_tab;
+        for (int i = tid; i < k * k; i += blockDim.x) {
+            if (TSWEEP) {
+                etab[2 * i] = e[i];
+                etab[2 * i + 1] = vt[i % k];
+            } else {
+                etab[i] = e[i];
+            }
+        }
+        for (int i = tid; i < k && !TSWEEP; i += blockDim.x) vtab[i] = vt[i];
+        __syncthreads();
+    }
+    const uint32_t most = (uint32_t)k - 1;
+    const double *erow[4];
+    uint32_t own[4];
+    bool bad = false;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        own[p] = own_ids >> (8 * p) & 0xffu;
+        bad |= own[p] > most;
+        own[p] = own[p] > most ? 0u : own[p];
+        erow[p] = etab + __umul24(own[p], (uint32_t)k * (TSWEEP ? 2 : 1));
+    }
+    if (live && bad) *a.status = CP_STATUS_BAD_DEVICE_ID;
+
+    int32_t acc[4] = {0, 0, 0, 0};
+    for (int32_t e = e0; e < e1; e += kColumnUnroll * step) {
+        uint32_t te[kColumnUnroll], cu[kColumnUnroll], pu[kColumnUnroll];
+        int4 vu[kColumnUnroll];
+#pragma unroll
+        for (int i = 0; i < kColumnUnroll; ++i) {
+            const uint32_t at = __umul24(next_u[i], P) + qc;
+            pu[i] = *(const uint32_t *)(a.pT + at);
+            vu[i] = *(const int4 *)((const char *)a.val + (size_t)(at * 4u));
+            if (TSWEEP) cu[i] = cw[next_u[i]];
+            te[i] = next_t[i];
+        }
+        if (e + kColumnUnroll * step < e1) look_up(e + kColumnUnroll * step);
+#pragma unroll
+        for (int i = 0; i < kColumnUnroll; ++i) {
+            const double t = less_half(te[i]), c = TSWEEP ? less_half(cu[i]) : 0.0;
+            const int32_t v[4] = {vu[i].x, vu[i].y, vu[i].z, vu[i].w};
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const uint32_t pd = min(pu[i] >> (8 * p) & 0xffu, most);
+                uint32_t x;
+                if (TSWEEP) {            // a predecessor: its finish time is tl(u) + w(u)
+                    const double2 m = ((const double2 *)erow[p])[pd];
+                    x = inverse_div(t, m.x, base) + inverse_div(c, m.y, base);
+                } else {
+                    x = inverse_div(t, erow[p][pd], base);
+                }
+                acc[p] = max(acc[p], (int32_t)((uint32_t)v[p] + x));
+            }
+        }
+    }
+
+    if (split) {                         // fold the lanes of a partition
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            acc[p] = max(acc[p], __shfl_xor(acc[p], 16));
+            acc[p] = max(acc[p], __shfl_xor(acc[p], 32));
+        }
+    }
+    if (HUB) {                           // ... and the wavefronts' maxima
+        int4 *parts = (int4 *)lds16 + ((TSWEEP ? 2 : 1) * k * k + k + 1) / 2;
+        if (part == 0) parts[wave * 16 + lane] = make_int4(acc[0], acc[1], acc[2], acc[3]);
+        __syncthreads();
+        if (wave != 0) return;
+        for (int w = 1; w < kHubWaves; ++w) {
+            const int4 x = parts[w * 16 + (lane & 15)];
+            acc[0] = max(acc[0], x.x);
+            acc[1] = max(acc[1], x.y);
+            acc[2] = max(acc[2], x.z);
+            acc[3] = max(acc[3], x.w);
+        }
+    }
+    if (!live || (split && part != 0)) return;
+    const double c = less_half(own_c);
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+        if (!TSWEEP) acc[p] += (int32_t)inverse_div(c, vtab[own[p]], base);
+    *(int4 *)((char *)a.val + (size_t)(own_at * 4u)) = make_int4(acc[0], acc[1], acc[2], acc[3]);
 }
 
 // CP[q] = max over sources of b: b never decreases against the edge direction
@@ -1401,6 +1536,48 @@ int launch_column_sweep_t(const SweepLaunch &s, hipStream_t st, int32_t *launche
     return hip_ok(hipGetLastError());
 }
 
+template <bool TSWEEP>
+int launch_column4_t(const SweepLaunch &s, hipStream_t st, int32_t *launches) {
+    const ColumnDir &dir = *s.dir;
+    const int L = (int)dir.lvl_begin.size();
+    const size_t tab_bytes = align_up(8 * ((size_t)(TSWEEP ? 2 : 1) * s.k * s.k + s.k), 16);
+    ColumnArgs a{};
+    a.idx = (const int32_t *)(s.blob + dir.idx_off);
+    a.wt = s.blob + dir.wt_off;
+    a.c = s.blob + s.c_off;
+    a.pT = s.pT;
+    a.val = s.val;
+    a.edge_tab = s.edge_tab;
+    a.vert_tab = s.vert_tab;
+    a.status = s.status;
+    a.P = s.P; a.ncol = (s.P + 63) / 64; a.k = s.k;
+    const int4 *rows = (const int4 *)(s.blob + dir.rows_off);
+    int32_t count = 0;
+    for (int l = 0; l < L; ++l) {
+        const int32_t hubs = dir.lvl_hubs[l], others = dir.lvl_count[l] - hubs;
+        if (hubs > 0) {
+            a.rows = rows + dir.lvl_begin[l];
+            a.count = hubs;
+            a.deal = column_deal(hubs, a.ncol, 1, column_by_runs(kHubDegree, a.ncol));
+            hipLaunchKernelGGL((column4_kernel<TSWEEP, true>), dim3((unsigned)column_blocks(a.deal, hubs, a.ncol, 1)),
+                               dim3(kHubWaves * 64), tab_bytes + sizeof(int4) * 16 * kHubWaves, st, a);
+            ++count;
+        }
+        if (others > 0) {
+            a.rows = rows + dir.lvl_begin[l] + hubs;
+            a.count = others;
+            a.split = dir.lvl_split[l];
+            const int32_t tasks = a.split + (others - a.split + 3) / 4;
+            a.deal = column_deal(tasks, a.ncol, 4, column_by_runs(dir.lvl_longest[l], a.ncol));
+            hipLaunchKernelGGL((column4_kernel<TSWEEP, false>), dim3((unsigned)column_blocks(a.deal, tasks, a.ncol, 4)),
+                               dim3(256), tab_bytes, st, a);
+            ++count;
+        }
+    }
+    if (launches) *launches = count;
+    return hip_ok(hipGetLastError());
+}
+
 // What both forms of launch hand the kernel for one sweep (no mask, no far reads).
 WindowArgs window_args(const SweepLaunch &s, const WindowCfg &cfg) {
     const WindowDir &dir = *s.win;
@@ -1633,6 +1810,11 @@ int launch_transpose(const uint8_t *in, uint8_t *out, int32_t n, int32_t P, void
     dim3 grid((unsigned)((n + 63) / 64), (unsigned)((P + 63) / 64));
     hipLaunchKernelGGL(transpose_kernel, grid, dim3(256), 0, (hipStream_t)stream, in, out, n, P);
     return hip_ok(hipGetLastError());
+}
+
+int launch_column4(const SweepLaunch &s, void *stream, int32_t *launches) {
+    return s.tsweep ? launch_column4_t<true>(s, (hipStream_t)stream, launches)
+                    : launch_column4_t<false>(s, (hipStream_t)stream, launches);
 }
 
 int launch_column_sweep(const SweepLaunch &s, void *stream, int32_t *launches) {
