@@ -532,7 +532,7 @@ int critical_path(const cp_graph *g, int32_t batch, int32_t k, const uint8_t *as
     s.magic = tabs.magic_ok;
     s.narrow = p.narrow;
     s.tick_bytes = tick_dtype;
-    s.n = p.n; s.m = p.m; s.hops = p.hops; s.P = batch; s.k = k; s.L = p.L;
+    s.n = p.n; s.m = p.m; s.hops = p.hops; s.reach = p.reach; s.P = batch; s.k = k; s.L = p.L;
     s.assign = assignments;
     if (assign_layout == CP_ASSIGN_PARTITION_MAJOR) { s.a_stride_p = p.n; s.a_stride_v = 1; }
     else { s.a_stride_p = 1; s.a_stride_v = batch; }

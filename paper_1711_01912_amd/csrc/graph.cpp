@@ -853,11 +853,16 @@ int pack_graph(int32_t n, int64_t m, int32_t L,
         }
     }
     double per_level = 0;
+    out.reach = 0;
+    bool along = true;
     for (int64_t e = 0; e < m; ++e) {
+        along = along && succ_idx[e] > edge_src[e];
+        out.reach = std::max(out.reach, succ_idx[e] - edge_src[e]);
         const int32_t climbs = level[succ_idx[e]] - level[edge_src[e]];
         if (climbs <= 0) return CP_ERR_LEVELS;
         per_level += 1.0 / climbs;
     }
+    if (!along) out.reach = 0;
     out.hops = m > 0 ? (int32_t)(L * (per_level / (double)m)) : 0;
 
     int64_t max_c = 0, max_t = 0;

@@ -822,6 +822,207 @@ __global__ __launch_bounds__(kPathThreads) void critical_path_records_kernel(Pat
     if (lane == 0) a.len[q] = len;
 }
 
+// The walk over records with b and the device ids streamed past it.  Where rows lie along a partition and every edge leads
+// to a later vertex, at most `reach` further on, the walk goes through its rows from front to back, so three wavefronts read
+// them once, ahead of the walker, into a ring of LDS, and a path vertex costs a look into the ring and one round of loads for
+// the records, which all partitions share, from the L2.  The rows are read whole for that, at the rate of a stream.
+//
+//   loaders   read kPathChunk vertices at a time, every third chunk, the next one in registers while they wait for the
+//             walker to be past those that this one replaces; `done` of a loader: its first vertex that is not there yet
+//   walker    waits until all its candidates are there; `at`: the vertex it stands on, or the largest number at its end
+// The ring holds the reach and four chunks more, so that the chunks up to a walker's candidates always find room.
+// Bound by a path vertex's chain, 1,450 cycles: the records from the L2, behind the loaders' requests, some 800, two LDS round
+// trips 360, waiting for the ring 150 (121,000 vertices, 777 partitions: 304 -> 271 us; the rows are read at 1.7 TB/s).
+constexpr int kPathChunk = 512;
+
+__global__ __launch_bounds__(256) void critical_path_stream_kernel(PathArgs a, const uint32_t *__restrict__ records,
+                                                                   int32_t n, int32_t ring) {
+    extern __shared__ __align__(16) uint64_t path_lds[];
+    constexpr int kLoaders = 3;
+    __shared__ uint32_t starts[4];
+    __shared__ int32_t done[kLoaders], at;
+    const int lane = threadIdx.x & 63, tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t q = blockIdx.x, k = a.k;
+    const int32_t *b = (const int32_t *)a.b + (int64_t)q * a.b_sq;
+    const uint8_t *row = a.assign + (int64_t)q * a.a_stride_p;
+    const uint64_t *ge = (const uint64_t *)a.edge_tab, *gv = (const uint64_t *)a.vert_tab;
+    for (int i = tid; i < k * k; i += 256) path_lds[i] = ge[i];
+    for (int i = tid; i < k; i += 256) path_lds[k * k + i] = gv[i];
+    const Magic *etab = (const Magic *)path_lds, *vtab = etab + k * k;
+    int32_t *ring_b = (int32_t *)(path_lds + k * k + k);
+    uint8_t *ring_id = (uint8_t *)(ring_b + ring);
+    int32_t *path = a.path + (int64_t)q * a.max_len;
+    for (int i = tid; i < a.max_len; i += 256) path[i] = -1;
+    uint32_t low = lowest_start(a, b, 1u, a.cp[q], tid, 256);
+    if (lane == 0) starts[wave] = low;
+    __syncthreads();
+    low = min(min(starts[0], starts[1]), min(starts[2], starts[3]));
+    low = (uint32_t)__builtin_amdgcn_readfirstlane((int)low);
+    if (tid < kLoaders) done[tid] = 0;
+    if (tid == 0) at = (int32_t)low;         // (none: the largest number, and the loaders leave)
+    __syncthreads();
+    auto get = [](int32_t *x) { return __hip_atomic_load(x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    auto set = [](int32_t *x, int32_t to) { __hip_atomic_store(x, to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    constexpr int32_t kEnd = 0x7fffffff;
+
+    if (wave > 0) {
+        constexpr int kEach = kPathChunk / 64;
+        int32_t got_b[2][kEach];
+        uint32_t got_id[2][kEach];
+        // The records of a chunk are fetched into the XCD's L2 by all of its workgroups together (blocks go round the eight
+        // XCDs), an equal share each: a walker's few are rarely those of another, and would come from the last cache.
+        const uint32_t sharers = (gridDim.x + 7 - blockIdx.x % 8) / 8, mine = blockIdx.x / 8;
+        uint32_t touched[2] = {0, 0};
+        auto ask = [&](int32_t v0, int r) {
+            touched[r] = 0;
+            for (uint32_t i = mine + sharers * (uint32_t)lane; __ballot(i < (uint32_t)kPathChunk); i += sharers * 64)
+                touched[r] ^= records[(size_t)min(v0 + (int32_t)min(i, (uint32_t)kPathChunk - 1), n - 1) * 16];
+#pragma unroll
+            for (int i = 0; i < kEach; ++i) got_b[r][i] = b[min(v0 + i * 64 + lane, n - 1)];
+#pragma unroll
+            for (int i = 0; i < kEach; ++i) got_id[r][i] = row[min(v0 + i * 64 + lane, n - 1)];
+        };
+        if (low == (uint32_t)kEnd) return;
+        int32_t v0 = ((int32_t)low / kPathChunk + wave - 1) * kPathChunk;
+        ask(v0, 0);
+        // (n and the chunks behind it stay below 2^31: records take 64 bytes a vertex)
+        while (v0 < n) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                if (v0 < n) {
+                    ask(v0 + kLoaders * kPathChunk, r ^ 1);
+                    for (;;) {
+                        const int32_t now = get(&at);
+                        if (now == kEnd) return;
+                        if (v0 + kPathChunk - ring <= now) break;        // all that this chunk replaces lies behind the walker
+                        __builtin_amdgcn_s_sleep(4);
+                    }
+                    const int32_t to = (v0 & (ring - 1)) + lane;
+#pragma unroll
+                    for (int i = 0; i < kEach; ++i) {
+                        ring_b[to + i * 64] = got_b[r][i];
+                        ring_id[to + i * 64] = (uint8_t)got_id[r][i];
+                    }
+                    asm volatile("" ::"v"(touched[r]));      // (nothing else reads them)
+                    v0 += kLoaders * kPathChunk;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                    if (lane == 0) set(&done[wave - 1], v0);
+                }
+            }
+        }
+        if (lane == 0) set(&done[wave - 1], kEnd);
+        return;
+    }
+
+    __builtin_amdgcn_s_setprio(3);
+    const int word = lane & 15, part = lane >> 4;        // four records a load, sixteen lanes each
+    auto load_record = [&](uint32_t v) { return records[(size_t)v * 16 + word]; };
+    int32_t v = (int32_t)low, bv = 0;
+    uint32_t pv = 0, rec = 0;                // rec: the current vertex's record, in the sixteen lanes from `base` on
+    int base = 0;
+    if (v != kEnd) {
+        pv = row[v];
+        bv = b[v];
+        rec = load_record((uint32_t)v);
+    }
+    // A path vertex is a chain: the candidates' numbers, b and devices (one LDS round trip), the table (a second one) beside the
+    // records, which the next vertex waits for.  So everything that the first needs is asked for at once, and what
+    // belongs to the vertex itself is kept in vector registers (`opaque`): the compiler would fetch it for the scalar unit
+    // and wait for it at once.
+    auto opaque = [](uint32_t x) { asm("" : "+v"(x)); return x; };
+    const uint32_t most = (uint32_t)k - 1, turn = (uint32_t)ring - 1;
+    const uint32_t my_slot = (uint32_t)(2 + 2 * part) * 4, my_slot1 = (uint32_t)(2 + 2 * min(4 + part, kRecordEdges - 1)) * 4;
+    const uint32_t even = (lane & 1) == 0 ? 0u : 0x40000000u;
+    const char *my_word = (const char *)(records + word);
+    bool bad_id = false;
+    int32_t len = 0, step = 0, there = 0;    // there: all vertices from the start up to it are in the ring
+    while (v != kEnd && len < a.max_len) {
+        const int32_t deg = __builtin_amdgcn_readlane((int)rec, base + 1);
+        unsigned long long hits = 0;
+        int won = 0;
+        int32_t n_b = 0;                     // of this lane's candidate: b, device
+        uint32_t n_p = 0;
+        const uint32_t own = opaque(min(pv, most));      // (a device that does not exist is reported, and counts as 0)
+        bad_id |= pv > most;
+        const uint32_t own_row = pv > most ? 0u : own;
+        step = lane == (len & 63) ? v : step;            // (a store per vertex is waited for with the loads behind it)
+        if (__builtin_expect(deg <= kRecordEdges, 1)) {
+            // a candidate stays in the lane that holds its number; t is in the lane behind it
+            const uint32_t u = rec;
+            const bool mine = (uint32_t)(lane - base - 2) + even < (uint32_t)(2 * deg);
+            if (__ballot(mine && (int32_t)u >= there)) {
+                if (lane == 0) set(&at, v);
+                do {
+                    there = min(min(get(&done[0]), get(&done[1])), get(&done[2]));
+                } while (__ballot(mine && (int32_t)u >= there));
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+            }
+            const uint32_t u0 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(base * 4 + my_slot), (int)rec);
+            n_b = ring_b[u & turn];
+            n_p = ring_id[u & turn];
+            const Magic mw = vtab[own_row];
+            const uint32_t cv = opaque((uint32_t)__builtin_amdgcn_readlane((int)rec, base));
+            const uint32_t te = dpp_row<0x101>(rec);
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t rec0 = *(const uint32_t *)(my_word + (size_t)(u0 * 64ull));
+            uint32_t rec1 = 0;
+            if (deg > 4) {
+                const uint32_t u1 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(base * 4 + my_slot1), (int)rec);
+                rec1 = *(const uint32_t *)(my_word + (size_t)(u1 * 64ull));
+            }
+            const Magic me = etab[__umul24(own_row, (uint32_t)k) + min(n_p, most)];
+            const int32_t rest = bv - (int32_t)magic_div(cv, mw) - n_b;
+            hits = __ballot(mine && (int32_t)magic_div(te, me) == rest);
+            if ((len & 63) == 63) path[len - 63 + lane] = step;
+            if ((len & 3) == 3 && lane == 0) set(&at, v);
+            ++len;
+            if (!hits) break;
+            won = __ffsll((long long)hits) - 1;
+            if (hits & (hits - 1)) {         // several: the lowest vertex
+                const uint32_t best = min_over_wave(hits >> lane & 1 ? u : (uint32_t)kEnd);
+                won = __ffsll((long long)__ballot((hits >> lane & 1) && u == best)) - 1;
+            }
+            v = __builtin_amdgcn_readlane((int)rec, won);
+            pv = wave_bcast<uint32_t>(n_p, won);
+            bv = wave_bcast<int32_t>(n_b, won);
+            const int edge = (won - base - 2) / 2;
+            rec = edge < 4 ? rec0 : rec1;
+            base = 16 * (edge & 3);
+        } else {
+            // a row longer than a record, out of the CSR
+            if ((len & 63) == 63) path[len - 63 + lane] = step;
+            ++len;
+            const Magic *costs = etab + own_row * (uint32_t)k;
+            const int32_t rest = bv - (int32_t)magic_div((uint32_t)__builtin_amdgcn_readlane((int)rec, base), vtab[own_row]);
+            int32_t next = kEnd;
+            const int32_t first = __builtin_amdgcn_readlane((int)rec, base + 2);
+            for (int32_t e = first + lane; e < first + deg; e += 64) {
+                const int32_t u = a.idx[e];
+                const uint32_t te = ((const uint32_t *)a.wt)[e], pu = row[u];
+                const int32_t bu = b[u];
+                if ((int32_t)magic_div(te, costs[min(pu, most)]) + bu == rest && u < next) {
+                    next = u;
+                    n_p = pu;
+                    n_b = bu;
+                }
+            }
+            const uint32_t best = min_over_wave((uint32_t)next);
+            if (best == (uint32_t)kEnd) break;
+            won = __ffsll((long long)__ballot((uint32_t)next == best)) - 1;
+            v = (int32_t)best;
+            pv = wave_bcast<uint32_t>(n_p, won);
+            bv = wave_bcast<int32_t>(n_b, won);
+            rec = load_record(best);
+            base = 0;
+        }
+    }
+    if (lane == 0) set(&at, kEnd);
+    if (lane < (len & 63)) path[(len & ~63) + lane] = step;
+    if (bad_id) *a.status = CP_STATUS_BAD_DEVICE_ID;
+    if (lane == 0) a.len[q] = len;
+}
+
 // One partition's path where the whole GPU has nothing else to do (cp_search, cp_seed_partition): every vertex
 // names the vertex the path would take from it, all at once; three rounds of "the next one's next one" make
 // that a jump of eight; one lane then jumps, and every landing is filled up to the following one by a thread of
@@ -1972,6 +2173,15 @@ int launch_critical_path(const SweepLaunch &s, const int32_t *sources, int32_t n
     if (records && s.magic && lds_tab && path_by_records(s.n, s.m, s.L, s.hops)) {
         const dim3 words((unsigned)(((int64_t)s.n * kPathRecordWords + 255) / 256));
         hipLaunchKernelGGL(path_records_kernel, words, dim3(256), 0, st, a, s.n, records);
+        const int32_t ring = path_ring(s.n, s.P, s.hops, s.reach);
+        const size_t stream_lds = lds + (size_t)ring * 5;
+        if (ring && s.tick_bytes == 4 && s.a_stride_v == 1 && s.out_sv == 1 && stream_lds <= kPathLdsBytes) {
+            if (hipFuncSetAttribute((const void *)critical_path_stream_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)stream_lds) != hipSuccess)
+                return CP_ERR_HIP;
+            hipLaunchKernelGGL(critical_path_stream_kernel, grid, dim3(256), stream_lds, st, a, records, s.n, ring);
+            return hip_ok(hipGetLastError());
+        }
         if (s.tick_bytes == 4)
             hipLaunchKernelGGL(critical_path_records_kernel<int32_t>, grid, block, lds, st, a, records);
         else

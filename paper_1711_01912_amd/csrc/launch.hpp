@@ -18,7 +18,7 @@ struct SweepLaunch {
     int tick_bytes = 4;
     int32_t n = 0, P = 0, k = 0, L = 0, max_width = 0;
     int64_t m = 0;                      // critical-path walk only, and Packed::hops
-    int32_t hops = 0;
+    int32_t hops = 0, reach = 0;
     const uint8_t *pT = nullptr;        // [n][P] device ids (wave-column)
     const uint8_t *assign = nullptr;    // caller's assignments (resident-window: input of the gather)
     const uint8_t *pperm = nullptr;     // [P][ticks*wpad] device ids in sweep order (resident-window)
@@ -332,6 +332,21 @@ inline bool path_by_jumps(int32_t n, int32_t P, int32_t L, int32_t hops) {
 // 225 and 341 us.
 inline bool path_by_records(int32_t n, int64_t m, int32_t L, int32_t hops) {
     return L >= 256 && n / L < 1024 && m / n <= 5 && hops >= 64;
+}
+// Vertices of the LDS ring that b and the device ids are streamed through on a walk over records, or 0 where they are not.
+// The whole rows are read for it, 5 bytes a vertex at 4.5 TB/s, which half a microsecond a path vertex has to outweigh.  With
+// fewer than 64 partitions b comes from the caches, and past 1,024 the walks of a compute unit hide each other's round trips.
+// Loaded as asked for and streamed: 121,000 vertices in 701 levels, 8, 100 and 777 partitions 196 and 274 us, 227 and 171,
+// 326 and 292; 18,000 in 300 levels, 64, 777 and 3,000 partitions 136 and 128, 138 and 107, 196 and 237; 240,000 in 1,000
+// levels, 200 partitions 684 and 469.  Not with rings of 16,384, one workgroup a compute unit (240,000 in 400 levels, 300
+// partitions 178 both), nor where every XCD's records are more than the rows (950,000 in 1,900 levels, 80 partitions 673
+// and 799).
+constexpr size_t kPathLdsBytes = 64 * 1024;
+inline int32_t path_ring(int32_t n, int32_t P, int32_t hops, int32_t reach) {
+    if (reach <= 0 || P < 64 || P > 1024 || n > 500000 || (double)n * P * 5 / 4.5e6 > 0.5 * hops) return 0;
+    for (int32_t ring : {4096, 8192})
+        if (reach + 4 * 512 <= ring) return ring;
+    return 0;
 }
 // cp_eval of one partition (CP_PLAN_AUTO) with scratch of its own for the chain sweep (eval_chain_bytes), or null;
 // `workspace` as for a call that goes without it (eval_one_bytes).
