@@ -310,12 +310,13 @@ double side_window_sweep_us(const Packed &p, const WindowDir &d, int32_t batch) 
     return d.ticks * std::max(0.65 + 0.015 * d.smax, slice * d.smax * std::ceil(2.0 * batch / 256.0));
 }
 
+bool dividends_fit_floats(const Packed &p) { return p.info.max_c < kFloatMost && p.info.max_t < kFloatMost; }
+
 // The cheapest shape for this batch: true and its time if the lane-window kernel applies.
 bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, const int64_t *speeds, const int64_t *bandwidth,
                   int32_t batch, int tick_bytes, bool with_out, bool by_partition, int sweeps, size_t lds_limit,
                   LaneCfg &out, double *us_out) {
     if (!p.have_lanes || k > kMagicMaxK) return false;
-    // the multiply-shift forms go with 32-bit ring words, the rounded form with 64-bit ones
     const int word = p.lane_word == 4 && tabs.magic_ok ? 4 : 8;
     if (word == 8 && !round_fits(k, speeds, bandwidth, p.info.max_c, p.info.max_t)) return false;
     // the outputs of a group are addressed with 32-bit offsets
@@ -333,6 +334,7 @@ bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, const int6
             found = true;
             *us_out = us;
             out = c;
+            out.floats = dividends_fit_floats(p);
         }
     }
     return found;
@@ -384,7 +386,7 @@ bool choose_whole(const Packed &p, const CostTables &tabs, int32_t k, const int6
     for (int groups : {4, 8}) {
         if (groups == 4 && mask && !by_partition) continue;        // (a workgroup writes whole bytes of a vertex's mask)
         WholeCfg c;
-        if (!whole_config(p.whole, p.n, k, groups, word, word == 4 && tabs.tab4_ok, sweeps, lds_limit, c)) continue;
+        if (!whole_config(p.whole, p.n, k, groups, word, dividends_fit_floats(p), sweeps, lds_limit, c)) continue;
         const double us = whole_us(p, c, batch, by_partition);
         if (!found || us < *us_out) {
             found = true;
@@ -398,15 +400,19 @@ bool choose_whole(const Packed &p, const CostTables &tabs, int32_t k, const int6
 size_t tables_bytes(int32_t k) { return align_up(table_words(k) * 8); }
 
 // One call's tables as they lie in device memory: the 8-byte entries (multiply-shift constants,
-// or plain divisors), then, where they exist, the 4-byte entries.
-std::vector<uint64_t> table_image(const CostTables &tabs, int32_t k, const std::vector<Magic> &round,
-                                  const std::vector<double> &inverse = {}) {
+// plain divisors, or inverses), then, where they exist, the 4-byte entries (compact, or inverses).
+enum class Inverses { kNone, kDoubles, kFloats };
+std::vector<uint64_t> table_image(const CostTables &tabs, int32_t k, const int64_t *speeds, const int64_t *bandwidth,
+                                  Inverses as) {
     std::vector<uint64_t> img(table_words(k), 0);
     const size_t entries = table_entries(k);
-    const void *from = !inverse.empty() ? (const void *)inverse.data() : !round.empty() ? (const void *)round.data()
-                                      : (tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data());
+    std::vector<double> inverse;
+    if (as != Inverses::kNone) build_inverse_table(k, speeds, bandwidth, inverse);
+    const void *from = as == Inverses::kDoubles ? (const void *)inverse.data()
+                       : tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data();
     std::memcpy(img.data(), from, entries * 8);
-    if (tabs.tab4_ok) std::memcpy(img.data() + entries, tabs.tab4.data(), entries * 4);
+    if (as == Inverses::kFloats) build_float_table(inverse, (float *)(img.data() + entries));
+    else if (tabs.tab4_ok) std::memcpy(img.data() + entries, tabs.tab4.data(), entries * 4);
     return img;
 }
 size_t column_scratch_bytes(const Packed &p, int32_t batch, int tick_bytes) {
@@ -895,13 +901,12 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
 
     // ---- stage: prep
     CP_MARK(CP_STAGE_PREP);
+    const Inverses inverses = column4 ? Inverses::kDoubles
+                              : !lanes && !whole ? Inverses::kNone
+                              : (lanes ? lane_cfg.floats : whole_cfg.floats) ? Inverses::kFloats : Inverses::kDoubles;
     std::vector<uint64_t> tab_img;
     try {
-        std::vector<Magic> round;
-        std::vector<double> inverse;
-        if (column4) build_inverse_table(k, speeds, bandwidth, inverse);
-        if ((lanes && lane_cfg.word == 8) || (whole && whole_cfg.word == 8)) build_round_table(k, speeds, bandwidth, round);
-        tab_img = table_image(tabs, k, round, inverse);
+        tab_img = table_image(tabs, k, speeds, bandwidth, inverses);
     } catch (const std::bad_alloc &) {
         return CP_ERR_ALLOC;
     }
@@ -928,7 +933,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     s.narrow = p.narrow;
     s.tick_bytes = tick_dtype;
     s.n = p.n; s.P = batch; s.k = k; s.L = p.L; s.max_width = p.max_width;
-    const uint32_t *d_tab4 = tabs.tab4_ok ? (const uint32_t *)(d_tab + table_entries(k) * 8) : nullptr;
+    const uint32_t *d_tab4 = tabs.tab4_ok || inverses == Inverses::kFloats ? (const uint32_t *)(d_tab + table_entries(k) * 8) : nullptr;
     s.vert_tab4 = d_tab4 ? d_tab4 + 2 * kk : nullptr;
     s.pT = pT;
     s.assign = assignments;
@@ -1024,8 +1029,8 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
             // edge entries of the b sweep, then the vertices', as the image has them
             std::vector<uint8_t> table;
             if (all_in_one) {
-                const size_t entry = whole_cfg.tab4 ? 4 : 8;
-                const uint8_t *from = (const uint8_t *)tab_img.data() + (whole_cfg.tab4 ? table_entries(k) * 8 : 0);
+                const size_t entry = whole_cfg.floats ? 4 : 8;
+                const uint8_t *from = (const uint8_t *)tab_img.data() + (whole_cfg.floats ? table_entries(k) * 8 : 0);
                 try {
                     table.assign(from, from + kk * entry);
                     table.insert(table.end(), from + 2 * kk * entry, from + (2 * kk + k) * entry);

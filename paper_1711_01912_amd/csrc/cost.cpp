@@ -2,6 +2,7 @@
 // speeds) and of every transfer cost (bandwidth matrix), as plain divisors and,
 // where it is provably exact, as 32-bit multiply-shift constants.
 #include <algorithm>
+#include <cmath>
 
 #include "cpeval_internal.hpp"
 
@@ -107,13 +108,27 @@ void build_round_table(int32_t k, const int64_t *speeds, const int64_t *bandwidt
     }
 }
 
+// 1.0 / d is at most half a unit off; fma tells which way (d and the inverse are exact, past 2^53 the divisor is rounded and
+// only has to be larger than every dividend).
 void build_inverse_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<double> &out) {
+    auto entry = [](int64_t d) {
+        const double x = 1.0 / (double)d;
+        return std::fma(x, (double)d, -1.0) > 0.0 ? std::nextafter(x, 0.0) : x;
+    };
     const size_t kk = (size_t)k * k;
     out.assign(table_entries(k), 0.0);
     for (size_t i = 0; i < (size_t)k; ++i) {
         for (size_t j = 0; j < (size_t)k; ++j)
-            if (i != j) out[i * k + j] = out[kk + j * k + i] = 1.0 / (double)bandwidth[i * k + j];
-        out[2 * kk + i] = 1.0 / (double)speeds[i];
+            if (i != j) out[i * k + j] = out[kk + j * k + i] = entry(bandwidth[i * k + j]);
+        out[2 * kk + i] = entry(speeds[i]);
+    }
+}
+
+void build_float_table(const std::vector<double> &inverse, float *out) {
+    for (size_t i = 0; i < inverse.size(); ++i) {
+        const double x = inverse[i] * kFloatUnit;
+        const float f = (float)x;
+        out[i] = (double)f > x ? std::nextafterf(f, 0.0f) : f;
     }
 }
 

@@ -235,13 +235,18 @@ int build_cost_tables(int32_t k, const int64_t *speeds, const int64_t *bandwidth
 
 // The rounded form, exact for every 32-bit N = a + dm1 (no condition on the product):
 //   q = (N * mul) >> 32, one more if N - q * (dm1 + 1) > dm1      with mul = floor(2^32/d), dm1 = d - 1
-// A free transfer is {0, 2^32 - 1}, which yields 0.  Same layout as `magic`.  Only the lane-window plan with 64-bit
-// ring words reads it: the other calls do not pay for it (92 against 69 us of host time at 50 devices).
+// A free transfer is {0, 2^32 - 1}, which yields 0.  Same layout as `magic`.  No kernel reads it any more (inverse_div is
+// shorter), a host test does; the condition stays the one under which 64-bit ring words are chosen.
 bool round_fits(int32_t k, const int64_t *speeds, const int64_t *bandwidth, int64_t max_c, int64_t max_t);
 void build_round_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<Magic> &out);
 
-// 1 / divisor as doubles, 0 for a free transfer; same layout.  For kernels that divide by one rounded multiply-add (inverse_div).
+// 1 / divisor as doubles rounded down, 0 for a free transfer; same layout.  For kernels that divide by one multiply-add rounded
+// up (inverse_div).
 void build_inverse_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<double> &out);
+// The same as floats rounded down, in units of kFloatUnit: for dividends below kFloatMost.
+void build_float_table(const std::vector<double> &inverse, float *out);
+constexpr float kFloatUnit = 0.015625f;      // 2^-6
+constexpr int64_t kFloatMost = 1 << 23;
 
 inline size_t table_entries(int32_t k) { return (size_t)2 * k * k + k; }
 // 64-bit words of one call's tables in device memory: the 8-byte entries, then the 4-byte ones

@@ -1,4 +1,4 @@
-// Device-side arithmetic shared by the kernels: the two forms of ceil(a/d) of the cost
+// Device-side arithmetic shared by the kernels: the forms of ceil(a/d) of the cost
 // model (section 2: execution time c/s, transfer time t/B, each rounded up to whole ticks)
 // and lane permutations inside a row of 16 lanes.
 #pragma once
@@ -26,28 +26,34 @@ __device__ __forceinline__ uint32_t magic_div(uint32_t a, uint32_t entry) {
     return (uint32_t)(((uint64_t)nn * (entry | 0xffu) + nn) >> 32);
 }
 
-// The same through the rounded form (CostTables::round): exact whatever the product, at the price of
-// the remainder.
-__device__ __forceinline__ uint32_t round_div(uint32_t a, Magic mg) {
-    const uint32_t nn = a + mg.dm1;
-    const uint32_t q = __umulhi(nn, mg.mul);
-    return q + (nn - q * (mg.dm1 + 1u) > mg.dm1 ? 1u : 0u);
-}
-
-// ceil(a/d) as one multiply-add of doubles rounded up: a - 1/2 lies between two multiples of 1/d next to a/d, adding 1.5 * 2^52
-// makes the rounding one to whole numbers (also below 0: a = 0, d = 1), and they end up in the low word.  Exact for every 32-bit a and every divisor:
-// 1/d and the product are off by 2^-52 of a/d at most, the margin is 1/(2d).  inverse = 0 (a free transfer) yields 0.  One
-// instruction of four cycles where the multiply-shift forms take three, one of them a 64-bit product at a quarter of that
-// rate.  `base` is 1.5 * 2^52 from round_up_doubles, which sets the wavefront's rounding of doubles: whatever uses it comes after.
-// (Set behind the compiler's back, which would set it back in front of every operation on doubles.)
-__device__ __forceinline__ double round_up_doubles() {
-    double base = 6755399441055744.0;
+// ceil(a/d) as one multiply-add rounded up: the tables hold 1/d rounded down (build_inverse_table), so that a times it lies above
+// the whole number below a/d and not above the one at or above it; adding `base` makes the rounding one to whole numbers, which
+// end up in the low bits.  Exact while a times the inverse's relative error is below 1: doubles for every 32-bit a, floats for
+// a < 2^23 (kFloatMost), whatever the divisor.  An inverse of 0 (a free transfer) yields 0.  One instruction of four cycles where
+// the multiply-shift forms take three or more, one of them a 64-bit product at a quarter of that rate.
+// `base` comes from round_up, which sets the wavefront's rounding: whatever uses it comes after.  (Set behind the compiler's
+// back, which would set it back in front of every operation on doubles.  A division of whole numbers that are not constants
+// is done in floats: none behind round_up(float).)
+__device__ __forceinline__ double round_up(double) {
+    double base = 4503599627370496.0;        // 2^52
     asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 1" : "+v"(base));
     return base;
 }
-__device__ __forceinline__ double less_half(uint32_t a) { return (double)a - 0.5; }      // (exact)
-__device__ __forceinline__ uint32_t inverse_div(double a_less_half, double inverse, double base) {
-    return (uint32_t)(uint64_t)__double_as_longlong(__builtin_fma(a_less_half, inverse, base));
+__device__ __forceinline__ uint32_t inverse_div(uint32_t a, double inverse, double base) {
+    return (uint32_t)(uint64_t)__double_as_longlong(__builtin_fma((double)a, inverse, base));
+}
+// Floats count in units of 2^-6 (kFloatUnit): base is 2^17, and its bits, 0x48000000, leave a 32-bit word that the
+// quotient is shifted into by kLaneIdBits.
+__device__ __forceinline__ float round_up(float) {
+    float base = kFloatUnit * 8388608.0f;
+    asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 1" : "+v"(base));
+    return base;
+}
+__device__ __forceinline__ uint32_t inverse_bits(uint32_t a, float inverse, float base) {
+    return __float_as_uint(__builtin_fmaf((float)a, inverse, base));
+}
+__device__ __forceinline__ uint32_t inverse_div(uint32_t a, float inverse, float base) {
+    return inverse_bits(a, inverse, base) & 0x7fffffu;
 }
 
 // ceil(a/d) by division; d = 0 marks a free transfer.
@@ -86,25 +92,21 @@ __device__ __forceinline__ uint32_t min_over_wave(uint32_t x) {
                min((uint32_t)__builtin_amdgcn_readlane((int)x, 32), (uint32_t)__builtin_amdgcn_readlane((int)x, 48)));
 }
 
-// The cost tables' three forms: 8-byte multiply-shift entries, the same with the remainder looked at, and
-// 4-byte entries.  A table read by 64 lanes is the lane kernels' most expensive LDS access (random rows): 4-byte
-// entries are taken where they are exact, and the remainder form where nothing else is, with 64-bit words.
-enum Form { kMagic8, kRound8, kMagic4 };
-template <int FORM> struct TabOf { typedef Magic type; };
-template <> struct TabOf<kMagic4> { typedef uint32_t type; };
-
-template <int FORM>
-__device__ __forceinline__ uint32_t div_by(uint32_t x, typename TabOf<FORM>::type m) {
-    if constexpr (FORM == kRound8) return round_div(x, m);
-    else return magic_div(x, m);
-}
-
-// value + (x << 6) as one shift-and-add: the compiler would otherwise fold the shift into the product's
-// upper half, which takes three instructions
+// value + (ceil(a/d) << kLaneIdBits), the division by one multiply-add, the rest as one shift-and-add: the compiler would
+// otherwise take the two apart.
 template <typename Word>
 __device__ __forceinline__ Word add_shifted(Word value, uint32_t x) {
     asm("" : "+v"(x));
     return value + ((Word)x << kLaneIdBits);
+}
+template <typename Word>
+__device__ __forceinline__ Word add_quotient(Word value, uint32_t a, double inverse, double base) {
+    return add_shifted(value, inverse_div(a, inverse, base));
+}
+template <typename Word>
+__device__ __forceinline__ Word add_quotient(Word value, uint32_t a, float inverse, float base) {
+    static_assert(kFloatUnit * 8388608.0f == 131072.0f && kLaneIdBits == 6, "0x48000000 << 6 leaves 32 bits");
+    return add_shifted(value, sizeof(Word) == 4 ? inverse_bits(a, inverse, base) : inverse_div(a, inverse, base));
 }
 
 }  // namespace cpeval

@@ -269,7 +269,7 @@ __global__ __launch_bounds__(HUB ? kHubWaves * 64 : 256) void column_level_kerne
 template <bool TSWEEP, bool HUB>
 __global__ __launch_bounds__(HUB ? kHubWaves * 64 : 256, 8) void column4_kernel(ColumnArgs a) {
     extern __shared__ uint4 lds16[];
-    const double base = round_up_doubles();
+    const double base = round_up(double());
     const int tid = threadIdx.x, lane = tid & 63, part = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int k = a.k;
@@ -349,7 +349,6 @@ __global__ __launch_bounds__(HUB ? kHubWaves * 64 : 256, 8) void column4_kernel(
         if (e + kColumnUnroll * step < e1) look_up(e + kColumnUnroll * step);
 #pragma unroll
         for (int i = 0; i < kColumnUnroll; ++i) {
-            const double t = less_half(te[i]), c = TSWEEP ? less_half(cu[i]) : 0.0;
             const int32_t v[4] = {vu[i].x, vu[i].y, vu[i].z, vu[i].w};
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
@@ -357,9 +356,9 @@ __global__ __launch_bounds__(HUB ? kHubWaves * 64 : 256, 8) void column4_kernel(
                 uint32_t x;
                 if (TSWEEP) {            // a predecessor: its finish time is tl(u) + w(u)
                     const double2 m = ((const double2 *)erow[p])[pd];
-                    x = inverse_div(t, m.x, base) + inverse_div(c, m.y, base);
+                    x = inverse_div(te[i], m.x, base) + inverse_div(cu[i], m.y, base);
                 } else {
-                    x = inverse_div(t, erow[p][pd], base);
+                    x = inverse_div(te[i], erow[p][pd], base);
                 }
                 acc[p] = max(acc[p], (int32_t)((uint32_t)v[p] + x));
             }
@@ -387,10 +386,9 @@ __global__ __launch_bounds__(HUB ? kHubWaves * 64 : 256, 8) void column4_kernel(
         }
     }
     if (!live || (split && part != 0)) return;
-    const double c = less_half(own_c);
 #pragma unroll
     for (int p = 0; p < 4; ++p)
-        if (!TSWEEP) acc[p] += (int32_t)inverse_div(c, vtab[own[p]], base);
+        if (!TSWEEP) acc[p] += (int32_t)inverse_div(own_c, vtab[own[p]], base);
     *(int4 *)((char *)a.val + (size_t)(own_at * 4u)) = make_int4(acc[0], acc[1], acc[2], acc[3]);
 }
 

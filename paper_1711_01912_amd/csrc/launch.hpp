@@ -30,7 +30,7 @@ struct SweepLaunch {
     int64_t *cp_out = nullptr;          // resident-window b sweep only
     const void *edge_tab = nullptr;
     const void *vert_tab = nullptr;
-    const uint32_t *edge_tab4 = nullptr;   // the same tables as 4-byte entries, or null
+    const uint32_t *edge_tab4 = nullptr;   // the same tables as 4-byte entries (compact, or inverses as floats), or null
     const uint32_t *vert_tab4 = nullptr;
     int32_t *status = nullptr;
     // resident-window t sweep that also writes the mask rows (partition-major): b, CP and the
@@ -148,7 +148,8 @@ CP_HOST_DEVICE void column_place(uint32_t block, uint32_t wave, const ColumnDeal
 struct LaneCfg {
     int groups = 0;    // partitions per workgroup: 4 or 8
     int nl = 0;        // 16-byte loads per loader lane per tick
-    int width = 0, word = 0;           // entries of a sub-row, bytes of a ring word (8: tables in the rounded form)
+    int width = 0, word = 0;           // entries of a sub-row, bytes of a ring word
+    bool floats = false;               // cost tables of floats, else doubles
     int nc = 0, nlw = 0, nsw = 0, nfw = 0;     // compute, loader, store and far wavefronts
     size_t stage_off = 0, stage_bytes = 0, tab_off = 0, ticks_off = 0, lds_bytes = 0;
 };
@@ -172,11 +173,11 @@ int launch_chain(const SweepLaunch &sb, const SweepLaunch &st, const ChainDir &d
 constexpr int kWholeTableWords = 880;        // 3.4 KB of cost tables among a kernel's arguments
 struct WholeCfg {
     int groups = 0, word = 0, threads = 0;   // partitions per workgroup, bytes of a ring word, lanes of a workgroup
-    bool tab4 = false;
+    bool floats = false;                     // tables of floats, else doubles
     size_t lds_bytes = 0, table_bytes = 0;   // ... of edge and vertex entries
 };
 // False if a workgroup of `groups` partitions and that many sweeps does not fit `lds_limit` bytes of LDS or 1,024 lanes.
-bool whole_config(const WholeDir &d, int32_t n, int32_t k, int groups, int word_bytes, bool tab4, int sweeps,
+bool whole_config(const WholeDir &d, int32_t n, int32_t k, int groups, int word_bytes, bool floats, int sweeps,
                   size_t lds_limit, WholeCfg &out);
 // table: cfg.table_bytes of edge and vertex entries that go with the launch, or null: they are in device memory.
 // check_all: the launch writes the status itself; else it has been cleared, and cp_out as well.

@@ -54,9 +54,8 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <typename Word, int G, int FORM, typename Table>
+template <typename Word, int G, typename Tab, typename Table>
 __global__ __launch_bounds__(1024) void whole_kernel(WholeArgs a, Table table) {
-    typedef typename TabOf<FORM>::type Tab;
     constexpr int S = G + 1, kAhead = kWholeAhead, RPW = 64 / G;
     constexpr uint32_t ID = (1u << kLaneIdBits) - 1, kWord = sizeof(Word);
     extern __shared__ uint4 lds16[];
@@ -127,6 +126,7 @@ __global__ __launch_bounds__(1024) void whole_kernel(WholeArgs a, Table table) {
         for (int i = bytes / 16 * 16 + tid; i < bytes; i += nt) bad |= a.assign[i] >= (uint32_t)k;
     }
 
+    const Tab base = round_up(Tab());        // (no variable divisions behind this)
     // this lane's unit of a tick
     const int t_lane = second && a.sweeps == 3 ? tid - per_sweep : tid, g = lane % G, unit = t_lane / G;
     const Tab *const etab = tabs + (second ? kk : 0), *const vtab = tabs + 2 * kk;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(1024) void whole_kernel(WholeArgs a, Table table) {
     };
     auto vertex = [&](uint32_t id, uint32_t c, Tab m) {
         erow = etab + __umul24(id, (uint32_t)k);
-        own = add_shifted((Word)id, div_by<FORM>(c, m));
+        own = add_quotient((Word)id, c, m, base);
     };
     {
         places(from[0]);
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(1024) void whole_kernel(WholeArgs a, Table table) {
             const Tab next_m = vtab[next_id];
             Word acc = 0;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc = max(acc, add_shifted(v[j], div_by<FORM>(wt[r][j], m[j])));
+            for (int j = 0; j < 4; ++j) acc = max(acc, add_quotient(v[j], wt[r][j], m[j], base));
             const Word fin = (acc & ~(Word)ID) + own;
             atomicMax(mine, fin);
             __builtin_amdgcn_sched_barrier(0);       // (nothing in front of what the next tick waits for)
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(1024) void whole_kernel(WholeArgs a, Table table) {
         const size_t row = (size_t)v * S + gl;
         Word b = 0, tl = 0;
         if (a.sweeps != 2) b = ring_b[row] >> kLaneIdBits;
-        if (a.sweeps != 1) tl = (ring_t[row] >> kLaneIdBits) - (Word)div_by<FORM>(c, vtab[(uint32_t)ids[row] & ID]);
+        if (a.sweeps != 1) tl = (ring_t[row] >> kLaneIdBits) - (Word)inverse_div(c, vtab[(uint32_t)ids[row] & ID], base);
         if (there) {
             if (a.out64) {
                 if (a.out[0]) ((int64_t *)a.out[0])[to] = (int64_t)b;
@@ -260,9 +260,9 @@ __global__ __launch_bounds__(1024) void whole_kernel(WholeArgs a, Table table) {
     }
 }
 
-template <typename Word, int FORM, typename Table>
+template <typename Word, typename Tab, typename Table>
 int launch_whole_k(const WholeArgs &a, const Table &table, const WholeCfg &cfg, hipStream_t st) {
-    const auto kernel = cfg.groups == 8 ? whole_kernel<Word, 8, FORM, Table> : whole_kernel<Word, 4, FORM, Table>;
+    const auto kernel = cfg.groups == 8 ? whole_kernel<Word, 8, Tab, Table> : whole_kernel<Word, 4, Tab, Table>;
     if (cfg.lds_bytes > 64 * 1024 && hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                          (int)cfg.lds_bytes) != hipSuccess)
         return CP_ERR_HIP;
@@ -273,19 +273,20 @@ int launch_whole_k(const WholeArgs &a, const Table &table, const WholeCfg &cfg, 
 
 template <typename Table>
 int launch_whole_t(const WholeArgs &a, const Table &table, const WholeCfg &cfg, hipStream_t st) {
-    if (cfg.word == 8) return launch_whole_k<unsigned long long, kRound8>(a, table, cfg, st);
-    if (cfg.tab4) return launch_whole_k<uint32_t, kMagic4>(a, table, cfg, st);
-    return launch_whole_k<uint32_t, kMagic8>(a, table, cfg, st);
+    if (cfg.word == 8)
+        return cfg.floats ? launch_whole_k<unsigned long long, float>(a, table, cfg, st)
+                          : launch_whole_k<unsigned long long, double>(a, table, cfg, st);
+    return cfg.floats ? launch_whole_k<uint32_t, float>(a, table, cfg, st) : launch_whole_k<uint32_t, double>(a, table, cfg, st);
 }
 
 }  // namespace
 
-bool whole_config(const WholeDir &d, int32_t n, int32_t k, int groups, int word_bytes, bool tab4, int sweeps,
+bool whole_config(const WholeDir &d, int32_t n, int32_t k, int groups, int word_bytes, bool floats, int sweeps,
                   size_t lds_limit, WholeCfg &out) {
-    const size_t entry_bytes = tab4 ? 4 : 8;
+    const size_t entry_bytes = floats ? 4 : 8;
     out.groups = groups;
     out.word = word_bytes;
-    out.tab4 = tab4;
+    out.floats = floats;
     out.table_bytes = ((size_t)k * k + k) * entry_bytes;
     const size_t ring = (size_t)(n + 2) * (groups + 1);
     out.lds_bytes = align_up(((sweeps * ring + 1) & ~(size_t)1) * word_bytes + ((size_t)2 * k * k + k) * entry_bytes, 16);
@@ -319,8 +320,8 @@ int launch_whole(const SweepLaunch &sb, const SweepLaunch &st, const WholeDir &d
     a.sweeps = (want_b ? 1 : 0) | (want_t ? 2 : 0);
     a.check_all = check_all;
     a.by_partition = by_partition;
-    a.edge_tab = cfg.tab4 ? (const void *)sb.edge_tab4 : sb.edge_tab;
-    a.vert_tab = cfg.tab4 ? (const void *)sb.vert_tab4 : sb.vert_tab;
+    a.edge_tab = cfg.floats ? (const void *)sb.edge_tab4 : sb.edge_tab;
+    a.vert_tab = cfg.floats ? (const void *)sb.vert_tab4 : sb.vert_tab;
     if (!table) return launch_whole_t(a, NoTable{}, cfg, (hipStream_t)stream);
     WholeTable args;
     std::memcpy(args.v, table, cfg.table_bytes);

@@ -14,6 +14,10 @@
 // the chain of a tick (two LDS round trips, publication, barrier: 0.2 to 0.3 us; with far reads, 660 levels, 1.0 us with one
 // workgroup on a compute unit, 1.3, 1.7 and 2.4 with two, three and four, no part of the unit busy a third of the time), on wide ones the LDS pipe of a compute unit (121,000 vertices: 72 % busy, a third of it bank
 // conflicts; vector ALUs 62 %, 27 instructions per 64 relaxations with what loaders and stores add).
+// Divisions are one multiply-add (inverse_div): floats where no volume reaches 2^23, doubles above.  Against multiply-shift
+// constants, whose 64-bit product alone takes four times as long: 121,000 vertices in 701 levels, 777 partitions
+// 1,160 -> 1,140 us a call; 19,800 in 660, 4,096 partitions 1,693 -> 1,551; 29,000 in 301 with 64-bit words, 320
+// partitions 316 -> 282.
 //
 // A ring word is value << 6 | device id, one LDS read per relaxation; x << 6 is added to it and the
 // maximum taken over whole words, whose upper bits are the maximum of the sums.  Words are 32 bits while
@@ -91,13 +95,12 @@ __device__ __forceinline__ uint32_t tick_units(uint32_t word) { return word & 0x
 __device__ __forceinline__ uint32_t tick_verts(uint32_t word) { return word >> 14 & 0x1ffu; }
 __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 
-template <typename Word, bool TSWEEP, int G, int W, int FORM, int NL, bool FAR>
+template <typename Word, bool TSWEEP, int G, int W, typename Tab, int NL, bool FAR>
 __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &sh, uint8_t *lds,
                                            unsigned long long *red, int32_t grp) {
     constexpr int kDepth = 8 / NL;           // ticks a loader runs ahead of the stage, NL 16-byte loads a lane each
     constexpr int RPW = 64 / G;              // sub-rows a wavefront relaxes at a time
     constexpr int IU = RPW / kLaneUnit;      // units of an item
-    typedef typename TabOf<FORM>::type Tab;
     constexpr int VS = G + 1;                // words between two rows of the ring
     constexpr int UNIT = 64 * (1 + W);       // bytes of a unit
     constexpr uint32_t ID = (1u << kLaneIdBits) - 1;
@@ -178,6 +181,7 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
         const uint32_t sv = a.off_sv, sq = a.off_sq;           // bytes; a group's outputs span less than 4 GB
         char *base = (char *)a.out + (size_t)q0 * (size_t)a.out_sq * (a.out64 ? 8 : 4);
         const bool by_row = a.out_sv == 1;
+        const Tab up = round_up(Tab());    // (no variable divisions behind this)
         uint32_t slot0 = 0;                  // of the tick being stored
         int copied = 0;                      // numbers given to far copies so far
         uint64_t recent = 0;                 // stores of each of the last kFarWait iterations, a byte each
@@ -190,8 +194,8 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
             const uint32_t at_a = ra.x * sv + (uint32_t)ga * sq, at_b = rb.x * sv + (uint32_t)gb * sq;
             if constexpr (TSWEEP) {
                 const Tab ma = vtab[(uint32_t)xa & ID], mb = vtab[(uint32_t)xb & ID];
-                xa = (xa >> kLaneIdBits) - (Word)div_by<FORM>(ra.y, ma);
-                xb = (xb >> kLaneIdBits) - (Word)div_by<FORM>(rb.y, mb);
+                xa = (xa >> kLaneIdBits) - (Word)inverse_div(ra.y, ma, up);
+                xb = (xb >> kLaneIdBits) - (Word)inverse_div(rb.y, mb, up);
             } else {
                 xa >>= kLaneIdBits;
                 xb >>= kLaneIdBits;
@@ -213,6 +217,7 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
             word = words[t];                 // of the next iteration's tick
             const int w = (int)tick_verts(tick);
             const uint2 *verts = (const uint2 *)(stage + (size_t)((t - 1) % kSlots) * sh.stage_bytes + tick_units(tick) * UNIT);
+            uint32_t sure = 0;               // stores this iteration issues, at least
             if (FAR && a.far_cap > 0) {
                 // the copies first: what is left of this iteration's stores may stay on its way
                 const int copies = (int)(tick >> 23);
@@ -223,6 +228,7 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
                     const uint32_t slot = slots[min(f, copies - 1)];
                     const Word x = ring[__umul24(slot, (uint32_t)VS) + lane % G];
                     if (f < copies) __hip_atomic_store(to + (size_t)f * G, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    ++sure;
                 }
                 copied += copies;
             }
@@ -239,6 +245,7 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
                     for (int g0 = sw * gs; g0 < G; g0 += 2 * nsw * gs) {
                         const int ga = g0 + gl, gb = ga + nsw * gs;
                         put2(slot, min(ga, G - 1), r, mine && ga < live, slot, min(gb, G - 1), r, mine && gb < live);
+                        if (FAR) sure += (uint32_t)(g0 < live) + (uint32_t)(g0 + nsw * gs < live);
                     }
                 }
             } else {
@@ -249,20 +256,14 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
                     const int ca = min(va, w - 1), cb = min(vb, w - 1);
                     const uint2 ra = verts[ca], rb = verts[cb];
                     put2(ring_slot(ca), g, ra, va < w && g < live, ring_slot(cb), g, rb, vb < w && g < live);
+                    if (FAR) sure += 1u + (uint32_t)(v0 + nsw * RPW < w);
                 }
             }
             slot0 += (uint32_t)w;
             if (slot0 >= (uint32_t)R) slot0 -= (uint32_t)R;
             if (FAR && a.far_cap > 0) {
                 // copies of kFarWait iterations ago have arrived once no more stores are on their way than
-                // the later iterations issued (counted as the loops above issue them, or fewer)
-                uint32_t sure = (uint32_t)max(0, ((int)(tick >> 23) - sw * RPW + nsw * RPW - 1) / (nsw * RPW));
-                if (a.out && by_row) {
-                    const int gs = w >= 64 ? 1 : 64 >> (32 - __clz(w - 1));
-                    sure += (uint32_t)((w + 63) / 64 * max(0, (live - sw * gs + nsw * gs - 1) / (nsw * gs)));
-                } else if (a.out) {
-                    sure += (uint32_t)max(0, (w - sw * RPW + nsw * RPW - 1) / (nsw * RPW));
-                }
+                // the later iterations issued
                 recent = recent << 8 | min(sure, 31u);
                 uint32_t later = 0;
 #pragma unroll
@@ -345,6 +346,7 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
         // An item = RPW sub-rows of a unit: two dependent LDS round trips (ring words, table entries) and a
         // publication; the next item's records and entries are on their way meanwhile.
         __builtin_amdgcn_s_setprio(1);
+        const Tab up = round_up(Tab());
         const int g = lane % G, rg = lane / G;
         uint2 rec, ent[W];
         const uint32_t lane_off = (uint32_t)(rg / kLaneUnit) * UNIT + (uint32_t)(rg % kLaneUnit) * 8;
@@ -387,8 +389,8 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
                 for (int j = 0; j < W; ++j) m[j] = erow[(uint32_t)v[j] & ID];
                 Word acc = 0;
 #pragma unroll
-                for (int j = 0; j < W; ++j) acc = max(acc, add_shifted(v[j], div_by<FORM>(x_t[j], m[j])));
-                const Word fin = add_shifted((acc & ~(Word)ID) | own, div_by<FORM>(rec_c.y, mw));
+                for (int j = 0; j < W; ++j) acc = max(acc, add_quotient(v[j], x_t[j], m[j], up));
+                const Word fin = add_quotient((acc & ~(Word)ID) | own, rec_c.y, mw, up);
                 atomicMax(mine, fin);
                 best = max(best, fin);
             }
@@ -405,7 +407,7 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
 
 // Both sweeps (sweeps = 3) or one of them; workgroups of one partition group sit side by side, and an
 // XCD gets consecutive groups, so that lines of a vertex's row meet in one L2.
-template <typename Word, int G, int W, int FORM, int NL, bool FAR>
+template <typename Word, int G, int W, typename Tab, int NL, bool FAR>
 __global__ __launch_bounds__(kWindowMaxWaves * 64, FAR && sizeof(Word) == 4 ? 8 : 4) void window_lanes_kernel(LaneArgs b, LaneArgs t, LaneShape sh,
                                                                             int32_t sweeps, int32_t total,
                                                                             int32_t per_xcd) {
@@ -415,8 +417,8 @@ __global__ __launch_bounds__(kWindowMaxWaves * 64, FAR && sizeof(Word) == 4 ? 8 
     if (id >= total) return;                   // whole workgroup: no barrier has been reached yet
     const bool second = sweeps == 3 ? (id & 1) != 0 : sweeps == 2;
     const int32_t grp = sweeps == 3 ? id >> 1 : id;
-    if (second) lane_sweep<Word, true, G, W, FORM, NL, FAR>(t, sh, (uint8_t *)lds16, red, grp);
-    else lane_sweep<Word, false, G, W, FORM, NL, FAR>(b, sh, (uint8_t *)lds16, red, grp);
+    if (second) lane_sweep<Word, true, G, W, Tab, NL, FAR>(t, sh, (uint8_t *)lds16, red, grp);
+    else lane_sweep<Word, false, G, W, Tab, NL, FAR>(b, sh, (uint8_t *)lds16, red, grp);
 }
 
 // Device ids as the loaders want them: [groups][n][G] by position of either sweep, groups past the batch
@@ -450,7 +452,7 @@ __global__ __launch_bounds__(256) void group_ids_kernel(const uint8_t *__restric
     if (bad) *status = CP_STATUS_BAD_DEVICE_ID;
 }
 
-LaneArgs lane_args(const SweepLaunch &s, const LaneDir &d, const uint8_t *ids, int form, uint8_t *far) {
+LaneArgs lane_args(const SweepLaunch &s, const LaneDir &d, const uint8_t *ids, bool floats, uint8_t *far) {
     LaneArgs a{};
     a.stream = (const uint4 *)(s.blob + d.stream_off);
     a.tick_tab = (const uint32_t *)(s.blob + d.tick_off);
@@ -462,8 +464,8 @@ LaneArgs lane_args(const SweepLaunch &s, const LaneDir &d, const uint8_t *ids, i
     a.off_sv = (uint32_t)(s.out_sv * s.tick_bytes);
     a.off_sq = (uint32_t)(s.out_sq * s.tick_bytes);
     a.cp_out = s.cp_out;
-    a.edge_tab = form == kMagic4 ? (const void *)s.edge_tab4 : s.edge_tab;
-    a.vert_tab = form == kMagic4 ? (const void *)s.vert_tab4 : s.vert_tab;
+    a.edge_tab = floats ? (const void *)s.edge_tab4 : s.edge_tab;
+    a.vert_tab = floats ? (const void *)s.vert_tab4 : s.vert_tab;
     a.far_list = (const int32_t *)(s.blob + d.far_off);
     a.far = far;
     a.far_cap = d.far_cap;
@@ -472,9 +474,9 @@ LaneArgs lane_args(const SweepLaunch &s, const LaneDir &d, const uint8_t *ids, i
     return a;
 }
 
-template <typename Word, int G, int W, int FORM, int NL, bool FAR>
+template <typename Word, int G, int W, typename Tab, int NL, bool FAR>
 int launch_lanes_k(const LaneArgs &b, const LaneArgs &t, const LaneCfg &cfg, int sweeps, int32_t P, hipStream_t st) {
-    auto kern = window_lanes_kernel<Word, G, W, FORM, NL, FAR>;
+    auto kern = window_lanes_kernel<Word, G, W, Tab, NL, FAR>;
     if (cfg.lds_bytes > 64 * 1024 &&
         hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)cfg.lds_bytes) !=
             hipSuccess)
@@ -491,23 +493,23 @@ int launch_lanes_k(const LaneArgs &b, const LaneArgs &t, const LaneCfg &cfg, int
     return hipGetLastError() == hipSuccess ? CP_OK : CP_ERR_HIP;
 }
 
-template <typename Word, int G, int W, int FORM>
+template <typename Word, int G, int W, typename Tab>
 int launch_lanes_n(const LaneArgs &b, const LaneArgs &t, const LaneCfg &cfg, int sweeps, int32_t P, hipStream_t st) {
-    if (cfg.nfw > 0) return launch_lanes_k<Word, G, W, FORM, 2, true>(b, t, cfg, sweeps, P, st);
-    return cfg.nl == 4 ? launch_lanes_k<Word, G, W, FORM, 4, false>(b, t, cfg, sweeps, P, st)
-                       : launch_lanes_k<Word, G, W, FORM, 2, false>(b, t, cfg, sweeps, P, st);
+    if (cfg.nfw > 0) return launch_lanes_k<Word, G, W, Tab, 2, true>(b, t, cfg, sweeps, P, st);
+    return cfg.nl == 4 ? launch_lanes_k<Word, G, W, Tab, 4, false>(b, t, cfg, sweeps, P, st)
+                       : launch_lanes_k<Word, G, W, Tab, 2, false>(b, t, cfg, sweeps, P, st);
 }
 
-template <typename Word, int G, int FORM>
+template <typename Word, int G, typename Tab>
 int launch_lanes_g(const LaneArgs &b, const LaneArgs &t, const LaneCfg &cfg, int sweeps, int32_t P, hipStream_t st) {
-    return cfg.width == 2 ? launch_lanes_n<Word, G, 2, FORM>(b, t, cfg, sweeps, P, st)
-                          : launch_lanes_n<Word, G, 4, FORM>(b, t, cfg, sweeps, P, st);
+    return cfg.width == 2 ? launch_lanes_n<Word, G, 2, Tab>(b, t, cfg, sweeps, P, st)
+                          : launch_lanes_n<Word, G, 4, Tab>(b, t, cfg, sweeps, P, st);
 }
 
-template <typename Word, int FORM>
+template <typename Word, typename Tab>
 int launch_lanes_w(const LaneArgs &b, const LaneArgs &t, const LaneCfg &cfg, int sweeps, int32_t P, hipStream_t st) {
-    return cfg.groups == 8 ? launch_lanes_g<Word, 8, FORM>(b, t, cfg, sweeps, P, st)
-                           : launch_lanes_g<Word, 4, FORM>(b, t, cfg, sweeps, P, st);
+    return cfg.groups == 8 ? launch_lanes_g<Word, 8, Tab>(b, t, cfg, sweeps, P, st)
+                           : launch_lanes_g<Word, 4, Tab>(b, t, cfg, sweeps, P, st);
 }
 
 }  // namespace
@@ -587,11 +589,12 @@ int launch_window_lanes(const SweepLaunch &sb, const SweepLaunch &st, const Lane
     else return CP_ERR_ARG;
 #undef CP_GROUP
     if (hipGetLastError() != hipSuccess) return CP_ERR_HIP;
-    const int form = cfg.word == 8 ? kRound8 : (sb.edge_tab4 ? kMagic4 : kMagic8);
-    const LaneArgs b = lane_args(sb, db, ids_b, form, far_b), t = lane_args(st, dt, ids_t, form, far_t);
-    if (form == kRound8) return launch_lanes_w<unsigned long long, kRound8>(b, t, cfg, sweeps, sb.P, hs);
-    if (form == kMagic4) return launch_lanes_w<uint32_t, kMagic4>(b, t, cfg, sweeps, sb.P, hs);
-    return launch_lanes_w<uint32_t, kMagic8>(b, t, cfg, sweeps, sb.P, hs);
+    const LaneArgs b = lane_args(sb, db, ids_b, cfg.floats, far_b), t = lane_args(st, dt, ids_t, cfg.floats, far_t);
+    if (cfg.word == 8)
+        return cfg.floats ? launch_lanes_w<unsigned long long, float>(b, t, cfg, sweeps, sb.P, hs)
+                          : launch_lanes_w<unsigned long long, double>(b, t, cfg, sweeps, sb.P, hs);
+    return cfg.floats ? launch_lanes_w<uint32_t, float>(b, t, cfg, sweeps, sb.P, hs)
+                      : launch_lanes_w<uint32_t, double>(b, t, cfg, sweeps, sb.P, hs);
 }
 
 }  // namespace cpeval
