@@ -902,6 +902,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     // ---- stage: prep
     CP_MARK(CP_STAGE_PREP);
     const Inverses inverses = column4 ? Inverses::kDoubles
+                              : use == CP_PLAN_RESIDENT_WINDOW && !chain && (p.win_b.ent4 || p.win_t.ent4) ? Inverses::kFloats
                               : !lanes && !whole ? Inverses::kNone
                               : (lanes ? lane_cfg.floats : whole_cfg.floats) ? Inverses::kFloats : Inverses::kDoubles;
     std::vector<uint64_t> tab_img;

@@ -1217,6 +1217,7 @@ struct WindowArgs {
     void *out;                 // [n][P] ticks, or NULL
     int64_t *cp_out;           // [P] or NULL: receives the maximum of b over the partition
     const Magic *edge_tab;
+    const float *edge_tab4;    // entries with 16-bit volumes: the transfer costs' inverses instead
     const Magic *vert_tab;
     int32_t P, L, k, slots, wpad, smax;   // L counts ticks
     int32_t idpad;             // bytes of a stage slot set aside for device ids
@@ -1253,7 +1254,7 @@ typedef const uint32_t __attribute__((address_space(4))) *const_u32_ptr;   // un
 // LDS layout: per partition of the workgroup [ring][far pairs][2 stage slots], then the cost
 // tables, which the partitions share; a stage slot is
 // [wpad bytes of device ids][packet], NL*nlw*1024 bytes in all.  The ring is
-// either (slots+1) x {value, device*8} (PACKED: one 8-byte read per relaxation, and
+// either (slots+1) x {value, device * bytes of a transfer cost} (PACKED: one 8-byte read per relaxation, and
 // an entry's ring field is the byte offset itself) or (slots+1) values followed by
 // (slots+1) device bytes.
 //
@@ -1300,17 +1301,18 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
     Tick *ring_val = (Tick *)lds;                                  // split layout
     uint8_t *ring_dev = lds + sizeof(Tick) * ((size_t)R + 1);
     const uint32_t far_bytes = FAR ? 8u * (uint32_t)a.far_cap : 0u;   // per tick parity, behind the ring
+    // transfer costs: inverses where an entry's volume has 16 bits, a division is then one multiply-add
+    typedef typename std::conditional<ENT4, float, Magic>::type Tab;
     // byte offsets from this partition's LDS: the shared tables lie behind the last partition
     const uint32_t etab_off = (uint32_t)(a.groups - sub) * a.sub_bytes;
-    const uint32_t vtab_off = etab_off + 8u * (uint32_t)(k * k);
+    const uint32_t vtab_off = etab_off + (((uint32_t)sizeof(Tab) * (uint32_t)(k * k) + 7u) & ~7u);
     const int slot_bytes = NL * a.nlw * 1024;
     uint8_t *stage = lds + ring_bytes + 2u * far_bytes;
     (void)tab_bytes;
     {
-        const uint64_t *e = (const uint64_t *)a.edge_tab, *v = (const uint64_t *)a.vert_tab;
-        uint64_t *t64 = (uint64_t *)(lds + etab_off);
-        for (int i = tid; i < k * k; i += nt) t64[i] = e[i];
-        for (int i = tid; i < k; i += nt) t64[k * k + i] = v[i];
+        const Tab *e = (const Tab *)(ENT4 ? (const void *)a.edge_tab4 : (const void *)a.edge_tab);
+        for (int i = tid; i < k * k; i += nt) ((Tab *)(lds + etab_off))[i] = e[i];
+        for (int i = tid; i < k; i += nt) ((Magic *)(lds + vtab_off))[i] = a.vert_tab[i];
         if constexpr (MASK)
             for (int i = tid; i < 2 * kMaskWords; i += nt) (&mbits[0][0])[i] = 0;
         if (wave == 0 && lane == 0) {        // the constant-zero slot padding entries point at
@@ -1354,7 +1356,7 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
             uint32_t dev = arow[(size_t)e.x * (size_t)a.far_a_sv];
             if (dev >= (uint32_t)k) { bad = true; dev = (uint32_t)k - 1; }
             if (TSWEEP) val += (Tick)magic_div(e.y, vtab[dev]);      // the ring holds tl + w
-            return make_uint2((uint32_t)val, 8u * dev);
+            return make_uint2((uint32_t)val, (uint32_t)sizeof(Tab) * dev);
         };
         uint2 lst[X], got[X];
 #pragma unroll
@@ -1478,7 +1480,12 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
         typedef typename std::conditional<ENT4, uint32_t, uint2>::type Ent;
         Tick *out = a.out ? (Tick *)a.out + (size_t)q * (size_t)a.out_sq : nullptr;
         const uint32_t out_sv = a.out_sv;
-        const uint32_t k8 = 8u * (uint32_t)k;
+        const uint32_t row_bytes = (uint32_t)sizeof(Tab) * (uint32_t)k;
+        // Inverses: the sums carry the base's bits until the maximum is taken (values below 2^31, so 32 bits hold them)
+        constexpr uint32_t kBias = ENT4 && sizeof(Tick) == 4 ? 0x48000000u : 0u;
+        typedef typename std::conditional<sizeof(Tick) == 4, uint32_t, Tick>::type Acc;
+        float up = 0.0f;
+        if constexpr (ENT4) up = round_up(float());     // (no variable divisions behind this)
         const uint32_t rec_off = (uint32_t)head + 16u * (uint32_t)a.smax;   // records, from the slot base
         const uint32_t brow_mis = MASK ? (uint32_t)(((uintptr_t)a.bvals + (size_t)q * (size_t)a.n * sizeof(Tick)) & 15)
                                        : 0u;
@@ -1493,7 +1500,13 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
         auto ent_t = [](Ent e) -> uint32_t {
             if constexpr (ENT4) return e >> 16; else return e.y;
         };
-        // value and 8 * device of the vertex behind ring field f
+        // value + transfer time
+        auto plus_transfer = [&](Tick value, uint32_t volume, Tab m) -> Acc {
+            if constexpr (!ENT4) return (Acc)value + (Acc)magic_div(volume, m);
+            else if constexpr (sizeof(Tick) == 4) return (Acc)value + inverse_bits(volume, m, up);
+            else return (Acc)value + (Acc)inverse_div(volume, m, up);
+        };
+        // value and sizeof(Tab) * device of the vertex behind ring field f
         auto ring_get = [&](uint32_t f, Tick &vu, uint32_t &pu8) {
             if constexpr (PACKED) {
                 const uint2 x = *(const uint2 *)(lds + f);
@@ -1501,11 +1514,11 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
                 pu8 = x.y;
             } else {
                 vu = ring_val[f];
-                pu8 = 8u * ring_dev[f];
+                pu8 = (uint32_t)sizeof(Tab) * ring_dev[f];
             }
         };
         // fold the lanes of a row; afterwards the row's first lane holds the row's maximum
-        auto fold = [&](Tick acc, int lsh) -> Tick {
+        auto fold = [&](Acc acc, int lsh) -> Acc {
             if (lsh == 0) return acc;
             if (lsh >= 1) acc = max(acc, __shfl_xor(acc, 1));
             if (lsh >= 2) acc = max(acc, __shfl_xor(acc, 2));
@@ -1525,7 +1538,7 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
                 int rs = rbase + row;
                 if (rs >= R) rs -= R;
                 if constexpr (PACKED) {
-                    ((uint2 *)lds)[rs] = make_uint2((uint32_t)fin, 8u * pv);
+                    ((uint2 *)lds)[rs] = make_uint2((uint32_t)fin, (uint32_t)sizeof(Tab) * pv);
                 } else {
                     ring_val[rs] = fin;
                     ring_dev[rs] = (uint8_t)pv;
@@ -1563,7 +1576,8 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
             uint2 rc;
             uint32_t pv;
             Magic mv;
-            Tick acc = 0, bv = 0;
+            Acc acc = kBias;
+            Tick bv = 0;
             // byte (v - lo) * sizeof(Tick) of the staged b range, which starts at a 16-byte boundary
             const uint32_t b_bias = ((brow_mis + (uint32_t)sizeof(Tick) * lo) & 15u) - (uint32_t)sizeof(Tick) * lo;
             // The vertex's own reads (record, then its device id, then its cost-table entry)
@@ -1577,7 +1591,7 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
         Ent en_[N + 1];                                                                         \
         Tick vu_[N + 1];                                                                        \
         uint32_t pu8_[N + 1];                                                                   \
-        Magic mg_[N + 1];                                                                       \
+        Tab mg_[N + 1];                                                                        \
         rc = *rec;                                                                              \
         _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_) en_[i_] = ent[i_ * 64];                \
         pv = st[a.direct ? rc.x + id_bias : (uint32_t)p];                                       \
@@ -1585,11 +1599,11 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
         _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_) ring_get(ent_field(en_[i_]), vu_[i_], pu8_[i_]); \
         worst = max(worst, pv);                                                                 \
         pv = min(pv, (uint32_t)(k - 1));                                                        \
-        erow = etab_off + __umul24(pv, k8);                                                     \
+        erow = etab_off + __umul24(pv, row_bytes);                                              \
         mv = *(const Magic *)(lds + vtab_off + 8u * pv);                                        \
-        _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_) mg_[i_] = *(const Magic *)(lds + erow + pu8_[i_]); \
+        _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_) mg_[i_] = *(const Tab *)(lds + erow + pu8_[i_]);   \
         _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_)                                        \
-            acc = max(acc, (Tick)(vu_[i_] + (Tick)magic_div(ent_t(en_[i_]), mg_[i_])));         \
+            acc = max(acc, plus_transfer(vu_[i_], ent_t(en_[i_]), mg_[i_]));                    \
     } while (0)
             // N further relaxations as one straight-line block: N entry reads, N ring reads,
             // N cost-table reads, then the arithmetic -- three LDS round trips whatever N is
@@ -1598,12 +1612,12 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
         Ent en_[N];                                                                             \
         Tick vu_[N];                                                                            \
         uint32_t pu8_[N];                                                                       \
-        Magic mg_[N];                                                                           \
+        Tab mg_[N];                                                                             \
         _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_) en_[i_] = ent[(jj + i_) * 64];         \
         _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_) ring_get(ent_field(en_[i_]), vu_[i_], pu8_[i_]); \
-        _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_) mg_[i_] = *(const Magic *)(lds + erow + pu8_[i_]); \
+        _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_) mg_[i_] = *(const Tab *)(lds + erow + pu8_[i_]);   \
         _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_)                                        \
-            acc = max(acc, (Tick)(vu_[i_] + (Tick)magic_div(ent_t(en_[i_]), mg_[i_])));         \
+            acc = max(acc, plus_transfer(vu_[i_], ent_t(en_[i_]), mg_[i_]));                    \
     } while (0)
             uint32_t erow;
             switch (min(width, 8)) {
@@ -1632,7 +1646,7 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
 #undef CP_BLOCK
 #undef CP_HEAD
             acc = fold(acc, lsh);
-            publish(acc, (Tick)magic_div(rc.y, mv), lsh, rows, rbase, rc.x, pv, bv, lo);
+            publish((Tick)(acc - kBias), (Tick)magic_div(rc.y, mv), lsh, rows, rbase, rc.x, pv, bv, lo);
         };
 
         lds_barrier();                       // packet 0 is staged
@@ -1792,6 +1806,7 @@ WindowArgs window_args(const SweepLaunch &s, const WindowCfg &cfg) {
     a.cp_out = s.cp_out;
     a.edge_tab = (const Magic *)s.edge_tab;
     a.vert_tab = (const Magic *)s.vert_tab;
+    a.edge_tab4 = dir.ent4 ? (const float *)s.edge_tab4 : nullptr;
     a.P = s.P; a.L = dir.ticks; a.k = s.k; a.slots = dir.slots; a.wpad = dir.wpad; a.smax = dir.smax;
     a.nc = cfg.nc; a.nlw = cfg.nlw;
     // every byte offset of a vertex inside a partition's row of outputs fits 32 bits (and both factors 24)
@@ -2034,6 +2049,7 @@ int launch_column_sweep(const SweepLaunch &s, void *stream, int32_t *launches) {
 }
 
 int launch_window_sweep(const SweepLaunch &s, const WindowCfg &cfg, void *stream, int32_t *launches) {
+    if (s.win->ent4 && !s.edge_tab4) return CP_ERR_ARG;
     if (launches) *launches = 1;
     return s.tsweep ? launch_window_sweep_d<true>(s, cfg, (hipStream_t)stream)
                     : launch_window_sweep_d<false>(s, cfg, (hipStream_t)stream);
@@ -2080,7 +2096,7 @@ int launch_window_pair(const SweepLaunch &sb, const SweepLaunch &st, const Windo
     if (sb.tick_bytes != 4 || st.tick_bytes != 4 || sb.tsweep || !st.tsweep || sb.mask_out || st.mask_out)
         return CP_ERR_ARG;
     if (cfg_b.nl != kPairNl || cfg_t.nl != kPairNl || cfg_b.groups != 1 || cfg_t.groups != 1 ||
-        cfg_b.lds_bytes != cfg_t.lds_bytes || sb.win->ent4 != st.win->ent4 || sb.win->far_cap > 0 || st.win->far_cap > 0)
+        cfg_b.lds_bytes != cfg_t.lds_bytes || sb.win->ent4 != st.win->ent4 || (sb.win->ent4 && (!sb.edge_tab4 || !st.edge_tab4)) || sb.win->far_cap > 0 || st.win->far_cap > 0)
         return CP_ERR_ARG;
     const WindowArgs ab = window_args(sb, cfg_b), at = window_args(st, cfg_t);
     const uint32_t nb = (uint32_t)(8 * ab.pgroups), nt = (uint32_t)(8 * at.pgroups);
