@@ -107,53 +107,68 @@ __device__ __forceinline__ uint64_t heap_pop(uint64_t *h, int32_t &size) {
     return top;
 }
 
-// A queue = its smallest key in a register + the heap above in memory for the rest.  Device
+// A queue = its three smallest keys in registers, in order, + the heap above in memory for the rest.  Device
 // queues are short most of the time (a handful of executable vertices), so most pushes and
-// pops never touch memory, and the decision time is read from the register.
+// pops never touch memory, and the decision time is read from a register.  Three, because with four three partitions
+// of a wavefront need more registers than the wavefronts of a full unit have (20,000 partitions on 3 devices: 5.8 ms, 4.4
+// with three); on 50 devices one to six differ by 3 %.
+constexpr uint64_t kNoKey = ~0ull;         // above every key: times and 2^31 - 1 - b lie below 2^31
+constexpr int kHeld = 3;
+
 struct Queue {
-    uint64_t top = 0;
-    int32_t size = 0;          // keys held, the one in the register included
+    uint64_t key[kHeld];
+    uint32_t b[kHeld];         // pending under PCT: b of each, so that it is loaded once
+    int32_t in_memory = 0;
+    __device__ Queue() {
+        for (int i = 0; i < kHeld; ++i) { key[i] = kNoKey; b[i] = 0; }
+    }
 };
 
-__device__ __forceinline__ void queue_push(uint64_t *h, Queue &q, uint64_t key) {
-    if (q.size == 0) {
-        q.top = key;
-    } else {
-        const uint64_t keep = min(q.top, key), spill = max(q.top, key);
-        q.top = keep;
-        int32_t in_memory = q.size - 1;
-        heap_push(h, in_memory, spill);
+__device__ __forceinline__ void queue_push(uint64_t *h, Queue &q, uint64_t key, uint32_t b = 0) {
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) {
+        const uint64_t k0 = q.key[i];
+        const uint32_t b0 = q.b[i];
+        const bool before = key < k0;
+        q.key[i] = before ? key : k0;
+        q.b[i] = before ? b : b0;
+        key = before ? k0 : key;
+        b = before ? b0 : b;
     }
-    ++q.size;
+    if (key != kNoKey) heap_push(h, q.in_memory, key);
 }
 
-// Taking the smallest key and bringing the next one into the register are two calls, so that
+// Taking the smallest key and bringing the next one into the registers are two calls, so that
 // the caller can start the loads that depend on the key before the heap in memory is put in
 // order again.  Nothing else may touch the queue in between.
 __device__ __forceinline__ uint64_t queue_take(Queue &q) {
-    --q.size;
-    return q.top;
-}
-
-__device__ __forceinline__ void queue_refill(uint64_t *h, Queue &q) {
-    if (q.size > 0) {
-        int32_t in_memory = q.size;
-        q.top = heap_pop(h, in_memory);
+    const uint64_t out = q.key[0];
+#pragma unroll
+    for (int i = 0; i + 1 < kHeld; ++i) {
+        q.key[i] = q.key[i + 1];
+        q.b[i] = q.b[i + 1];
     }
-}
-
-__device__ __forceinline__ uint64_t queue_pop(uint64_t *h, Queue &q) {
-    const uint64_t out = queue_take(q);
-    queue_refill(h, q);
+    q.key[kHeld - 1] = kNoKey;
     return out;
 }
 
-// b(z) of the lane's partition; a value outside [0, 2^31) is reported and replaced by 0.
-__device__ __forceinline__ long long load_b(const uint8_t *bq, int32_t z, int64_t bsv, int32_t b_bytes, bool &bad) {
-    long long bz = b_bytes == 4 ? (long long)*(const int32_t *)(bq + (int64_t)z * bsv * 4)
-                                : *(const long long *)(bq + (int64_t)z * bsv * 8);
-    if (bz < 0 || bz > 0x7fffffffll) { bad = true; bz = 0; }
-    return bz;
+// Whether a key came from memory, whose b the caller then has to ask for.
+__device__ __forceinline__ bool queue_refill(uint64_t *h, Queue &q) {
+    if (q.in_memory == 0) return false;
+    q.key[kHeld - 1] = heap_pop(h, q.in_memory);
+    return true;
+}
+
+// b(z) of the lane's partition as it is in memory, anything outside 32 bits as ~0; used, a value outside [0, 2^31) is
+// reported and replaced by 0.  Two steps, so that several loads of 32 bits can be on their way.
+__device__ __forceinline__ uint32_t load_b(const uint8_t *bq, int32_t z, int64_t bsv, int32_t b_bytes) {
+    if (b_bytes == 4) return *(const uint32_t *)(bq + (int64_t)z * bsv * 4);
+    const uint64_t wide = *(const uint64_t *)(bq + (int64_t)z * bsv * 8);
+    return wide >> 32 ? 0xffffffffu : (uint32_t)wide;
+}
+__device__ __forceinline__ uint64_t available_key(uint32_t b, int32_t z, bool &bad) {
+    if (b > 0x7fffffffu) { bad = true; b = 0; }
+    return ((uint64_t)(0x7fffffffu - b) << 32) | (uint32_t)z;
 }
 
 // How much of a partition's state a wavefront with one partition keeps in LDS.  A step is a chain of dependent
@@ -168,7 +183,7 @@ enum Resident { kNothing, kOwnersAndInputs, kNearInboxToo, kAll };
 
 // kNearInboxToo: the first two vertices handed to a device in a step wait in LDS, the others in its inbox in memory,
 // which then costs most steps neither a store to wait for nor a round trip (5,271 vertices, 50 devices, 4,096
-// partitions: PCT 4.46 -> 3.93 ms, FIFO 3.88 -> 3.40).  From kNearFrom wavefronts a compute unit on: one alone finds its
+// partitions: PCT 4.46 -> 3.93 ms, FIFO 3.88 -> 3.40, before the records).  From kNearFrom wavefronts a compute unit on: one alone finds its
 // inbox in the L1 (24,000 vertices, 8 devices: 64 and 256 partitions 1.02 times as long with it, 512 as long,
 // 1,024 0.98, on 50 devices 0.96).  Two, because the static LDS then still is kSimStaticLds; 16 bits, because state in LDS
 // means at most 43,690 vertices.
@@ -176,11 +191,26 @@ constexpr size_t kNearFrom = 3;
 constexpr int32_t kNearInbox = 2;
 static_assert(3 * 64 * sizeof(int32_t) + 64 * kNearInbox * sizeof(uint16_t) <= kSimStaticLds, "fits() counts on it");
 
+// An entry of the cost tables, and ceil(a / d) by it.
+template <bool MAGIC> struct DivisorOf {
+    Magic m = {0, 0};
+};
+template <> struct DivisorOf<false> {
+    int64_t d = 1;
+};
+template <typename WT> __device__ __forceinline__ uint32_t quotient(WT a, const DivisorOf<true> &by) {
+    return magic_div((uint32_t)a, by.m);
+}
+template <typename WT> __device__ __forceinline__ uint32_t quotient(WT a, const DivisorOf<false> &by) {
+    return (uint32_t)plain_div((uint64_t)a, (uint64_t)by.d);
+}
+
 struct SimArgs {
     const int32_t *ptr;        // successor CSR over original ids
     const int32_t *idx;
     const void *wt;            // t(e) in that order
     const void *c;
+    const uint4 *records;      // [n][2] where weights have 32 bits: see simulate_records_kernel
     const int32_t *pred_ptr;   // predecessor CSR row bounds: the in-degrees
     const uint8_t *assign;
     int64_t a_stride_p, a_stride_v;
@@ -205,8 +235,40 @@ struct SimArgs {
     int32_t need_bits;         // LDS: bits of an open-input count, 4 or 8
 };
 
+// What a step reads of a vertex, 32 bytes: c, its out-edges' number, and up to kRecordEdges of them as (head, t), or the
+// number of the first one.  A lane's loads go to lines of their own, and the address unit and the L1 were busy two thirds
+// of the time: one line in place of four (c, row bounds, heads, t), and a round trip less where the edges are in it.  With
+// b asked for beside the ready time and three keys a queue in registers, 5,271 vertices of 1 to 3 out-edges on 50 devices,
+// PCT: 256 partitions 1.60 -> 1.33 ms, 1,024 1.78 -> 1.50, 4,096 3.97 -> 3.06, FIFO 3.39 -> 2.87; out-edges 1 to 7 7.62 -> 7.20.
+// The launch that writes them takes some 5 us.
+constexpr int32_t kRecordEdges = 3;
+__global__ __launch_bounds__(256) void simulate_records_kernel(const int32_t *__restrict__ ptr,
+                                                               const int32_t *__restrict__ idx,
+                                                               const uint32_t *__restrict__ wt,
+                                                               const uint32_t *__restrict__ c, int32_t n,
+                                                               uint4 *__restrict__ records) {
+    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (v >= n) return;
+    const int32_t e0 = ptr[v], degree = ptr[v + 1] - e0;
+    uint32_t w[2 * kRecordEdges] = {};
+    if (degree > kRecordEdges) {
+        w[0] = (uint32_t)e0;
+    } else {
+#pragma unroll
+        for (int j = 0; j < kRecordEdges; ++j) {
+            if (j < degree) {
+                w[2 * j] = (uint32_t)idx[e0 + j];
+                w[2 * j + 1] = wt[e0 + j];
+            }
+        }
+    }
+    records[2 * v] = make_uint4(c[v], (uint32_t)degree, w[0], w[1]);
+    records[2 * v + 1] = make_uint4(w[2], w[3], w[4], w[5]);
+}
+
 template <typename WT, bool MAGIC, bool PCT, int KEEP>
 __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
+    constexpr bool kRecords = sizeof(WT) == 4;
     extern __shared__ uint32_t sim_lds[];
     __shared__ int32_t count[64];      // vertices per device, then handed to it so far (kNearInboxToo: in this step)
     __shared__ int32_t seg[64];        // first slot of the device's segment
@@ -227,8 +289,8 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
     const int64_t asv = a.a_stride_v;
     const WT *wt = (const WT *)a.wt;
     const WT *cw = (const WT *)a.c;
-    const Magic *etab_m = (const Magic *)a.edge_tab, *vtab_m = (const Magic *)a.vert_tab;
-    const int64_t *etab_g = (const int64_t *)a.edge_tab, *vtab_g = (const int64_t *)a.vert_tab;
+    using Divisor = DivisorOf<MAGIC>;
+    const Divisor *etab = (const Divisor *)a.edge_tab, *vtab = (const Divisor *)a.vert_tab;
     int32_t *ready = a.ready + qq * n;
     int32_t *need = a.need + qq * n;
     int32_t *start = a.start ? a.start + qq * n : nullptr;
@@ -293,6 +355,9 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
     }
     step_fence();
     int32_t *inbox = a.inbox + qq * n;
+    const int64_t bsv = a.b_sv;
+    const uint8_t *bq = (const uint8_t *)a.b + (PCT ? qq * a.b_sq * a.b_bytes : 0);
+    bool b_bad = false;
     if (alive) {
         for (int32_t v = dev; v < n; v += k) {
             if (a.pred_ptr[v + 1] == a.pred_ptr[v]) {
@@ -311,13 +376,11 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
     uint64_t *hp = a.pending + qq * n + base;
     uint64_t *ha = PCT ? a.available + qq * n + base : nullptr;
     const int32_t *my_inbox = inbox + base;
-    const int64_t bsv = a.b_sv;
-    const uint8_t *bq = (const uint8_t *)a.b + (PCT ? qq * a.b_sq * a.b_bytes : 0);
     const int last_lane = min(first + k - 1, 63);
     Queue pending, available;
+    const Divisor my_speed = vtab[dev];
     int32_t taken = 0, done = 0;
     uint32_t free_at = 0;
-    bool b_bad = false;
     // what a started vertex does to a successor of its own partition
     auto raise_ready = [&](int32_t z, uint32_t arrival) {
         if (KEEP == kAll) atomicMax(&l_ready[z], arrival);
@@ -339,46 +402,28 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
     // every step with work left starts at least one vertex in every unfinished group, so
     // n + 1 steps always suffice
     for (int64_t step = 0; step <= n; ++step) {
-        if (alive) {   // vertices handed to this device since its last step, four loads in flight at a time
+        if (alive) {   // vertices handed to this device since its last step
             const int32_t have = count[lane];
             if (KEEP == kNearInboxToo) {            // what is handed over in a step is numbered from 0
                 taken = 0;
                 count[lane] = 0;
             }
-            while (taken < have) {
-                const int32_t cnt = min(4, have - taken);
-                int32_t z[4];
-                uint32_t rz[4], low[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int32_t at = taken + min(j, cnt - 1);
-                    if (KEEP == kAll) z[j] = (int32_t)l_inbox[base + at];
-                    else if (KEEP == kNearInboxToo && at < kNearInbox) z[j] = (int32_t)near_in[lane][at];
-                    else z[j] = inbox_load(my_inbox + at);
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    rz[j] = KEEP == kAll ? l_ready[z[j]] : (uint32_t)l2_read(ready + z[j]);
-                    low[j] = PCT ? (uint32_t)z[j] : (a.tie ? (uint32_t)a.tie[z[j]] : (uint32_t)z[j]);
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (j < cnt) {
-                        if (PCT && rz[j] <= free_at) {
-                            // executable at every decision this device has still to take
-                            const long long bz = load_b(bq, z[j], bsv, a.b_bytes, b_bad);
-                            queue_push(ha, available, ((uint64_t)(0x7fffffffu - (uint32_t)bz) << 32) | (uint32_t)z[j]);
-                        } else {
-                            queue_push(hp, pending, ((uint64_t)rz[j] << 32) | low[j]);
-                        }
-                    }
-                }
-                taken += cnt;
+            for (; taken < have; ++taken) {
+                int32_t z;
+                if (KEEP == kAll) z = (int32_t)l_inbox[base + taken];
+                else if (KEEP == kNearInboxToo && taken < kNearInbox) z = (int32_t)near_in[lane][taken];
+                else z = inbox_load(my_inbox + taken);
+                const uint32_t rz = KEEP == kAll ? l_ready[z] : (uint32_t)l2_read(ready + z);
+                const uint32_t bz = PCT ? load_b(bq, z, bsv, a.b_bytes) : 0u;
+                if (PCT && rz <= free_at)    // executable at every decision this device has still to take
+                    queue_push(ha, available, available_key(bz, z, b_bad));
+                else
+                    queue_push(hp, pending, ((uint64_t)rz << 32) | (!PCT && a.tie ? (uint32_t)a.tie[z] : (uint32_t)z), bz);
             }
         }
         uint32_t T = kNever;
-        if (PCT && available.size > 0) T = free_at;
-        else if (pending.size > 0) T = max(free_at, (uint32_t)(pending.top >> 32));
+        if (PCT && available.key[0] != kNoKey) T = free_at;
+        else if (pending.key[0] != kNoKey) T = max(free_at, (uint32_t)(pending.key[0] >> 32));
         // the group's earliest decision time (several groups: a running minimum over each
         // group's lanes, read from its last lane)
         uint32_t tmin = T;
@@ -405,11 +450,12 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
         if (T != kNever && T - tmin <= a.window) {
             int32_t v;
             if (PCT) {
-                for (int32_t moved = 0; pending.size > 0 && (uint32_t)(pending.top >> 32) <= T && moved < n;
-                     ++moved) {
-                    const int32_t z = (int32_t)(uint32_t)queue_pop(hp, pending);
-                    const long long bz = load_b(bq, z, bsv, a.b_bytes, b_bad);
-                    queue_push(ha, available, ((uint64_t)(0x7fffffffu - (uint32_t)bz) << 32) | (uint32_t)z);
+                for (int32_t moved = 0; (uint32_t)(pending.key[0] >> 32) <= T && moved < n; ++moved) {
+                    const uint32_t bz = pending.b[0];
+                    const int32_t z = (int32_t)(uint32_t)queue_take(pending);
+                    if (queue_refill(hp, pending))
+                        pending.b[kHeld - 1] = load_b(bq, (int32_t)(uint32_t)pending.key[kHeld - 1], bsv, a.b_bytes);
+                    queue_push(ha, available, available_key(bz, z, b_bad));
                 }
                 v = (int32_t)(uint32_t)queue_take(available);
             } else {
@@ -417,44 +463,60 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
                 v = a.tie_inv ? a.tie_inv[low] : (int32_t)low;
             }
             // what the vertex needs from the graph is on its way while the queue is put in order
-            const WT cv = cw[v];
-            const int32_t e0 = a.ptr[v], e1 = a.ptr[v + 1];
+            uint4 r0, r1;
+            WT cv;
+            int32_t e0, degree;
+            if (kRecords) {
+                r0 = a.records[2 * (int64_t)v];
+                r1 = a.records[2 * (int64_t)v + 1];
+                cv = (WT)r0.x;
+                degree = (int32_t)r0.y;
+                e0 = (int32_t)r0.z;
+            } else {
+                cv = cw[v];
+                e0 = a.ptr[v];
+                degree = a.ptr[v + 1] - e0;
+            }
             if (PCT) queue_refill(ha, available);
             else queue_refill(hp, pending);
             if (start) start[v] = (int32_t)T;
             ++done;
-            const uint32_t w = MAGIC ? magic_div((uint32_t)cv, vtab_m[dev])
-                                     : (uint32_t)plain_div((uint64_t)cv, (uint64_t)vtab_g[dev]);
+            const uint32_t w = quotient(cv, my_speed);
             free_at = T + w;
             // the out-edges four at a time, so that the dependent loads of four edges (successor,
-            // its device, the table entry) and their atomics overlap; slots past the row's end
-            // repeat its last edge for the loads and take no part in the atomics
-            int32_t e_end = e1;
-            if (e1 - e0 >= kWideRow) {
+            // its device, the table entry) and their atomics overlap; slots past the row's end take
+            // no part but for the table's first entries, whose loads need no branch
+            const bool held = kRecords && degree <= kRecordEdges;      // in the record
+            if (degree >= kWideRow) {
                 wide_e0 = e0;
-                wide_e1 = e1;
-                e_end = e0;
+                wide_e1 = e0 + degree;
+                degree = 0;
             }
-            for (int32_t e = e0; e < e_end; e += 4) {
-                const int32_t cnt = min(4, e_end - e);
+            for (int32_t i = 0; i < degree; i += 4) {
+                const int32_t cnt = min(4, degree - i), e = e0 + i;
                 int32_t z[4], before[4];
                 WT te[4];
                 uint32_t dz[4], arrive[4];
+                Divisor by[4];
+                if (held) {
+                    z[0] = (int32_t)r0.z; te[0] = (WT)r0.w;
+                    z[1] = (int32_t)r1.x; te[1] = (WT)r1.y;
+                    z[2] = (int32_t)r1.z; te[2] = (WT)r1.w;
+                    z[3] = 0; te[3] = 0;
+                } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int32_t ej = e + min(j, cnt - 1);
-                    z[j] = a.idx[ej];
-                    te[j] = wt[ej];
+                    for (int j = 0; j < 4; ++j) {
+                        const int32_t ej = e + min(j, cnt - 1);
+                        z[j] = a.idx[ej];
+                        te[j] = wt[ej];
+                    }
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) dz[j] = owner(z[j]);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t x = MAGIC ? magic_div((uint32_t)te[j], etab_m[dev * k + dz[j]])
-                                             : (uint32_t)plain_div((uint64_t)te[j],
-                                                                       (uint64_t)etab_g[dev * k + dz[j]]);
-                    arrive[j] = free_at + x;
-                }
+                for (int j = 0; j < 4; ++j) by[j] = etab[dev * k + dz[j]];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) arrive[j] = free_at + quotient(te[j], by[j]);
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     if (j < cnt) raise_ready(z[j], arrive[j]);
@@ -482,8 +544,7 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
                 const int32_t z = a.idx[e];
                 const WT te = wt[e];
                 const uint32_t dz = KEEP != kNothing ? (uint32_t)l_dev[z] : (uint32_t)hrow[(int64_t)z * asv];
-                const uint32_t x = MAGIC ? magic_div((uint32_t)te, etab_m[hdev * k + dz])
-                                         : (uint32_t)plain_div((uint64_t)te, (uint64_t)etab_g[hdev * k + dz]);
+                const uint32_t x = quotient(te, etab[hdev * k + dz]);
                 if (KEEP != kNothing) {              // the wavefront's only partition
                     raise_ready(z, hfree + x);
                     if (take_input(z) == 1) hand_over(z, dz);
@@ -566,6 +627,11 @@ int launch_simulate(const SimulateLaunch &s, void *stream) {
     a.wt = s.blob + s.succ->wt_off;
     a.c = s.blob + s.c_off;
     a.pred_ptr = (const int32_t *)(s.blob + s.pred->ptr_off);
+    if (s.narrow) {
+        a.records = (const uint4 *)s.records;
+        hipLaunchKernelGGL(simulate_records_kernel, dim3((unsigned)((s.n + 255) / 256)), dim3(256), 0, st, a.ptr, a.idx,
+                           (const uint32_t *)a.wt, (const uint32_t *)a.c, s.n, (uint4 *)s.records);
+    }
     a.assign = s.assign;
     a.a_stride_p = s.a_stride_p;
     a.a_stride_v = s.a_stride_v;
