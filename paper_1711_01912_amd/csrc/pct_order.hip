@@ -360,13 +360,18 @@ __device__ __forceinline__ uint32_t cell_of(uint32_t d) { return d ^ (d >> 5); }
 // advances the wavefront's counter for that digit.  The tile is then put in digit order
 // in LDS and written out in runs: first the keys, then, through the same LDS buffer,
 // the vertex numbers.
+// Where nothing was found against a partition (found[q] == 0, the leading scatter only: see pct_bucket_check_kernel), its
+// buckets are sorted with the vertex number as part of the key, and an item takes its place among equal digits by one
+// returning LDS add in place of nine ballots (130 vector instructions an item): 211,000 vertices, 512 partitions, the call
+// 982 -> 895 us on 16 devices, 979 -> 918 on 2; 17 partitions 99 -> 92.  Keys that repeat keep the ballots and their time.
 template <typename Key, int kSortThreads, int RB, bool FIRST, bool LAST>
 __global__ __launch_bounds__(kSortThreads) void pct_scatter_kernel(const Key *__restrict__ keys_in,
                                                                    const int32_t *__restrict__ vals_in,
                                                                    Key *__restrict__ keys_out,
                                                                    int32_t *__restrict__ vals_out, int32_t n,
                                                                    int32_t tiles, int shift,
-                                                                   const uint32_t *__restrict__ starts, Gate gate) {
+                                                                   const uint32_t *__restrict__ starts, Gate gate,
+                                                                   const int32_t *__restrict__ found, int32_t found_stride) {
     constexpr int kSortWaves = kSortThreads / 64, kSortTile = kSortThreads * kSortRounds, kRadix = 1 << RB;
     static_assert(kSortThreads >= kRadix, "one thread per digit when the tile's digit starts are computed");
     if (gate.closed()) return;
@@ -384,6 +389,7 @@ __global__ __launch_bounds__(kSortThreads) void pct_scatter_kernel(const Key *__
     for (int i = tid; i < kSortWaves * kRadix; i += kSortThreads) (&cnt[0][0])[i] = 0;
     __syncthreads();
 
+    const bool any_order = FIRST && !LAST && found != nullptr && found[(int64_t)q * found_stride] == 0;
     Key key[kSortRounds];
     int32_t val[kSortRounds];
     uint32_t loc[kSortRounds];       // rank among equal digits, then position in the sorted tile
@@ -394,11 +400,18 @@ __global__ __launch_bounds__(kSortThreads) void pct_scatter_kernel(const Key *__
         key[r] = valid ? keys_in[seg + base + t] : (Key)0;
         val[r] = FIRST ? (int32_t)(base + t) : (valid ? vals_in[seg + base + t] : 0);
     }
+    if (any_order) {
 #pragma unroll
-    for (int r = 0; r < kSortRounds; ++r) {
-        const int32_t t = wave * (kSortRounds * 64) + r * 64 + lane;
-        const bool valid = t < tile_items;
-        loc[r] = rank_in_wavefront<RB>(cnt[wave], cell_of(digit_of<RB>(key[r], shift)), valid);
+        for (int r = 0; r < kSortRounds; ++r)
+            if (wave * (kSortRounds * 64) + r * 64 + lane < tile_items)
+                loc[r] = atomicAdd(&cnt[wave][cell_of(digit_of<RB>(key[r], shift))], 1u);
+    } else {
+#pragma unroll
+        for (int r = 0; r < kSortRounds; ++r) {
+            const int32_t t = wave * (kSortRounds * 64) + r * 64 + lane;
+            const bool valid = t < tile_items;
+            loc[r] = rank_in_wavefront<RB>(cnt[wave], cell_of(digit_of<RB>(key[r], shift)), valid);
+        }
     }
     __syncthreads();
     uint32_t run = 0, inc = 0;
@@ -468,17 +481,19 @@ constexpr int kBucketCapSmall = 256 * kSortRounds, kBucketCapLarge = 512 * kSort
 
 // After the scan of the leading digit's counts, bucket d of partition q starts where tile 0's
 // run of digit d starts.  flag |= 1 if some bucket holds more than `cap` items.
-// crowded[q] = 1 where 512 * kEach of the partition's keys, spread over its vertices, fall into common bins of
+// found[q]: kLeftOver where some bucket holds more than `bins_cap` items, which the bins leave to the ranking by digits;
+// kCrowded where 512 * kEach of the partition's keys, spread over its vertices, fall into common bins of
 // pct_bucket_bins_kernel (keys without their low `shift` bits) as they would with more than kBinAverage items in an average
 // item's bin: then ranking by digits is the faster way, and the bins would be tried in vain.  Few partitions are sampled
 // more finely, because the call then takes as long as the one that was misjudged (a million vertices on 16 devices in 66
 // items a bin, of 512 samples one partition in 14 passed for spread; 8 partitions: 231 us, 203 with 2,048).
 constexpr int kBinMost = 96, kBinAverage = 32, kFineSamples = 128;
+constexpr int32_t kCrowded = 1, kLeftOver = 2;
 template <int kEach>
 __global__ __launch_bounds__(kBuckets) void pct_bucket_check_kernel(const uint32_t *__restrict__ starts,
                                                                     const uint32_t *__restrict__ keys, int32_t n,
-                                                                    int32_t tiles, int32_t cap, int shift, uint32_t *flag,
-                                                                    int32_t *crowded, int32_t crowded_stride) {
+                                                                    int32_t tiles, int32_t cap, int32_t bins_cap, int shift,
+                                                                    uint32_t *flag, int32_t *found, int32_t found_stride) {
     constexpr int kTableBits = kEach > 1 ? 13 : 12, kSamples = kBuckets * kEach;
     __shared__ uint32_t table[1 << kTableBits], wave_pairs[kBuckets / 64];
     const int32_t q = blockIdx.x, d = threadIdx.x;
@@ -490,6 +505,7 @@ __global__ __launch_bounds__(kBuckets) void pct_bucket_check_kernel(const uint32
     for (int i = d; i < 1 << kTableBits; i += kBuckets) table[i] = 0xffffffffu;
     // (one atomic per partition at most, none once the flag is up: they queue up on the one word)
     const int any = __syncthreads_or(hi - lo > (uint32_t)cap);
+    const int left_over = __syncthreads_or(hi - lo > (uint32_t)bins_cap);
     if (any && threadIdx.x == 0 && *(volatile const uint32_t *)flag == 0) atomicOr(flag, 1u);
     uint32_t before[kEach];
 #pragma unroll
@@ -503,7 +519,8 @@ __global__ __launch_bounds__(kBuckets) void pct_bucket_check_kernel(const uint32
 #pragma unroll
     for (int w = 0; w < kBuckets / 64; ++w) pairs += (int)wave_pairs[w];
     if (d == 0)
-        crowded[(int64_t)q * crowded_stride] = (int64_t)pairs * n > (int64_t)kSamples * kSamples / 2 * kBinAverage ? 1 : 0;
+        found[(int64_t)q * found_stride] =
+            ((int64_t)pairs * n > (int64_t)kSamples * kSamples / 2 * kBinAverage ? kCrowded : 0) | (left_over ? kLeftOver : 0);
 }
 
 // Inclusive sum over the lanes of a wavefront: inside rows of 16 by shifts, then a row's last lane
@@ -666,7 +683,7 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
                                                                    int32_t *__restrict__ vals_out, int32_t n, int32_t each,
                                                                    int32_t tiles, int bits, int val_bits,
                                                                    const uint32_t *__restrict__ starts, Gate gate,
-                                                                   const int32_t *__restrict__ crowded, int32_t crowded_stride,
+                                                                   const int32_t *__restrict__ found, int32_t found_stride,
                                                                    uint32_t *left) {
     __shared__ uint32_t sorted[kThreads * kBinRounds];
     __shared__ __align__(16) uint32_t bins[kThreads * 8];
@@ -680,7 +697,7 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
     if (lane <= each && d0 + lane < kBuckets) bound = starts[((int64_t)q * kBuckets + d0 + lane) * tiles];
     if (gate.closed()) return;
     left += (int64_t)q * kBuckets + d0;
-    if (crowded[(int64_t)q * crowded_stride] != 0) {
+    if ((found[(int64_t)q * found_stride] & kCrowded) != 0) {
         const uint32_t next = __shfl_down(bound, 1);
         if ((int)threadIdx.x < each) left[threadIdx.x] = next != bound ? 1u : 0u;
         return;
@@ -704,11 +721,12 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
 // WHOLE: the "bucket" is a whole partition (at most kBucketThreads * kRounds vertices), its keys
 // in vertex order and already in `key`, sorted on all `bits` key bits: short partitions need no pass over
 // HBM at all.
+// BY_VAL: items of equal keys do not stand in the order of their vertex numbers yet, whose digits (val_bits) are sorted first (a bin that is crowded after all, in a partition that nothing was found against).
 // slot: kBucketThreads * kRounds words; cnt: 256 per wavefront
-template <int kBucketThreads, int kRounds, bool WHOLE>
+template <int kBucketThreads, int kRounds, bool WHOLE, bool BY_VAL>
 __device__ __forceinline__ void sort_bucket(const uint32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
-                                            int32_t *__restrict__ vals_out, int32_t items, int bits, uint32_t *slot,
-                                            uint32_t (*cnt)[256], int tid, uint32_t (&key)[kRounds]) {
+                                            int32_t *__restrict__ vals_out, int32_t items, int bits, int val_bits,
+                                            uint32_t *slot, uint32_t (*cnt)[256], int tid, uint32_t (&key)[kRounds]) {
     constexpr int kWaves = kBucketThreads / 64, kRadix = 256;
     __shared__ uint32_t wave_sum[kRadix / 64];
     const int lane = tid & 63, wave = tid >> 6;
@@ -716,17 +734,20 @@ __device__ __forceinline__ void sort_bucket(const uint32_t *__restrict__ keys_in
     // [w * nr * 64, (w + 1) * nr * 64) of the bucket)
     const int nr = (items + kBucketThreads - 1) / kBucketThreads;
 
+    const uint32_t *first_words = BY_VAL ? (const uint32_t *)vals_in : keys_in;
+    const uint32_t *other_words = BY_VAL ? keys_in : (const uint32_t *)vals_in;
     uint32_t loc[kRounds];
     int32_t val[kRounds];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
         const int32_t t = wave * (nr * 64) + r * 64 + lane;
         const bool valid = r < nr && t < items;
-        if (!WHOLE) key[r] = valid ? keys_in[t] : 0u;
-        val[r] = WHOLE ? t : (valid ? vals_in[t] : 0);
+        if (!WHOLE) key[r] = valid ? first_words[t] : 0u;
+        val[r] = WHOLE ? t : (valid ? (int32_t)other_words[t] : 0);
     }
-    for (int shift = 0; shift < bits; shift += 8) {
-        const bool last = shift + 8 >= bits;
+    bool by_val = BY_VAL;                                 // key and val hold each other's words
+    for (int shift = 0; by_val || shift < bits; shift += 8) {
+        const bool last = !by_val && shift + 8 >= bits;
         for (int i = tid; i < kWaves * kRadix; i += kBucketThreads) (&cnt[0][0])[i] = 0;
         __syncthreads();
 #pragma unroll
@@ -798,6 +819,16 @@ __device__ __forceinline__ void sort_bucket(const uint32_t *__restrict__ keys_in
             }
             __syncthreads();
         }
+        if (BY_VAL && by_val && shift + 8 >= val_bits) {
+#pragma unroll
+            for (int r = 0; r < kRounds; ++r) {
+                const uint32_t x = key[r];
+                key[r] = (uint32_t)val[r];
+                val[r] = (int32_t)x;
+            }
+            by_val = false;
+            shift = -8;
+        }
     }
 }
 
@@ -834,7 +865,7 @@ __global__ __launch_bounds__(kThreads, kThreads == 1024 ? 4 : 6) void pct_whole_
             }
         }
     }
-    sort_bucket<kThreads, kRounds, true>(nullptr, nullptr, vals_out + at, n, bits, slot, (uint32_t (*)[256])counters, tid,
+    sort_bucket<kThreads, kRounds, true, false>(nullptr, nullptr, vals_out + at, n, bits, 0, slot, (uint32_t (*)[256])counters, tid,
                                          key);
 }
 
@@ -857,14 +888,15 @@ __global__ __launch_bounds__(kThreads, 6) void pct_bucket_kernel(const uint32_t 
                                                               const int32_t *__restrict__ vals_in,
                                                               int32_t *__restrict__ vals_out, int32_t n, int32_t tiles, int bits,
                                                               int val_bits, const uint32_t *__restrict__ starts, Gate gate,
-                                                              const int32_t *__restrict__ crowded, int32_t crowded_stride) {
+                                                              const int32_t *__restrict__ found, int32_t found_stride) {
     // sorted words and bins, or the ranking's slots
     __shared__ __align__(16) uint32_t slot[kThreads * kSortRounds], counters[kThreads / 64][256], wave_sum[kThreads / 64];
     static_assert(kSortRounds == kBinRounds + 8, "eight bins per thread behind the sorted words");
     const uint32_t q = blockIdx.x / kBuckets, d = (blockIdx.x + q) % kBuckets;    // (turned, as in pct_bucket_bins_kernel)
     const uint32_t *at_bucket = starts + ((int64_t)q * kBuckets + d) * tiles;
     const uint32_t lo = at_bucket[0], hi = d + 1 == kBuckets ? (uint32_t)n : at_bucket[tiles];
-    const bool bins = crowded[(int64_t)q * crowded_stride] == 0;
+    const int32_t what = found[(int64_t)q * found_stride];
+    const bool bins = (what & kCrowded) == 0;
     if (gate.closed()) return;
     uint32_t few[kBinRounds], key[kSortRounds];
     const int32_t items = (int32_t)(hi - lo);
@@ -874,8 +906,12 @@ __global__ __launch_bounds__(kThreads, 6) void pct_bucket_kernel(const uint32_t 
         sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, val_bits, slot,
                                                    slot + kThreads * kBinRounds, wave_sum, few))
         return;
-    sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters,
-                                              threadIdx.x, key);
+    if (what == 0)
+        sort_bucket<kThreads, kSortRounds, false, true>(keys_in + at, vals_in + at, vals_out + at, items, bits, val_bits, slot,
+                                                        counters, threadIdx.x, key);
+    else
+        sort_bucket<kThreads, kSortRounds, false, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, 0, slot,
+                                                         counters, threadIdx.x, key);
 }
 
 // The buckets that pct_bucket_bins_kernel left, out of the `each` that a workgroup looks at (left_over_bucket).
@@ -885,12 +921,14 @@ template <int kThreads>
 __global__ __launch_bounds__(kThreads, 6) void pct_bucket_sort_kernel(const uint32_t *__restrict__ keys_in,
                                                                    const int32_t *__restrict__ vals_in,
                                                                    int32_t *__restrict__ vals_out, int32_t n, int32_t each,
-                                                                   int32_t tiles, int bits,
+                                                                   int32_t tiles, int bits, int val_bits,
                                                                    const uint32_t *__restrict__ starts, Gate gate,
+                                                                   const int32_t *__restrict__ found, int32_t found_stride,
                                                                    const uint32_t *__restrict__ left) {
     __shared__ uint32_t slot[kThreads * kSortRounds], counters[kThreads / 64][256];
     if (gate.closed()) return;
     const uint32_t q = blockIdx.x / (uint32_t)(kBuckets / each);
+    const bool by_val = found[(int64_t)q * found_stride] == 0;
     uint32_t lo = 0, hi = 0;
     if ((int)(threadIdx.x & 63) < each) {
         const uint32_t d = left_over_bucket<kBuckets>(blockIdx.x, threadIdx.x & 63, each);
@@ -911,8 +949,12 @@ __global__ __launch_bounds__(kThreads, 6) void pct_bucket_sort_kernel(const uint
         const int32_t items = (int32_t)((uint32_t)__builtin_amdgcn_readlane((int)hi, which) - first);
         const int64_t at = (int64_t)q * n + first;
         uint32_t key[kSortRounds];
-        sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters, tid,
-                                                  key);
+        if (by_val)
+            sort_bucket<kThreads, kSortRounds, false, true>(keys_in + at, vals_in + at, vals_out + at, items, bits, val_bits,
+                                                            slot, counters, tid, key);
+        else
+            sort_bucket<kThreads, kSortRounds, false, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, 0, slot,
+                                                             counters, tid, key);
         __syncthreads();
     }
 }
@@ -951,7 +993,8 @@ struct DigitPass {
     void scan() const {
         hipLaunchKernelGGL(pct_scan_kernel, dim3((unsigned)s.P), dim3(1024), 0, st, s.counts, (1 << RB) * tiles(), gate);
     }
-    int scatter(bool first, bool last, const Key *kin, Key *kout, const int32_t *vin, int32_t *vout) const {
+    int scatter(bool first, bool last, const Key *kin, Key *kout, const int32_t *vin, int32_t *vout,
+                const int32_t *found = nullptr) const {
         const size_t lds = (size_t)kTile * sizeof(Key);
 #define CP_SCATTER(F, L)                                                                                   \
     do {                                                                                                   \
@@ -961,7 +1004,7 @@ struct DigitPass {
                                                    (int)lds) != hipSuccess)                                \
             return CP_ERR_HIP;                                                                             \
         hipLaunchKernelGGL(kern, grid(), dim3(THREADS), lds, st, kin, vin, kout, vout, s.n, tiles(), shift, s.counts, \
-                           gate);                                                                          \
+                           gate, found, s.k + 1);                                                                          \
     } while (0)
         if (first && last) CP_SCATTER(true, true);
         else if (first) CP_SCATTER(true, false);
@@ -1071,15 +1114,15 @@ int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     const int threads = both ? in_one : for_bins;
     const int shift = std::max(0, rem - bin_bits(threads));
     // (noted where the partition's list bounds will stand)
-    int32_t *crowded = s.seg_out;
+    int32_t *found = s.seg_out;
     auto check = s.P <= kFineSamples ? pct_bucket_check_kernel<4> : pct_bucket_check_kernel<1>;
     hipLaunchKernelGGL(check, dim3((unsigned)s.P), dim3(kBuckets), 0, st, s.counts, (const uint32_t *)s.keys_a, s.n, tiles,
-                       small ? kBucketCapSmall : kBucketCapLarge, shift, flag, crowded, s.k + 1);
+                       small ? kBucketCapSmall : kBucketCapLarge, threads * kBinRounds, shift, flag, found, s.k + 1);
     if (hipGetLastError() != hipSuccess) return CP_ERR_HIP;
     const Gate fit{flag, 0u};
     const DigitPass<uint32_t, kLeadThreads, kBucketBits> lead_if_fit{s, st, rem, fit};
     const int rc = lead_if_fit.scatter(/*first=*/true, /*last=*/false, (const uint32_t *)s.keys_a, (uint32_t *)s.keys_b,
-                                       nullptr, s.vals_tmp);
+                                       nullptr, s.vals_tmp, found);
     if (rc) return rc;
     // (what the bins leave is noted in keys_a, which nothing reads any more on this way)
     uint32_t *left = (uint32_t *)s.keys_a;
@@ -1093,7 +1136,7 @@ int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     if (both) {
 #define CP_BOTH(T)                                                                                                    \
     hipLaunchKernelGGL(pct_bucket_kernel<T>, dim3((unsigned)all), dim3(T), 0, st, keys, vals, s.order_out, s.n, tiles, rem, \
-                       val_bits, starts, fit, (const int32_t *)crowded, s.k + 1)
+                       val_bits, starts, fit, (const int32_t *)found, s.k + 1)
         if (threads == 256) CP_BOTH(256);
         else CP_BOTH(512);
 #undef CP_BOTH
@@ -1102,7 +1145,7 @@ int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     }
 #define CP_BINS(T)                                                                                                    \
     hipLaunchKernelGGL(pct_bucket_bins_kernel<T>, dim3((unsigned)(all / dealt)), dim3(T), 0, st, keys, vals, s.order_out, s.n, dealt, tiles, \
-                       rem, val_bits, starts, fit, (const int32_t *)crowded, s.k + 1, left)
+                       rem, val_bits, starts, fit, (const int32_t *)found, s.k + 1, left)
     if (threads == 128) CP_BINS(128);
     else if (threads == 256) CP_BINS(256);
     else CP_BINS(512);
@@ -1110,7 +1153,7 @@ int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     const int32_t each = left_over_each(all);
 #define CP_LEFT(T)                                                                                                    \
     hipLaunchKernelGGL(pct_bucket_sort_kernel<T>, dim3((unsigned)(all / each)), dim3(T), 0, st, keys, vals, s.order_out, \
-                       s.n, each, tiles, rem, starts, fit, (const uint32_t *)left)
+                       s.n, each, tiles, rem, val_bits, starts, fit, (const int32_t *)found, s.k + 1, (const uint32_t *)left)
     if (small) CP_LEFT(256);
     else CP_LEFT(512);
 #undef CP_LEFT

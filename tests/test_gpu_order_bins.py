@@ -83,3 +83,28 @@ def test_left_buckets_among_others(gpu, oracle, n, P):
     assert np.array_equal(seg.cpu().numpy(), ref_seg)
     assert np.array_equal(order.cpu().numpy(), ref_order)
     g.close()
+
+
+@pytest.mark.parametrize("n,P", [(65_537, 3), (65_537, 65), (262_145, 5), (262_145, 49), (524_801, 5), (524_801, 49)])
+def test_a_crowded_bin_among_spread_keys(gpu, oracle, n, P):
+    """Too few equal values for the sample to find, too many for a bin: the bucket's items are dealt in no order of their vertex
+    numbers and then ranked, in one launch with the bins and in one of its own."""
+    import torch
+    k, top = 9, 3_000_000
+    rng = np.random.default_rng(n + P)
+    n, level, src, dst = random_layered_dag(rng, [n // 2, n - n // 2], 1, 1, 1)
+    a = rng.integers(0, k, (P, n), dtype=np.uint8)
+    w = T._custom("crowded", n, src, dst, np.ones(len(src), dtype=np.int64), np.ones(n, dtype=np.int64), [1] * k,
+                  np.ones((k, k), dtype=np.int64), a, level)
+    b = rng.integers(0, top + 1, (P, n), dtype=np.int32)
+    for q in range(P):
+        for d in range(q % 3):
+            same = rng.choice(np.nonzero(a[q] == d)[0], 200 + 20 * d, replace=False)
+            b[q, same] = top // (d + 2)
+    ref_order, ref_seg = oracle.pct_order(k, w.assignments, b.astype(np.int64), threads=8)
+    g = gpu.CpGraph.from_workload(w, device="cuda:0")
+    order, seg = gpu.cp_pct_order(g, torch.from_numpy(w.assignments).to("cuda:0"), k, torch.from_numpy(b).to("cuda:0"),
+                                  max_b=top, b_layout=1)
+    assert np.array_equal(seg.cpu().numpy(), ref_seg)
+    assert np.array_equal(order.cpu().numpy(), ref_order)
+    g.close()
