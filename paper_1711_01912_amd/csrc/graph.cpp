@@ -2,6 +2,7 @@
 // into the device image used by the two kernel families.  No GPU call here.
 #include <algorithm>
 #include <cstring>
+#include <future>
 #include <memory>
 #include <new>
 #include <numeric>
@@ -810,6 +811,25 @@ void pack_whole(BlobWriter &w, int32_t n, int32_t L, const int64_t *c, const Csr
     }
 }
 
+// Both directions for the chain sweep, offsets from the start of a piece of the blob of their own; `ok` false and nothing in
+// it where either is refused.
+struct ChainPacked {
+    std::vector<uint8_t> blob;
+    ChainDir b, t;
+    int32_t width = 0;
+    bool ok = false;
+};
+ChainPacked pack_chain(int32_t n, int32_t L, size_t word_bytes, const Csr &succ, const Csr &pred, const int32_t *level_ptr,
+                       const int32_t *level_vtx) {
+    ChainPacked p;
+    BlobWriter w(p.blob);
+    const ChainRows rows_b(n, L, succ, level_ptr, level_vtx, false), rows_t(n, L, pred, level_ptr, level_vtx, true);
+    p.width = chain_width(rows_b, rows_t);
+    p.ok = pack_chain_dir(w, word_bytes, succ, rows_b, p.width, p.b) && pack_chain_dir(w, word_bytes, pred, rows_t, p.width, p.t);
+    if (!p.ok) p.blob.clear();
+    return p;
+}
+
 }  // namespace
 
 int pack_graph(int32_t n, int64_t m, int32_t L,
@@ -932,6 +952,12 @@ int pack_graph(int32_t n, int64_t m, int32_t L,
         P.blob.clear();
         P.blob.reserve(blob_room(n, m, L, P.narrow));
         BlobWriter w(P.blob);
+        // beside the rest, on a thread of its own where there is one to have (211,000 vertices: 170 -> 120 ms in all)
+        std::future<ChainPacked> chain;
+        if (L >= kChainLevels && n < (1 << 24) - 1 && (uint64_t)max_c + (uint64_t)max_t < (1ull << 32))
+            chain = std::async([&] {
+                return pack_chain(n, L, (size_t)info.min_tick_bytes, succ, pred, level_ptr, level_vtx);
+            });
         pack_column_dir(w, n, m, P.narrow, succ, order_b, P.col_b);
         pack_column_dir(w, n, m, P.narrow, pred, order_t, P.col_t);
         if (P.narrow) {
@@ -973,13 +999,18 @@ int pack_graph(int32_t n, int64_t m, int32_t L,
         P.whole = WholeDir{};
         if (P.have_whole) pack_whole(w, n, L, c, succ, pred, level_ptr, level_vtx, P.whole);
         P.have_chain = false;
-        if (L >= kChainLevels && n < (1 << 24) - 1 && (uint64_t)max_c + (uint64_t)max_t < (1ull << 32)) {
-            const size_t mark = P.blob.size(), word = (size_t)info.min_tick_bytes;
-            const ChainRows rows_b(n, L, succ, level_ptr, level_vtx, false), rows_t(n, L, pred, level_ptr, level_vtx, true);
-            P.chain_width = chain_width(rows_b, rows_t);
-            P.have_chain = pack_chain_dir(w, word, succ, rows_b, P.chain_width, P.chain_b) &&
-                           pack_chain_dir(w, word, pred, rows_t, P.chain_width, P.chain_t);
-            if (!P.have_chain) P.blob.resize(mark);
+        if (chain.valid()) {
+            const ChainPacked packed = chain.get();
+            P.have_chain = packed.ok;
+            P.chain_width = packed.width;
+            P.chain_b = packed.b;
+            P.chain_t = packed.t;
+            P.blob.resize(align_up(P.blob.size()));
+            for (ChainDir *dir : {&P.chain_b, &P.chain_t}) {
+                dir->unit_off += P.blob.size();
+                dir->edge_off += P.blob.size();
+            }
+            P.blob.insert(P.blob.end(), packed.blob.begin(), packed.blob.end());
         }
         P.blob.resize(align_up(P.blob.size()));
     } catch (const std::bad_alloc &) {
