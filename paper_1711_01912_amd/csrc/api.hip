@@ -465,7 +465,7 @@ int pct_plan(const cp_graph *g, int32_t batch, int32_t k, int64_t max_b, PctPlan
 namespace {
 
 struct SimPlan {
-    size_t tab = 0, tie_inv = 0, records = 0, per_i32 = 0, per_u64 = 0, total = 0;
+    size_t tab = 0, tie_inv = 0, per_i32 = 0, per_u64 = 0, total = 0;
     bool pct = false, with_tie = false;
 };
 
@@ -480,8 +480,7 @@ int sim_plan(const cp_graph *g, int32_t batch, int32_t k, int policy, bool with_
     out.tie_inv = out.with_tie ? align_up(n * 4) : 0;
     out.per_i32 = align_up(n * (size_t)batch * 4);
     out.per_u64 = align_up(n * (size_t)batch * 8);
-    out.records = g->packed.narrow ? align_up(n * kSimRecordBytes) : 0;
-    out.total = out.tab + out.tie_inv + out.records + 3 * out.per_i32 + (out.pct ? 2 : 1) * out.per_u64;
+    out.total = out.tab + out.tie_inv + 3 * out.per_i32 + (out.pct ? 2 : 1) * out.per_u64;
     return CP_OK;
 }
 
@@ -1386,7 +1385,6 @@ int cp_simulate(const cp_graph *g, int32_t batch, int32_t k,
         s.tie_inv = (int32_t *)at;
         at += plan.tie_inv;
     }
-    s.records = (uint32_t *)at; at += plan.records;
     s.ready = (int32_t *)at; at += plan.per_i32;
     s.need = (int32_t *)at; at += plan.per_i32;
     s.inbox = (int32_t *)at; at += plan.per_i32;

@@ -297,12 +297,10 @@ struct SimulateLaunch {
     const void *edge_tab = nullptr, *vert_tab = nullptr;
     int32_t *ready = nullptr, *need = nullptr, *inbox = nullptr;   // [P][n] each
     uint64_t *pending = nullptr, *available = nullptr;             // [P][n] each (available: PCT only)
-    uint32_t *records = nullptr;        // scratch of n records of kSimRecordBytes where weights have 32 bits, 16-byte aligned
     int64_t *makespan = nullptr;
     int32_t *start = nullptr;
     int32_t *status = nullptr;
 };
-constexpr size_t kSimRecordBytes = 32;
 int launch_simulate(const SimulateLaunch &s, void *stream);
 
 int launch_validate(const uint8_t *assign, int64_t a_stride_p, int64_t a_stride_v, int32_t n, int32_t P, int32_t k,

@@ -210,7 +210,7 @@ struct SimArgs {
     const int32_t *idx;
     const void *wt;            // t(e) in that order
     const void *c;
-    const uint4 *records;      // [n][2] where weights have 32 bits: see simulate_records_kernel
+    const uint4 *records;      // [n][2] or null: see simulate_records_kernel
     const int32_t *pred_ptr;   // predecessor CSR row bounds: the in-degrees
     const uint8_t *assign;
     int64_t a_stride_p, a_stride_v;
@@ -240,8 +240,8 @@ struct SimArgs {
 // of the time: one line in place of four (c, row bounds, heads, t), and a round trip less where the edges are in it.  With
 // b asked for beside the ready time and three keys a queue in registers, 5,271 vertices of 1 to 3 out-edges on 50 devices,
 // PCT: 256 partitions 1.60 -> 1.33 ms, 1,024 1.78 -> 1.50, 4,096 3.97 -> 3.06, FIFO 3.39 -> 2.87; out-edges 1 to 7 7.62 -> 7.20.
-// The launch that writes them takes some 5 us.
-constexpr int32_t kRecordEdges = 3;
+// The launch that writes them takes some 5 us; they stand where the open inputs would be in memory, so not beside those.
+constexpr int32_t kRecordEdges = 3, kRecordsFrom = 8;       // (8 words a vertex, one for each of 8 partitions)
 __global__ __launch_bounds__(256) void simulate_records_kernel(const int32_t *__restrict__ ptr,
                                                                const int32_t *__restrict__ idx,
                                                                const uint32_t *__restrict__ wt,
@@ -266,9 +266,8 @@ __global__ __launch_bounds__(256) void simulate_records_kernel(const int32_t *__
     records[2 * v + 1] = make_uint4(w[2], w[3], w[4], w[5]);
 }
 
-template <typename WT, bool MAGIC, bool PCT, int KEEP>
+template <typename WT, bool MAGIC, bool PCT, int KEEP, bool RECORDS>
 __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
-    constexpr bool kRecords = sizeof(WT) == 4;
     extern __shared__ uint32_t sim_lds[];
     __shared__ int32_t count[64];      // vertices per device, then handed to it so far (kNearInboxToo: in this step)
     __shared__ int32_t seg[64];        // first slot of the device's segment
@@ -399,6 +398,10 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
         else if (KEEP == kNearInboxToo && pos < kNearInbox) near_in[to][pos] = (uint16_t)z;
         else inbox_store(inbox + seg[to] + pos, z);
     };
+    // vertices of its inbox that a device looks at side by side: large graphs hand over many in a step (200,000 vertices of up
+    // to 7 out-edges on 8 devices, 64 partitions: one at a time 1.2 % slower), small ones one or two (5,271 vertices, 50
+    // devices, 256 partitions: three at a time 5 % slower)
+    constexpr int32_t kDrain = KEEP == kNothing ? 4 : 1;
     // every step with work left starts at least one vertex in every unfinished group, so
     // n + 1 steps always suffice
     for (int64_t step = 0; step <= n; ++step) {
@@ -408,17 +411,33 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
                 taken = 0;
                 count[lane] = 0;
             }
-            for (; taken < have; ++taken) {
-                int32_t z;
-                if (KEEP == kAll) z = (int32_t)l_inbox[base + taken];
-                else if (KEEP == kNearInboxToo && taken < kNearInbox) z = (int32_t)near_in[lane][taken];
-                else z = inbox_load(my_inbox + taken);
-                const uint32_t rz = KEEP == kAll ? l_ready[z] : (uint32_t)l2_read(ready + z);
-                const uint32_t bz = PCT ? load_b(bq, z, bsv, a.b_bytes) : 0u;
-                if (PCT && rz <= free_at)    // executable at every decision this device has still to take
-                    queue_push(ha, available, available_key(bz, z, b_bad));
-                else
-                    queue_push(hp, pending, ((uint64_t)rz << 32) | (!PCT && a.tie ? (uint32_t)a.tie[z] : (uint32_t)z), bz);
+            while (taken < have) {
+                const int32_t cnt = min(kDrain, have - taken);
+                int32_t z[kDrain];
+                uint32_t rz[kDrain], bz[kDrain], low[kDrain];
+#pragma unroll
+                for (int j = 0; j < kDrain; ++j) {
+                    const int32_t at = taken + min(j, cnt - 1);
+                    if (KEEP == kAll) z[j] = (int32_t)l_inbox[base + at];
+                    else if (KEEP == kNearInboxToo && at < kNearInbox) z[j] = (int32_t)near_in[lane][at];
+                    else z[j] = inbox_load(my_inbox + at);
+                }
+#pragma unroll
+                for (int j = 0; j < kDrain; ++j) {
+                    rz[j] = KEEP == kAll ? l_ready[z[j]] : (uint32_t)l2_read(ready + z[j]);
+                    bz[j] = PCT ? load_b(bq, z[j], bsv, a.b_bytes) : 0u;
+                    low[j] = !PCT && a.tie ? (uint32_t)a.tie[z[j]] : (uint32_t)z[j];
+                }
+#pragma unroll
+                for (int j = 0; j < kDrain; ++j) {
+                    if (j < cnt) {
+                        if (PCT && rz[j] <= free_at)    // executable at every decision this device has still to take
+                            queue_push(ha, available, available_key(bz[j], z[j], b_bad));
+                        else
+                            queue_push(hp, pending, ((uint64_t)rz[j] << 32) | low[j], bz[j]);
+                    }
+                }
+                taken += cnt;
             }
         }
         uint32_t T = kNever;
@@ -466,7 +485,7 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
             uint4 r0, r1;
             WT cv;
             int32_t e0, degree;
-            if (kRecords) {
+            if (RECORDS) {
                 r0 = a.records[2 * (int64_t)v];
                 r1 = a.records[2 * (int64_t)v + 1];
                 cv = (WT)r0.x;
@@ -486,7 +505,7 @@ __global__ __launch_bounds__(64) void simulate_kernel(SimArgs a) {
             // the out-edges four at a time, so that the dependent loads of four edges (successor,
             // its device, the table entry) and their atomics overlap; slots past the row's end take
             // no part but for the table's first entries, whose loads need no branch
-            const bool held = kRecords && degree <= kRecordEdges;      // in the record
+            const bool held = RECORDS && degree <= kRecordEdges;      // in the record
             if (degree >= kWideRow) {
                 wide_e0 = e0;
                 wide_e1 = e0 + degree;
@@ -627,11 +646,6 @@ int launch_simulate(const SimulateLaunch &s, void *stream) {
     a.wt = s.blob + s.succ->wt_off;
     a.c = s.blob + s.c_off;
     a.pred_ptr = (const int32_t *)(s.blob + s.pred->ptr_off);
-    if (s.narrow) {
-        a.records = (const uint4 *)s.records;
-        hipLaunchKernelGGL(simulate_records_kernel, dim3((unsigned)((s.n + 255) / 256)), dim3(256), 0, st, a.ptr, a.idx,
-                           (const uint32_t *)a.wt, (const uint32_t *)a.c, s.n, (uint4 *)s.records);
-    }
     a.assign = s.assign;
     a.a_stride_p = s.a_stride_p;
     a.a_stride_v = s.a_stride_v;
@@ -669,18 +683,28 @@ int launch_simulate(const SimulateLaunch &s, void *stream) {
         if (s.n <= 65535 && fits(all)) keep = kAll;
         else if (fits(owners)) keep = there < kNearFrom ? kOwnersAndInputs : kNearInboxToo;
     }
+    // (the open inputs sit in LDS, and their array holds the records)
+    if (keep != kNothing && s.narrow && s.P >= kRecordsFrom) {
+        a.records = (const uint4 *)s.need;
+        hipLaunchKernelGGL(simulate_records_kernel, dim3((unsigned)((s.n + 255) / 256)), dim3(256), 0, st, a.ptr, a.idx,
+                           (const uint32_t *)a.wt, (const uint32_t *)a.c, s.n, (uint4 *)s.need);
+    }
     const size_t lds = keep == kAll ? all : (keep != kNothing ? owners : 0);
     const dim3 grid((unsigned)((s.P + groups - 1) / groups)), block(64);
+#define CP_SIM_R(WT, MAGIC, PCT, KEEP)                                                                              \
+    do {                                                                                                            \
+        constexpr bool kCan = sizeof(WT) == 4;                                                                      \
+        if (kCan && a.records)                                                                                      \
+            hipLaunchKernelGGL((simulate_kernel<WT, MAGIC, PCT, KEEP, kCan>), grid, block, lds, st, a);             \
+        else                                                                                                        \
+            hipLaunchKernelGGL((simulate_kernel<WT, MAGIC, PCT, KEEP, false>), grid, block, lds, st, a);            \
+    } while (0)
 #define CP_SIM_K(WT, MAGIC, PCT)                                                                                    \
     do {                                                                                                            \
-        if (keep == kAll)                                                                                           \
-            hipLaunchKernelGGL((simulate_kernel<WT, MAGIC, PCT, kAll>), grid, block, lds, st, a);                   \
-        else if (keep == kNearInboxToo)                                                                             \
-            hipLaunchKernelGGL((simulate_kernel<WT, MAGIC, PCT, kNearInboxToo>), grid, block, lds, st, a);          \
-        else if (keep == kOwnersAndInputs)                                                                          \
-            hipLaunchKernelGGL((simulate_kernel<WT, MAGIC, PCT, kOwnersAndInputs>), grid, block, lds, st, a);       \
-        else                                                                                                        \
-            hipLaunchKernelGGL((simulate_kernel<WT, MAGIC, PCT, kNothing>), grid, block, 0, st, a);                 \
+        if (keep == kAll) CP_SIM_R(WT, MAGIC, PCT, kAll);                                                           \
+        else if (keep == kNearInboxToo) CP_SIM_R(WT, MAGIC, PCT, kNearInboxToo);                                    \
+        else if (keep == kOwnersAndInputs) CP_SIM_R(WT, MAGIC, PCT, kOwnersAndInputs);                              \
+        else hipLaunchKernelGGL((simulate_kernel<WT, MAGIC, PCT, kNothing, false>), grid, block, 0, st, a);         \
     } while (0)
 #define CP_SIM(WT, MAGIC)                       \
     do {                                        \
@@ -692,6 +716,7 @@ int launch_simulate(const SimulateLaunch &s, void *stream) {
     else CP_SIM(int64_t, false);
 #undef CP_SIM
 #undef CP_SIM_K
+#undef CP_SIM_R
     return hipGetLastError() == hipSuccess ? CP_OK : CP_ERR_HIP;
 }
 
