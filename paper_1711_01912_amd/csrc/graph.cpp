@@ -6,6 +6,7 @@
 #include <memory>
 #include <new>
 #include <numeric>
+#include <system_error>
 
 #include "cpeval_internal.hpp"
 
@@ -954,10 +955,14 @@ int pack_graph(int32_t n, int64_t m, int32_t L,
         BlobWriter w(P.blob);
         // beside the rest, on a thread of its own where there is one to have (211,000 vertices: 170 -> 120 ms in all)
         std::future<ChainPacked> chain;
-        if (L >= kChainLevels && n < (1 << 24) - 1 && (uint64_t)max_c + (uint64_t)max_t < (1ull << 32))
-            chain = std::async([&] {
-                return pack_chain(n, L, (size_t)info.min_tick_bytes, succ, pred, level_ptr, level_vtx);
-            });
+        if (L >= kChainLevels && n < (1 << 24) - 1 && (uint64_t)max_c + (uint64_t)max_t < (1ull << 32)) {
+            auto pack = [&] { return pack_chain(n, L, (size_t)info.min_tick_bytes, succ, pred, level_ptr, level_vtx); };
+            try {
+                chain = std::async(std::launch::async, pack);
+            } catch (const std::system_error &) {             // no thread to have: when it is asked for
+                chain = std::async(std::launch::deferred, pack);
+            }
+        }
         pack_column_dir(w, n, m, P.narrow, succ, order_b, P.col_b);
         pack_column_dir(w, n, m, P.narrow, pred, order_t, P.col_t);
         if (P.narrow) {
