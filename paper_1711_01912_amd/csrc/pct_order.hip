@@ -27,6 +27,8 @@
 // ordinary passes from the low digit up -- and a flag the bucket check sets lets the kernels of
 // one of them return at once.  With rows of b per partition, one kernel writes the keys and
 // counts their leading digit.
+// The leading scatter keeps vertices in order only where a bucket may have to be ranked by digits; bins have the vertex
+// number in their key.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

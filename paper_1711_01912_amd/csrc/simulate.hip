@@ -239,7 +239,8 @@ struct SimArgs {
 // number of the first one.  A lane's loads go to lines of their own, and the address unit and the L1 were busy two thirds
 // of the time: one line in place of four (c, row bounds, heads, t), and a round trip less where the edges are in it.  With
 // b asked for beside the ready time and three keys a queue in registers, 5,271 vertices of 1 to 3 out-edges on 50 devices,
-// PCT: 256 partitions 1.60 -> 1.33 ms, 1,024 1.78 -> 1.50, 4,096 3.97 -> 3.06, FIFO 3.39 -> 2.87; out-edges 1 to 7 7.62 -> 7.20.
+// PCT: 256 partitions 1.60 -> 1.33 ms, 1,024 1.78 -> 1.50, 4,096 3.97 -> 3.06, FIFO 3.39 -> 2.87; out-edges 1 to 7, most of them not
+// in the record, 7.62 -> 7.58.
 // The launch that writes them takes some 5 us; they stand where the open inputs would be in memory, so not beside those.
 constexpr int32_t kRecordEdges = 3, kRecordsFrom = 8;       // (8 words a vertex, one for each of 8 partitions)
 __global__ __launch_bounds__(256) void simulate_records_kernel(const int32_t *__restrict__ ptr,
