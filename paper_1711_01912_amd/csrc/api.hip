@@ -353,14 +353,26 @@ bool chain_cost16(const Packed &p, int32_t k, const int64_t *speeds, const int64
     }
     return p.info.max_c / slowest + 1 + (k > 1 ? p.info.max_t / narrowest + 1 : 0) < 1 << 16;
 }
-// Fitted to 70 calls (300 to 1,500 levels of 20 to 600 vertices, 1 to 64 partitions): a tick 0.1 us and 0.016 a wavefront, 0.05
-// more with 64-bit words; the launch that writes the costs 8 (or, with 32 bits each, 13) us for a million lanes of
-// ticks and partitions; rows per vertex 10 us for a million outputs.
+// Fitted to 512 calls (260 to 2,000 levels of 8 to 900 vertices, 1 to 64 partitions): a tick 0.1 us and 0.016 a wavefront, 0.05
+// more with 64-bit words; 8 to 15 us for a million lanes of ticks and partitions (1.6 times that with 32 bits a cost), the
+// wider the tick and the more values there are, which stop fitting the caches at some millions of either sweep; rows per
+// vertex, whose lines come together from as many workgroups as there are partitions, up to 45 us for a million
+// values of the first sixteen, and 25 for what is past seven million.  Half of them are within 4 % of it, nine tenths within 12 %.
+// A tenth on top where it has been wrong by as much, on wide ticks and many values: with 8 us a million for all, 1,000
+// levels of 500 vertices and 64 partitions took 1,589 us under this plan and 851 under the resident-window plan.
 double chain_us(const Packed &p, int32_t batch, int sweeps, bool cost16, bool by_partition) {
-    const double lanes = (double)p.chain_width * ((double)p.chain_b.ticks + p.chain_t.ticks) / 2 * sweeps * batch;
+    const double lanes = (double)p.chain_width * ((double)p.chain_b.ticks + p.chain_t.ticks) / 2 * sweeps * batch * 1e-6;
+    const double values = (double)p.n * batch * sweeps / 2 * 1e-6;
     const double tick = 0.1 + 0.016 * (p.chain_width / kWave) + (p.info.min_tick_bytes == 8 ? 0.05 : 0.0);
-    return 18.0 + lanes * (cost16 ? 8e-6 : 13e-6) + std::max(p.chain_b.ticks, p.chain_t.ticks) * tick +
-           (by_partition ? 0.0 : (double)p.n * batch * sweeps * 10e-6);
+    const bool wide = p.chain_width >= 512;
+    const double each = wide                   ? 10.0 + 5.0 * std::clamp((values - 4.0) / 4.0, 0.0, 1.0)
+                        : p.chain_width <= 128 ? 8.0
+                                               : 9.0 + 2.0 * std::min(1.0, values / 10.0);
+    double us = 18.0 + std::max(p.chain_b.ticks, p.chain_t.ticks) * tick + lanes * each * (cost16 ? 1.0 : 1.6);
+    if (!by_partition)
+        us += (wide ? 45.0 : p.chain_width <= 192 ? 5.0 : 20.0) * values * std::min(1.0, 16.0 / batch) +
+              25.0 * std::max(0.0, values - 7.0);
+    return wide && values > 8.0 ? 1.1 * us : us;
 }
 
 // Fitted to 100 calls (64 to 3,600 vertices, 8 to 300 levels, 8 to 4,096 partitions), with what the launch itself takes: a
@@ -777,6 +789,10 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
             const bool rows = assign_layout == CP_ASSIGN_PARTITION_MAJOR &&
                               ((uint64_t)p.n * (uint64_t)batch) % 16 == 0 && ((uintptr_t)assignments % 16) == 0;
             double other_us = 0.0;
+            // mask_more_us: a mask pass that the plan chosen so far does without.  apart_us: what the pair launch takes less than
+            // `other_us` where every workgroup has a compute unit for itself (2,000 levels of 500 vertices, 64 partitions
+            // 1,690 us a call, 2,070 by other_us); the lane-window plan is ranked without it
+            double mask_more_us = 0.0, apart_us = 0.0;
             if (use == CP_PLAN_WAVE_COLUMN) other_us = column_plan_us(p, batch, (size_t)tick_dtype) * (both ? 1.0 : 0.5);
             if (use == CP_PLAN_RESIDENT_WINDOW) {
                 const double b_us = crowded_window_sweep_us(p.win_b, cfg_b, batch, by_partition);
@@ -787,21 +803,25 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                 if (both && by_partition && tick_dtype == CP_TICK_I32 &&
                     window_pair_config(p.win_b, p.win_t, k, lds_limit, x, y)) {
                     side = true;
-                    if (window_wg_per_cu(cfg_b) == 1.0 && window_wg_per_cu(cfg_t) == 1.0) other_us *= 0.66;
-                    else if (2.0 * std::ceil((double)batch / 256.0) <= std::min(window_wg_per_cu(x), window_wg_per_cu(y)))
+                    if (window_wg_per_cu(cfg_b) == 1.0 && window_wg_per_cu(cfg_t) == 1.0) {
+                        other_us *= 0.66;
+                        if (batch <= 128) apart_us = other_us - std::max(b_us, t_us);
+                    } else if (2.0 * std::ceil((double)batch / 256.0) <= std::min(window_wg_per_cu(x), window_wg_per_cu(y)))
                         other_us = std::max(side_window_sweep_us(p, p.win_b, batch), side_window_sweep_us(p, p.win_t, batch));
                     else side = false;
                 }
                 const int launches_past_two = (side ? 1 : lane_sweeps) + (want_b && !(rows && p.win_b.direct_ok)) +
                                               (tlevel_out && !(rows && p.win_t.direct_ok)) - 2;
                 other_us += 2.5 * launches_past_two;
-                if (!side && tick_dtype == CP_TICK_I32 && rows && p.win_t.direct_ok && p.win_t.smax >= 4) lane_us += mask_pass_us;
+                if (!side && tick_dtype == CP_TICK_I32 && rows && p.win_t.direct_ok && p.win_t.smax >= 4)
+                    mask_more_us = mask_pass_us;
             } else if (use == CP_PLAN_SHARED_WINDOW_2 || use == CP_PLAN_SHARED_WINDOW_4) {
                 const int shared_by = use == CP_PLAN_SHARED_WINDOW_4 ? 4 : 2;
                 other_us = (want_b ? shared_sweep_us(p.win_b, shared_by, batch) : 0.0) +
                            (tlevel_out ? shared_sweep_us(p.win_t, shared_by, batch) : 0.0);
-                lane_us += mask_pass_us;
+                mask_more_us = mask_pass_us;
             }
+            lane_us += mask_more_us;
             if (use != CP_PLAN_WAVE_COLUMN) {
                 other_us += mb * ((rows && p.win_b.direct_ok ? 0.0 : 1.0) + (rows && p.win_t.direct_ok ? 0.0 : 1.0)) *
                             (both ? 1.0 : 0.5);
@@ -821,8 +841,8 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                     chain_scratch_bytes = workspace_bytes - std::min(workspace_bytes, tables_bytes(k));
                 }
                 chain = work <= chain_scratch_bytes && tables_bytes(k) <= workspace_bytes &&
-                        chain_us(p, batch, lane_sweeps, cost16, by_partition) <
-                            (whole ? whole_us_of : lanes ? 1.0 + 0.7 * mb + lane_us : other_us);
+                        chain_us(p, batch, lane_sweeps, cost16, by_partition) + mask_more_us <
+                            (whole ? whole_us_of : lanes ? 1.0 + 0.7 * mb + lane_us : other_us - apart_us);
                 lanes = lanes && !chain;
                 whole = whole && !chain;
             }

@@ -90,3 +90,9 @@ def test_a_device_id_too_large_is_reported(gpu):
     with pytest.raises(ValueError):
         gpu.cp_eval(g, a, w.speeds, w.bandwidth, out_layout=1)
     g.close()
+
+
+def test_not_where_other_plans_are_faster(gpu, oracle):
+    """Wide levels: 300 of 500 vertices and 48 partitions took 330 us in the chain sweep, 268 in the resident-window plan."""
+    _check(gpu, oracle, _graph(12, [500] * 300, 5, 6, 48, 16), 1, chain=False)
+    _check(gpu, oracle, _graph(12, [500] * 300, 5, 6, 8, 16), 1)
