@@ -178,6 +178,11 @@ void cp_graph_destroy(cp_graph *g);
 /*
  * Bytes of device workspace cp_eval needs for this batch size, device count,
  * assignment layout, plan (CP_PLAN_AUTO allowed), output layout and tick type.
+ * For up to 64 partitions of a graph of 256 levels or more CP_PLAN_AUTO also asks for what
+ * CP_PLAN_CHAIN works on, 18 bytes or more a vertex and partition (36 where the volumes do not
+ * keep every cost below 2^16) and never more than 512 MB: such a call may ask for more than one of
+ * 65 partitions.  With less it runs all the same, in more rounds or under another plan, where
+ * there is room for what that takes.
  */
 int cp_eval_workspace_bytes(const cp_graph *g, int32_t batch, int32_t k, int assign_layout,
                             int plan, int out_layout, int tick_dtype, size_t *out_bytes);
@@ -249,8 +254,8 @@ int cp_eval(const cp_graph *g, int32_t batch, int32_t k,
  * sweep) when the resident-window plan cannot read them straight from the caller's rows
  * (vertex-major assignments, rows not 16-byte aligned, or a graph whose levels are
  * scattered over the vertex numbers); the same and the copies of far reads for the lane-window plan, and
- * what every edge costs (20 bytes for up to four of a vertex) for CP_PLAN_CHAIN, which
- * CP_PLAN_AUTO leaves aside where they do not fit.  A resident-window call on aligned partition-major
+ * what every edge costs (8 to 20 bytes for up to four of a vertex and sweep) for CP_PLAN_CHAIN, which
+ * CP_PLAN_AUTO runs on fewer partitions at a time, or leaves aside, where they do not fit.  A resident-window call on aligned partition-major
  * rows needs the tables only.
  *
  * All calls on one GPU share that GPU's array: calls that may overlap in time on one GPU

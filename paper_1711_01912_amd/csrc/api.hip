@@ -343,7 +343,8 @@ bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, const int6
 // The chain sweep: a workgroup per sweep and partition, behind a launch that writes what every edge costs.  Up to 64
 // partitions (measured up to there).
 constexpr int32_t kChainMostPartitions = 64;
-// No edge's cost and its vertex's execution time together reach 2^16.
+// No edge's cost and its vertex's execution time together reach 2^16: whatever the devices, or on these.
+bool chain_cost16(const Packed &p) { return p.info.max_c + p.info.max_t + 2 < 1 << 16; }
 bool chain_cost16(const Packed &p, int32_t k, const int64_t *speeds, const int64_t *bandwidth) {
     int64_t slowest = speeds[0], narrowest = INT64_MAX;
     for (int32_t i = 0; i < k; ++i) {
@@ -360,7 +361,7 @@ bool chain_cost16(const Packed &p, int32_t k, const int64_t *speeds, const int64
 // values of the first sixteen, and 25 for what is past seven million.  Half of them are within 4 % of it, nine tenths within 12 %.
 // A tenth on top where it has been wrong by as much, on wide ticks and many values: with 8 us a million for all, 1,000
 // levels of 500 vertices and 64 partitions took 1,589 us under this plan and 851 under the resident-window plan.
-double chain_us(const Packed &p, int32_t batch, int sweeps, bool cost16, bool by_partition) {
+double chain_us(const Packed &p, int32_t batch, int sweeps, bool cost16, bool by_partition, int32_t rounds) {
     const double lanes = (double)p.chain_width * ((double)p.chain_b.ticks + p.chain_t.ticks) / 2 * sweeps * batch * 1e-6;
     const double values = (double)p.n * batch * sweeps / 2 * 1e-6;
     const double tick = 0.1 + 0.016 * (p.chain_width / kWave) + (p.info.min_tick_bytes == 8 ? 0.05 : 0.0);
@@ -368,11 +369,27 @@ double chain_us(const Packed &p, int32_t batch, int sweeps, bool cost16, bool by
     const double each = wide                   ? 10.0 + 5.0 * std::clamp((values - 4.0) / 4.0, 0.0, 1.0)
                         : p.chain_width <= 128 ? 8.0
                                                : 9.0 + 2.0 * std::min(1.0, values / 10.0);
-    double us = 18.0 + std::max(p.chain_b.ticks, p.chain_t.ticks) * tick + lanes * each * (cost16 ? 1.0 : 1.6);
+    double us = rounds * (18.0 + std::max(p.chain_b.ticks, p.chain_t.ticks) * tick) + lanes * each * (cost16 ? 1.0 : 1.6);
     if (!by_partition)
         us += (wide ? 45.0 : p.chain_width <= 192 ? 5.0 : 20.0) * values * std::min(1.0, 16.0 / batch) +
               25.0 * std::max(0.0, values - 7.0);
     return wide && values > 8.0 ? 1.1 * us : us;
+}
+
+// A workspace has room for at most these bytes of costs (64 partitions of 211,000 vertices with 16 bits each, 11 of a million with
+// 32); a call of more partitions takes them in rounds, if that is still the faster way.
+constexpr size_t kChainMostBytes = (size_t)512 << 20;
+// Partitions at a time whose costs fit `bytes`, in rounds of equal size; 0 if not one does.
+int32_t chain_at_once(const ChainDir *db, const ChainDir *dt, int32_t width, int32_t batch, bool cost16, size_t bytes) {
+    int32_t most = batch;
+    while (most > 0 && chain_work_bytes(db, dt, width, most, cost16) > bytes) --most;
+    if (most == 0) return 0;
+    const int32_t rounds = (batch + most - 1) / most;
+    return (batch + rounds - 1) / rounds;
+}
+// Rows per vertex: the output offsets of the kernel's stores take 24 bits by 8.
+bool chain_takes(const Packed &p, int32_t batch, int tick_dtype, bool by_partition) {
+    return p.have_chain && batch <= kChainMostPartitions && (by_partition || batch * tick_dtype <= 256);
 }
 
 // Fitted to 100 calls (64 to 3,600 vertices, 8 to 300 levels, 8 to 4,096 partitions), with what the launch itself takes: a
@@ -656,8 +673,12 @@ static int eval_bytes(const cp_graph *g, int32_t batch, int32_t k, int assign_la
         for (int groups : {4, 8})
             lanes = std::max(lanes, lane_work_bytes(&g->packed.lane_b, &g->packed.lane_t, g->packed.n, batch, groups, 8));
     size_t chain = 0;
-    if (with_chain && plan == CP_PLAN_AUTO && g->packed.have_chain && batch <= kChainMostPartitions)
-        chain = chain_work_bytes(&g->packed.chain_b, &g->packed.chain_t, g->packed.chain_width, batch, false);
+    if (with_chain && plan == CP_PLAN_AUTO && chain_takes(g->packed, batch, tick_dtype, out_layout == CP_OUT_PARTITION_MAJOR)) {
+        const Packed &p = g->packed;
+        const bool cost16 = chain_cost16(p);
+        const int32_t at_once = chain_at_once(&p.chain_b, &p.chain_t, p.chain_width, batch, cost16, kChainMostBytes);
+        chain = chain_work_bytes(&p.chain_b, &p.chain_t, p.chain_width, at_once, cost16);
+    }
     *out_bytes = bytes + std::max({column, window, lanes, chain});
     return CP_OK;
 }
@@ -758,12 +779,12 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     bool lanes = false;
     size_t lane_work = 0;
     // a few partitions, each sweep of each by a workgroup of its own
-    const bool chain_fits = plan == CP_PLAN_AUTO && lane_sweeps > 0 && p.have_chain && batch <= kChainMostPartitions &&
+    const bool chain_fits = plan == CP_PLAN_AUTO && lane_sweeps > 0 && chain_takes(p, batch, tick_dtype, by_partition) &&
                             std::max(chain_lds_bytes(p.chain_b, p.info.min_tick_bytes),
-                                     chain_lds_bytes(p.chain_t, p.info.min_tick_bytes)) <= lds_limit &&
-                            (by_partition || batch * tick_dtype <= 256);      // (its output offsets take 24 bits by 8)
+                                     chain_lds_bytes(p.chain_t, p.info.min_tick_bytes)) <= lds_limit;
     const bool cost16 = chain_fits && chain_cost16(p, k, speeds, bandwidth);
     bool chain = false;
+    int32_t at_once = 0, rounds = 0;
     // a small graph, everything in one launch
     WholeCfg whole_cfg;
     double whole_us_of = 0.0;
@@ -834,14 +855,15 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                 lanes = lanes && !whole;
             }
             if (chain_fits) {
-                const size_t work = chain_work_bytes((blevel_out || cp_out) ? &p.chain_b : nullptr,
-                                                     tlevel_out ? &p.chain_t : nullptr, p.chain_width, batch, cost16);
                 if (!chain_scratch) {
                     chain_scratch = (uint8_t *)workspace + tables_bytes(k);
                     chain_scratch_bytes = workspace_bytes - std::min(workspace_bytes, tables_bytes(k));
                 }
-                chain = work <= chain_scratch_bytes && tables_bytes(k) <= workspace_bytes &&
-                        chain_us(p, batch, lane_sweeps, cost16, by_partition) + mask_more_us <
+                at_once = chain_at_once((blevel_out || cp_out) ? &p.chain_b : nullptr, tlevel_out ? &p.chain_t : nullptr,
+                                        p.chain_width, batch, cost16, chain_scratch_bytes);
+                rounds = at_once > 0 ? (batch + at_once - 1) / at_once : 0;
+                chain = rounds > 0 && tables_bytes(k) <= workspace_bytes &&
+                        chain_us(p, batch, lane_sweeps, cost16, by_partition, rounds) + mask_more_us <
                             (whole ? whole_us_of : lanes ? 1.0 + 0.7 * mb + lane_us : other_us - apart_us);
                 lanes = lanes && !chain;
                 whole = whole && !chain;
@@ -1063,13 +1085,13 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
                               all_in_one ? table.data() : nullptr, all_in_one, stream);
         } else if (chain) {
             rc = launch_chain(s, t, p.chain_b, p.chain_t, p.chain_width, p.info.min_tick_bytes, cost16, want_b,
-                              tlevel_out != nullptr, chain_scratch, stream);
+                              tlevel_out != nullptr, chain_scratch, at_once, stream);
         } else {
             rc = launch_window_lanes(s, t, p.lane_b, p.lane_t, lane_cfg, want_b, tlevel_out != nullptr,
                                      d_tab + tables_bytes(k), stream);
         }
         if (rc) return rc;
-        if (launches) launches[chain && !want_b ? 1 : 0] = 1;
+        if (launches) launches[chain && !want_b ? 1 : 0] = chain ? rounds : 1;
     } else if (blevel_out || cp_out) {
         s.tsweep = false;
         s.dir = &p.col_b;
@@ -1181,7 +1203,7 @@ namespace cpeval {
 
 size_t eval_chain_bytes(const cp_graph *g, bool both) {
     const Packed &p = g->packed;
-    return p.have_chain ? chain_work_bytes(&p.chain_b, both ? &p.chain_t : nullptr, p.chain_width, 1, false) : 0;
+    return p.have_chain ? chain_work_bytes(&p.chain_b, both ? &p.chain_t : nullptr, p.chain_width, 1, chain_cost16(p)) : 0;
 }
 
 int eval_one(const cp_graph *g, int32_t k, const uint8_t *assignment, const int64_t *speeds, const int64_t *bandwidth,

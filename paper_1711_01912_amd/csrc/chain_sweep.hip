@@ -13,6 +13,9 @@
 //   tick      four ring reads, four additions, maxima (over the lanes of a row by register permutations, one step for
 //             up to 8 edges, 16, 32, 64), one ring write, barrier; beside it the last tick's outputs are stored
 //
+// Costs take 18 or 36 bytes a lane of a tick and partition for both sweeps; where there is room for fewer partitions' than the
+// call has, it goes in rounds over one block of them.
+//
 // R covers the largest distance of an edge in positions and two ticks, so a slot is written after its last reader.  Both sweeps of
 // a call run side by side.  Whole calls, the plan before -> this one, one and 32 partitions: 211,000 vertices in 1,000 levels 799
 // -> 223 us and 803 -> 484 (rows per vertex 1,486 -> 241, 1,485 -> 710), 121,000 in 701 levels 503 -> 139 and 508 -> 257,
@@ -264,7 +267,7 @@ size_t chain_work_bytes(const ChainDir *db, const ChainDir *dt, int32_t width, i
 size_t chain_lds_bytes(const ChainDir &d, int word_bytes) { return ((size_t)(d.slots + 1 + kWave) * word_bytes + 15) & ~(size_t)15; }
 
 int launch_chain(const SweepLaunch &sb, const SweepLaunch &st, const ChainDir &db, const ChainDir &dt, int32_t width,
-                 int word_bytes, bool cost16, bool want_b, bool want_t, uint8_t *work, void *stream) {
+                 int word_bytes, bool cost16, bool want_b, bool want_t, uint8_t *work, int32_t at_once, void *stream) {
     ChainArgs args[2]{};
     const SweepLaunch *launch[2] = {&sb, &st};
     const ChainDir *dir[2] = {&db, &dt};
@@ -279,41 +282,46 @@ int launch_chain(const SweepLaunch &sb, const SweepLaunch &st, const ChainDir &d
         a.idx = (const int32_t *)(s.blob + s.dir->idx_off);
         a.wt = (const uint32_t *)(s.blob + s.dir->wt_off);
         a.edge_tab = s.edge_tab;
-        const size_t items = (size_t)s.P * d.ticks * width;
+        const size_t items = (size_t)at_once * d.ticks * width;
         a.cost = work;
         a.w = work + items * (cost16 ? 8 : 16);
         work += align_up(items * (i ? 20 : 16) / (cost16 ? 2 : 1));
-        a.out = s.val;
         a.out_sv = s.out_sv;
         a.out_sq = s.out_sq;
-        a.cp_out = s.cp_out;
         a.ticks = d.ticks;
         a.slots = d.slots;
     }
     ChainShape sh{};
-    sh.assign = sb.assign;
     sh.a_sp = sb.a_stride_p;
     sh.a_sv = sb.a_stride_v;
     sh.c = (const uint32_t *)(sb.blob + sb.c_off);
     sh.vert_tab = sb.vert_tab;
     sh.status = sb.status;
     sh.n = sb.n;
-    sh.P = sb.P;
     sh.k = sb.k;
     sh.width = width;
     sh.sweeps = (want_b ? 1 : 0) | (want_t ? 2 : 0);
     const unsigned both = sh.sweeps == 3 ? 2 : 1;
     const int32_t most = std::max(want_b ? db.ticks : 0, want_t ? dt.ticks : 0);
-    const dim3 grid((unsigned)(((int64_t)most * width + 255) / 256), (unsigned)sb.P, both);
-    hipStream_t s = (hipStream_t)stream;
-#define CP_COST(MAGIC, C16) hipLaunchKernelGGL((chain_cost_kernel<MAGIC, C16>), grid, dim3(256), 0, s, args[0], args[1], sh)
-    if (sb.magic && cost16) CP_COST(true, true);
-    else if (sb.magic) CP_COST(true, false);
-    else if (cost16) CP_COST(false, true);
-    else CP_COST(false, false);
-#undef CP_COST
     const size_t lds = std::max(want_b ? chain_lds_bytes(db, word_bytes) : 0, want_t ? chain_lds_bytes(dt, word_bytes) : 0);
-    const dim3 groups((unsigned)sb.P * both), lanes((unsigned)width);
+    hipStream_t s = (hipStream_t)stream;
+    for (int32_t q0 = 0; q0 < sb.P; q0 += at_once) {
+        sh.P = std::min(at_once, sb.P - q0);
+        sh.assign = sb.assign + (int64_t)q0 * sb.a_stride_p;
+        for (int i = 0; i < 2; ++i) {
+            const SweepLaunch &l = *launch[i];
+            if (!want[i]) continue;
+            args[i].out = l.val ? (uint8_t *)l.val + (int64_t)q0 * l.out_sq * l.tick_bytes : nullptr;
+            args[i].cp_out = l.cp_out ? l.cp_out + q0 : nullptr;
+        }
+        const dim3 grid((unsigned)(((int64_t)most * width + 255) / 256), (unsigned)sh.P, both);
+#define CP_COST(MAGIC, C16) hipLaunchKernelGGL((chain_cost_kernel<MAGIC, C16>), grid, dim3(256), 0, s, args[0], args[1], sh)
+        if (sb.magic && cost16) CP_COST(true, true);
+        else if (sb.magic) CP_COST(true, false);
+        else if (cost16) CP_COST(false, true);
+        else CP_COST(false, false);
+#undef CP_COST
+        const dim3 groups((unsigned)sh.P * both), lanes((unsigned)width);
 #define CP_CHAIN(WORD, T64, ONE, C16)                                                                                \
     do {                                                                                                             \
         const auto kernel = chain_kernel<WORD, T64, ONE, C16>;                                                       \
@@ -328,12 +336,14 @@ int launch_chain(const SweepLaunch &sb, const SweepLaunch &st, const ChainDir &d
         else if (cost16) CP_CHAIN(WORD, T64, false, true);                                                           \
         else CP_CHAIN(WORD, T64, false, false);                                                                      \
     } while (0)
-    if (word_bytes == 8) CP_CHAIN_OF(unsigned long long, true);
-    else if (sb.tick_bytes == 8) CP_CHAIN_OF(uint32_t, true);
-    else CP_CHAIN_OF(uint32_t, false);
+        if (word_bytes == 8) CP_CHAIN_OF(unsigned long long, true);
+        else if (sb.tick_bytes == 8) CP_CHAIN_OF(uint32_t, true);
+        else CP_CHAIN_OF(uint32_t, false);
 #undef CP_CHAIN_OF
 #undef CP_CHAIN
-    return hipGetLastError() == hipSuccess ? CP_OK : CP_ERR_HIP;
+        if (hipGetLastError() != hipSuccess) return CP_ERR_HIP;
+    }
+    return CP_OK;
 }
 
 }  // namespace cpeval

@@ -162,12 +162,13 @@ size_t lane_work_bytes(const LaneDir *db, const LaneDir *dt, int32_t n, int32_t 
 int launch_window_lanes(const SweepLaunch &sb, const SweepLaunch &st, const LaneDir &db, const LaneDir &dt,
                         const LaneCfg &cfg, bool want_b, bool want_t, uint8_t *ids, void *stream);
 
-// The chain sweep of a few partitions (null: not that sweep): what a call's costs take, LDS of a workgroup, the launches.
+// The chain sweep of a few partitions (null: not that sweep): what the costs of P of them take, LDS of a workgroup, the
+// launches, two for every `at_once` partitions, whose costs `work` has room for.
 // cost16: no edge's cost and its vertex's w together reach 2^16.
 size_t chain_work_bytes(const ChainDir *db, const ChainDir *dt, int32_t width, int32_t P, bool cost16);
 size_t chain_lds_bytes(const ChainDir &d, int word_bytes);
 int launch_chain(const SweepLaunch &sb, const SweepLaunch &st, const ChainDir &db, const ChainDir &dt, int32_t width,
-                 int word_bytes, bool cost16, bool want_b, bool want_t, uint8_t *work, void *stream);
+                 int word_bytes, bool cost16, bool want_b, bool want_t, uint8_t *work, int32_t at_once, void *stream);
 
 // The whole-graph sweep.
 constexpr int kWholeTableWords = 880;        // 3.4 KB of cost tables among a kernel's arguments

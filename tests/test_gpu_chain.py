@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import test_gpu_parity as T
+from paper_1711_01912_amd import binding
 from workloads import random_layered_dag
 
 pytestmark = pytest.mark.gpu
@@ -96,3 +97,25 @@ def test_not_where_other_plans_are_faster(gpu, oracle):
     """Wide levels: 300 of 500 vertices and 48 partitions took 330 us in the chain sweep, 268 in the resident-window plan."""
     _check(gpu, oracle, _graph(12, [500] * 300, 5, 6, 48, 16), 1, chain=False)
     _check(gpu, oracle, _graph(12, [500] * 300, 5, 6, 8, 16), 1)
+
+
+@pytest.mark.parametrize("room,rounds", [(1, 7), (2, 4), (3, 3), (4, 2), (6, 2), (7, 1)])
+@pytest.mark.parametrize("layout,tick_bytes", [(0, 4), (1, 4), (0, 8), (1, 8)])
+def test_in_rounds_where_the_workspace_holds_fewer_partitions(gpu, oracle, layout, tick_bytes, room, rounds):
+    import torch
+    w = _graph(11, [211] * 260, 7, 10, 7, 16)
+    g = gpu.CpGraph.from_workload(w, device="cuda:0")
+    a = torch.from_numpy(w.assignments).to("cuda:0")
+    ref = oracle.evaluate_workload(w, threads=8)
+    size = binding.workspace_bytes(g, room, w.k, out_layout=layout, tick_bytes=tick_bytes)
+    work = torch.empty(size, dtype=torch.uint8, device="cuda:0")
+    prof = gpu.CpProfile(1)
+    out = gpu.cp_eval(g, a, w.speeds, w.bandwidth, out_layout=layout, tick_bytes=tick_bytes, workspace=work, profile=prof)
+    rows = (lambda x: x.cpu().numpy()) if layout == 1 else (lambda x: x.cpu().numpy().T)
+    assert np.array_equal(out["cp"].cpu().numpy(), ref["cp"])
+    for key in ("b", "tl"):
+        assert np.array_equal(rows(out[key]).astype(np.int64), ref[key]), key
+    assert prof.plan(0) == gpu.PLAN_CHAIN or rounds > 2       # (three take as long as what other plans do)
+    if prof.plan(0) == gpu.PLAN_CHAIN:
+        assert prof.read(0)[1] == (rounds, 0)
+    g.close()
