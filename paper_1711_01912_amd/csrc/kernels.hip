@@ -1512,7 +1512,7 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
         };
         // value + transfer time
         auto plus_transfer = [&](Tick value, uint32_t volume, Tab m) -> Acc {
-            if constexpr (WORDS) return add_quotient((uint32_t)value, volume, m, up);
+            if constexpr (WORDS) return add_shifted((uint32_t)value, inverse_bits(volume, m, up));
             else if constexpr (!ENT4) return (Acc)value + (Acc)magic_div(volume, m);
             else if constexpr (sizeof(Tick) == 4) return (Acc)value + inverse_bits(volume, m, up);
             else return (Acc)value + (Acc)inverse_div(volume, m, up);

@@ -194,8 +194,8 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
             const uint32_t at_a = ra.x * sv + (uint32_t)ga * sq, at_b = rb.x * sv + (uint32_t)gb * sq;
             if constexpr (TSWEEP) {
                 const Tab ma = vtab[(uint32_t)xa & ID], mb = vtab[(uint32_t)xb & ID];
-                xa = (xa >> kLaneIdBits) - (Word)inverse_div(ra.y, ma, up);
-                xb = (xb >> kLaneIdBits) - (Word)inverse_div(rb.y, mb, up);
+                xa = (xa >> kLaneIdBits) - (Word)inverse_div(word_of(ra.y), ma, up);
+                xb = (xb >> kLaneIdBits) - (Word)inverse_div(word_of(rb.y), mb, up);
             } else {
                 xa >>= kLaneIdBits;
                 xb >>= kLaneIdBits;
