@@ -1113,7 +1113,7 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
             t.cp_out = nullptr;
             t.pperm = d_pperm_t;
             t.direct_ids = direct_t;
-            rc = launch_window_pair(s, t, pr_b, pr_t, p.lane_word == 4, stream);
+            rc = launch_window_pair(s, t, pr_b, pr_t, stream);
             if (launches) { launches[0] = 1; launches[1] = 0; }
         } else if (shared || streamed) {
             rc = shared ? launch_window_shared(s, sh_b, stream) : launch_window_stream(s, st_b, stream);

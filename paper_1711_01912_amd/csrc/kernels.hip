@@ -1246,7 +1246,6 @@ struct WindowArgs {
     int32_t groups;            // partitions per workgroup
     int32_t wgs;               // workgroups that have partitions
     uint32_t sub_bytes;        // LDS of one partition: ring, far pairs, two stage slots
-    int32_t tab_rs;            // WORDS: every transfer cost sits 2^tab_rs times in LDS
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // stays in registers when indexed statically
@@ -1270,7 +1269,7 @@ typedef const uint32_t __attribute__((address_space(4))) *const_u32_ptr;   // un
 //
 // `block` is the workgroup's number within its sweep (the pair kernel below runs both sweeps in
 // one launch).  Wavefronts the sweep's shape does not use end at once.
-template <typename Tick, bool TSWEEP, bool PACKED, bool ENT4, int NL, int DR, bool MASK, bool FAR, bool WORDS = false>
+template <typename Tick, bool TSWEEP, bool PACKED, bool ENT4, int NL, int DR, bool MASK, bool FAR>
 __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uint32_t block) {
     extern __shared__ uint4 lds16[];
     __shared__ long long red[kWindowMaxWaves];
@@ -1297,9 +1296,7 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
     // places) so that every wavefront meets every barrier
     const int32_t q = min(wg * a.groups + sub, a.P - 1);
 
-    static_assert(!WORDS || (PACKED && ENT4 && sizeof(Tick) == 4 && !FAR), "words: packed, 16-bit volumes, no far reads");
-    const uint32_t ring_bytes =
-        (uint32_t)((((size_t)R + 1) * (WORDS ? 4 : PACKED ? 8 : sizeof(Tick) + 1) + 15) & ~(size_t)15);
+    const uint32_t ring_bytes = (uint32_t)((((size_t)R + 1) * (PACKED ? 8 : sizeof(Tick) + 1) + 15) & ~(size_t)15);
     const uint32_t tab_bytes = (uint32_t)((sizeof(Magic) * ((size_t)k * k + k) + 15) & ~(size_t)15);
     Tick *ring_val = (Tick *)lds;                                  // split layout
     uint8_t *ring_dev = lds + sizeof(Tick) * ((size_t)R + 1);
@@ -1308,21 +1305,18 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
     typedef typename std::conditional<ENT4, float, Magic>::type Tab;
     // byte offsets from this partition's LDS: the shared tables lie behind the last partition
     const uint32_t etab_off = (uint32_t)(a.groups - sub) * a.sub_bytes;
-    const int tab_rs = WORDS ? a.tab_rs : 0;
-    const uint32_t vtab_off = etab_off + ((((uint32_t)sizeof(Tab) * (uint32_t)(k * k) << tab_rs) + 7u) & ~7u);
+    const uint32_t vtab_off = etab_off + (((uint32_t)sizeof(Tab) * (uint32_t)(k * k) + 7u) & ~7u);
     const int slot_bytes = NL * a.nlw * 1024;
     uint8_t *stage = lds + ring_bytes + 2u * far_bytes;
     (void)tab_bytes;
     {
         const Tab *e = (const Tab *)(ENT4 ? (const void *)a.edge_tab4 : (const void *)a.edge_tab);
-        for (int i = tid; i < k * k << tab_rs; i += nt) ((Tab *)(lds + etab_off))[i] = e[i >> tab_rs];
+        for (int i = tid; i < k * k; i += nt) ((Tab *)(lds + etab_off))[i] = e[i];
         for (int i = tid; i < k; i += nt) ((Magic *)(lds + vtab_off))[i] = a.vert_tab[i];
         if constexpr (MASK)
             for (int i = tid; i < 2 * kMaskWords; i += nt) (&mbits[0][0])[i] = 0;
         if (wave == 0 && lane == 0) {        // the constant-zero slot padding entries point at
-            if (WORDS) {
-                ((uint32_t *)lds)[R] = 0;
-            } else if (PACKED) {
+            if (PACKED) {
                 ((uint2 *)lds)[R] = make_uint2(0, 0);
             } else {
                 ring_val[R] = 0;
@@ -1486,11 +1480,9 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
         typedef typename std::conditional<ENT4, uint32_t, uint2>::type Ent;
         Tick *out = a.out ? (Tick *)a.out + (size_t)q * (size_t)a.out_sq : nullptr;
         const uint32_t out_sv = a.out_sv;
-        const int dev_sh = 2 + tab_rs;       // (WORDS) bytes between the entries of two devices, as a shift
-        const uint32_t row_bytes = (uint32_t)sizeof(Tab) * (uint32_t)k << tab_rs;
-        const uint32_t copy_off = WORDS ? 4u * ((uint32_t)lane & ((1u << tab_rs) - 1u)) : 0u;   // this lane's copy
+        const uint32_t row_bytes = (uint32_t)sizeof(Tab) * (uint32_t)k;
         // Inverses: the sums carry the base's bits until the maximum is taken (values below 2^31, so 32 bits hold them)
-        constexpr uint32_t kBias = ENT4 && sizeof(Tick) == 4 && !WORDS ? 0x48000000u : 0u;
+        constexpr uint32_t kBias = ENT4 && sizeof(Tick) == 4 ? 0x48000000u : 0u;
         typedef typename std::conditional<sizeof(Tick) == 4, uint32_t, Tick>::type Acc;
         float up = 0.0f;
         if constexpr (ENT4) up = round_up(float());     // (no variable divisions behind this)
@@ -1503,27 +1495,20 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
         uint32_t worst = 0;                  // largest device id seen
 
         auto ent_field = [](Ent e) -> uint32_t {
-            if constexpr (WORDS) return e >> 1 & 0x7fffu;     // (the field is 8 * slot)
-            else if constexpr (ENT4) return e & 0xffffu;
-            else return e.x;
+            if constexpr (ENT4) return e & 0xffffu; else return e.x;
         };
         auto ent_t = [](Ent e) -> uint32_t {
             if constexpr (ENT4) return e >> 16; else return e.y;
         };
         // value + transfer time
         auto plus_transfer = [&](Tick value, uint32_t volume, Tab m) -> Acc {
-            if constexpr (WORDS) return add_shifted((uint32_t)value, inverse_bits(volume, m, up));
-            else if constexpr (!ENT4) return (Acc)value + (Acc)magic_div(volume, m);
+            if constexpr (!ENT4) return (Acc)value + (Acc)magic_div(volume, m);
             else if constexpr (sizeof(Tick) == 4) return (Acc)value + inverse_bits(volume, m, up);
             else return (Acc)value + (Acc)inverse_div(volume, m, up);
         };
         // value and sizeof(Tab) * device of the vertex behind ring field f
         auto ring_get = [&](uint32_t f, Tick &vu, uint32_t &pu8) {
-            if constexpr (WORDS) {
-                const uint32_t x = *(const uint32_t *)(lds + f);
-                vu = (Tick)x;
-                pu8 = (x & ((1u << kLaneIdBits) - 1u)) << dev_sh;
-            } else if constexpr (PACKED) {
+            if constexpr (PACKED) {
                 const uint2 x = *(const uint2 *)(lds + f);
                 vu = (Tick)x.x;
                 pu8 = x.y;
@@ -1552,9 +1537,7 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
                 const Tick fin = acc + w;            // b(v), or tl(v) + w(v)
                 int rs = rbase + row;
                 if (rs >= R) rs -= R;
-                if constexpr (WORDS) {
-                    ((uint32_t *)lds)[rs] = (uint32_t)fin << kLaneIdBits | pv;
-                } else if constexpr (PACKED) {
+                if constexpr (PACKED) {
                     ((uint2 *)lds)[rs] = make_uint2((uint32_t)fin, (uint32_t)sizeof(Tab) * pv);
                 } else {
                     ring_val[rs] = fin;
@@ -1616,7 +1599,7 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
         _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_) ring_get(ent_field(en_[i_]), vu_[i_], pu8_[i_]); \
         worst = max(worst, pv);                                                                 \
         pv = min(pv, (uint32_t)(k - 1));                                                        \
-        erow = etab_off + __umul24(pv, row_bytes) + copy_off;                                   \
+        erow = etab_off + __umul24(pv, row_bytes);                                              \
         mv = *(const Magic *)(lds + vtab_off + 8u * pv);                                        \
         _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_) mg_[i_] = *(const Tab *)(lds + erow + pu8_[i_]);   \
         _Pragma("unroll") for (int i_ = 0; i_ < N; ++i_)                                        \
@@ -1663,7 +1646,7 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
 #undef CP_BLOCK
 #undef CP_HEAD
             acc = fold(acc, lsh);
-            publish((Tick)(WORDS ? acc >> kLaneIdBits : acc - kBias), (Tick)magic_div(rc.y, mv), lsh, rows, rbase, rc.x, pv, bv, lo);
+            publish((Tick)(acc - kBias), (Tick)magic_div(rc.y, mv), lsh, rows, rbase, rc.x, pv, bv, lo);
         };
 
         lds_barrier();                       // packet 0 is staged
@@ -1710,11 +1693,11 @@ __global__ __launch_bounds__(kWindowMaxWaves * 64) void window_sweep_kernel(Wind
 // and at most 16 wavefronts and half the LDS each.  Large sparse workload, 256 partitions:
 // 2.07 ms for both sweeps against 1.47 + 1.75 ms one after the other.
 constexpr int kPairNl = 4, kPairDr = 2;
-template <bool ENT4, bool WORDS>
+template <bool ENT4>
 __global__ __launch_bounds__(kWindowMaxWaves * 64) void window_pair_kernel(WindowArgs ab, WindowArgs at, uint32_t nb) {
     (void)nb;
-    if ((blockIdx.x & 1) == 0) window_sweep_body<int32_t, false, true, ENT4, kPairNl, kPairDr, false, false, WORDS>(ab, blockIdx.x >> 1);
-    else window_sweep_body<int32_t, true, true, ENT4, kPairNl, kPairDr, false, false, WORDS>(at, blockIdx.x >> 1);
+    if ((blockIdx.x & 1) == 0) window_sweep_body<int32_t, false, true, ENT4, kPairNl, kPairDr, false, false>(ab, blockIdx.x >> 1);
+    else window_sweep_body<int32_t, true, true, ENT4, kPairNl, kPairDr, false, false>(at, blockIdx.x >> 1);
 }
 
 // ---------------------------------------------------------------- launch helpers
@@ -2109,24 +2092,13 @@ bool window_pair_config(const WindowDir &db, const WindowDir &dt, int32_t k, siz
 }
 
 int launch_window_pair(const SweepLaunch &sb, const SweepLaunch &st, const WindowCfg &cfg_b, const WindowCfg &cfg_t,
-                       bool words, void *stream) {
+                       void *stream) {
     if (sb.tick_bytes != 4 || st.tick_bytes != 4 || sb.tsweep || !st.tsweep || sb.mask_out || st.mask_out)
         return CP_ERR_ARG;
     if (cfg_b.nl != kPairNl || cfg_t.nl != kPairNl || cfg_b.groups != 1 || cfg_t.groups != 1 ||
         cfg_b.lds_bytes != cfg_t.lds_bytes || sb.win->ent4 != st.win->ent4 || (sb.win->ent4 && (!sb.edge_tab4 || !st.edge_tab4)) || sb.win->far_cap > 0 || st.win->far_cap > 0)
         return CP_ERR_ARG;
-    WindowArgs ab = window_args(sb, cfg_b), at = window_args(st, cfg_t);
-    words = words && sb.win->ent4;
-    if (words) {
-        // what the ring saves goes to copies of the transfer costs, up to one for every second bank
-        int rs = 5;
-        for (WindowArgs *x : {&ab, &at}) {
-            const size_t pairs = ((size_t)x->slots + 1) * 8 + 15 & ~(size_t)15, single = ((size_t)x->slots + 1) * 4 + 15 & ~(size_t)15;
-            x->sub_bytes -= (uint32_t)(pairs - single);
-            while (rs > 0 && x->sub_bytes + ((size_t)sb.k * sb.k * 4 << rs) + 8 * ((size_t)sb.k + 1) > cfg_b.lds_bytes) --rs;
-        }
-        ab.tab_rs = at.tab_rs = rs;
-    }
+    const WindowArgs ab = window_args(sb, cfg_b), at = window_args(st, cfg_t);
     const uint32_t nb = (uint32_t)(8 * ab.pgroups), nt = (uint32_t)(8 * at.pgroups);
     if (nb != nt) return CP_ERR_ARG;         // (the same batch both ways)
     const int waves = std::max(cfg_b.nc + cfg_b.nlw, cfg_t.nc + cfg_t.nlw);
@@ -2139,8 +2111,7 @@ int launch_window_pair(const SweepLaunch &sb, const SweepLaunch &st, const Windo
         hipLaunchKernelGGL(kern, dim3(nb + nt), dim3(waves * 64), cfg_b.lds_bytes, (hipStream_t)stream, ab, at, nb);
         return hip_ok(hipGetLastError());
     };
-    if (words) return launch(window_pair_kernel<true, true>);
-    return sb.win->ent4 ? launch(window_pair_kernel<true, false>) : launch(window_pair_kernel<false, false>);
+    return sb.win->ent4 ? launch(window_pair_kernel<true>) : launch(window_pair_kernel<false>);
 }
 
 int launch_cp_sources(const int32_t *sources, int32_t nsrc, const void *b, int32_t P,

@@ -194,7 +194,7 @@ bool window_config(const WindowDir &d, int32_t k, size_t tick_bytes, size_t lds_
 bool window_pair_config(const WindowDir &db, const WindowDir &dt, int32_t k, size_t lds_limit, WindowCfg &out_b,
                         WindowCfg &out_t);
 int launch_window_pair(const SweepLaunch &sb, const SweepLaunch &st, const WindowCfg &cfg_b, const WindowCfg &cfg_t,
-                       bool words, void *stream);
+                       void *stream);
 int32_t window_mask_bpad(const WindowDir &d);
 int launch_gather_assign(const SweepLaunch &s, uint8_t *out, void *stream);
 
