@@ -1297,21 +1297,23 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
     const int32_t q = min(wg * a.groups + sub, a.P - 1);
 
     const uint32_t ring_bytes = (uint32_t)((((size_t)R + 1) * (PACKED ? 8 : sizeof(Tick) + 1) + 15) & ~(size_t)15);
-    const uint32_t tab_bytes = (uint32_t)((sizeof(Magic) * ((size_t)k * k + k) + 15) & ~(size_t)15);
     Tick *ring_val = (Tick *)lds;                                  // split layout
     uint8_t *ring_dev = lds + sizeof(Tick) * ((size_t)R + 1);
     const uint32_t far_bytes = FAR ? 8u * (uint32_t)a.far_cap : 0u;   // per tick parity, behind the ring
     // transfer costs: inverses where an entry's volume has 16 bits, a division is then one multiply-add
     typedef typename std::conditional<ENT4, float, Magic>::type Tab;
+    // Entries from one device's row to the next: an odd number of words, so that lanes on different devices meet in few banks
+    // (a pair of sweeps on 500 vertices a level, 16 and 32 devices, 256 partitions: 443 -> 430 and 459 -> 411 us in 400 levels;
+    // other numbers of devices within 1 %).  LDS is laid out for 8-byte entries, which take more room.
+    const uint32_t row = ENT4 ? (uint32_t)k | 1u : (uint32_t)k;
     // byte offsets from this partition's LDS: the shared tables lie behind the last partition
     const uint32_t etab_off = (uint32_t)(a.groups - sub) * a.sub_bytes;
-    const uint32_t vtab_off = etab_off + (((uint32_t)sizeof(Tab) * (uint32_t)(k * k) + 7u) & ~7u);
+    const uint32_t vtab_off = etab_off + (((uint32_t)sizeof(Tab) * (uint32_t)k * row + 7u) & ~7u);
     const int slot_bytes = NL * a.nlw * 1024;
     uint8_t *stage = lds + ring_bytes + 2u * far_bytes;
-    (void)tab_bytes;
     {
         const Tab *e = (const Tab *)(ENT4 ? (const void *)a.edge_tab4 : (const void *)a.edge_tab);
-        for (int i = tid; i < k * k; i += nt) ((Tab *)(lds + etab_off))[i] = e[i];
+        for (int i = tid; i < k * k; i += nt) ((Tab *)(lds + etab_off))[i + (ENT4 ? i / k * (int)(row - k) : 0)] = e[i];
         for (int i = tid; i < k; i += nt) ((Magic *)(lds + vtab_off))[i] = a.vert_tab[i];
         if constexpr (MASK)
             for (int i = tid; i < 2 * kMaskWords; i += nt) (&mbits[0][0])[i] = 0;
@@ -1480,7 +1482,7 @@ __device__ __forceinline__ void window_sweep_body(const WindowArgs &a, const uin
         typedef typename std::conditional<ENT4, uint32_t, uint2>::type Ent;
         Tick *out = a.out ? (Tick *)a.out + (size_t)q * (size_t)a.out_sq : nullptr;
         const uint32_t out_sv = a.out_sv;
-        const uint32_t row_bytes = (uint32_t)sizeof(Tab) * (uint32_t)k;
+        const uint32_t row_bytes = (uint32_t)sizeof(Tab) * row;
         // Inverses: the sums carry the base's bits until the maximum is taken (values below 2^31, so 32 bits hold them)
         constexpr uint32_t kBias = ENT4 && sizeof(Tick) == 4 ? 0x48000000u : 0u;
         typedef typename std::conditional<sizeof(Tick) == 4, uint32_t, Tick>::type Acc;
