@@ -435,12 +435,9 @@ std::vector<uint64_t> table_image(const CostTables &tabs, int32_t k, const int64
                                   Inverses as) {
     std::vector<uint64_t> img(table_words(k), 0);
     const size_t entries = table_entries(k);
-    std::vector<double> inverse;
-    if (as != Inverses::kNone) build_inverse_table(k, speeds, bandwidth, inverse);
-    const void *from = as == Inverses::kDoubles ? (const void *)inverse.data()
-                       : tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data();
-    std::memcpy(img.data(), from, entries * 8);
-    if (as == Inverses::kFloats) build_float_table(inverse, (float *)(img.data() + entries));
+    if (as == Inverses::kDoubles) build_inverse_table(k, speeds, bandwidth, (double *)img.data());
+    else std::memcpy(img.data(), tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data(), entries * 8);
+    if (as == Inverses::kFloats) build_float_table(k, speeds, bandwidth, (float *)(img.data() + entries));
     else if (tabs.tab4_ok) std::memcpy(img.data() + entries, tabs.tab4.data(), entries * 4);
     return img;
 }

@@ -2,7 +2,7 @@
 // speeds) and of every transfer cost (bandwidth matrix), as plain divisors and,
 // where it is provably exact, as 32-bit multiply-shift constants.
 #include <algorithm>
-#include <cmath>
+#include <cstring>
 
 #include "cpeval_internal.hpp"
 
@@ -59,19 +59,22 @@ int build_cost_tables(int32_t k, const int64_t *speeds, const int64_t *bandwidth
     // a free transfer's entry 0 multiplies by 255: 0 ticks only while the volume is below 2^24
     bool ok4 = ok && max_t < ((int64_t)1 << 24) && max_c < ((int64_t)1 << 24);
 
-    for (int own = 0; own < k; ++own)
-        for (int nbr = 0; nbr < k; ++nbr) {
-            if (own == nbr) continue;  // same device: free, stays {0,0} / divisor 0
-            // b sweep: own = device of the edge's source vertex, nbr = device of its target
-            int64_t db = bandwidth[(size_t)own * k + nbr];
-            // t sweep: own = device of the edge's target vertex, nbr = device of its source
-            int64_t dt = bandwidth[(size_t)nbr * k + own];
-            out.divisor[(size_t)own * k + nbr] = db;
-            out.divisor[kk + (size_t)own * k + nbr] = dt;
-            if (ok) ok = magic_for(db, max_t, out.magic[(size_t)own * k + nbr]);
-            if (ok) ok = magic_for(dt, max_t, out.magic[kk + (size_t)own * k + nbr]);
-            if (ok4) ok4 = magic4_for(db, max_t, out.tab4[(size_t)own * k + nbr]);
-            if (ok4) ok4 = magic4_for(dt, max_t, out.tab4[kk + (size_t)own * k + nbr]);
+    // (an entry is worked out once: the division in it takes longer than all the rest)
+    for (size_t i = 0; i < (size_t)k; ++i)
+        for (size_t j = 0; j < (size_t)k; ++j) {
+            if (i == j) continue;  // same device: free, stays {0,0} / divisor 0
+            // b sweep: row = device of the edge's source vertex, column = device of its target; t sweep: the other way round
+            const int64_t d = bandwidth[i * k + j];
+            const size_t at_b = i * k + j, at_t = kk + j * k + i;
+            out.divisor[at_b] = out.divisor[at_t] = d;
+            if (ok) {
+                ok = magic_for(d, max_t, out.magic[at_b]);
+                out.magic[at_t] = out.magic[at_b];
+            }
+            if (ok4) {
+                ok4 = magic4_for(d, max_t, out.tab4[at_b]);
+                out.tab4[at_t] = out.tab4[at_b];
+            }
         }
     for (int i = 0; i < k; ++i) {
         out.divisor[2 * kk + i] = speeds[i];
@@ -108,28 +111,45 @@ void build_round_table(int32_t k, const int64_t *speeds, const int64_t *bandwidt
     }
 }
 
-// 1.0 / d is at most half a unit off; fma tells which way (d and the inverse are exact, past 2^53 the divisor is rounded and
-// only has to be larger than every dividend).
-void build_inverse_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<double> &out) {
-    auto entry = [](int64_t d) {
-        const double x = 1.0 / (double)d;
-        return std::fma(x, (double)d, -1.0) > 0.0 ? std::nextafter(x, 0.0) : x;
-    };
+// The next number below 1.0 / d, which is at most half a unit above 1 / d, is a unit and a half below it at most, and no branch
+// tells (past 2^53 the divisor is rounded, and only has to be larger than every dividend).
+static double inverse_below(int64_t d) {
+    const double x = 1.0 / (double)d;
+    uint64_t bits;
+    std::memcpy(&bits, &x, 8);
+    --bits;
+    double out;
+    std::memcpy(&out, &bits, 8);
+    return out;
+}
+
+// Rounded to the nearest float, and to the next one below where that is above.
+static float float_below(double x) {
+    const float f = (float)x;
+    uint32_t bits;
+    std::memcpy(&bits, &f, 4);
+    bits -= (double)f > x ? 1u : 0u;
+    float out;
+    std::memcpy(&out, &bits, 4);
+    return out;
+}
+
+template <typename T, typename Entry>
+static void fill_inverses(int32_t k, const int64_t *speeds, const int64_t *bandwidth, T *out, Entry entry) {
     const size_t kk = (size_t)k * k;
-    out.assign(table_entries(k), 0.0);
     for (size_t i = 0; i < (size_t)k; ++i) {
         for (size_t j = 0; j < (size_t)k; ++j)
-            if (i != j) out[i * k + j] = out[kk + j * k + i] = entry(bandwidth[i * k + j]);
+            out[i * k + j] = out[kk + j * k + i] = i == j ? T(0) : entry(bandwidth[i * k + j]);
         out[2 * kk + i] = entry(speeds[i]);
     }
 }
 
-void build_float_table(const std::vector<double> &inverse, float *out) {
-    for (size_t i = 0; i < inverse.size(); ++i) {
-        const double x = inverse[i] * kFloatUnit;
-        const float f = (float)x;
-        out[i] = (double)f > x ? std::nextafterf(f, 0.0f) : f;
-    }
+void build_inverse_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, double *out) {
+    fill_inverses(k, speeds, bandwidth, out, inverse_below);
+}
+
+void build_float_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, float *out) {
+    fill_inverses(k, speeds, bandwidth, out, [](int64_t d) { return float_below(inverse_below(d) * kFloatUnit); });
 }
 
 }  // namespace cpeval

@@ -240,11 +240,11 @@ int build_cost_tables(int32_t k, const int64_t *speeds, const int64_t *bandwidth
 bool round_fits(int32_t k, const int64_t *speeds, const int64_t *bandwidth, int64_t max_c, int64_t max_t);
 void build_round_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<Magic> &out);
 
-// 1 / divisor as doubles rounded down, 0 for a free transfer; same layout.  For kernels that divide by one multiply-add rounded
-// up (inverse_div).
-void build_inverse_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<double> &out);
-// The same as floats rounded down, in units of kFloatUnit: for dividends below kFloatMost.
-void build_float_table(const std::vector<double> &inverse, float *out);
+// Numbers just below 1 / divisor, 0 for a free transfer; same layout.  For kernels that divide by one multiply-add rounded up
+// (inverse_div), exact for every dividend a below 2^32: a / divisor less a times the entry is below 1 / divisor.
+void build_inverse_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, double *out);
+// The same as floats, in units of kFloatUnit: for dividends below kFloatMost.
+void build_float_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, float *out);
 constexpr float kFloatUnit = 0.015625f;      // 2^-6
 constexpr int64_t kFloatMost = 1 << 23;
 

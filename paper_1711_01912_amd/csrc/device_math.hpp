@@ -26,9 +26,9 @@ __device__ __forceinline__ uint32_t magic_div(uint32_t a, uint32_t entry) {
     return (uint32_t)(((uint64_t)nn * (entry | 0xffu) + nn) >> 32);
 }
 
-// ceil(a/d) as one multiply-add rounded up: the tables hold 1/d rounded down (build_inverse_table), so that a times it lies above
-// the whole number below a/d and not above the one at or above it; adding `base` makes the rounding one to whole numbers, which
-// end up in the low bits.  Exact while a times the inverse's relative error is below 1: doubles for every 32-bit a, floats for
+// ceil(a/d) as one multiply-add rounded up: the tables hold a number just below 1/d (build_inverse_table), so that a times it
+// lies above the whole number below a/d and not above the one at or above it; adding `base` makes the rounding one to whole
+// numbers, which end up in the low bits.  Exact while a times the inverse's relative error is below 1: doubles for every 32-bit a, floats for
 // a < 2^23 (kFloatMost), whatever the divisor.  An inverse of 0 (a free transfer) yields 0.  One instruction of four cycles where
 // the multiply-shift forms take three or more, one of them a 64-bit product at a quarter of that rate.
 // `base` comes from round_up, which sets the wavefront's rounding: whatever uses it comes after.  (Set behind the compiler's

@@ -1,5 +1,8 @@
 // Host-only driver of the launch rules and tables that the GPU entry points build on the host.
 // argv[1] names the check; exit status 0 = it holds, 1 = it does not (with a line that says where).
+#include <cfenv>
+#include <cmath>
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -104,6 +107,66 @@ static int rounded() {
                 if ((int64_t)got != want) return std::printf("%lld / %lld: %u\n", (long long)a, (long long)d, got), 1;
             }
         }
+    }
+    return 0;
+}
+
+// Quotients by the tables of inverses, as the kernels take them: one multiply-add rounded up to whole numbers (or to units of
+// 2^-6, for floats, which 2^17 makes the last bit of).
+static uint32_t by_double(uint32_t a, double inverse) {
+    volatile double x = (double)a, y = inverse, base = 4503599627370496.0;
+    volatile double sum = std::fma(x, y, base);
+    const double got = sum;
+    uint64_t bits;
+    std::memcpy(&bits, &got, 8);
+    return (uint32_t)bits;
+}
+static uint32_t by_float(uint32_t a, float inverse) {
+    volatile float x = (float)a, y = inverse, base = kFloatUnit * 8388608.0f;
+    volatile float sum = std::fmaf(x, y, base);
+    const float got = sum;
+    uint32_t bits;
+    std::memcpy(&bits, &got, 4);
+    return bits & 0x7fffffu;
+}
+
+static int inverses() {
+    std::vector<int64_t> divisors;
+    for (int64_t d = 1; d <= 1200; ++d) divisors.push_back(d);
+    for (int bit = 10; bit < 63; ++bit)
+        for (int64_t off : {-1, 0, 1}) divisors.push_back(((int64_t)1 << bit) + off);
+    for (int64_t d : std::vector<int64_t>{3000017, 8388593, 8388607, 12345678, 2147483647, 4294967295, INT64_MAX}) divisors.push_back(d);
+    std::vector<int64_t> dividends;
+    const int32_t k = 2;
+    std::vector<double> wide(table_entries(k));
+    std::vector<float> narrow(table_entries(k));
+    for (size_t at = 0; at < divisors.size(); ++at) {
+        const int64_t d = divisors[at], e = divisors[(at * 7 + 3) % divisors.size()];
+        const int64_t speeds[2] = {d, e}, bw[4] = {5, d, e, 5};
+        build_inverse_table(k, speeds, bw, wide.data());
+        build_float_table(k, speeds, bw, narrow.data());
+        // b sweep (own, neighbour), t sweep transposed, vertices
+        const int64_t of[10] = {0, d, e, 0, 0, e, d, 0, d, e};
+        dividends = {0, 1, 2, kFloatMost - 1, kFloatMost - 2, 4294967295ll, 4294967294ll, 2147483648ll, 65535, 65536};
+        for (int64_t x : {d, e})
+            for (int64_t times : std::vector<int64_t>{1, 2, 3, 1000, kFloatMost / x, 4294967295 / x})
+                for (int64_t off : {-1, 0, 1})
+                    if (times <= 4294967296ll / x) dividends.push_back(x * times + off);
+        std::fesetround(FE_UPWARD);
+        int64_t wrong = -1;
+        size_t entry = 0;
+        for (size_t i = 0; i < 10 && wrong < 0; ++i)
+            for (int64_t a : dividends) {
+                if (a < 0 || a >= (int64_t)1 << 32) continue;
+                const uint32_t want = of[i] ? (uint32_t)(a / of[i] + (a % of[i] != 0)) : 0;
+                if (by_double((uint32_t)a, wide[i]) != want || (a < kFloatMost && by_float((uint32_t)a, narrow[i]) != want)) {
+                    wrong = a;
+                    entry = i;
+                    break;
+                }
+            }
+        std::fesetround(FE_TONEAREST);
+        if (wrong >= 0) return std::printf("%lld / %lld, entry %zu\n", (long long)wrong, (long long)of[entry], entry), 1;
     }
     return 0;
 }
@@ -213,6 +276,7 @@ int main(int argc, char **argv) {
     if (argc > 3 && !std::strcmp(argv[1], "paths")) return paths(argv[2], argv[3]);
     if (!std::strcmp(argv[1], "prepare")) return prepare();
     if (!std::strcmp(argv[1], "rounded")) return rounded();
+    if (!std::strcmp(argv[1], "inverses")) return inverses();
     if (!std::strcmp(argv[1], "column")) return column();
     if (!std::strcmp(argv[1], "left-over")) return left_over();
     if (!std::strcmp(argv[1], "bucket-sizes")) return bucket_sizes();

@@ -43,6 +43,10 @@ def test_rounded_cost_tables_are_exact_and_built_only_on_request(harness):
     _holds(harness, "rounded")
 
 
+def test_quotients_by_tables_of_inverses_are_exact(harness):
+    _holds(harness, "inverses")
+
+
 def test_left_over_buckets_are_shared_out_over_the_gpu(harness):
     _holds(harness, "left-over")
 
