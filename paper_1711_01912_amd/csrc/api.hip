@@ -354,26 +354,34 @@ bool chain_cost16(const Packed &p, int32_t k, const int64_t *speeds, const int64
     }
     return p.info.max_c / slowest + 1 + (k > 1 ? p.info.max_t / narrowest + 1 : 0) < 1 << 16;
 }
-// Fitted to 512 calls (260 to 2,000 levels of 8 to 900 vertices, 1 to 64 partitions): a tick 0.1 us and 0.016 a wavefront, 0.05
-// more with 64-bit words; 8 to 15 us for a million lanes of ticks and partitions (1.6 times that with 32 bits a cost), the
-// wider the tick and the more values there are, which stop fitting the caches at some millions of either sweep; rows per
-// vertex, whose lines come together from as many workgroups as there are partitions, up to 45 us for a million
-// values of the first sixteen, and 25 for what is past seven million.  Half of them are within 4 % of it, nine tenths within 12 %.
-// A tenth on top where it has been wrong by as much, on wide ticks and many values: with 8 us a million for all, 1,000
-// levels of 500 vertices and 64 partitions took 1,589 us under this plan and 851 under the resident-window plan.
+// Fitted to 6,900 calls (260 to 2,000 levels of 5 to 900 vertices, 1 to 64 partitions, one sweep or both).
+//   ticks      0.1 us and 0.016 a wavefront, 0.05 more with 64-bit words
+//   costs      8 to 15 us for a million lanes of ticks, sweeps and partitions (1.6 times that with 32 bits a cost): the wider the
+//              tick and the more vertices times partitions there are, some millions of which stop fitting the caches
+//   rows per vertex   up to 45 us for a million values of the first sixteen partitions, whose lines come together from as many
+//              workgroups, and 25, or 70 in graphs of 400,000 vertices, for each million past seven
+//   scattered  vertex numbers in no relation to the levels: ids and outputs then lie in lines of their own, 0.055 us a tick and
+//              wavefront past two, and 38 us, or up to 138 on large graphs, for a million vertices and partitions
+// Half of the calls are within 6 % of it, nine tenths within 20 %; up to 15 % on top on ticks of 256 lanes and more, where it is off
+// by most.  With 8 us a million for all, the plan was up to 3.3 times as slow as the one it stood in for: 800 levels of 600
+// vertices in no order, 64 partitions 4,090 us against the resident-window plan's 1,220, 1,000 of 500 in order 1,589 against 851.
+// With this, 4 of the 6,900 are more than 3 % slower, by 1.17 times at most.
 double chain_us(const Packed &p, int32_t batch, int sweeps, bool cost16, bool by_partition, int32_t rounds) {
     const double lanes = (double)p.chain_width * ((double)p.chain_b.ticks + p.chain_t.ticks) / 2 * sweeps * batch * 1e-6;
-    const double values = (double)p.n * batch * sweeps / 2 * 1e-6;
-    const double tick = 0.1 + 0.016 * (p.chain_width / kWave) + (p.info.min_tick_bytes == 8 ? 0.05 : 0.0);
-    const bool wide = p.chain_width >= 512;
-    const double each = wide                   ? 10.0 + 5.0 * std::clamp((values - 4.0) / 4.0, 0.0, 1.0)
-                        : p.chain_width <= 128 ? 8.0
-                                               : 9.0 + 2.0 * std::min(1.0, values / 10.0);
-    double us = rounds * (18.0 + std::max(p.chain_b.ticks, p.chain_t.ticks) * tick) + lanes * each * (cost16 ? 1.0 : 1.6);
+    const double values = (double)p.n * batch * 1e-6, waves = p.chain_width / kWave;
+    const double ticks = std::max(p.chain_b.ticks, p.chain_t.ticks);
+    auto ramp = [](double x, double from, double to) { return std::clamp((x - from) / (to - from), 0.0, 1.0); };
+    const double each = waves >= 8   ? 10.0 + 5.0 * ramp(values, 4.0, 8.0)
+                        : waves <= 2 ? 8.0
+                                     : 9.0 + 2.0 * ramp(values, 0.0, 10.0);
+    double tick = 0.1 + 0.016 * waves + (p.info.min_tick_bytes == 8 ? 0.05 : 0.0);
+    tick += p.scattered * 0.055 * std::max(0.0, waves - 2.0);
+    double us = rounds * (18.0 + ticks * tick) + lanes * each * (cost16 ? 1.0 : 1.6);
     if (!by_partition)
-        us += (wide ? 45.0 : p.chain_width <= 192 ? 5.0 : 20.0) * values * std::min(1.0, 16.0 / batch) +
-              25.0 * std::max(0.0, values - 7.0);
-    return wide && values > 8.0 ? 1.1 * us : us;
+        us += sweeps * 0.5 * ((waves >= 8 ? 45.0 : waves <= 3 ? 5.0 : 20.0) * values * std::min(1.0, 16.0 / batch) +
+                              (25.0 + 45.0 * ramp(p.n, 200e3, 400e3)) * std::max(0.0, values - 7.0));
+    us += p.scattered * sweeps * 0.5 * values * (38.0 + 100.0 * ramp(values, 3.0, 9.0) * ramp(p.n, 0.0, 400e3));
+    return waves >= 4 ? us * (1.0 + 0.15 * ramp(values, 0.0, 8.0)) : us;
 }
 
 // A workspace has room for at most these bytes of costs (64 partitions of 211,000 vertices with 16 bits each, 11 of a million with

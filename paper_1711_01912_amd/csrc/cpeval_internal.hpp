@@ -186,6 +186,7 @@ struct Packed {
     ChainDir chain_b, chain_t;
     int32_t max_width = 0;
     int32_t hops = 0;           // L times the mean of 1 / (levels an edge climbs)
+    double scattered = 0;       // share of vertices that are 64 numbers or more from the one before them in level order
     int32_t reach = 0;          // every edge leads to a later vertex, this many further on at most; else 0
     std::vector<uint8_t> blob;  // host image of the device blob
 };

@@ -884,6 +884,9 @@ int pack_graph(int32_t n, int64_t m, int32_t L,
         per_level += 1.0 / climbs;
     }
     if (!along) out.reach = 0;
+    int64_t apart = 0;
+    for (int32_t i = 1; i < n; ++i) apart += std::abs((int64_t)level_vtx[i] - level_vtx[i - 1]) >= 64;
+    out.scattered = (double)apart / n;
     out.hops = m > 0 ? (int32_t)(L * (per_level / (double)m)) : 0;
 
     int64_t max_c = 0, max_t = 0;

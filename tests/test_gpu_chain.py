@@ -97,6 +97,14 @@ def test_not_where_other_plans_are_faster(gpu, oracle):
     """Wide levels: 300 of 500 vertices and 48 partitions took 330 us in the chain sweep, 268 in the resident-window plan."""
     _check(gpu, oracle, _graph(12, [500] * 300, 5, 6, 48, 16), 1, chain=False)
     _check(gpu, oracle, _graph(12, [500] * 300, 5, 6, 8, 16), 1)
+    # and vertex numbers in no relation to the levels: 300 of 400 and 64 partitions, one sweep 608 us, 280 in that plan
+    for width, P, chain in ((400, 64, False), (40, 2, True)):
+        w = _graph(13, [width] * 300, 7, 4, P, 10)
+        name = np.random.default_rng(1).permutation(w.n)
+        src, c, level = np.repeat(np.arange(w.n), np.diff(w.succ_ptr)), np.empty(w.n, np.int64), np.empty(w.n, np.int64)
+        c[name], level[name] = w.c, w.level
+        w = T._custom("scattered", w.n, name[src], name[w.succ_idx], w.succ_t, c, w.speeds, w.bandwidth, w.assignments, level)
+        _check(gpu, oracle, w, 1, chain=chain)
 
 
 @pytest.mark.parametrize("room,rounds", [(1, 7), (2, 4), (3, 3), (4, 2), (6, 2), (7, 1)])
