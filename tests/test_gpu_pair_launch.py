@@ -4,8 +4,8 @@ every output, element by element, bit-exact; the stage profile shows that the pa
 import numpy as np
 import pytest
 
-from workloads import make_workload
-from test_gpu_parity import _oracle, gpu  # noqa: F401
+from workloads import make_workload, random_layered_dag
+from test_gpu_parity import _custom, _oracle, gpu  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -81,4 +81,23 @@ def test_pair_launch_reports_a_bad_device_id(gpu):
     bad[3, w.n // 2] = w.k
     with pytest.raises(ValueError):
         gpu.cp_eval(g, torch.from_numpy(bad).to("cuda:0"), w.speeds, w.bandwidth, plan=WINDOW, out_layout=1)
+    g.close()
+
+
+@pytest.mark.parametrize("top", [65_535, 65_536])            # entries of 4 bytes with 16-bit volumes, and of 8
+@pytest.mark.parametrize("k", [1, 2, 16, 31, 64])
+def test_pair_launch_volumes_and_devices(gpu, oracle, top, k):
+    rng = np.random.default_rng([top, k])
+    n, level, src, dst = random_layered_dag(rng, [170] * 60, 1, 4, 4)
+    t = rng.integers(0, top + 1, len(src))
+    t[0] = top
+    w = _custom("pair", n, src, dst, t, rng.integers(0, 500, n), rng.integers(1, 9, k), rng.integers(1, 200, (k, k)),
+                rng.integers(0, k, (9, n), dtype=np.uint8), level)
+    ref = _oracle(oracle, w)
+    g = gpu.CpGraph.from_workload(w, device="cuda:0")
+    out, launches = _eval(gpu, g, w, w.assignments, 0, ("cp", "b", "tl"))
+    assert launches == (1, 0), launches
+    assert np.array_equal(out["cp"].cpu().numpy(), ref["cp"])
+    assert np.array_equal(out["b"].cpu().numpy().astype(np.int64), ref["b"])
+    assert np.array_equal(out["tl"].cpu().numpy().astype(np.int64), ref["tl"])
     g.close()

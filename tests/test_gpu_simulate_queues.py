@@ -28,7 +28,7 @@ def _stars(seed, stars, leaves, k, P, t_hi=100):
 
 
 @pytest.mark.parametrize("leaves", [1, 2, 3, 4, 5, 8, 9, 31, 33])       # 3: the most a record holds; 32: a wide row
-@pytest.mark.parametrize("k,P", [(1, 3), (2, 700), (33, 3)])            # state all in LDS, shared by many, few vertices a device
+@pytest.mark.parametrize("k,P", [(1, 8), (2, 700), (33, 9), (2, 7)])    # state all in LDS, shared by many, few vertices a device; no records
 def test_rows_around_what_a_record_holds(gpu, oracle, leaves, k, P):
     S._check(gpu, oracle, _stars(leaves, leaves + 1, leaves, k, P), layouts=(0, 1) if P < 10 else (0,))
 
@@ -40,7 +40,7 @@ def test_queues_around_what_registers_hold(gpu, oracle, stars, k):
 
 
 def test_64_bit_weights_have_no_records(gpu, oracle):
-    S._check(gpu, oracle, _stars(7, 20, 9, 4, 5, t_hi=2 ** 40), layouts=(0, 1))
+    S._check(gpu, oracle, _stars(7, 20, 9, 4, 12, t_hi=2 ** 40), layouts=(0, 1))
 
 
 def test_priorities_out_of_range_are_reported_from_registers_and_memory(gpu, oracle):

@@ -45,7 +45,22 @@ def _deep(seed):
                    np.zeros((1, n), dtype=np.uint8))
 
 
-@pytest.mark.parametrize("case", ["tiny", "mlp", "inception", "hubs", "sparse", "deep0", "deep1", "wide-weights"])
+def _joined():
+    """Deep, with rows that the chain sweep puts together from rows of 64 edges, and those from others again."""
+    rng = np.random.default_rng(9600)
+    widths = np.full(300, 12)
+    widths[[5, 60, 200]] = 64, 200, 5000
+    n, level, src, dst = random_layered_dag(rng, widths, 1, 3, 2)
+    first = np.concatenate([[0], np.cumsum(widths)])
+    for at, degree in ((4, 64), (59, 65), (199, 4097), (199, 5000)):
+        src = np.concatenate([src, np.full(degree, first[at] + (degree == 5000))])
+        dst = np.concatenate([dst, first[at + 1] + np.arange(degree) % widths[at + 1]])
+    order = np.argsort(src, kind="stable")
+    csr = build_csr(n, src[order], dst[order], rng.integers(0, 3000, size=len(src)), level)
+    return _finish("joined", csr, rng.integers(1, 400, size=n), 2, [1, 2], [[1, 3], [3, 1]], np.zeros((1, n), dtype=np.uint8))
+
+
+@pytest.mark.parametrize("case", ["tiny", "mlp", "inception", "hubs", "sparse", "deep0", "deep1", "joined", "wide-weights"])
 def test_packer_is_clean_under_sanitizers(harness, tmp_path, case):
     if case == "hubs":
         w = make_workload("comm_heavy", P=1, levels=5, width=600, hub_degree=300)
@@ -53,6 +68,8 @@ def test_packer_is_clean_under_sanitizers(harness, tmp_path, case):
         w = make_workload("large_sparse", P=1, levels=150, width=200)
     elif case.startswith("deep"):
         w = _deep(int(case[4:]))
+    elif case == "joined":
+        w = _joined()
     elif case == "wide-weights":
         w = make_workload("tiny", P=1)
         w.c = w.c * 2**36
