@@ -318,7 +318,7 @@ bool choose_lanes(const Packed &p, const CostTables &tabs, int32_t k, const int6
                   LaneCfg &out, double *us_out) {
     if (!p.have_lanes || k > kMagicMaxK) return false;
     const int word = p.lane_word == 4 && tabs.magic_ok ? 4 : 8;
-    if (word == 8 && !round_fits(k, speeds, bandwidth, p.info.max_c, p.info.max_t)) return false;
+    if (word == 8 && !wide_words_fit(k, speeds, bandwidth, p.info.max_c, p.info.max_t)) return false;
     // the outputs of a group are addressed with 32-bit offsets
     const uint64_t span = (uint64_t)p.n * (by_partition ? 32 : (uint64_t)batch) * (uint64_t)tick_bytes;
     if (with_out && span >= (1ull << 32)) return false;
@@ -418,7 +418,7 @@ bool choose_whole(const Packed &p, const CostTables &tabs, int32_t k, const int6
                   int32_t batch, bool mask, bool by_partition, int sweeps, size_t lds_limit, WholeCfg &out, double *us_out) {
     if (!p.have_whole || k > kMagicMaxK) return false;
     const int word = p.lane_word == 4 && tabs.magic_ok ? 4 : 8;
-    if (word == 8 && !round_fits(k, speeds, bandwidth, p.info.max_c, p.info.max_t)) return false;
+    if (word == 8 && !wide_words_fit(k, speeds, bandwidth, p.info.max_c, p.info.max_t)) return false;
     bool found = false;
     for (int groups : {4, 8}) {
         if (groups == 4 && mask && !by_partition) continue;        // (a workgroup writes whole bytes of a vertex's mask)

@@ -86,7 +86,7 @@ int build_cost_tables(int32_t k, const int64_t *speeds, const int64_t *bandwidth
     return CP_OK;
 }
 
-bool round_fits(int32_t k, const int64_t *speeds, const int64_t *bandwidth, int64_t max_c, int64_t max_t) {
+bool wide_words_fit(int32_t k, const int64_t *speeds, const int64_t *bandwidth, int64_t max_c, int64_t max_t) {
     auto fits = [](int64_t d, int64_t amax) { return d < (int64_t)1 << 32 && (uint64_t)amax + (uint64_t)d - 1 < (1ull << 32); };
     for (int i = 0; i < k; ++i) {
         if (!fits(speeds[i], max_c)) return false;
@@ -94,21 +94,6 @@ bool round_fits(int32_t k, const int64_t *speeds, const int64_t *bandwidth, int6
             if (i != j && !fits(bandwidth[(size_t)i * k + j], max_t)) return false;
     }
     return true;
-}
-
-// floor(N * floor(2^32/d) / 2^32) is the quotient or one less, since N * (2^32/d - floor(2^32/d)) < 2^32; the
-// remainder tells.  2^32/1 does not fit: 2^32 - 1 is one less than it, and the same argument holds (N * 1 < 2^32).
-void build_round_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<Magic> &out) {
-    auto entry = [](int64_t d) {
-        return Magic{(uint32_t)std::min<uint64_t>((1ull << 32) / (uint64_t)d, 0xffffffffull), (uint32_t)(d - 1)};
-    };
-    const size_t kk = (size_t)k * k;
-    out.assign(table_entries(k), Magic{0, 0xffffffffu});
-    for (size_t i = 0; i < (size_t)k; ++i) {
-        for (size_t j = 0; j < (size_t)k; ++j)
-            if (i != j) out[i * k + j] = out[kk + j * k + i] = entry(bandwidth[i * k + j]);
-        out[2 * kk + i] = entry(speeds[i]);
-    }
 }
 
 // The next number below 1.0 / d, which is at most half a unit above 1 / d, is a unit and a half below it at most, and no branch

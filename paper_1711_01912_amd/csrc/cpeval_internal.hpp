@@ -234,12 +234,10 @@ struct CostTables {
 int build_cost_tables(int32_t k, const int64_t *speeds, const int64_t *bandwidth,
                       bool narrow, int64_t max_c, int64_t max_t, CostTables &out);
 
-// The rounded form, exact for every 32-bit N = a + dm1 (no condition on the product):
-//   q = (N * mul) >> 32, one more if N - q * (dm1 + 1) > dm1      with mul = floor(2^32/d), dm1 = d - 1
-// A free transfer is {0, 2^32 - 1}, which yields 0.  Same layout as `magic`.  No kernel reads it any more (inverse_div is
-// shorter), a host test does; the condition stays the one under which 64-bit ring words are chosen.
-bool round_fits(int32_t k, const int64_t *speeds, const int64_t *bandwidth, int64_t max_c, int64_t max_t);
-void build_round_table(int32_t k, const int64_t *speeds, const int64_t *bandwidth, std::vector<Magic> &out);
+// Whether the lane-window and whole-graph sweeps take a call with 64-bit ring words: every divisor, and every volume and divisor
+// together, below 2^32.  (Their divisions are exact without that; it keeps the calls that they take, and those that
+// CP_PLAN_LANE_WINDOW refuses, as they were when it was needed.)
+bool wide_words_fit(int32_t k, const int64_t *speeds, const int64_t *bandwidth, int64_t max_c, int64_t max_t);
 
 // Numbers just below 1 / divisor, 0 for a free transfer; same layout.  For kernels that divide by one multiply-add rounded up
 // (inverse_div), exact for every dividend a below 2^32: a / divisor less a times the entry is below 1 / divisor.

@@ -68,45 +68,24 @@ static int column() {
     return 0;
 }
 
-// A call's cost tables come without the rounded form; that one, built where it is asked for, divides exactly.
-template <typename Tables>
-static auto rounded_in(const Tables &t, int) -> decltype(t.round.size()) { return t.round.size(); }
-template <typename Tables>
-static size_t rounded_in(const Tables &, long) { return 0; }
-
-static int rounded() {
+// Where calls with 64-bit ring words end: at divisors, and volumes and divisors together, of 32 bits.
+static int wide_words() {
     const int32_t k = 3;
     const int64_t top = (int64_t)1 << 32;
     for (int64_t amax : {(int64_t)0, (int64_t)1, (int64_t)1000, top / 2, top - 1000}) {
-        const int64_t most = top - amax;                     // the largest divisor that fits
+        const int64_t most = std::min(top - 1, top - amax);              // the largest divisor that fits
         const int64_t speeds[3] = {1, std::min<int64_t>(3, most), std::max<int64_t>(1, most / 2)};
         const int64_t bw[9] = {7, 1, most, std::max<int64_t>(1, most - 1), 7, std::min<int64_t>(2, most),
                                std::max<int64_t>(1, most / 3), std::min<int64_t>(10, most), 7};
-        CostTables tabs;
-        if (build_cost_tables(k, speeds, bw, true, amax, amax, tabs) != CP_OK) return 1;
-        if (rounded_in(tabs, 0)) return std::printf("built where nothing reads it\n"), 1;
-        if (most < top) {
+        if (!wide_words_fit(k, speeds, bw, amax, amax)) return std::printf("refused at %lld\n", (long long)amax), 1;
+        for (int at : {1, 5, 7}) {
             int64_t over[9];
             std::copy(bw, bw + 9, over);
-            over[5] = most + 1;
-            if (round_fits(k, speeds, over, amax, amax)) return std::printf("a divisor too large fits\n"), 1;
+            over[at] = most + 1;
+            if (wide_words_fit(k, speeds, over, amax, amax)) return std::printf("a divisor too large fits\n"), 1;
         }
-        if (most >= top) continue;                           // 2^32 itself is no 32-bit divisor
-        if (!round_fits(k, speeds, bw, amax, amax)) return std::printf("refused at %lld\n", (long long)amax), 1;
-        std::vector<Magic> round;
-        build_round_table(k, speeds, bw, round);
-        for (size_t at = 0; at < round.size(); ++at) {
-            const int own = (int)(at % 9 / 3), nbr = (int)(at % 3);
-            const int64_t d = at >= 18 ? speeds[at - 18] : (own == nbr ? 0 : (at < 9 ? bw[own * 3 + nbr] : bw[nbr * 3 + own]));
-            for (int64_t a : {(int64_t)0, (int64_t)1, d - 1, d, d + 1, 2 * d + 1, amax / 2, amax - 1, amax}) {
-                if (a < 0 || a > amax) continue;
-                const uint32_t nn = (uint32_t)a + round[at].dm1;
-                const uint32_t q = (uint32_t)((uint64_t)nn * round[at].mul >> 32);
-                const uint32_t got = q + (nn - q * (round[at].dm1 + 1u) > round[at].dm1 ? 1u : 0u);
-                const int64_t want = d ? (a + d - 1) / d : 0;
-                if ((int64_t)got != want) return std::printf("%lld / %lld: %u\n", (long long)a, (long long)d, got), 1;
-            }
-        }
+        const int64_t fast[3] = {1, most + 1, 1};
+        if (wide_words_fit(k, fast, bw, amax, amax)) return std::printf("a speed too large fits\n"), 1;
     }
     return 0;
 }
@@ -275,7 +254,7 @@ int main(int argc, char **argv) {
     if (argc > 2 && !std::strcmp(argv[1], "room")) return room(argv[2]);
     if (argc > 3 && !std::strcmp(argv[1], "paths")) return paths(argv[2], argv[3]);
     if (!std::strcmp(argv[1], "prepare")) return prepare();
-    if (!std::strcmp(argv[1], "rounded")) return rounded();
+    if (!std::strcmp(argv[1], "wide words")) return wide_words();
     if (!std::strcmp(argv[1], "inverses")) return inverses();
     if (!std::strcmp(argv[1], "column")) return column();
     if (!std::strcmp(argv[1], "left-over")) return left_over();

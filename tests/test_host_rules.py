@@ -39,8 +39,8 @@ def test_wave_column_blocks_cover_the_rows_and_leave_long_ones_in_order(harness)
     _holds(harness, "column")
 
 
-def test_rounded_cost_tables_are_exact_and_built_only_on_request(harness):
-    _holds(harness, "rounded")
+def test_where_calls_with_64_bit_ring_words_end(harness):
+    _holds(harness, "wide words")
 
 
 def test_quotients_by_tables_of_inverses_are_exact(harness):
