@@ -79,10 +79,10 @@ __global__ void table_write_kernel(TableChunk chunk, uint64_t *dst, int32_t coun
 // What a call needs before its kernels: cleared CP and status, and its cost tables in device memory.  Up to
 // 64 devices (66 KB) the tables travel as kernel arguments: nothing is allocated, nothing waits, and calls
 // on different streams or threads do not meet, and at 11 devices or fewer one launch does it all.  Larger
-// tables go through the pinned staging ring above.
+// tables (`by_kernel` false) go through the pinned staging ring above.
 int prepare_call(const void *src, size_t entries, void *dst, int64_t *cp_out, int32_t batch, int32_t *status,
-                 hipStream_t st, bool by_kernel_only = false) {
-    if (!by_kernel_only && entries > table_words(kMagicMaxK)) {
+                 hipStream_t st, bool by_kernel) {
+    if (!by_kernel) {
         const int rc = launch_clear(cp_out, batch, status, st);
         return rc ? rc : stage_and_copy(src, entries * 8, dst, st);
     }
@@ -563,7 +563,7 @@ int critical_path(const cp_graph *g, int32_t batch, int32_t k, const uint8_t *as
     hipStream_t st = (hipStream_t)stream;
     uint8_t *d_tab = (uint8_t *)workspace;
     const void *tab_src = tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data();
-    rc = prepare_call(tab_src, table_entries(k), d_tab, nullptr, 1, status_out, st);
+    rc = prepare_call(tab_src, table_entries(k), d_tab, nullptr, 1, status_out, st, table_entries(k) <= table_words(kMagicMaxK));
     if (rc) return rc;
     SweepLaunch s;
     s.blob = (const uint8_t *)g->device_blob;
@@ -963,7 +963,14 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     const bool all_in_one = whole && whole_cfg.table_bytes <= (size_t)kWholeTableWords * 4 &&
                             (uint64_t)p.n * (uint64_t)batch <= kWholeCheckBytes && ((uintptr_t)assignments % 16) == 0;
     if (!all_in_one) {
-        rc = prepare_call(tab_img.data(), tab_img.size(), d_tab, cp_out, batch, status_out, st, tables_by_kernel);
+        // Only the half that the call's kernels read: a launch moves 448 words, and 50 devices have 5,050 8-byte entries and half as
+        // many words of 4-byte ones (17 launches for both; 1,000 vertices in 20 levels, 20 partitions 92 -> 53 us a call).  The
+        // resident-window and shared-window sweeps read both.
+        const bool small_only = (lanes || whole) && inverses == Inverses::kFloats;
+        const bool large_only = !small_only && (lanes || whole || chain || columnish);
+        const size_t first = small_only ? table_entries(k) : 0, last = large_only ? table_entries(k) : tab_img.size();
+        rc = prepare_call(tab_img.data() + first, last - first, d_tab + first * 8, cp_out, batch, status_out, st,
+                          tables_by_kernel || k <= kMagicMaxK);
         if (rc) return rc;
     }
     const uint8_t *pT = assignments;
@@ -1399,7 +1406,7 @@ int cp_simulate(const cp_graph *g, int32_t batch, int32_t k,
     hipStream_t st = (hipStream_t)stream;
     uint8_t *ws = (uint8_t *)workspace;
     const void *tab_src = tabs.magic_ok ? (const void *)tabs.magic.data() : (const void *)tabs.divisor.data();
-    rc = prepare_call(tab_src, table_entries(k), ws, nullptr, 1, status_out, st);
+    rc = prepare_call(tab_src, table_entries(k), ws, nullptr, 1, status_out, st, table_entries(k) <= table_words(kMagicMaxK));
     if (rc) return rc;
     SimulateLaunch s;
     s.blob = (const uint8_t *)g->device_blob;
