@@ -39,13 +39,6 @@ __device__ __forceinline__ double round_up(double) {
     asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 1" : "+v"(base));
     return base;
 }
-// A dividend out of one half of a 64-bit load, made a word of its own: the compiler would convert all 64 bits, five instructions
-// in place of one, as it did in the lane-window kernel (1,578 levels of 34 vertices, 118 partitions: 885 -> 809 us a call).
-// Not for others: it keeps conversions from being moved or folded (200,000 vertices in 20 levels with hubs: 2.88 -> 2.92 ms).
-__device__ __forceinline__ uint32_t word_of(uint32_t a) {
-    asm("" : "+v"(a));
-    return a;
-}
 __device__ __forceinline__ uint32_t inverse_div(uint32_t a, double inverse, double base) {
     return (uint32_t)(uint64_t)__double_as_longlong(__builtin_fma((double)a, inverse, base));
 }
@@ -55,6 +48,15 @@ __device__ __forceinline__ float round_up(float) {
     float base = kFloatUnit * 8388608.0f;
     asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 1" : "+v"(base));
     return base;
+}
+// A dividend out of one half of a 64-bit load, made a word of its own for a division by floats: the compiler would convert all 64
+// bits, five instructions in place of one, as it did in the lane-window kernel (1,578 levels of 34 vertices, 118 partitions: 885
+// -> 809 us a call).  Not for others, since it keeps conversions from being moved or folded: by doubles 467 levels of 8 vertices with
+// 64-bit words took 174 us with it, 148 without, and 200,000 vertices in 20 levels with hubs 2.92 and 2.88 ms.
+template <typename Tab>
+__device__ __forceinline__ uint32_t word_for(uint32_t a) {
+    if constexpr (sizeof(Tab) == sizeof(float)) asm("" : "+v"(a));
+    return a;
 }
 __device__ __forceinline__ uint32_t inverse_bits(uint32_t a, float inverse, float base) {
     return __float_as_uint(__builtin_fmaf((float)a, inverse, base));
@@ -108,12 +110,13 @@ __device__ __forceinline__ Word add_shifted(Word value, uint32_t x) {
 }
 template <typename Word>
 __device__ __forceinline__ Word add_quotient(Word value, uint32_t a, double inverse, double base) {
-    return add_shifted(value, inverse_div(word_of(a), inverse, base));
+    return add_shifted(value, inverse_div(a, inverse, base));
 }
 template <typename Word>
 __device__ __forceinline__ Word add_quotient(Word value, uint32_t a, float inverse, float base) {
     static_assert(kFloatUnit * 8388608.0f == 131072.0f && kLaneIdBits == 6, "0x48000000 << 6 leaves 32 bits");
-    return add_shifted(value, sizeof(Word) == 4 ? inverse_bits(word_of(a), inverse, base) : inverse_div(word_of(a), inverse, base));
+    a = word_for<float>(a);
+    return add_shifted(value, sizeof(Word) == 4 ? inverse_bits(a, inverse, base) : inverse_div(a, inverse, base));
 }
 
 }  // namespace cpeval

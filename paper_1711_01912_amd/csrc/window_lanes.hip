@@ -9,15 +9,17 @@
 // lanes of a partition group share the packet entry they read, so a narrow level fills the
 // lanes and the tick's chain is paid once per G partitions.  Both sweeps of a call run side by
 // side in one launch.  Whole calls, before -> now: 2,016 vertices in 195 levels, 1,024 partitions 300 ->
-// 105 us; 121,000 in 701 levels, 777 partitions, rows per vertex 2.84 -> 1.15 ms; 29,000 in 301 levels with
-// 64-bit ticks (a launch per level before), 320 partitions 3.65 -> 0.32 ms.  What bounds it: on narrow ticks
+// 105 us; 121,000 in 701 levels, 777 partitions, rows per vertex 2.84 -> 1.08 ms; 29,000 in 301 levels with
+// 64-bit ticks (a launch per level before), 320 partitions 3.65 -> 0.28 ms.  What bounds it: on narrow ticks
 // the chain of a tick (two LDS round trips, publication, barrier: 0.2 to 0.3 us; with far reads, 660 levels, 1.0 us with one
-// workgroup on a compute unit, 1.3, 1.7 and 2.4 with two, three and four, no part of the unit busy a third of the time), on wide ones the LDS pipe of a compute unit (121,000 vertices: 72 % busy, a third of it bank
-// conflicts; vector ALUs 62 %, 27 instructions per 64 relaxations with what loaders and stores add).
+// workgroup on a compute unit, 1.3, 1.7 and 2.3 with two, three and four; there vector ALUs and LDS pipe are busy 36 and 37 % of
+// the time and wavefronts wait 68 % of theirs), on wide ones the LDS pipe of a compute unit (121,000 vertices: 77 % busy, a
+// third of it bank conflicts; vector ALUs 60 %, 25 instructions per 64 relaxations with what loaders and stores add).
 // Divisions are one multiply-add (inverse_div): floats where no volume reaches 2^23, doubles above.  Against multiply-shift
 // constants, whose 64-bit product alone takes four times as long: 121,000 vertices in 701 levels, 777 partitions
-// 1,160 -> 1,140 us a call; 19,800 in 660, 4,096 partitions 1,693 -> 1,551; 29,000 in 301 with 64-bit words, 320
-// partitions 316 -> 282.
+// 1,155 -> 1,079 us a call; 19,800 in 660, 4,096 partitions 1,685 -> 1,524; 29,000 in 301 with 64-bit words, 320
+// partitions 315 -> 280; narrow ticks, which wait for their chain, are where they were (1,578 levels of 34 vertices, 118
+// partitions 800 -> 809).
 //
 // A ring word is value << 6 | device id, one LDS read per relaxation; x << 6 is added to it and the
 // maximum taken over whole words, whose upper bits are the maximum of the sums.  Words are 32 bits while
@@ -194,8 +196,8 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
             const uint32_t at_a = ra.x * sv + (uint32_t)ga * sq, at_b = rb.x * sv + (uint32_t)gb * sq;
             if constexpr (TSWEEP) {
                 const Tab ma = vtab[(uint32_t)xa & ID], mb = vtab[(uint32_t)xb & ID];
-                xa = (xa >> kLaneIdBits) - (Word)inverse_div(word_of(ra.y), ma, up);
-                xb = (xb >> kLaneIdBits) - (Word)inverse_div(word_of(rb.y), mb, up);
+                xa = (xa >> kLaneIdBits) - (Word)inverse_div(word_for<Tab>(ra.y), ma, up);
+                xb = (xb >> kLaneIdBits) - (Word)inverse_div(word_for<Tab>(rb.y), mb, up);
             } else {
                 xa >>= kLaneIdBits;
                 xb >>= kLaneIdBits;
