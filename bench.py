@@ -34,9 +34,9 @@ MEASURED_TRAFFIC = {
     "runs": [
         # (workload, P, plan, out_layout) -> HBM bytes per launch of the dominant kernel: FETCH_SIZE x 2.00 +
         # WRITE_SIZE x 1.00 (KiB per dispatch, scaled by what the same counters read for a 1 GiB copy and fill)
-        (("large_sparse", 256, 2, 1), (2 * 463719.3 + 2000005.2) * 1024),        # both sweeps in one launch
-        (("large_sparse", 1024, 4, 1), (2 * 602783.1 + 4000023.8) * 1024),       # b-level sweep
-        (("large_sparse", 16384, 4, 1), (2 * 9642509.7 + 64001015.8) * 1024),    # b-level sweep
+        (("large_sparse", 256, 2, 1), (2 * 453344.4 + 2000004.5) * 1024),        # both sweeps in one launch
+        (("large_sparse", 1024, 4, 1), (2 * 602783.1 + 4000024.1) * 1024),       # b-level sweep
+        (("large_sparse", 16384, 4, 1), (2 * 9642661.8 + 64000922.3) * 1024),    # b-level sweep
     ],
 }
 TRAFFIC_SOURCES = ("kernels.hip", "window_shared.hip", "window_lanes.hip", "graph.cpp", "api.hip", "launch.hpp", "cpeval_internal.hpp",

@@ -162,8 +162,10 @@ struct WholeDir {
     int32_t ticks = 0, units_a_tick = 0;
 };
 constexpr int kWholeAhead = 4;
-// Two groups of 4 partitions on a compute unit.  Larger graphs, which leave it to one, are slower than under the lane-window plan:
-// 3,600 vertices in 60 levels, 8 and 4,096 partitions 57 and 224 us against 45 and 168.
+// Both sweeps of 4 partitions take 40 bytes a vertex of 32-bit words, beside the tables: two such groups share a compute unit up
+// to some 2,030 vertices on 4 devices and 1,980 on 16 (of 64-bit words half that, where the model's time decides).  Graphs
+// that leave it to one are slower than under the lane-window plan: 3,600 vertices in 60 levels, 8 and 4,096 partitions 57 and
+// 224 us against 45 and 168.
 constexpr int32_t kWholeVertices = 2048;
 
 struct Packed {

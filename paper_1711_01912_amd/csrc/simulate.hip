@@ -237,10 +237,14 @@ struct SimArgs {
 
 // What a step reads of a vertex, 32 bytes: c, its out-edges' number, and up to kRecordEdges of them as (head, t), or the
 // number of the first one.  A lane's loads go to lines of their own, and the address unit and the L1 were busy two thirds
-// of the time: one line in place of four (c, row bounds, heads, t), and a round trip less where the edges are in it.  With
-// b asked for beside the ready time and three keys a queue in registers, 5,271 vertices of 1 to 3 out-edges on 50 devices,
-// PCT: 256 partitions 1.60 -> 1.33 ms, 1,024 1.78 -> 1.50, 4,096 3.97 -> 3.06, FIFO 3.39 -> 2.87; out-edges 1 to 7, most of them not
-// in the record, 7.62 -> 7.58.
+// of the time: one line in place of four (c, row bounds, heads, t), and a round trip less where the edges are in it.
+// 5,271 vertices on 50 devices, ms as it is, without the records, with one key of a queue in a register, and with b asked for
+// only where a vertex becomes available:
+//   out-edges 1 to 3, PCT,    256 partitions  1.38  1.47  1.49  1.42
+//                           1,024             1.53  1.63  1.64  1.58
+//                           4,096             3.10  3.36  3.67  3.33
+//                     FIFO, 4,096             2.90  3.17  3.06  2.90
+//   out-edges 1 to 7, PCT,  4,096             4.47  4.63  4.95  4.71   (four in seven have too many for the record)
 // The launch that writes them takes some 5 us; they stand where the open inputs would be in memory, so not beside those.
 constexpr int32_t kRecordEdges = 3, kRecordsFrom = 8;       // (8 words a vertex, one for each of 8 partitions)
 __global__ __launch_bounds__(256) void simulate_records_kernel(const int32_t *__restrict__ ptr,
