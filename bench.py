@@ -30,7 +30,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X, published
 # a figure belongs to one build of the kernels and one configuration, and is reported only
 # while the sources it was taken on are unchanged and the configuration matches.
 MEASURED_TRAFFIC = {
-    "sources_sha256": "9c8417de4e1cf9bf88bd31eb9dee584fd8c80587958851e3db50bbdf4b50227a",
+    "sources_sha256": "6833b61873d7ad1e8008a20f8fea8b9b175e6921802c47d50024cad657474da5",
     "runs": [
         # (workload, P, plan, out_layout) -> HBM bytes per launch of the dominant kernel: FETCH_SIZE x 2.00 +
         # WRITE_SIZE x 1.00 (KiB per dispatch, scaled by what the same counters read for a 1 GiB copy and fill)
