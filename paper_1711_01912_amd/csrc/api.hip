@@ -120,7 +120,9 @@ int static_scratch(void **out) {
     return CP_OK;
 }
 
-constexpr uint64_t kWholeCheckBytes = 64 * 1024;       // ids that one workgroup looks at
+// Ids that one workgroup looks at, and a lane of it: with 64 lanes 64 KB took 16 us (45 vertices, 1,434 partitions, tl alone 30
+// us a call, 20 before there was a whole-graph sweep), a launch to clear the status and write the tables takes 4.
+constexpr uint64_t kWholeCheckBytes = 64 * 1024, kWholeCheckLane = 256;
 
 constexpr size_t kWindowLdsLimit = kLdsBudget - 256;   // room for the kernel's static LDS
 constexpr size_t kSharedStaticLds = 512;               // static LDS of the shared-window and streamed kernels beyond that
@@ -961,7 +963,9 @@ static int eval_run(const cp_graph *g, int32_t batch, int32_t k,
     // A call of few ids on few devices needs no launch before the whole-graph sweep's: its tables go with that one, which looks
     // at all ids in its first workgroup, so that nothing has to be cleared.
     const bool all_in_one = whole && whole_cfg.table_bytes <= (size_t)kWholeTableWords * 4 &&
-                            (uint64_t)p.n * (uint64_t)batch <= kWholeCheckBytes && ((uintptr_t)assignments % 16) == 0;
+                            (uint64_t)p.n * (uint64_t)batch <=
+                                std::min(kWholeCheckBytes, kWholeCheckLane * (uint64_t)whole_cfg.threads) &&
+                            ((uintptr_t)assignments % 16) == 0;
     if (!all_in_one) {
         // Only the half that the call's kernels read: a launch moves 448 words, and 50 devices have 5,050 8-byte entries and half as
         // many words of 4-byte ones (17 launches for both; 1,000 vertices in 20 levels, 20 partitions 92 -> 53 us a call).  The

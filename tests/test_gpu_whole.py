@@ -66,6 +66,8 @@ CASES = {
     "most devices": dict(widths=[20] * 10, deg=3, span=3, P=5, k=64),
     "64 KB of ids": dict(widths=[16] * 16, deg=3, span=3, P=256, k=7),
     "more": dict(widths=[16] * 16, deg=3, span=3, P=257, k=7),
+    "64 lanes, 16 KB of ids": dict(widths=[4] * 8, deg=2, span=2, P=512, k=7),
+    "64 lanes, more": dict(widths=[4] * 8, deg=2, span=2, P=513, k=7),
     "several workgroups a unit": dict(widths=[16] * 12, deg=3, span=3, P=5000, k=7),
     "groups of four only": dict(widths=[34] * 60, deg=3, span=3, P=1024, k=60),
     "too many vertices": dict(widths=[1] * 2049, deg=1, span=1, P=8, k=2),
