@@ -30,7 +30,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X, published
 # a figure belongs to one build of the kernels and one configuration, and is reported only
 # while the sources it was taken on are unchanged and the configuration matches.
 MEASURED_TRAFFIC = {
-    "sources_sha256": "6833b61873d7ad1e8008a20f8fea8b9b175e6921802c47d50024cad657474da5",
+    "sources_sha256": "74b88539ecb6bd17aae01f293ad0d5c6c71eda0408fce8290e3274e9cf6c65eb",
     "runs": [
         # (workload, P, plan, out_layout) -> HBM bytes per launch of the dominant kernel: FETCH_SIZE x 2.00 +
         # WRITE_SIZE x 1.00 (KiB per dispatch, scaled by what the same counters read for a 1 GiB copy and fill)
