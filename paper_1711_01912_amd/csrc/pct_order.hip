@@ -675,13 +675,41 @@ __device__ __forceinline__ bool sort_by_bins(const uint32_t *__restrict__ keys_i
     return true;
 }
 
+// What the ranking needs of a bucket whose items the scatter dealt by LDS adds, 64 vertices an add in whatever order it takes its
+// lanes (a bin that is crowded after all, in a partition that nothing was found against).  They are neighbours here, in runs of
+// vertex numbers that differ in their low six bits only, and mostly in order, which is looked at; if not, the first thread of a
+// run puts it in order.  (Sorting by the vertex numbers' digits instead took three passes more, and spilled registers in all
+// buckets: 142,000 vertices in 53 levels, 4 devices, 8 partitions, whose last level's keys repeat, 86 us a call before there was
+// the scatter by adds, 146 and more with those passes, 88 with this.)
+template <int kThreads>
+__device__ __forceinline__ void order_runs(uint32_t *keys, int32_t *vals, int32_t items) {
+    bool apart = false;
+    for (int32_t t = (int32_t)threadIdx.x + 1; t < items; t += kThreads) apart |= vals[t - 1] > vals[t];
+    if (!__syncthreads_or(apart)) return;
+    for (int32_t t = threadIdx.x; t < items; t += kThreads) {
+        const int32_t run = vals[t] >> 6;
+        if (t > 0 && vals[t - 1] >> 6 == run) continue;
+        for (int32_t i = t + 1; i < items && vals[i] >> 6 == run; ++i) {
+            const int32_t v = vals[i];
+            const uint32_t k = keys[i];
+            int32_t at = i;
+            for (; at > t && vals[at - 1] > v; --at) {
+                vals[at] = vals[at - 1];
+                keys[at] = keys[at - 1];
+            }
+            vals[at] = v;
+            keys[at] = k;
+        }
+    }
+    __syncthreads();
+}
+
 // The buckets of the leading digit, by bins, `each` neighbours per workgroup.  left[i] = 1 for those that
 // pct_bucket_sort_kernel has to sort: of more than eight items per thread, of a partition whose keys the sample of
 // pct_bucket_check_kernel found in common bins, or with a crowded bin after all.
 constexpr int kBinRounds = 8;
 template <int kThreads>
-__global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_t *__restrict__ keys_in,
-                                                                   const int32_t *__restrict__ vals_in,
+__global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(uint32_t *keys_in, int32_t *vals_in,
                                                                    int32_t *__restrict__ vals_out, int32_t n, int32_t each,
                                                                    int32_t tiles, int bits, int val_bits,
                                                                    const uint32_t *__restrict__ starts, Gate gate,
@@ -699,7 +727,8 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
     if (lane <= each && d0 + lane < kBuckets) bound = starts[((int64_t)q * kBuckets + d0 + lane) * tiles];
     if (gate.closed()) return;
     left += (int64_t)q * kBuckets + d0;
-    if ((found[(int64_t)q * found_stride] & kCrowded) != 0) {
+    const int32_t what = found[(int64_t)q * found_stride];
+    if ((what & kCrowded) != 0) {
         const uint32_t next = __shfl_down(bound, 1);
         if ((int)threadIdx.x < each) left[threadIdx.x] = next != bound ? 1u : 0u;
         return;
@@ -712,6 +741,7 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
         if (!done && items <= kThreads * kBinRounds)
             done = sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits,
                                                                    val_bits, sorted, bins, wave_sum, key);
+        if (!done && what == 0) order_runs<kThreads>(keys_in + at, vals_in + at, items);
         if (threadIdx.x == 0) left[i] = done ? 0u : 1u;
     }
 }
@@ -723,12 +753,11 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_
 // WHOLE: the "bucket" is a whole partition (at most kBucketThreads * kRounds vertices), its keys
 // in vertex order and already in `key`, sorted on all `bits` key bits: short partitions need no pass over
 // HBM at all.
-// BY_VAL: items of equal keys do not stand in the order of their vertex numbers yet, whose digits (val_bits) are sorted first (a bin that is crowded after all, in a partition that nothing was found against).
 // slot: kBucketThreads * kRounds words; cnt: 256 per wavefront
-template <int kBucketThreads, int kRounds, bool WHOLE, bool BY_VAL>
+template <int kBucketThreads, int kRounds, bool WHOLE>
 __device__ __forceinline__ void sort_bucket(const uint32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
-                                            int32_t *__restrict__ vals_out, int32_t items, int bits, int val_bits,
-                                            uint32_t *slot, uint32_t (*cnt)[256], int tid, uint32_t (&key)[kRounds]) {
+                                            int32_t *__restrict__ vals_out, int32_t items, int bits, uint32_t *slot,
+                                            uint32_t (*cnt)[256], int tid, uint32_t (&key)[kRounds]) {
     constexpr int kWaves = kBucketThreads / 64, kRadix = 256;
     __shared__ uint32_t wave_sum[kRadix / 64];
     const int lane = tid & 63, wave = tid >> 6;
@@ -736,20 +765,17 @@ __device__ __forceinline__ void sort_bucket(const uint32_t *__restrict__ keys_in
     // [w * nr * 64, (w + 1) * nr * 64) of the bucket)
     const int nr = (items + kBucketThreads - 1) / kBucketThreads;
 
-    const uint32_t *first_words = BY_VAL ? (const uint32_t *)vals_in : keys_in;
-    const uint32_t *other_words = BY_VAL ? keys_in : (const uint32_t *)vals_in;
     uint32_t loc[kRounds];
     int32_t val[kRounds];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
         const int32_t t = wave * (nr * 64) + r * 64 + lane;
         const bool valid = r < nr && t < items;
-        if (!WHOLE) key[r] = valid ? first_words[t] : 0u;
-        val[r] = WHOLE ? t : (valid ? (int32_t)other_words[t] : 0);
+        if (!WHOLE) key[r] = valid ? keys_in[t] : 0u;
+        val[r] = WHOLE ? t : (valid ? vals_in[t] : 0);
     }
-    bool by_val = BY_VAL;                                 // key and val hold each other's words
-    for (int shift = 0; by_val || shift < bits; shift += 8) {
-        const bool last = !by_val && shift + 8 >= bits;
+    for (int shift = 0; shift < bits; shift += 8) {
+        const bool last = shift + 8 >= bits;
         for (int i = tid; i < kWaves * kRadix; i += kBucketThreads) (&cnt[0][0])[i] = 0;
         __syncthreads();
 #pragma unroll
@@ -821,16 +847,6 @@ __device__ __forceinline__ void sort_bucket(const uint32_t *__restrict__ keys_in
             }
             __syncthreads();
         }
-        if (BY_VAL && by_val && shift + 8 >= val_bits) {
-#pragma unroll
-            for (int r = 0; r < kRounds; ++r) {
-                const uint32_t x = key[r];
-                key[r] = (uint32_t)val[r];
-                val[r] = (int32_t)x;
-            }
-            by_val = false;
-            shift = -8;
-        }
     }
 }
 
@@ -867,7 +883,7 @@ __global__ __launch_bounds__(kThreads, kThreads == 1024 ? 4 : 6) void pct_whole_
             }
         }
     }
-    sort_bucket<kThreads, kRounds, true, false>(nullptr, nullptr, vals_out + at, n, bits, 0, slot, (uint32_t (*)[256])counters, tid,
+    sort_bucket<kThreads, kRounds, true>(nullptr, nullptr, vals_out + at, n, bits, slot, (uint32_t (*)[256])counters, tid,
                                          key);
 }
 
@@ -886,8 +902,7 @@ inline bool bins_and_ranking_in_one(int32_t P, int for_bins, int threads) {
     return P <= (threads == 512 ? 16 : for_bins > 128 ? 48 : 24);
 }
 template <int kThreads>
-__global__ __launch_bounds__(kThreads, 6) void pct_bucket_kernel(const uint32_t *__restrict__ keys_in,
-                                                              const int32_t *__restrict__ vals_in,
+__global__ __launch_bounds__(kThreads, 6) void pct_bucket_kernel(uint32_t *keys_in, int32_t *vals_in,
                                                               int32_t *__restrict__ vals_out, int32_t n, int32_t tiles, int bits,
                                                               int val_bits, const uint32_t *__restrict__ starts, Gate gate,
                                                               const int32_t *__restrict__ found, int32_t found_stride) {
@@ -908,12 +923,9 @@ __global__ __launch_bounds__(kThreads, 6) void pct_bucket_kernel(const uint32_t 
         sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, val_bits, slot,
                                                    slot + kThreads * kBinRounds, wave_sum, few))
         return;
-    if (what == 0)
-        sort_bucket<kThreads, kSortRounds, false, true>(keys_in + at, vals_in + at, vals_out + at, items, bits, val_bits, slot,
-                                                        counters, threadIdx.x, key);
-    else
-        sort_bucket<kThreads, kSortRounds, false, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, 0, slot,
-                                                         counters, threadIdx.x, key);
+    if (what == 0) order_runs<kThreads>(keys_in + at, vals_in + at, items);
+    sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters,
+                                              threadIdx.x, key);
 }
 
 // The buckets that pct_bucket_bins_kernel left, out of the `each` that a workgroup looks at (left_over_bucket).
@@ -923,14 +935,12 @@ template <int kThreads>
 __global__ __launch_bounds__(kThreads, 6) void pct_bucket_sort_kernel(const uint32_t *__restrict__ keys_in,
                                                                    const int32_t *__restrict__ vals_in,
                                                                    int32_t *__restrict__ vals_out, int32_t n, int32_t each,
-                                                                   int32_t tiles, int bits, int val_bits,
+                                                                   int32_t tiles, int bits,
                                                                    const uint32_t *__restrict__ starts, Gate gate,
-                                                                   const int32_t *__restrict__ found, int32_t found_stride,
                                                                    const uint32_t *__restrict__ left) {
     __shared__ uint32_t slot[kThreads * kSortRounds], counters[kThreads / 64][256];
     if (gate.closed()) return;
     const uint32_t q = blockIdx.x / (uint32_t)(kBuckets / each);
-    const bool by_val = found[(int64_t)q * found_stride] == 0;
     uint32_t lo = 0, hi = 0;
     if ((int)(threadIdx.x & 63) < each) {
         const uint32_t d = left_over_bucket<kBuckets>(blockIdx.x, threadIdx.x & 63, each);
@@ -951,12 +961,8 @@ __global__ __launch_bounds__(kThreads, 6) void pct_bucket_sort_kernel(const uint
         const int32_t items = (int32_t)((uint32_t)__builtin_amdgcn_readlane((int)hi, which) - first);
         const int64_t at = (int64_t)q * n + first;
         uint32_t key[kSortRounds];
-        if (by_val)
-            sort_bucket<kThreads, kSortRounds, false, true>(keys_in + at, vals_in + at, vals_out + at, items, bits, val_bits,
-                                                            slot, counters, tid, key);
-        else
-            sort_bucket<kThreads, kSortRounds, false, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, 0, slot,
-                                                             counters, tid, key);
+        sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters, tid,
+                                                  key);
         __syncthreads();
     }
 }
@@ -1128,8 +1134,9 @@ int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     if (rc) return rc;
     // (what the bins leave is noted in keys_a, which nothing reads any more on this way)
     uint32_t *left = (uint32_t *)s.keys_a;
-    const uint32_t *keys = (const uint32_t *)s.keys_b, *starts = s.counts;
-    const int32_t *vals = s.vals_tmp;
+    uint32_t *keys = (uint32_t *)s.keys_b;
+    const uint32_t *starts = s.counts;
+    int32_t *vals = s.vals_tmp;
     const int32_t all = s.P * kBuckets;
     const int val_bits = 32 - __builtin_clz((unsigned)s.n - 1);
     // (keys of 32 bits: shift is 13, 12 or 11 at most for up to 2^18, 2^19 or 2^20 vertices, less for larger workgroups)
@@ -1155,7 +1162,7 @@ int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     const int32_t each = left_over_each(all);
 #define CP_LEFT(T)                                                                                                    \
     hipLaunchKernelGGL(pct_bucket_sort_kernel<T>, dim3((unsigned)(all / each)), dim3(T), 0, st, keys, vals, s.order_out, \
-                       s.n, each, tiles, rem, val_bits, starts, fit, (const int32_t *)found, s.k + 1, (const uint32_t *)left)
+                       s.n, each, tiles, rem, starts, fit, (const uint32_t *)left)
     if (small) CP_LEFT(256);
     else CP_LEFT(512);
 #undef CP_LEFT

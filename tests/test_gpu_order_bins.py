@@ -108,3 +108,29 @@ def test_a_crowded_bin_among_spread_keys(gpu, oracle, n, P):
     assert np.array_equal(seg.cpu().numpy(), ref_seg)
     assert np.array_equal(order.cpu().numpy(), ref_order)
     g.close()
+
+
+@pytest.mark.parametrize("n,P", [(65_537, 3), (65_537, 65), (262_145, 5), (262_145, 49), (524_801, 5), (524_801, 49)])
+@pytest.mark.parametrize("values", [1, 2, 5])
+def test_neighbours_in_a_crowded_bin(gpu, oracle, n, P, values):
+    """The same with vertices next to each other, so that all of a wavefront's may be dealt to one bucket: a level of a device's
+    vertices with few different values, at the first vertex, at the last one and in between."""
+    import torch
+    k, top = 9, 3_000_000
+    rng = np.random.default_rng([n, P, values])
+    n, level, src, dst = random_layered_dag(rng, [n // 2, n - n // 2], 1, 1, 1)
+    a = rng.integers(0, k, (P, n), dtype=np.uint8)
+    b = rng.integers(0, top + 1, (P, n), dtype=np.int32)
+    for q in range(P):
+        at, size = [0, n - 300, 1000 + 61 * q, 777][q % 4], 300 if q % 4 < 3 else 150
+        a[q, at:at + size] = np.where(rng.random(size) < (1.0 if q % 2 else 0.7), q % k, a[q, at:at + size])
+        b[q, at:at + size] = top // 2 - rng.integers(0, values, size)
+    w = T._custom("neighbours", n, src, dst, np.ones(len(src), dtype=np.int64), np.ones(n, dtype=np.int64), [1] * k,
+                  np.ones((k, k), dtype=np.int64), a, level)
+    ref_order, ref_seg = oracle.pct_order(k, w.assignments, b.astype(np.int64), threads=8)
+    g = gpu.CpGraph.from_workload(w, device="cuda:0")
+    order, seg = gpu.cp_pct_order(g, torch.from_numpy(w.assignments).to("cuda:0"), k, torch.from_numpy(b).to("cuda:0"),
+                                  max_b=top, b_layout=1)
+    assert np.array_equal(seg.cpu().numpy(), ref_seg)
+    assert np.array_equal(order.cpu().numpy(), ref_order)
+    g.close()
