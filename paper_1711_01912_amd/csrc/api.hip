@@ -1420,7 +1420,7 @@ int cp_simulate(const cp_graph *g, int32_t batch, int32_t k,
     s.magic = tabs.magic_ok;
     s.narrow = p.narrow;
     s.pct = plan.pct;
-    s.n = p.n; s.P = batch; s.k = k;
+    s.n = p.n; s.m = p.m; s.P = batch; s.k = k;
     s.window = (uint32_t)window;
     s.max_in_degree = p.info.max_in_degree;
     // One partition per wavefront until the batch alone fills the GPU several times over (8,192

@@ -286,6 +286,7 @@ struct SimulateLaunch {
     size_t c_off = 0;
     bool magic = false, narrow = false, pct = false;
     int32_t n = 0, P = 0, k = 0, max_in_degree = 0;
+    int64_t m = 0;
     uint32_t window = 0;                // shortest execution time + shortest transfer time - 1
     int32_t groups = 1;                 // partitions per wavefront (at most 64 / k)
     const uint8_t *assign = nullptr;

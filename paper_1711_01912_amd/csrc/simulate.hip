@@ -245,6 +245,9 @@ struct SimArgs {
 //                           4,096             3.10  3.36  3.67  3.33
 //                     FIFO, 4,096             2.90  3.17  3.06  2.90
 //   out-edges 1 to 7, PCT,  4,096             4.47  4.63  4.95  4.71   (four in seven have too many for the record)
+// Not where the mean row is longer than a record holds: the record is then one more line to most steps.  Over 600 calls (100 to 25,000
+// vertices, 1 to 64 devices) records took 0.96 times as long as none at 2 to 3 edges a vertex, 1.00 at 3 to 5 and 1.03 at 5
+// to 9 (11,500 vertices of nine edges, one device, ten partitions, FIFO 70 ms a call, 61 before there were records).
 // The launch that writes them takes some 5 us; they stand where the open inputs would be in memory, so not beside those.
 constexpr int32_t kRecordEdges = 3, kRecordsFrom = 8;       // (8 words a vertex, one for each of 8 partitions)
 __global__ __launch_bounds__(256) void simulate_records_kernel(const int32_t *__restrict__ ptr,
@@ -689,7 +692,7 @@ int launch_simulate(const SimulateLaunch &s, void *stream) {
         else if (fits(owners)) keep = there < kNearFrom ? kOwnersAndInputs : kNearInboxToo;
     }
     // (the open inputs sit in LDS, and their array holds the records)
-    if (keep != kNothing && s.narrow && s.P >= kRecordsFrom) {
+    if (keep != kNothing && s.narrow && s.P >= kRecordsFrom && s.m <= (int64_t)kRecordEdges * s.n) {
         a.records = (const uint4 *)s.need;
         hipLaunchKernelGGL(simulate_records_kernel, dim3((unsigned)((s.n + 255) / 256)), dim3(256), 0, st, a.ptr, a.idx,
                            (const uint32_t *)a.wt, (const uint32_t *)a.c, s.n, (uint4 *)s.need);
