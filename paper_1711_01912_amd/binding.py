@@ -457,7 +457,9 @@ def cp_critical_path(graph: CpGraph, assignments, speeds, bandwidth, b, cp, *,
     lens = torch.empty(batch, dtype=torch.int32, device=dev)
     status = torch.empty(1, dtype=torch.int32, device=dev)
     if workspace is None:
-        workspace = torch.empty(workspace_bytes(graph, batch, k, assign_layout), dtype=torch.uint8, device=dev)
+        # (the tables and 64 bytes a vertex are all that a call uses)
+        need = -(-12 * k * (2 * k + 1) // 256) * 256 + 64 * graph._n
+        workspace = torch.empty(min(need, workspace_bytes(graph, batch, k, assign_layout)), dtype=torch.uint8, device=dev)
     tick = 4 if b.dtype == torch.int32 else 8
     rc = lib.cp_critical_path(graph._handle, batch, k, C.c_void_p(assignments.data_ptr()), int(assign_layout),
                               _np_ptr(s, C.c_int64), _np_ptr(bw, C.c_int64), C.c_void_p(b.data_ptr()),

@@ -2186,7 +2186,7 @@ int launch_critical_path(const SweepLaunch &s, const int32_t *sources, int32_t n
     const size_t lds = lds_tab ? ((size_t)s.k * s.k + s.k) * 8 : 0;
     // one wavefront where that many sources leave the others nothing to do
     const dim3 grid((unsigned)s.P), block((unsigned)(nsrc > 512 ? kPathThreads : 64));
-    if (records && s.magic && lds_tab && path_by_records(s.n, s.m, s.L, s.hops)) {
+    if (records && s.magic && lds_tab && path_by_records(s.n, s.m, s.L, s.hops) && records_for(s.n, s.m, s.P, s.hops)) {
         const dim3 words((unsigned)(((int64_t)s.n * kPathRecordWords + 255) / 256));
         hipLaunchKernelGGL(path_records_kernel, words, dim3(256), 0, st, a, s.n, records);
         const int32_t ring = path_ring(s.n, s.P, s.hops, s.reach);

@@ -249,6 +249,20 @@ static int paths(const std::string &dir, const std::string &wanted) {
     return got != wanted;
 }
 
+// Where a few partitions take records at all.
+static int few_records() {
+    const int32_t n = 121000, hops = 300;
+    if (!records_for(n, 3 * n, 1, hops) || records_for(n, 4 * n, 7, hops) || !records_for(n, 4 * n, 8, hops) ||
+        records_for(n, 5 * n, 31, hops) || !records_for(n, 5 * n, 32, hops))
+        return std::printf("records by edges\n"), 1;
+    if (!records_for(5999, 5 * 5999, 4, hops) || records_for(6000, 5 * 6000, 4, hops) || !records_for(11999, 6 * 11999, 31, hops) ||
+        records_for(12000, 6 * 12000, 31, hops))
+        return std::printf("records of few vertices\n"), 1;
+    if (records_for(n, 3 * n, 31, n / 700 - 1) || !records_for(n, 3 * n, 32, 64) || records_for(n, n / 2, 5, hops))
+        return std::printf("records by paths\n"), 1;
+    return 0;
+}
+
 int main(int argc, char **argv) {
     if (argc < 2) return 2;
     if (argc > 2 && !std::strcmp(argv[1], "room")) return room(argv[2]);
@@ -257,6 +271,7 @@ int main(int argc, char **argv) {
     if (!std::strcmp(argv[1], "wide words")) return wide_words();
     if (!std::strcmp(argv[1], "inverses")) return inverses();
     if (!std::strcmp(argv[1], "column")) return column();
+    if (!std::strcmp(argv[1], "few records")) return few_records();
     if (!std::strcmp(argv[1], "left-over")) return left_over();
     if (!std::strcmp(argv[1], "bucket-sizes")) return bucket_sizes();
     return 2;

@@ -47,6 +47,10 @@ def test_quotients_by_tables_of_inverses_are_exact(harness):
     _holds(harness, "inverses")
 
 
+def test_where_a_few_partitions_take_records(harness):
+    _holds(harness, "few records")
+
+
 def test_left_over_buckets_are_shared_out_over_the_gpu(harness):
     _holds(harness, "left-over")
 
