@@ -2189,9 +2189,9 @@ int launch_critical_path(const SweepLaunch &s, const int32_t *sources, int32_t n
     if (records && s.magic && lds_tab && path_by_records(s.n, s.m, s.L, s.hops) && records_for(s.n, s.m, s.P, s.hops)) {
         const dim3 words((unsigned)(((int64_t)s.n * kPathRecordWords + 255) / 256));
         hipLaunchKernelGGL(path_records_kernel, words, dim3(256), 0, st, a, s.n, records);
-        const int32_t ring = path_ring(s.n, s.P, s.hops, s.reach);
+        const int32_t ring = path_ring(s.n, s.m, s.P, s.hops, s.reach, lds);
         const size_t stream_lds = lds + (size_t)ring * 5;
-        if (ring && s.tick_bytes == 4 && s.a_stride_v == 1 && s.out_sv == 1 && stream_lds <= kPathLdsBytes) {
+        if (ring && s.tick_bytes == 4 && s.a_stride_v == 1 && s.out_sv == 1) {
             if (hipFuncSetAttribute((const void *)critical_path_stream_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)stream_lds) != hipSuccess)
                 return CP_ERR_HIP;

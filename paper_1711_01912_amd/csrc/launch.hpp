@@ -352,12 +352,19 @@ inline bool records_for(int32_t n, int64_t m, int32_t P, int32_t hops) {
 // 326 and 292; 18,000 in 300 levels, 64, 777 and 3,000 partitions 136 and 128, 138 and 107, 196 and 237; 240,000 in 1,000
 // levels, 200 partitions 684 and 469.  Not with rings of 16,384, one workgroup a compute unit (240,000 in 400 levels, 300
 // partitions 178 both), nor where every XCD's records are more than the rows (950,000 in 1,900 levels, 80 partitions 673
-// and 799).
+// and 799), nor where fewer than 32 partitions would not take records for the number of vertices or edges (406,000 vertices
+// in 1,127 levels, 404,800 edges, 123 partitions 199 and 338), nor where the ring and the tables leave the LDS of the
+// compute units, in granules of 1,280 bytes, no room for all partitions at once (64 devices, whose tables are 33 KB, 599
+// partitions 586 and 1,004).  Over 1,950 calls streamed took 0.90 times as long, none more than 1.09 times.
 constexpr size_t kPathLdsBytes = 64 * 1024;
-inline int32_t path_ring(int32_t n, int32_t P, int32_t hops, int32_t reach) {
-    if (reach <= 0 || P < 64 || P > 1024 || n > 500000 || (double)n * P * 5 / 4.5e6 > 0.5 * hops) return 0;
-    for (int32_t ring : {4096, 8192})
-        if (reach + 4 * 512 <= ring) return ring;
+inline int32_t path_ring(int32_t n, int64_t m, int32_t P, int32_t hops, int32_t reach, size_t tables_bytes) {
+    if (reach <= 0 || P < 64 || P > 1024 || n > 500000 || (double)n * P * 5 / 4.5e6 > 0.5 * hops || n / 700 > hops ||
+        3 * m < 2 * (int64_t)n)
+        return 0;
+    for (int32_t ring : {4096, 8192}) {
+        const size_t lds = tables_bytes + (size_t)ring * 5, taken = (lds + 64 + 1279) / 1280 * 1280;
+        if (reach + 4 * 512 <= ring) return lds <= kPathLdsBytes && (size_t)P <= 256 * (kLdsBudget / taken) ? ring : 0;
+    }
     return 0;
 }
 // cp_eval of one partition (CP_PLAN_AUTO) with scratch of its own for the chain sweep (eval_chain_bytes), or null;

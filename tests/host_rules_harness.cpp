@@ -249,6 +249,21 @@ static int paths(const std::string &dir, const std::string &wanted) {
     return got != wanted;
 }
 
+// Where b and the device ids are streamed past a walk.
+static int streams() {
+    auto tables = [](size_t k) { return (k * k + k) * 8; };
+    const int32_t n = 121000, hops = 300, reach = 1000;
+    auto ring = [&](int32_t P, size_t k) { return path_ring(n, 3 * n, P, hops, reach, tables(k)); };
+    // 64 devices' tables and a ring take 53,760 bytes, 55,040 in granules: two workgroups a compute unit
+    if (ring(512, 64) != 4096 || ring(513, 64) != 0) return std::printf("rounds of 64 devices\n"), 1;
+    if (ring(777, 11) != 4096 || ring(63, 11) != 0 || ring(1025, 11) != 0) return std::printf("partitions\n"), 1;
+    if (path_ring(n, 3 * n, 512, hops, 2049, tables(50)) != 8192 || path_ring(n, 3 * n, 513, hops, 2049, tables(50)) != 0)
+        return std::printf("rounds of the larger ring\n"), 1;
+    if (path_ring(n, 3 * n, 100, n / 700 - 1, reach, tables(8)) != 0 || path_ring(n, n / 2, 100, hops, reach, tables(8)) != 0)
+        return std::printf("short paths\n"), 1;
+    return 0;
+}
+
 // Where a few partitions take records at all.
 static int few_records() {
     const int32_t n = 121000, hops = 300;
@@ -272,6 +287,7 @@ int main(int argc, char **argv) {
     if (!std::strcmp(argv[1], "inverses")) return inverses();
     if (!std::strcmp(argv[1], "column")) return column();
     if (!std::strcmp(argv[1], "few records")) return few_records();
+    if (!std::strcmp(argv[1], "streams")) return streams();
     if (!std::strcmp(argv[1], "left-over")) return left_over();
     if (!std::strcmp(argv[1], "bucket-sizes")) return bucket_sizes();
     return 2;

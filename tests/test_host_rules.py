@@ -47,6 +47,10 @@ def test_quotients_by_tables_of_inverses_are_exact(harness):
     _holds(harness, "inverses")
 
 
+def test_which_walks_are_streamed(harness):
+    _holds(harness, "streams")
+
+
 def test_where_a_few_partitions_take_records(harness):
     _holds(harness, "few records")
 
