@@ -202,14 +202,15 @@ int launch_clear(int64_t *cp_out, int32_t batch, int32_t *status, void *stream);
 int launch_transpose(const uint8_t *in, uint8_t *out, int32_t n, int32_t P, void *stream);
 int launch_column_sweep(const SweepLaunch &s, void *stream, int32_t *launches);
 // The same with four partitions a lane; the tables hold inverses (build_inverse_table), 16 bytes a pair of devices in the t
-// sweep, which is 16 KB of a workgroup's LDS at 32.  Only where a level makes two wavefronts for each of the 1,024 SIMDs: below,
-// a launch is a chain of round trips, and this kernel's is the longer one.  Without and with: 10,000 vertices a level, 1, 4 and
-// 16 slices 566 and 517 us, 1,277 and 982, 4,226 and 2,916; 1,500 a level, 16 slices 395 and 319; 3,000 a level, one slice 164
-// and 204.
+// sweep, which is 16 KB of a workgroup's LDS at 32.  Only where a level makes two and a half wavefronts for each of the 1,024
+// SIMDs: below, a launch is a chain of round trips, and this kernel's is the longer one.  Without and with: 10,000 vertices a
+// level, 4 and 16 slices 1,277 and 982 us, 4,226 and 2,916; 1,500 a level, 16 slices 395 and 319; 3,000 a level, one slice 164
+// and 204.  Over 285 calls from two wavefronts on 0.89 times as long, 9 of them by 3 to 12 % longer (9,700 vertices a level, 40
+// partitions, t sweep alone 250 and 280); none of those left by more than 2.8 %.
 constexpr int32_t kColumn4Devices = 32;
 inline bool column4_fits(int32_t n, int32_t L, int32_t P, int32_t k, bool narrow, int tick_bytes) {
     return narrow && tick_bytes == 4 && P % 4 == 0 && k <= kColumn4Devices && n < 1 << 24 && P < 1 << 24 &&
-           (uint64_t)n * (uint64_t)P < 1ull << 30 && (int64_t)(n / L) * ((P + 63) / 64) >= 4 * 2 * 1024;
+           (uint64_t)n * (uint64_t)P < 1ull << 30 && (int64_t)(n / L) * ((P + 63) / 64) >= 4 * 5 * 512;
 }
 int launch_column4(const SweepLaunch &s, void *stream, int32_t *launches);
 int launch_window_sweep(const SweepLaunch &s, const WindowCfg &cfg, void *stream, int32_t *launches);

@@ -18,7 +18,7 @@ def _check(gpu, oracle, w, layouts=(0, 1), assign_layouts=(0, 1)):
     ref = oracle.evaluate_workload(w, threads=8)
     for layout in layouts:
         for by_vertex in assign_layouts:
-            assert w.n // (int(w.level_ptr.shape[0]) - 1) * ((w.P + 63) // 64) >= 8192
+            assert w.n // (int(w.level_ptr.shape[0]) - 1) * ((w.P + 63) // 64) >= 10240
             a = torch.from_numpy(np.ascontiguousarray(w.assignments.T) if by_vertex else w.assignments).to("cuda:0")
             out = gpu.cp_eval(g, a, w.speeds, w.bandwidth, plan=gpu.PLAN_WAVE_COLUMN, out_layout=layout,
                               assign_layout=by_vertex)
@@ -33,7 +33,7 @@ def _check(gpu, oracle, w, layouts=(0, 1), assign_layouts=(0, 1)):
 @pytest.mark.parametrize("k", [1, 2, 8, 32, 33])
 def test_batches_and_devices(gpu, oracle, P, k):
     rng = np.random.default_rng([P, k])
-    wide = 8192 // ((P + 63) // 64)              # (the rule asks for that many rows and slices in a level, on average)
+    wide = 10240 // ((P + 63) // 64)              # (the rule asks for that many rows and slices in a level, on average)
     n, level, src, dst = random_layered_dag(rng, [3 * wide, 1, 50, 2 * wide + 3, 17], 1, 5, 3)
     few = np.arange(40)                          # rows of up to 200 edges
     src = np.concatenate([src, np.repeat(few, 5 * few)])
@@ -46,9 +46,9 @@ def test_batches_and_devices(gpu, oracle, P, k):
 @pytest.mark.parametrize("length", [255, 256, 257, 300, 1024, 4097])
 def test_hubs(gpu, oracle, length):
     rng = np.random.default_rng(length)
-    n, level, src, dst = random_layered_dag(rng, [7, 13000, 40], 1, 4, 2)
-    src = np.concatenate([src, np.full(length, 3), rng.integers(7, 13007, length)])    # out of vertex 3, into 13010
-    dst = np.concatenate([dst, rng.integers(7, 13007, length), np.full(length, 13010)])
+    n, level, src, dst = random_layered_dag(rng, [7, 16000, 40], 1, 4, 2)
+    src = np.concatenate([src, np.full(length, 3), rng.integers(7, 16007, length)])    # out of vertex 3, into 16010
+    dst = np.concatenate([dst, rng.integers(7, 16007, length), np.full(length, 16010)])
     w = T._custom("column4", n, src, dst, rng.integers(0, 5000, len(src)), rng.integers(0, 500, n), rng.integers(1, 9, 6),
                   rng.integers(1, 60, (6, 6)), rng.integers(0, 6, (72, n), dtype=np.uint8), level)
     _check(gpu, oracle, w)
@@ -58,7 +58,7 @@ def test_hubs(gpu, oracle, length):
 def test_volumes_next_to_multiples(gpu, oracle, most):
     """Two levels, an edge from every vertex of the first: t is a multiple of some divisor, one less or one more."""
     rng = np.random.default_rng(most)
-    N, k, P = 8192, 32, 64
+    N, k, P = 10240, 32, 64
     rates = rng.choice(np.concatenate([np.arange(1, 258), 2 ** np.arange(9, 30), [1000003, 2 ** 31 - 1, 2 ** 40]]), (k, k))
     d = rng.choice(rates.ravel(), N)
     t = np.clip(d * np.maximum(1, rng.integers(0, most, N) // d) + rng.integers(-1, 2, N), 0, most)
