@@ -281,10 +281,11 @@ int cp_eval_static(const cp_graph *g, int32_t batch, int32_t k,
  *   assignments, assign_layout, speeds, bandwidth   as for cp_eval (same values as the
  *                 call that produced blevel and cp)
  *   blevel        device ticks laid out per b_layout (CP_OUT_*), cp device int64 [batch]: outputs of cp_eval
- *   workspace     device, 256-byte aligned, >= cp_eval_workspace_bytes for this batch and k.  Graphs of 256 levels and
- *                 more, of up to 1,024 vertices each and up to five edges a vertex, are walked faster, with the same
- *                 result, where it holds 64 bytes a vertex behind the 12 k (2 k + 1) bytes, rounded up to 256, of the
- *                 tables; that many bytes do from a few dozen partitions on, and a larger workspace may be handed over
+ *   workspace     device, 256-byte aligned, >= the 12 k (2 k + 1) bytes, rounded up to 256, of the tables, which
+ *                 cp_eval_workspace_bytes never falls short of.  Graphs of 256 levels and more, of up to 1,024 vertices
+ *                 each and up to five edges a vertex, are walked faster, with the same result, where it holds 64 bytes
+ *                 a vertex behind them (fewer than 32 partitions: where vertices and edges are few enough to repay
+ *                 writing these); a larger workspace may be handed over
  *   max_len       row length of path_out, >= the graph's number of levels L
  *   path_out      device int32 [batch][max_len]; unused tail = -1
  *   len_out       device int32 [batch]: vertices on the path

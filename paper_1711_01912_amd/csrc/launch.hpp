@@ -337,13 +337,13 @@ inline bool path_by_jumps(int32_t n, int32_t P, int32_t L, int32_t hops) {
 inline bool path_by_records(int32_t n, int64_t m, int32_t L, int32_t hops) {
     return L >= 256 && n / L < 1024 && m / n <= 5 && hops >= 64;
 }
-// Fewer than 32 partitions have to share the launch: not with more than 700 vertices a path vertex, nor with fewer edges than two
+// Fewer than 32 partitions have to share the launch: not with more than 500 or, from 8 on, 700 vertices to one of a path, nor with fewer edges than two
 // for three vertices, whose paths end after a few, nor, unless the vertices are few, with rows near a record's seven edges, from
-// four on under 8 partitions and five under 32.  Of 800 calls of up to 7 partitions without and with records 508 take
+// four on under 8 partitions and five under 32.  Of 800 calls of up to 7 partitions without and with records 480 take
 // them, 0.91 times as long, three of those more than 1.1 times and 1.24 at most; of all 800 108 were more than 1.1 times, 2.1
 // at most (365,000 vertices, 182,000 edges, one partition 53 and 114 us; 236,000 vertices with six edges each, two 83 and 123).
 inline bool records_for(int32_t n, int64_t m, int32_t P, int32_t hops) {
-    return P >= 32 || (3 * m >= 2 * (int64_t)n && n / 700 <= hops &&
+    return P >= 32 || (3 * m >= 2 * (int64_t)n && n / (P < 8 ? 500 : 700) <= hops &&
                        (m < (P < 8 ? 4 : 5) * (int64_t)n || n < 1500 * std::min(P, 8)));
 }
 // Vertices of the LDS ring that b and the device ids are streamed through on a walk over records, or 0 where they are not.
