@@ -679,14 +679,15 @@ __device__ __forceinline__ bool sort_by_bins(const uint32_t *__restrict__ keys_i
 // lanes (a bin that is crowded after all, in a partition that nothing was found against).  They are neighbours here, in runs of
 // vertex numbers that differ in their low six bits only, and mostly in order, which is looked at; if not, the first thread of a
 // run puts it in order.  (Sorting by the vertex numbers' digits instead took three passes more, and spilled registers in all
-// buckets: 142,000 vertices in 53 levels, 4 devices, 8 partitions, whose last level's keys repeat, 86 us a call before there was
-// the scatter by adds, 146 and more with those passes, 88 with this.)
+// buckets: 142,000 vertices in 53 levels, 4 devices, 8 partitions, whose last level's keys repeat, 82 us a call before there was
+// the scatter by adds, 146 and more with those passes, 78 with this.  A call, because inlined it cost
+// registers: 66 instead of 60 in the bins of 128 threads, the call of 211,000 vertices and 512 partitions 888 -> 932 us.)
 template <int kThreads>
-__device__ __forceinline__ void order_runs(uint32_t *keys, int32_t *vals, int32_t items) {
+__device__ __noinline__ void order_runs(uint32_t *keys, int32_t *vals, int32_t items, int tid) {
     bool apart = false;
-    for (int32_t t = (int32_t)threadIdx.x + 1; t < items; t += kThreads) apart |= vals[t - 1] > vals[t];
+    for (int32_t t = tid + 1; t < items; t += kThreads) apart |= vals[t - 1] > vals[t];
     if (!__syncthreads_or(apart)) return;
-    for (int32_t t = threadIdx.x; t < items; t += kThreads) {
+    for (int32_t t = tid; t < items; t += kThreads) {
         const int32_t run = vals[t] >> 6;
         if (t > 0 && vals[t - 1] >> 6 == run) continue;
         for (int32_t i = t + 1; i < items && vals[i] >> 6 == run; ++i) {
@@ -709,7 +710,8 @@ __device__ __forceinline__ void order_runs(uint32_t *keys, int32_t *vals, int32_
 // pct_bucket_check_kernel found in common bins, or with a crowded bin after all.
 constexpr int kBinRounds = 8;
 template <int kThreads>
-__global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(uint32_t *keys_in, int32_t *vals_in,
+__global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(const uint32_t *__restrict__ keys_in,
+                                                                   const int32_t *__restrict__ vals_in,
                                                                    int32_t *__restrict__ vals_out, int32_t n, int32_t each,
                                                                    int32_t tiles, int bits, int val_bits,
                                                                    const uint32_t *__restrict__ starts, Gate gate,
@@ -727,8 +729,7 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(uint32_t *key
     if (lane <= each && d0 + lane < kBuckets) bound = starts[((int64_t)q * kBuckets + d0 + lane) * tiles];
     if (gate.closed()) return;
     left += (int64_t)q * kBuckets + d0;
-    const int32_t what = found[(int64_t)q * found_stride];
-    if ((what & kCrowded) != 0) {
+    if ((found[(int64_t)q * found_stride] & kCrowded) != 0) {
         const uint32_t next = __shfl_down(bound, 1);
         if ((int)threadIdx.x < each) left[threadIdx.x] = next != bound ? 1u : 0u;
         return;
@@ -741,7 +742,6 @@ __global__ __launch_bounds__(kThreads) void pct_bucket_bins_kernel(uint32_t *key
         if (!done && items <= kThreads * kBinRounds)
             done = sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits,
                                                                    val_bits, sorted, bins, wave_sum, key);
-        if (!done && what == 0) order_runs<kThreads>(keys_in + at, vals_in + at, items);
         if (threadIdx.x == 0) left[i] = done ? 0u : 1u;
     }
 }
@@ -923,7 +923,7 @@ __global__ __launch_bounds__(kThreads, 6) void pct_bucket_kernel(uint32_t *keys_
         sort_by_bins<kThreads, kBinRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, val_bits, slot,
                                                    slot + kThreads * kBinRounds, wave_sum, few))
         return;
-    if (what == 0) order_runs<kThreads>(keys_in + at, vals_in + at, items);
+    if (what == 0) order_runs<kThreads>(keys_in + at, vals_in + at, items, threadIdx.x);
     sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters,
                                               threadIdx.x, key);
 }
@@ -932,15 +932,16 @@ __global__ __launch_bounds__(kThreads, 6) void pct_bucket_kernel(uint32_t *keys_
 // (Six wavefronts a SIMD, and the thread's number new in every round: else the loop keeps every address that follows from
 // it, 110 registers, or spills some; so 77 and no scratch.)
 template <int kThreads>
-__global__ __launch_bounds__(kThreads, 6) void pct_bucket_sort_kernel(const uint32_t *__restrict__ keys_in,
-                                                                   const int32_t *__restrict__ vals_in,
+__global__ __launch_bounds__(kThreads, 6) void pct_bucket_sort_kernel(uint32_t *keys_in, int32_t *vals_in,
                                                                    int32_t *__restrict__ vals_out, int32_t n, int32_t each,
                                                                    int32_t tiles, int bits,
                                                                    const uint32_t *__restrict__ starts, Gate gate,
+                                                                   const int32_t *__restrict__ found, int32_t found_stride,
                                                                    const uint32_t *__restrict__ left) {
     __shared__ uint32_t slot[kThreads * kSortRounds], counters[kThreads / 64][256];
     if (gate.closed()) return;
     const uint32_t q = blockIdx.x / (uint32_t)(kBuckets / each);
+    const bool any_order = found[(int64_t)q * found_stride] == 0;
     uint32_t lo = 0, hi = 0;
     if ((int)(threadIdx.x & 63) < each) {
         const uint32_t d = left_over_bucket<kBuckets>(blockIdx.x, threadIdx.x & 63, each);
@@ -961,6 +962,7 @@ __global__ __launch_bounds__(kThreads, 6) void pct_bucket_sort_kernel(const uint
         const int32_t items = (int32_t)((uint32_t)__builtin_amdgcn_readlane((int)hi, which) - first);
         const int64_t at = (int64_t)q * n + first;
         uint32_t key[kSortRounds];
+        if (any_order) order_runs<kThreads>(keys_in + at, vals_in + at, items, tid);
         sort_bucket<kThreads, kSortRounds, false>(keys_in + at, vals_in + at, vals_out + at, items, bits, slot, counters, tid,
                                                   key);
         __syncthreads();
@@ -1162,7 +1164,7 @@ int run_bucket_sort(const PctOrderLaunch &s, KeyArgs a, hipStream_t st) {
     const int32_t each = left_over_each(all);
 #define CP_LEFT(T)                                                                                                    \
     hipLaunchKernelGGL(pct_bucket_sort_kernel<T>, dim3((unsigned)(all / each)), dim3(T), 0, st, keys, vals, s.order_out, \
-                       s.n, each, tiles, rem, starts, fit, (const uint32_t *)left)
+                       s.n, each, tiles, rem, starts, fit, (const int32_t *)found, s.k + 1, (const uint32_t *)left)
     if (small) CP_LEFT(256);
     else CP_LEFT(512);
 #undef CP_LEFT
