@@ -406,9 +406,12 @@ bool chain_takes(const Packed &p, int32_t batch, int tick_dtype, bool by_partiti
 // tick 0.27 us, 0.03 more for every wavefront past four on a compute unit; ids and outputs 0.08 us (rows per vertex 0.23) for
 // every vertex and partition that a lane has of them.  A fifth more where the workgroups take turns on a compute unit (1,800
 // vertices in 300 levels, 4,096 partitions 190 us against the lane-window plan's 179).
+double whole_wg_per_cu(const WholeCfg &c) {
+    return std::max(1.0, std::floor(std::min((double)kLdsBudget / (double)(c.lds_bytes + 256), 32.0 * kWave / c.threads)));
+}
 double whole_us(const Packed &p, const WholeCfg &c, int32_t batch, bool by_partition) {
     const double wgs = std::ceil((double)batch / c.groups), waves = (double)c.threads / kWave;
-    const double per_cu = std::max(1.0, std::floor(std::min((double)kLdsBudget / (double)(c.lds_bytes + 256), 32.0 / waves)));
+    const double per_cu = whole_wg_per_cu(c);
     const double there = std::min(per_cu, std::ceil(wgs / 256.0)), rounds = std::ceil(wgs / (256.0 * per_cu));
     return 9.0 + rounds * (rounds > 1.0 ? 1.2 : 1.0) *
                      ((double)p.n * c.groups / c.threads * (by_partition ? 0.08 : 0.23) +
@@ -426,6 +429,11 @@ bool choose_whole(const Packed &p, const CostTables &tabs, int32_t k, const int6
         if (groups == 4 && mask && !by_partition) continue;        // (a workgroup writes whole bytes of a vertex's mask)
         WholeCfg c;
         if (!whole_config(p.whole, p.n, k, groups, word, dividends_fit_floats(p), sweeps, lds_limit, c)) continue;
+        // 64-bit words leave a compute unit to one or two workgroups, and those that take turns there with few wavefronts are no
+        // match for the lane-window plan, which is dearer than it is in the model: of 181 such calls of under twelve wavefronts 58
+        // were slower than under that plan, up to 1.58 times (930 vertices in 93 levels, 4,779 partitions, b alone 55 and 87
+        // us), of 44 with twelve and more none (0.74 times as long).
+        if (word == 8 && batch > 256 * groups * whole_wg_per_cu(c) && whole_wg_per_cu(c) * c.threads < 12 * kWave) continue;
         const double us = whole_us(p, c, batch, by_partition);
         if (!found || us < *us_out) {
             found = true;
