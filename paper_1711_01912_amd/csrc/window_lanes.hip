@@ -17,9 +17,9 @@
 // third of it bank conflicts; vector ALUs 60 %, 25 instructions per 64 relaxations with what loaders and stores add).
 // Divisions are one multiply-add (inverse_div): floats where no volume reaches 2^23, doubles above.  Against multiply-shift
 // constants, whose 64-bit product alone takes four times as long: 121,000 vertices in 701 levels, 777 partitions
-// 1,155 -> 1,079 us a call; 19,800 in 660, 4,096 partitions 1,685 -> 1,524; 29,000 in 301 with 64-bit words, 320
-// partitions 315 -> 280; narrow ticks, which wait for their chain, are where they were (1,578 levels of 34 vertices, 118
-// partitions 800 -> 809).
+// 1,155 -> 1,077 us a call; 19,800 in 660, 4,096 partitions 1,685 -> 1,511; 29,000 in 301 with 64-bit words, 320
+// partitions 315 -> 274; narrow ticks, which wait for their chain, gain least (1,578 levels of 34 vertices, 118 partitions
+// 797 -> 763), and b alone of two vertices a level takes up to a tenth longer (530 levels, 908 partitions 141 -> 156).
 //
 // A ring word is value << 6 | device id, one LDS read per relaxation; x << 6 is added to it and the
 // maximum taken over whole words, whose upper bits are the maximum of the sums.  Words are 32 bits while
@@ -383,12 +383,15 @@ __device__ __forceinline__ void lane_sweep(const LaneArgs &a, const LaneShape &s
                 }
                 i += sh.nc;
                 ask(i < items ? item_at(t, i) : item_at(t + 1, wave));
+                // (before the ring's words are waited for: left to itself the compiler asks between them and the table, and the
+                // division by floats waits for all three; 1,578 levels of 34 vertices, 118 partitions 830 -> 765 us a call)
+                __builtin_amdgcn_sched_barrier(0);
                 const uint32_t own = (uint32_t)own_w & ID;
                 const Tab *erow = etab + __umul24(own, (uint32_t)k);
-                const Tab mw = vtab[own];
                 Tab m[W];
 #pragma unroll
                 for (int j = 0; j < W; ++j) m[j] = erow[(uint32_t)v[j] & ID];
+                const Tab mw = vtab[own];
                 Word acc = 0;
 #pragma unroll
                 for (int j = 0; j < W; ++j) acc = max(acc, add_quotient(v[j], x_t[j], m[j], up));
