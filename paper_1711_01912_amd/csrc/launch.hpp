@@ -203,14 +203,16 @@ int launch_transpose(const uint8_t *in, uint8_t *out, int32_t n, int32_t P, void
 int launch_column_sweep(const SweepLaunch &s, void *stream, int32_t *launches);
 // The same with four partitions a lane; the tables hold inverses (build_inverse_table), 16 bytes a pair of devices in the t
 // sweep, which is 16 KB of a workgroup's LDS at 32.  Only where a level makes two and a half wavefronts for each of the 1,024
-// SIMDs: below, a launch is a chain of round trips, and this kernel's is the longer one.  Without and with: 10,000 vertices a
+// SIMDs, or two with several slices and tables of up to 8 devices: below, a launch is a chain of round trips, and this kernel's is the longer one.  Without and with: 10,000 vertices a
 // level, 4 and 16 slices 1,277 and 982 us, 4,226 and 2,916; 1,500 a level, 16 slices 395 and 319; 3,000 a level, one slice 164
 // and 204.  Over 285 calls from two wavefronts on 0.89 times as long, 9 of them by 3 to 12 % longer (9,700 vertices a level, 40
-// partitions, t sweep alone 250 and 280); none of those left by more than 2.8 %.
+// partitions, t sweep alone 250 and 280), but none with several slices and up to 8 devices (1,057 a level, 532 partitions, b
+// alone 201 and 175); none of those left by more than 2.8 %.
 constexpr int32_t kColumn4Devices = 32;
 inline bool column4_fits(int32_t n, int32_t L, int32_t P, int32_t k, bool narrow, int tick_bytes) {
     return narrow && tick_bytes == 4 && P % 4 == 0 && k <= kColumn4Devices && n < 1 << 24 && P < 1 << 24 &&
-           (uint64_t)n * (uint64_t)P < 1ull << 30 && (int64_t)(n / L) * ((P + 63) / 64) >= 4 * 5 * 512;
+           (uint64_t)n * (uint64_t)P < 1ull << 30 &&
+           (int64_t)(n / L) * ((P + 63) / 64) >= (P > 64 && k <= 8 ? 4 * 2 * 1024 : 4 * 5 * 512);
 }
 int launch_column4(const SweepLaunch &s, void *stream, int32_t *launches);
 int launch_window_sweep(const SweepLaunch &s, const WindowCfg &cfg, void *stream, int32_t *launches);
@@ -339,12 +341,13 @@ inline bool path_by_records(int32_t n, int64_t m, int32_t L, int32_t hops) {
 }
 // Fewer than 32 partitions have to share the launch: not with more than 500 or, from 8 on, 700 vertices to one of a path, nor with fewer edges than two
 // for three vertices, whose paths end after a few, nor, unless the vertices are few, with rows near a record's seven edges, from
-// four on under 8 partitions and five under 32.  Of 800 calls of up to 7 partitions without and with records 480 take
-// them, 0.91 times as long, three of those more than 1.1 times and 1.24 at most; of all 800 108 were more than 1.1 times, 2.1
+// four on under 8 partitions and five under 32.  Of 800 calls of up to 7 partitions without and with records 466 take
+// them, 0.90 times as long, one of those more than 1.1 times, 1.24; of all 800 108 were more than 1.1 times, 2.1
 // at most (365,000 vertices, 182,000 edges, one partition 53 and 114 us; 236,000 vertices with six edges each, two 83 and 123).
 inline bool records_for(int32_t n, int64_t m, int32_t P, int32_t hops) {
     return P >= 32 || (3 * m >= 2 * (int64_t)n && n / (P < 8 ? 500 : 700) <= hops &&
-                       (m < (P < 8 ? 4 : 5) * (int64_t)n || n < 1500 * std::min(P, 8)));
+                       (m < (P < 8 ? 4 : 5) * (int64_t)n ||
+                        (n < std::min(2000 * P, 12000) && m < (P < 8 ? 5 : 6) * (int64_t)n)));
 }
 // Vertices of the LDS ring that b and the device ids are streamed through on a walk over records, or 0 where they are not.
 // The whole rows are read for it, 5 bytes a vertex at 4.5 TB/s, which half a microsecond a path vertex has to outweigh.  With

@@ -270,8 +270,8 @@ static int few_records() {
     if (!records_for(n, 3 * n, 1, hops) || records_for(n, 4 * n, 7, hops) || !records_for(n, 4 * n, 8, hops) ||
         records_for(n, 5 * n, 31, hops) || !records_for(n, 5 * n, 32, hops))
         return std::printf("records by edges\n"), 1;
-    if (!records_for(5999, 5 * 5999, 4, hops) || records_for(6000, 5 * 6000, 4, hops) || !records_for(11999, 6 * 11999, 31, hops) ||
-        records_for(12000, 6 * 12000, 31, hops))
+    if (!records_for(7999, 5 * 7999 - 1, 4, hops) || records_for(7999, 5 * 7999, 4, hops) || records_for(8000, 4 * 8000, 4, hops) ||
+        !records_for(11999, 6 * 11999 - 1, 31, hops) || records_for(12000, 5 * 12000, 31, hops))
         return std::printf("records of few vertices\n"), 1;
     if (records_for(n, 3 * n, 31, n / 700 - 1) || records_for(n, 3 * n, 7, n / 500 - 1) || !records_for(n, 3 * n, 32, 64) || records_for(n, n / 2, 5, hops))
         return std::printf("records by paths\n"), 1;
